@@ -32,6 +32,7 @@ static_assert(kParams == 74754, "parameter count");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 // fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32 on gfx950); f2bf2
 // converts two values with one instruction, a in the low half
@@ -43,419 +44,538 @@ __device__ __forceinline__ uint32_t f2bf2(float a, float b) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// ------------------------------------------------------------------ GEMM
-// C[m,n] = sum_k A(m,k) B(k,n), A(m,k) = A[m*sam + k*sak], B(k,n) =
-// B[k*sbk + n*sbn] (bf16), accumulated in fp32, then: + bias[n], ReLU,
-// * (mask(m,n) > 0), stored to C32 (fp32) and/or C16 (bf16); colpart gets
-// each 64-row tile's column sums of the final fp32 values (summed later in a
-// fixed order, so training is bit-reproducible).  64 x 64 tile per 256-thread block; each wave owns a
-// 32 x 32 quarter as 2 x 2 MFMA 16x16x32 tiles; K advances 32 at a time
-// through LDS (A row-major, B transposed so both fragments are 16-byte reads).
-// Staging reads 8 consecutive bf16 per thread (16 bytes) along whichever
-// index of an operand is contiguous in memory (amode/bmode 1: k, 2: m or n;
-// 0: element by element).  With ksplit > 1, block z of the grid's third
-// dimension sums K range [z kchunk, (z + 1) kchunk) into C32 + z pstride
-// (partials, reduced in z order by k_ksum); no epilogue then.
-struct GemmArgs {
-    int M, N, K;
-    const uint16_t *A;
-    int64_t sam, sak;
-    const uint16_t *B;
-    int64_t sbk, sbn;
-    const float *bias;
-    int relu;
-    const uint16_t *mask;
-    int64_t smm, smn;
-    float *C32;
-    int64_t ldc;
-    uint16_t *C16;
-    int64_t ldc16;
-    float *colpart;  // [ceil(M/64)][N] per-tile column sums of the final values
-    int amode, bmode;
-    int ksplit, kchunk;
-    int64_t pstride;
+// Weights and activations that a product reads as MFMA operands are kept in
+// fragment order: element k of operand row n (a 16 x 32 fragment holds rows
+// n / 16 and elements k / 32) at frag(n, k, K), so that a wave's fragment load
+// is 1 KB of consecutive bytes, eight whole cache lines, where row-major
+// order would touch half of sixteen.
+__device__ __forceinline__ int64_t frag(int n, int64_t k, int64_t K) {
+    return (((int64_t)(n >> 4) * (K >> 5) + (k >> 5)) * 64 + (n & 15) + ((k & 31) >> 3) * 16) * 8 + (k & 7);
+}
+
+// ------------------------------------------------------------- training
+// One step is two kernels: k_rows_step, the forward and backward passes of
+// 32 rows per work-group, and k_params_step, the weight gradients with the
+// sums over the batch and (training) Adam.  Every sum is taken in a fixed
+// order that does not depend on the launch, so training is bit-reproducible.
+//
+// What bounds a step: not the matrix cores (0.46 GFLOP at batch 1024 is 0.2 us
+// of them) but the launches (about 3.4 us each, however little they do) and
+// the chain of dependent loads, LDS trips and barriers inside.  A step of
+// batch 1024 takes 16.6 us (10.3 + 6.3; gradients alone 17.2 us with the
+// caller's launch gaps, 61.7 before), against 58.7 as eleven kernels, one per
+// product, reduction and update.
+//
+// Between the two kernels the activations travel transposed, [unit][row]:
+// a lane's MFMA accumulator holds four consecutive rows of one unit (one
+// 8-byte store), and the weight-gradient products then read both operands
+// as 16-byte fragments along the batch with no LDS staging.
+constexpr int kRows = 32;               // rows per work-group of k_rows_step
+constexpr int kRowWaves = 8;            // its waves; wave w owns hidden units [32 w, 32 w + 32)
+constexpr int kRowLds = kHid + 8;       // LDS row of activations (16-byte aligned, rows 4 banks apart)
+constexpr int kPart = kHid + 3;         // partial sums per 4 rows: db2, db3, loss
+constexpr int kChunks = 16;             // batch chunks whose partial products meet in LDS at once
+
+struct StepArgs {
+    const float *x, *t;                 // features and targets (minibatch 0 when tab is set)
+    int64_t rows;
+    const int32_t *tab;                 // graph-captured training: see k_params_step
+    int32_t steps;                      // ... minibatches per epoch
+    const float *p;                     // fp32 parameters (biases)
+    const uint16_t *w1t, *w2, *w2t, *w3;  // bf16 weights: [256][32], [256][256], its transpose, [256][2]
+    uint16_t *xt, *h1t, *h2t, *d2t, *d1t; // bf16 [unit][rows]: features, hidden layers, their gradients
+    float *y;                           // [rows][2]
+    float *part;                        // [rows / 4][kPart] column sums of dH2, dY and the loss per 4 rows
+    float *colpart;                     // [rows / 32][256] column sums of dH1 per 32 rows
+    int32_t *cur;                       // tab[1]: the step index, for k_params_step
 };
 
-constexpr int kTM = 64, kTN = 64, kTK = 32, kLdsRow = kTK + 8;
-
-// K sub-tiles staged per global round trip.  Deeper panels (8, all of a
-// 256-deep K in one trip) measured no faster on the training shapes, whose
-// kernels sit near the per-launch floor, and cost 4x the LDS.
-constexpr int kSub = 1;
-
-// One operand tile, T[r][kk] = X(r0 + r, k0 + kk) with X(r, k) =
-// X[r sr + k sk], zero outside rows < R and k < kend, as 8 bf16 per thread:
-// mode 2 (sr == 1) thread = (k, 8 consecutive rows), one 16-byte read (the
-// host guarantees R % 8 == 0 and alignment); otherwise thread = (row, 8
-// consecutive k), one 16-byte read in mode 1 (sk == 1), 8 single reads in
-// mode 0.  Loading and storing are split so that a whole panel's reads are
-// in flight together.
-__device__ __forceinline__ uint4 load_tile(const uint16_t *X, int64_t sr, int64_t sk, int mode, int R, int r0, int k0,
-                                           int kend, int tid) {
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (mode == 2) {
-        const int kk = tid >> 3, r = (tid & 7) * 8;
-        if (r0 + r < R && k0 + kk < kend)
-            v = *reinterpret_cast<const uint4 *>(X + (int64_t)(k0 + kk) * sk + (r0 + r));
-    } else if (mode == 1) {
-        const int r = tid >> 2, kk = (tid & 3) * 8;
-        if (r0 + r < R && k0 + kk < kend)
-            v = *reinterpret_cast<const uint4 *>(X + (int64_t)(r0 + r) * sr + (k0 + kk));
-    } else {
-        const int r = tid >> 2, kk = (tid & 3) * 8;
-        uint32_t h[8];
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const int rr = r0 + r, k = k0 + kk + i;
-            h[i] = (rr < R && k < kend) ? X[(int64_t)rr * sr + (int64_t)k * sk] : 0u;
-        }
-        v = uint4{h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16};
-    }
-    return v;
+// The sum of x over the wave, by halves (lane l holds the sum over l ^ off at
+// each step): 32 and 16 by lane swaps, then rotations within 16-lane rows
+// (after the step of 8 a rotation by 4 reaches l ^ 4 or its equal l ^ 12).
+__device__ __forceinline__ float wave_sum_halving(float x) {
+    x += __shfl_xor(x, 32, 64);
+    x += __shfl_xor(x, 16, 64);
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xF, 0xF, false));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x124, 0xF, 0xF, false));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, false));
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false));
+    return x;
 }
 
-__device__ __forceinline__ void store_tile(uint4 v, int mode, int tid, uint16_t *T) {
-    if (mode == 2) {
-        const int kk = tid >> 3, r = (tid & 7) * 8;
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            T[(r + 2 * j) * kLdsRow + kk] = (uint16_t)(w[j] & 0xFFFFu);
-            T[(r + 2 * j + 1) * kLdsRow + kk] = (uint16_t)(w[j] >> 16);
-        }
-    } else {
-        const int r = tid >> 2, kk = (tid & 3) * 8;
-        *reinterpret_cast<uint4 *>(&T[r * kLdsRow + kk]) = v;
-    }
+// A work-group barrier that orders LDS accesses only: global stores in flight
+// (activations that only the next kernel reads) and prefetched loads are not
+// waited for, as __syncthreads would.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// One 64x64 output tile (bx, by) of g, K split bz when g.ksplit > 1.
-__device__ __forceinline__ void gemm_tile(const GemmArgs &g, int bx, int by, int bz) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[kSub][kTM * kLdsRow];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[kSub][kTN * kLdsRow];
-    __shared__ float cpart[2 * kTN];
+// Forward and backward of 32 rows.  Each wave keeps the fragments of its 32
+// columns of W1, W2 and W2^T in registers; accumulator value i of a lane is
+// row 4 (lane / 16) + i, unit lane % 16, in all three products, so masks and
+// hidden values stay in the lane that made them.  A work-group is bound by
+// its 272 KB of weights, read cold (1.8 us at the L1's 64 bytes a clock), and
+// by its five short phases (0.7 to 1 us each) between barriers: 7.4 us in all
+// at batch 1024.  Weights in row-major order (half-used cache lines) took 8 us
+// instead of 1.8, and barriers that also wait for the global stores 1 us
+// each; 16 waves of 16 columns measured 13.7 against 10.3 us a launch.  32
+// rows per work-group because the reduction order of db1 is by 32 rows.
+// X16: x is 16-byte aligned (rows are then read as float4).
+template <bool X16>
+__global__ __launch_bounds__(64 * kRowWaves) void k_rows_step(StepArgs A) {
+    __shared__ __attribute__((aligned(16))) uint16_t H1s[kRows * kRowLds];  // H1, later dH2
+    __shared__ __attribute__((aligned(16))) uint16_t H2s[kRows * kRowLds];
+    __shared__ float ds[kRows][2];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int m0 = by * kTM, n0 = bx * kTN;
-    const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; a++)
-#pragma unroll
-        for (int b = 0; b < 2; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int kbeg = g.ksplit > 1 ? bz * g.kchunk : 0;
-    const int kend = g.ksplit > 1 ? min(g.K, kbeg + g.kchunk) : g.K;
-    for (int k0 = kbeg; k0 < kend; k0 += kSub * kTK) {
-        // stage kSub tiles of A [64 x 32] and B^T [64 x 32]: all reads first
-        const int ns = min(kSub, (kend - k0 + kTK - 1) / kTK);
-        uint4 ra[kSub], rb[kSub];
-#pragma unroll
-        for (int j = 0; j < kSub; j++) {
-            if (j >= ns) break;
-            ra[j] = load_tile(g.A, g.sam, g.sak, g.amode, g.M, m0, k0 + j * kTK, kend, tid);
-            rb[j] = load_tile(g.B, g.sbn, g.sbk, g.bmode, g.N, n0, k0 + j * kTK, kend, tid);
-        }
-#pragma unroll
-        for (int j = 0; j < kSub; j++) {
-            if (j >= ns) break;
-            store_tile(ra[j], g.amode, tid, As[j]);
-            store_tile(rb[j], g.bmode, tid, Bs[j]);
-        }
-        __syncthreads();
-        const int fr = lane & 15, fk = (lane >> 4) * 8;
-#pragma unroll
-        for (int j = 0; j < kSub; j++) {
-            if (j >= ns) break;
-            bf16x8 af[2], bfr[2];
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-                af[a] = *reinterpret_cast<const bf16x8 *>(&As[j][(wm + a * 16 + fr) * kLdsRow + fk]);
-#pragma unroll
-            for (int b = 0; b < 2; b++)
-                bfr[b] = *reinterpret_cast<const bf16x8 *>(&Bs[j][(wn + b * 16 + fr) * kLdsRow + fk]);
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-#pragma unroll
-                for (int b = 0; b < 2; b++)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-        }
-        __syncthreads();
+    const int wn = wv * 32, lc = lane & 15, lg = lane >> 4, lk = lg * 8;
+    const int64_t r0 = (int64_t)blockIdx.x * kRows, B = A.rows;
+    int64_t o = 0;
+    if (A.tab) {
+        const int32_t s = A.tab[0];
+        o = B * (int64_t)((uint32_t)s % (uint32_t)A.steps);
+        if (blockIdx.x == 0 && tid == 0) A.cur[0] = s;
     }
-    // accumulator layout: value i of a lane is row 4*(lane/16)+i, column lane%16
-    if (g.ksplit > 1) {
-        float *P = g.C32 + (int64_t)bz * g.pstride;
+    const float *x = A.x + (o + r0) * kIn, *t = A.t + (o + r0) * kOut;
+    bf16x8 w1f[2], w2f[2][8], w2b[2][8], xf[2];
+    float bias1[2], bias2[2];
+    float v[2][8];
 #pragma unroll
-        for (int b = 0; b < 2; b++) {
-            const int n = n0 + wn + b * 16 + (lane & 15);
+    for (int rt = 0; rt < 2; rt++) {
+        const float *q = x + (rt * 16 + lc) * kIn + lk;
+        if (X16) {
+            const float4 a = *reinterpret_cast<const float4 *>(q), b = *reinterpret_cast<const float4 *>(q + 4);
+            v[rt][0] = a.x; v[rt][1] = a.y; v[rt][2] = a.z; v[rt][3] = a.w;
+            v[rt][4] = b.x; v[rt][5] = b.y; v[rt][6] = b.z; v[rt][7] = b.w;
+        } else {
 #pragma unroll
-            for (int a = 0; a < 2; a++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int m = m0 + wm + a * 16 + (lane >> 4) * 4 + i;
-                    if (m < g.M && n < g.N) P[(int64_t)m * g.ldc + n] = acc[a][b][i];
-                }
+            for (int i = 0; i < 8; i++) v[rt][i] = q[i];
         }
-        return;
     }
 #pragma unroll
-    for (int b = 0; b < 2; b++) {
-        const int n = n0 + wn + b * 16 + (lane & 15);
-        float csum = 0.f;
+    for (int ct = 0; ct < 2; ct++) {
+        const int n = wn + ct * 16 + lc;
+        w1f[ct] = *reinterpret_cast<const bf16x8 *>(A.w1t + ((wv * 2 + ct) * 64 + lane) * 8);
+        bias1[ct] = A.p[kOffB1 + n];
+        bias2[ct] = A.p[kOffB2 + n];
 #pragma unroll
-        for (int a = 0; a < 2; a++)
+        for (int ks = 0; ks < 8; ks++)
+            w2f[ct][ks] = *reinterpret_cast<const bf16x8 *>(A.w2t + (((wv * 2 + ct) * 8 + ks) * 64 + lane) * 8);
+    }
+    // output weights: of this lane's four units in the output dot products,
+    // and of its two columns in dH2
+    const uint4 w3d = *reinterpret_cast<const uint4 *>(A.w3 + lane * 8);
+    uint32_t w3c[2];
+#pragma unroll
+    for (int ct = 0; ct < 2; ct++) w3c[ct] = *reinterpret_cast<const uint32_t *>(A.w3 + (wn + ct * 16 + lc) * 2);
+    const float b30 = A.p[kOffB3], b31 = A.p[kOffB3 + 1];
+    float tt[4][2];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        tt[k][0] = t[(wv * 4 + k) * 2];
+        tt[k][1] = t[(wv * 4 + k) * 2 + 1];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // every load above is issued before any of them is waited for
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++) {
+        const uint4 h = {f2bf2(v[rt][0], v[rt][1]), f2bf2(v[rt][2], v[rt][3]), f2bf2(v[rt][4], v[rt][5]),
+                         f2bf2(v[rt][6], v[rt][7])};
+        xf[rt] = __builtin_bit_cast(bf16x8, h);
+    }
+    // the features transposed, for dW1: wave w stores k = w, w + 8, w + 16, w + 24 of either 16-row half
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++) {
+        const u16x8 h = __builtin_bit_cast(u16x8, xf[rt]);
+        uint16_t e = 0;
+#pragma unroll
+        for (int i = 0; i < 8; i++) e = i == wv ? h[i] : e;
+        A.xt[frag(lk + wv, r0 + rt * 16 + lc, B)] = e;
+    }
+    // layer 1
+    bool on1[2][2][4];
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+        for (int ct = 0; ct < 2; ct++) {
+            const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[rt], w1f[ct], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            const int n = wn + ct * 16 + lc;
+            uint16_t h[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const int m = m0 + wm + a * 16 + (lane >> 4) * 4 + i;
-                if (m < g.M && n < g.N) {
-                    float v = acc[a][b][i];
-                    if (g.bias) v += g.bias[n];
-                    if (g.relu) v = fmaxf(v, 0.f);
-                    if (g.mask && !(bf2f(g.mask[(int64_t)m * g.smm + (int64_t)n * g.smn]) > 0.f)) v = 0.f;
-                    if (g.C32) g.C32[(int64_t)m * g.ldc + n] = v;
-                    if (g.C16) g.C16[(int64_t)m * g.ldc16 + n] = f2bf(v);
-                    csum += v;
-                }
+                h[i] = f2bf(fmaxf(acc[i] + bias1[ct], 0.f));
+                on1[rt][ct][i] = bf2f(h[i]) > 0.f;
+                H1s[(rt * 16 + lg * 4 + i) * kRowLds + n] = h[i];
             }
-        if (g.colpart) {
-            // rows of this lane group, then the four lane groups in order
-            const float c0 = __shfl(csum, (lane & 15), 64), c1 = __shfl(csum, (lane & 15) + 16, 64);
-            const float c2 = __shfl(csum, (lane & 15) + 32, 64), c3 = __shfl(csum, (lane & 15) + 48, 64);
-            if (lane < 16) cpart[(wv >> 1) * kTN + wn + b * 16 + lane] = ((c0 + c1) + c2) + c3;
+            const uint2 q = {(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+            *reinterpret_cast<uint2 *>(A.h1t + frag(n, r0 + rt * 16 + lg * 4, B)) = q;
         }
-    }
-    if (g.colpart) {
-        __syncthreads();
-        // the two row halves of the tile, in order; one partial per M-tile
-        if (tid < kTN && n0 + tid < g.N)
-            g.colpart[(int64_t)by * g.N + n0 + tid] = cpart[tid] + cpart[kTN + tid];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) { gemm_tile(g, blockIdx.x, blockIdx.y, blockIdx.z); }
-
-// Two independent products in one launch: blocks [0, n0) take g0's tiles
-// (x fastest, then y, then the K split), the rest g1's.
-__global__ __launch_bounds__(256) void k_gemm2(GemmArgs g0, int gx0, int gy0, int n0, GemmArgs g1, int gx1,
-                                                int gy1) {
-    int b = blockIdx.x;
-    if (b < n0) {
-        gemm_tile(g0, b % gx0, b / gx0 % gy0, b / (gx0 * gy0));
-    } else {
-        b -= n0;
-        gemm_tile(g1, b % gx1, b / gx1 % gy1, b / (gx1 * gy1));
-    }
-}
-
-// Column c of a [rows][cols] array of partial sums, summed by a 1024-thread
-// block that owns 64 columns: wave w adds its contiguous share of the rows in
-// row order, then the 16 wave sums are added in wave order (a fixed order,
-// so the result is reproducible).  Every thread of the block must call it.
-__device__ __forceinline__ float col_sum(const float *part, int rows, int cols, int c) {
-    __shared__ float red[16][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int per = (rows + 15) / 16, r0 = min(rows, w * per), r1 = min(rows, r0 + per);
-    float s = 0.f;
-    if (c < cols) {
-#pragma unroll 8
-        for (int r = r0; r < r1; r++) s += part[(int64_t)r * cols + c];
-    }
-    red[w][lane] = s;
-    __syncthreads();
-    float t = red[0][lane];
+    lds_barrier();
+    // layer 2
+    float h2[2][2][4];
 #pragma unroll
-    for (int i = 1; i < 16; i++) t += red[i][lane];
-    return t;
-}
-
-__global__ __launch_bounds__(1024) void k_colreduce(const float *part, int rows, int cols, float *out) {
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const float t = col_sum(part, rows, cols, c);
-    if (threadIdx.x < 64 && c < cols) out[c] = t;
-}
-
-// k_colreduce over its first `cb` work-groups and, in the others, the sum of
-// S split-K partials (k_ksum's order), one output per thread: two
-// independent reductions in one launch.
-__global__ __launch_bounds__(1024) void k_colreduce_ksum(const float *part, int rows, int cols, float *out, int cb,
-                                                          const float *kpart, int S, int64_t pstride, int64_t n,
-                                                          float *kout) {
-    if ((int)blockIdx.x < cb) {
-        const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-        const float t = col_sum(part, rows, cols, c);
-        if (threadIdx.x < 64 && c < cols) out[c] = t;
-        return;
-    }
-    const int64_t i = (int64_t)(blockIdx.x - cb) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = kpart[i];
-#pragma unroll 8
-    for (int z = 1; z < S; z++) s += kpart[z * pstride + i];
-    kout[i] = s;
-}
-
-// -------------------------------------------------------------- helpers
-__global__ void k_to_bf16(const float *x, uint16_t *y, int64_t n) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) y[i] = f2bf(x[i]);
-}
-
-__global__ void k_fill(float *x, int64_t n, float v) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) x[i] = v;
-}
-
-// Output layer and loss gradient, one wave per row (4 rows per block):
-// Y = H2 W3 + b3; with a target T: dY = 2 (Y - T) / (2B), dH2 = (dY W3^T) *
-// (H2 > 0) stored as bf16, and per-block partials (in row order) of db2,
-// db3 and the loss into `part` [blocks][kHid + 3].
-__global__ __launch_bounds__(256) void k_out(const uint16_t *H2, const uint16_t *W3, const float *b3, int64_t rows,
-                                             float *Y, const float *T, float *part, uint16_t *dH2,
-                                             int32_t *est) {
-    __shared__ float rowg[4][kHid];
-    __shared__ float rowx[4][3];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t r = blockIdx.x * 4LL + wv;
-    float w30[4], w31[4], h[4];
-    float s0 = 0.f, s1 = 0.f;
+    for (int rt = 0; rt < 2; rt++) {
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int i = lane * 4 + j;
-        w30[j] = bf2f(W3[i * 2]);
-        w31[j] = bf2f(W3[i * 2 + 1]);
-        h[j] = r < rows ? bf2f(H2[r * kHid + i]) : 0.f;
-        s0 += h[j] * w30[j];
-        s1 += h[j] * w31[j];
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-        s0 += __shfl_xor(s0, off, 64);
-        s1 += __shfl_xor(s1, off, 64);
-    }
-    const float y0 = s0 + b3[0], y1 = s1 + b3[1];
-    if (r < rows && lane == 0) {
-        if (Y) {
-            Y[2 * r] = y0;
-            Y[2 * r + 1] = y1;
+        for (int ks = 0; ks < 8; ks++) {
+            const bf16x8 hf = *reinterpret_cast<const bf16x8 *>(&H1s[(rt * 16 + lc) * kRowLds + ks * 32 + lk]);
+#pragma unroll
+            for (int ct = 0; ct < 2; ct++)
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hf, w2f[ct][ks], acc[ct], 0, 0, 0);
         }
-        if (est) {
-            // integer estimate: clamp(rint(exp(y)), 1, 2^20)
-            est[2 * r] = (int32_t)fminf(fmaxf(rintf(expf(y0)), 1.f), (float)(1 << 20));
-            est[2 * r + 1] = (int32_t)fminf(fmaxf(rintf(expf(y1)), 1.f), (float)(1 << 20));
+#pragma unroll
+        for (int ct = 0; ct < 2; ct++) {
+            const int n = wn + ct * 16 + lc;
+            uint16_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                h[i] = f2bf(fmaxf(acc[ct][i] + bias2[ct], 0.f));
+                h2[rt][ct][i] = bf2f(h[i]);
+                H2s[(rt * 16 + lg * 4 + i) * kRowLds + n] = h[i];
+            }
+            const uint2 q = {(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+            *reinterpret_cast<uint2 *>(A.h2t + (int64_t)n * B + r0 + rt * 16 + lg * 4) = q;
         }
     }
-    if (!T) return;
-    const float scale = 1.0f / (float)rows;  // 2 / (2 rows)
-    float d0 = 0.f, d1 = 0.f, l2 = 0.f;
-    if (r < rows) {
-        const float e0 = y0 - T[2 * r], e1 = y1 - T[2 * r + 1];
-        d0 = e0 * scale;
-        d1 = e1 * scale;
-        l2 = (e0 * e0 + e1 * e1) * 0.5f * scale;
+    lds_barrier();
+    // W2^T's fragments, for dH1: issued only here so that the first two layers
+    // do not queue behind them (the 272 KB of weights take the L1 1.8 us at 64
+    // bytes a clock) and the output layer covers them
+#pragma unroll
+    for (int ct = 0; ct < 2; ct++)
+#pragma unroll
+        for (int ks = 0; ks < 8; ks++)
+            w2b[ct][ks] = *reinterpret_cast<const bf16x8 *>(A.w2 + (((wv * 2 + ct) * 8 + ks) * 64 + lane) * 8);
+    __builtin_amdgcn_sched_barrier(0);
+    // outputs, their gradient and the loss: wave w has rows 4 w .. 4 w + 3
+    const float scale = 1.0f / (float)B;  // 2 / (2 rows)
+    {
+        float w30[4], w31[4], s0[4], s1[4];
+        const uint32_t wq[4] = {w3d.x, w3d.y, w3d.z, w3d.w};
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            w30[j] = bf2f((uint16_t)(wq[j] & 0xFFFFu));
+            w31[j] = bf2f((uint16_t)(wq[j] >> 16));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint2 q = *reinterpret_cast<const uint2 *>(&H2s[(wv * 4 + k) * kRowLds + lane * 4]);
+            const float h[4] = {bf2f((uint16_t)(q.x & 0xFFFFu)), bf2f((uint16_t)(q.x >> 16)),
+                                bf2f((uint16_t)(q.y & 0xFFFFu)), bf2f((uint16_t)(q.y >> 16))};
+            float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                a0 += h[j] * w30[j];
+                a1 += h[j] * w31[j];
+            }
+            s0[k] = a0;
+            s1[k] = a1;
+        }
+        float d0[4], d1[4], l2[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const float y0 = wave_sum_halving(s0[k]) + b30, y1 = wave_sum_halving(s1[k]) + b31;
+            const float e0 = y0 - tt[k][0], e1 = y1 - tt[k][1];
+            d0[k] = e0 * scale;
+            d1[k] = e1 * scale;
+            l2[k] = (e0 * e0 + e1 * e1) * 0.5f * scale;
+            if (lane == 0) {
+                const int row = wv * 4 + k;
+                A.y[(r0 + row) * 2] = y0;
+                A.y[(r0 + row) * 2 + 1] = y1;
+                ds[row][0] = d0[k];
+                ds[row][1] = d1[k];
+            }
+        }
+        if (lane == 0) {
+            float *pp = A.part + (r0 / 4 + wv) * kPart + kHid;
+            pp[0] = ((d0[0] + d0[1]) + d0[2]) + d0[3];
+            pp[1] = ((d1[0] + d1[1]) + d1[2]) + d1[3];
+            pp[2] = ((l2[0] + l2[1]) + l2[2]) + l2[3];
+        }
+    }
+    lds_barrier();
+    // dH2 = (dY W3^T) * (H2 > 0), its column sums per 4 rows
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+        for (int ct = 0; ct < 2; ct++) {
+            const int n = wn + ct * 16 + lc;
+            const float w30 = bf2f((uint16_t)(w3c[ct] & 0xFFFFu)), w31 = bf2f((uint16_t)(w3c[ct] >> 16));
+            float gv[4];
+            uint16_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int row = rt * 16 + lg * 4 + i;
+                gv[i] = ds[row][0] * w30 + ds[row][1] * w31;
+                if (!(h2[rt][ct][i] > 0.f)) gv[i] = 0.f;
+                h[i] = f2bf(gv[i]);
+                H1s[row * kRowLds + n] = h[i];
+            }
+            const uint2 q = {(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+            *reinterpret_cast<uint2 *>(A.d2t + frag(n, r0 + rt * 16 + lg * 4, B)) = q;
+            A.part[(r0 / 4 + rt * 4 + lg) * kPart + n] = ((gv[0] + gv[1]) + gv[2]) + gv[3];
+        }
+    lds_barrier();
+    // dH1 = (dH2 W2^T) * (H1 > 0), its column sums: per lane its rows in
+    // order, then the four lane groups
+    float cs[2] = {0.f, 0.f};
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++) {
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int ks = 0; ks < 8; ks++) {
+            const bf16x8 df = *reinterpret_cast<const bf16x8 *>(&H1s[(rt * 16 + lc) * kRowLds + ks * 32 + lk]);
+#pragma unroll
+            for (int ct = 0; ct < 2; ct++)
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df, w2b[ct][ks], acc[ct], 0, 0, 0);
+        }
+#pragma unroll
+        for (int ct = 0; ct < 2; ct++) {
+            const int n = wn + ct * 16 + lc;
+            uint16_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float v = on1[rt][ct][i] ? acc[ct][i] : 0.f;
+                h[i] = f2bf(v);
+                cs[ct] += v;
+            }
+            const uint2 q = {(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+            *reinterpret_cast<uint2 *>(A.d1t + frag(n, r0 + rt * 16 + lg * 4, B)) = q;
+        }
     }
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int i = lane * 4 + j;
-        float gv = d0 * w30[j] + d1 * w31[j];
-        if (!(h[j] > 0.f) || r >= rows) gv = 0.f;
-        if (r < rows) dH2[r * kHid + i] = f2bf(gv);
-        rowg[wv][i] = gv;
+    for (int ct = 0; ct < 2; ct++) {
+        const float c0 = __shfl(cs[ct], lc, 64), c1 = __shfl(cs[ct], lc + 16, 64);
+        const float c2 = __shfl(cs[ct], lc + 32, 64), c3 = __shfl(cs[ct], lc + 48, 64);
+        if (lane < 16) A.colpart[(int64_t)blockIdx.x * kHid + wn + ct * 16 + lane] = ((c0 + c1) + c2) + c3;
     }
-    if (lane == 0) {
-        rowx[wv][0] = d0;
-        rowx[wv][1] = d1;
-        rowx[wv][2] = l2;
-    }
-    __syncthreads();
-    float *pp = part + (int64_t)blockIdx.x * (kHid + 3);
-    pp[tid] = ((rowg[0][tid] + rowg[1][tid]) + rowg[2][tid]) + rowg[3][tid];
-    if (tid < 3) pp[kHid + tid] = ((rowx[0][tid] + rowx[1][tid]) + rowx[2][tid]) + rowx[3][tid];
 }
 
-// db2, db3 and the loss from k_out's per-block partials [rows][kHid + 3].
-// Under graph-captured training (tab) this also advances the step index
-// tab[0]: the step's minibatch is staged by then and Adam reads tab[0] - 1.
-__global__ __launch_bounds__(1024) void k_reduce_out(const float *part, int rows, float *grads, float *loss,
-                                                      int32_t *tab) {
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const float t = col_sum(part, rows, kHid + 3, c);
-    if (threadIdx.x < 64) {
-        if (c < kHid) grads[kOffB2 + c] = t;
-        else if (c < kHid + 2) grads[kOffB3 + (c - kHid)] = t;
-        else if (c == kHid + 2) loss[0] = t;
-    }
-    if (tab && blockIdx.x == 0 && threadIdx.x == 0) tab[0] += 1;
-}
-
-// dW3[i, c] = sum_r H2[r, i] dY[r, c]; dY recomputed from Y and T.
-__global__ __launch_bounds__(256) void k_dw3(const uint16_t *H2, const float *Y, const float *T, int64_t rows,
-                                             float *grads) {
-    const int i = blockIdx.x;  // hidden unit
-    const float scale = 1.0f / (float)rows;
-    float a0 = 0.f, a1 = 0.f;
-    for (int64_t r = threadIdx.x; r < rows; r += 256) {
-        const float h = bf2f(H2[r * kHid + i]);
-        a0 += h * (Y[2 * r] - T[2 * r]) * scale;
-        a1 += h * (Y[2 * r + 1] - T[2 * r + 1]) * scale;
-    }
-    __shared__ float s0[256], s1[256];
-    s0[threadIdx.x] = a0;
-    s1[threadIdx.x] = a1;
-    __syncthreads();
-    for (int off = 128; off >= 1; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            s0[threadIdx.x] += s0[threadIdx.x + off];
-            s1[threadIdx.x] += s1[threadIdx.x + off];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        grads[kOffW3 + 2 * i] = s0[0];
-        grads[kOffW3 + 2 * i + 1] = s1[0];
-    }
-}
+struct ParamArgs {
+    const float *t;                     // targets (minibatch 0 when tab is set)
+    int64_t rows;
+    int32_t *tab;                       // graph-captured training: step index, index of the step in hand, corrections
+    int32_t steps, tabn;
+    const uint16_t *xt, *h1t, *h2t, *d2t, *d1t;
+    const float *y, *part, *colpart;
+    int32_t chunk1, n1, chunk2, n2;     // batch rows per partial product and their number: dW1, dW2
+    float *grads, *loss;                // gradients out (nullptr: Adam)
+    float *p, *m, *v;                   // Adam
+    float lr, bc1, bc2;
+    uint16_t *w1t, *w2, *w2t, *w3;
+};
 
 // Adam (Kingma and Ba) with bias correction, then the bf16 weight shadows.
-// With a table `tab` (graph-captured training) the corrections of the
-// current step are read from it instead: tab[0] - 1 is the step index i
-// within the call (advanced by k_reduce_out), tab[1 + 2i] and tab[2 + 2i]
-// hold 1 - 0.9^step and 1 - 0.999^step as computed by the host for the eager
-// step, so both routes round alike.
-__global__ void k_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float bc1, float bc2,
-                       uint16_t *w1, uint16_t *w2, uint16_t *w3, const int32_t *tab, int32_t tabn) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (tab) {
-        const int32_t s = min(max(tab[0] - 1, 0), tabn - 1);
-        bc1 = __int_as_float(tab[1 + 2 * s]);
-        bc2 = __int_as_float(tab[2 + 2 * s]);
+__device__ __forceinline__ void put_param(const ParamArgs &A, int64_t i, float gi, float bc1, float bc2) {
+    if (A.grads) {
+        A.grads[i] = gi;
+        return;
     }
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-    p[i] = pi;
-    if (i < kOffB1) w1[i - kOffW1] = f2bf(pi);
-    else if (i >= kOffW2 && i < kOffB2) w2[i - kOffW2] = f2bf(pi);
-    else if (i >= kOffW3 && i < kOffB3) w3[i - kOffW3] = f2bf(pi);
+    const float mi = b1 * A.m[i] + (1.f - b1) * gi;
+    const float vi = b2 * A.v[i] + (1.f - b2) * gi * gi;
+    A.m[i] = mi;
+    A.v[i] = vi;
+    const float pi = A.p[i] - A.lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+    A.p[i] = pi;
+    const uint16_t h = f2bf(pi);
+    if (i < kOffB1) {
+        const int k = (int)(i - kOffW1);
+        A.w1t[frag(k % kHid, k / kHid, kIn)] = h;
+    } else if (i >= kOffW2 && i < kOffB2) {
+        const int k = (int)(i - kOffW2);
+        A.w2[frag(k / kHid, k % kHid, kHid)] = h;
+        A.w2t[frag(k % kHid, k / kHid, kHid)] = h;
+    } else if (i >= kOffW3 && i < kOffB3) {
+        A.w3[i - kOffW3] = h;
+    }
 }
 
-// Minibatch of graph-captured training: rows [o, o + rows) of x (to bf16)
-// and of t (copied), o = rows * (tab[0] mod steps), so one captured step
-// serves every minibatch of an epoch.
-__global__ void k_stage(const float *x, const float *t, const int32_t *tab, int32_t steps, int64_t rows,
-                        uint16_t *xb, float *ts) {
-    const int64_t o = rows * (int64_t)((uint32_t)tab[0] % (uint32_t)steps);
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < rows * kIn) xb[i] = f2bf(x[o * kIn + i]);
-    if (i < rows * kOut) ts[i] = t[o * kOut + i];
+// A 16 x 16 tile of a weight gradient, sum over the batch of P[m0 + r][k]
+// Q[n0 + c][k] (operands [unit][rows]): the batch in `nch` chunks, each
+// chunk's product accumulated on the matrix cores, the chunks summed in
+// order.  A wave takes four chunks of every kChunks; returns element
+// (tid / 16, tid % 16).
+__device__ __forceinline__ float grad_tile(const uint16_t *P, const uint16_t *Q, int64_t rows, int32_t chunk,
+                                           int32_t nch, float *sum_lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lc = lane & 15;
+    const uint16_t *p = P + lane * 8, *q = Q + lane * 8;
+    float s = 0.f;
+    for (int32_t c0 = 0; c0 < nch; c0 += kChunks) {
+        f32x4 acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // the wave's four chunks side by side, so that their loads overlap;
+        // reads past a chunk's end are replaced by zeros, which add nothing
+        const int64_t k0 = (int64_t)(c0 + wv * 4) * chunk;
+        for (int32_t k = 0; k < chunk; k += 64) {
+            bf16x8 a[4][2], b[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    const int64_t kk = k0 + (int64_t)j * chunk + k + u * 32;
+                    const bool ok = k + u * 32 < chunk && kk < rows;
+                    a[j][u] = ok ? *reinterpret_cast<const bf16x8 *>(p + kk * 16) : bf16x8{};
+                    b[j][u] = ok ? *reinterpret_cast<const bf16x8 *>(q + kk * 16) : bf16x8{};
+                }
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+#pragma unroll
+                for (int u = 0; u < 2; u++)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][u], b[j][u], acc[j], 0, 0, 0);
+        }
+        if (c0) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                sum_lds[(wv * 4 + j) * 256 + ((lane >> 4) * 4 + i) * 16 + lc] = acc[j][i];
+        __syncthreads();
+        const int32_t m = min(kChunks, nch - c0);
+        for (int32_t z = 0; z < m; z++) s = c0 + z == 0 ? sum_lds[tid] : s + sum_lds[z * 256 + tid];
+    }
+    return s;
 }
 
-__global__ void k_shadow(const float *p, uint16_t *w1, uint16_t *w2, uint16_t *w3) {
+// Columns [c0, c0 + 16) of partial sums: share w of 16 adds its contiguous
+// part of the rows in order, then the 16 shares are added in order; the
+// result is in threads 0..15.  `get` reads row r, column c.
+template <typename F>
+__device__ __forceinline__ float col_sum16(int rows, bool ok, float *red, F get) {
+    const int tid = threadIdx.x, w = tid >> 4, c = tid & 15;
+    const int per = (rows + 15) / 16, a = min(rows, w * per), z = min(rows, a + per);
+    float s = 0.f;
+    if (ok) {
+#pragma unroll 16
+        for (int r = a; r < z; r++) s += get(r);
+    }
+    red[w * 16 + c] = s;
+    __syncthreads();
+    float u = red[c];
+#pragma unroll
+    for (int i = 1; i < 16; i++) u += red[i * 16 + c];
+    return u;
+}
+
+// Work-groups of k_params_step, the longest first: dW2's 16 x 16 tiles, dW1's,
+// dW3 (a wave per hidden unit), db1, and db2 with db3 and the loss.
+constexpr int kGW2 = (kHid / 16) * (kHid / 16), kGW1 = (kIn / 16) * (kHid / 16), kGW3 = kHid / 4, kGB1 = kHid / 16,
+              kGB2 = (kPart + 15) / 16, kGrid2 = kGW2 + kGW1 + kGW3 + kGB1 + kGB2;
+
+// Weight gradients and (without `grads`) Adam.  One 16 x 16 tile per
+// work-group gives dW2 all 256 CUs at any batch; each work-group reads 16
+// rows of either operand along the whole batch (64 KB at batch 1024, from
+// the L2).  With a table (graph-captured training) tab[1] is the step in
+// hand, left by k_rows_step, whose bias corrections 1 - 0.9^step and
+// 1 - 0.999^step, computed by the host, are at tab[2 + 2 i] and tab[3 + 2 i];
+// tab[0] becomes the next step's index.  (No work-group of either kernel reads
+// the word that the same kernel writes.)
+__global__ __launch_bounds__(256) void k_params_step(ParamArgs A) {
+    __shared__ float lds[kChunks * 256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    float bc1 = A.bc1, bc2 = A.bc2;
+    int64_t o = 0;
+    if (A.tab) {
+        const int32_t s = A.tab[1], i = min(max(s, 0), A.tabn - 1);
+        bc1 = __int_as_float(A.tab[2 + 2 * i]);
+        bc2 = __int_as_float(A.tab[3 + 2 * i]);
+        o = A.rows * (int64_t)((uint32_t)s % (uint32_t)A.steps);
+        if (blockIdx.x == gridDim.x - 1 && tid == 0) A.tab[0] = s + 1;
+    }
+    const int64_t B = A.rows;
+    int b = blockIdx.x;
+    if (b < kGW2) {
+        const int m0 = b / 16 * 16, n0 = b % 16 * 16;
+        const float g = grad_tile(A.h1t + (int64_t)m0 * B, A.d2t + (int64_t)n0 * B, B, A.chunk2, A.n2, lds);
+        put_param(A, kOffW2 + (m0 + (tid >> 4)) * kHid + n0 + (tid & 15), g, bc1, bc2);
+        return;
+    }
+    b -= kGW2;
+    if (b < kGW1) {
+        const int m0 = b / 16 * 16, n0 = b % 16 * 16;
+        const float g = grad_tile(A.xt + (int64_t)m0 * B, A.d1t + (int64_t)n0 * B, B, A.chunk1, A.n1, lds);
+        put_param(A, kOffW1 + (m0 + (tid >> 4)) * kHid + n0 + (tid & 15), g, bc1, bc2);
+        return;
+    }
+    b -= kGW1;
+    if (b < kGW3) {
+        // dW3[i][c] = sum over rows of H2[r][i] dY[r][c]: 256 running sums,
+        // row r into sum r % 256 (lane l has sums l, l + 64, l + 128 and
+        // l + 192), then halved down to one
+        const int i = b * 4 + wv;
+        const float *t = A.t + o * kOut;
+        const uint16_t *h2 = A.h2t + (int64_t)i * B;
+        const float scale = 1.0f / (float)B;
+        float a0[4] = {0.f, 0.f, 0.f, 0.f}, a1[4] = {0.f, 0.f, 0.f, 0.f};
+        // four rounds of 256 rows are read together
+        for (int64_t r1 = 0; r1 < B; r1 += 1024) {
+            uint16_t hh[4][4];
+            float yy[4][4][2], ty[4][4][2];
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int64_t r = r1 + u * 256 + j * 64 + lane, q = min(r, B - 1);
+                    hh[u][j] = h2[q];
+                    yy[u][j][0] = A.y[2 * q];
+                    yy[u][j][1] = A.y[2 * q + 1];
+                    ty[u][j][0] = t[2 * q];
+                    ty[u][j][1] = t[2 * q + 1];
+                }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    if (r1 + u * 256 + j * 64 + lane < B) {
+                        const float h = bf2f(hh[u][j]);
+                        a0[j] += h * (yy[u][j][0] - ty[u][j][0]) * scale;
+                        a1[j] += h * (yy[u][j][1] - ty[u][j][1]) * scale;
+                    }
+                }
+        }
+        const float g0 = wave_sum_halving((a0[0] + a0[2]) + (a0[1] + a0[3]));
+        const float g1 = wave_sum_halving((a1[0] + a1[2]) + (a1[1] + a1[3]));
+        if (lane < 2) put_param(A, kOffW3 + 2 * i + lane, lane ? g1 : g0, bc1, bc2);
+        return;
+    }
+    b -= kGW3;
+    const int c = tid & 15;
+    if (b < kGB1) {
+        // tiles of 64 rows, each the sum of its two halves
+        const int n = b * 16 + c, halves = (int)(B / kRows);
+        const float g = col_sum16((halves + 1) / 2, true, lds, [&](int r) {
+            const float *q = A.colpart + (int64_t)(2 * r) * kHid + n;
+            return q[0] + (2 * r + 1 < halves ? q[kHid] : 0.f);
+        });
+        if (tid < 16) put_param(A, kOffB1 + n, g, bc1, bc2);
+        return;
+    }
+    b -= kGB1;
+    const int n = b * 16 + c;
+    const float g = col_sum16((int)(B / 4), n < kPart, lds, [&](int r) { return A.part[(int64_t)r * kPart + n]; });
+    if (tid < 16) {
+        if (n < kHid) put_param(A, kOffB2 + n, g, bc1, bc2);
+        else if (n < kHid + 2) put_param(A, kOffB3 + (n - kHid), g, bc1, bc2);
+        else if (n == kHid + 2) A.loss[0] = g;
+    }
+}
+
+// The bf16 weight shadows of the fp32 parameters.
+__global__ void k_shadow(const float *p, uint16_t *w1t, uint16_t *w2, uint16_t *w2t, uint16_t *w3) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < kOffB1) w1[i] = f2bf(p[i]);
-    else if (i >= kOffW2 && i < kOffB2) w2[i - kOffW2] = f2bf(p[i]);
-    else if (i >= kOffW3 && i < kOffB3) w3[i - kOffW3] = f2bf(p[i]);
+    if (i < kOffB1) {
+        const int k = (int)(i - kOffW1);
+        w1t[frag(k % kHid, k / kHid, kIn)] = f2bf(p[i]);
+    } else if (i >= kOffW2 && i < kOffB2) {
+        const int k = (int)(i - kOffW2);
+        w2[frag(k / kHid, k % kHid, kHid)] = f2bf(p[i]);
+        w2t[frag(k % kHid, k / kHid, kHid)] = f2bf(p[i]);
+    } else if (i >= kOffW3 && i < kOffB3) {
+        w3[i - kOffW3] = f2bf(p[i]);
+    }
 }
 
 // Fused inference: y = W3^T relu(W2^T relu(W1^T x + b1) + b2) + b3 and the
@@ -470,7 +590,6 @@ __global__ void k_shadow(const float *p, uint16_t *w1, uint16_t *w2, uint16_t *w
 // one row.  With NW = 8 the fragments take half the registers of
 // NW = 4, so two waves share each SIMD and one's MFMA overlaps the other's
 // conversions and LDS traffic.
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 // ReLU of two packed bf16 values at once: a bf16 is negative exactly when its
@@ -485,8 +604,8 @@ constexpr int kRT = 64, kH1Row = kHid + 8;
 constexpr int kInferWaves = 8;
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows, const uint16_t *W1, const float *b1,
-                                                    const uint16_t *W2, const float *b2, const uint16_t *W3,
+__global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows, const uint16_t *W1t, const float *b1,
+                                                    const uint16_t *W2t, const float *b2, const uint16_t *W3,
                                                     const float *b3, float *Y, int32_t *est) {
     constexpr int CT = kHid / NW / 16;  // 16-column MFMA tiles per wave
     __shared__ __attribute__((aligned(16))) uint16_t H1s[kRT * kH1Row];
@@ -498,17 +617,11 @@ __global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows,
     bf16x2_t w30[CT][2], w31[CT][2];  // output weights of hidden units (i, i + 1), as packed bf16 pairs
 #pragma unroll
     for (int ct = 0; ct < CT; ct++) {
-        const int n = wn + ct * 16 + lc;
-        u16x8 t;
+        const int nt = wv * CT + ct;  // the tile's place among the fragments
+        w1f[ct] = *reinterpret_cast<const bf16x8 *>(W1t + (nt * 64 + lane) * 8);
 #pragma unroll
-        for (int i = 0; i < 8; i++) t[i] = W1[(lk + i) * kHid + n];
-        w1f[ct] = __builtin_bit_cast(bf16x8, t);
-#pragma unroll
-        for (int ks = 0; ks < 8; ks++) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) t[i] = W2[(ks * 32 + lk + i) * kHid + n];
-            w2f[ks][ct] = __builtin_bit_cast(bf16x8, t);
-        }
+        for (int ks = 0; ks < 8; ks++)
+            w2f[ks][ct] = *reinterpret_cast<const bf16x8 *>(W2t + ((nt * 8 + ks) * 64 + lane) * 8);
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             // the hidden unit this lane's accumulator value i holds in either layer
@@ -631,65 +744,14 @@ __global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows,
 
 static unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
-// out[i] = sum over z = 0 .. S-1, in order, of part[z pstride + i].
-__global__ void k_ksum(const float *part, int S, int64_t pstride, int64_t n, float *out) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = part[i];
-#pragma unroll 8
-    for (int z = 1; z < S; z++) s += part[z * pstride + i];
-    out[i] = s;
-}
-
-constexpr int64_t kKSplitFloats = 16 * kHid * kHid;  // split-K partial buffer
-
 static bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
-// Launch C = A B.  A plain fp32 product with a contiguous C (ldc == N) and
-// few output tiles splits K over the partial buffer `kpart`
-// (kKSplitFloats floats) so that the grid fills the chip.
-// A product's launch shape: operand read modes, the output tiles (gx, gy)
-// and, for a plain fp32 output when kpart is given, a split of K over S
-// work-groups whose partials go to kpart (out: where their sum belongs).
-struct GemmPlan {
-    int gx, gy, S;
-    float *out;
-};
-static GemmPlan gemm_plan(GemmArgs &g, float *kpart) {
-    g.amode = (g.sak == 1 && g.sam % 8 == 0 && g.K % 8 == 0 && aligned16(g.A)) ? 1
-              : (g.sam == 1 && g.sak % 8 == 0 && g.M % 8 == 0 && aligned16(g.A)) ? 2 : 0;
-    g.bmode = (g.sbk == 1 && g.sbn % 8 == 0 && g.K % 8 == 0 && aligned16(g.B)) ? 1
-              : (g.sbn == 1 && g.sbk % 8 == 0 && g.N % 8 == 0 && aligned16(g.B)) ? 2 : 0;
-    GemmPlan pl;
-    pl.gx = (g.N + kTN - 1) / kTN;
-    pl.gy = (g.M + kTM - 1) / kTM;
-    pl.out = g.C32;
-    const int kt = (g.K + kTK - 1) / kTK;
-    int S = 1;
-    if (kpart && g.C32 && !g.C16 && !g.bias && !g.relu && !g.mask && !g.colpart && g.ldc == g.N) {
-        const int64_t mn = (int64_t)g.M * g.N;
-        S = std::min<int64_t>({(int64_t)kt, std::max(1, 256 / (pl.gx * pl.gy)),
-                               kKSplitFloats / std::max<int64_t>(mn, 1)});
-        if (S > 1) {
-            g.kchunk = ((kt + S - 1) / S) * kTK;
-            S = (g.K + g.kchunk - 1) / g.kchunk;
-        }
-    }
-    pl.S = std::max(S, 1);
-    g.ksplit = pl.S;
-    if (pl.S > 1) {
-        g.pstride = (int64_t)g.M * g.N;
-        g.C32 = kpart;
-    }
-    return pl;
-}
-
-static void gemm(hipStream_t st, GemmArgs g, float *kpart = nullptr) {
-    const GemmPlan pl = gemm_plan(g, kpart);
-    hipLaunchKernelGGL(k_gemm, dim3(pl.gx, pl.gy, pl.S), dim3(256), 0, st, g);
-    if (pl.S > 1)
-        hipLaunchKernelGGL(k_ksum, dim3(blocks(g.pstride, 256)), dim3(256), 0, st, kpart, pl.S, g.pstride, g.pstride,
-                           pl.out);
+// Chunks of the batch in a weight gradient of `tiles` 64 x 64 output tiles:
+// as many as fill 256 work-groups of one tile each, at most `most`.
+static void batch_chunks(int64_t rows, int tiles, int64_t most, int32_t *chunk, int32_t *n) {
+    const int64_t kt = (rows + 31) / 32, S = std::min<int64_t>({kt, (int64_t)std::max(1, 256 / tiles), most});
+    *chunk = (int32_t)((kt + S - 1) / S * 32);
+    *n = (int32_t)((rows + *chunk - 1) / *chunk);
 }
 
 }  // namespace insp
@@ -700,17 +762,15 @@ struct insp_mlp {
     int device = 0;
     int64_t step = 0;
     DevBuf p, g, m, v;            // fp32 [kParams]
-    DevBuf w1, w2, w3;            // bf16 shadows
+    DevBuf w1t, w2, w2t, w3;      // bf16 shadows: [256][32], [256][256], its transpose, [256][2]
     DevBuf loss;                  // fp32 [1]
     int64_t cap = 0;              // rows the activation buffers hold
-    DevBuf xb, h1, h2, dh2, dh1;  // bf16 activations and gradients
+    DevBuf xt, h1t, h2t, d2t, d1t;  // bf16 [unit][rows] activations and gradients
     DevBuf y;                     // fp32 [cap, 2]
-    DevBuf part;                  // fp32 partial sums for the fixed-order reductions
-    DevBuf kpart;                 // fp32 [kKSplitFloats] split-K partial products
+    DevBuf part, colpart;         // fp32 partial sums for the fixed-order reductions
     int64_t gen = 0;              // bumped whenever a buffer above moves
     // graph-captured training
-    DevBuf ts;                    // fp32 [cap, 2] staged targets
-    DevBuf tab;                   // int32 step index, then the bias-correction table
+    DevBuf tab;                   // int32 step index, step in hand, then the bias-correction table
     hipStream_t cs = nullptr;     // capture stream
     hipGraphExec_t exec = nullptr;
     struct Key {
@@ -736,10 +796,10 @@ struct insp_mlp {
 // succeeded, so a failure (INSP_E_NOMEM) leaves the model as it was.
 static int mlp_reserve(insp_mlp *m, int64_t rows) {
     if (rows <= m->cap) return INSP_OK;
-    DevBuf *cur[8] = {&m->xb, &m->h1, &m->h2, &m->dh2, &m->dh1, &m->y, &m->part, &m->ts};
+    DevBuf *cur[8] = {&m->xt, &m->h1t, &m->h2t, &m->d2t, &m->d1t, &m->y, &m->part, &m->colpart};
     const size_t bytes[8] = {(size_t)(2 * kIn * rows),  (size_t)(2 * kHid * rows), (size_t)(2 * kHid * rows),
                              (size_t)(2 * kHid * rows), (size_t)(2 * kHid * rows), (size_t)(4 * kOut * rows),
-                             (size_t)(4 * ((rows + 3) / 4 + 1) * (kHid + 3)), (size_t)(4 * kOut * rows)};
+                             (size_t)(4 * (rows / 4) * kPart), (size_t)(4 * (rows / kRows) * kHid)};
     DevBuf fresh[8];
     for (int i = 0; i < 8; i++)
         if (int rc = fresh[i].alloc(bytes[i])) return rc;
@@ -749,87 +809,71 @@ static int mlp_reserve(insp_mlp *m, int64_t rows) {
     return INSP_OK;
 }
 
-// Forward over `rows` rows of fp32 features into the bf16 activation buffers
-// (x == nullptr: the bf16 features are already staged in m->xb).
-static void mlp_forward(insp_mlp *m, const float *x, int64_t rows, hipStream_t st) {
-    const float *P = m->p.as<float>();
-    if (x)
-        hipLaunchKernelGGL(k_to_bf16, dim3(blocks(rows * kIn, 256)), dim3(256), 0, st, x, m->xb.as<uint16_t>(),
-                           rows * kIn);
-    GemmArgs g;
-    memset(&g, 0, sizeof g);
-    g.M = (int)rows; g.N = kHid; g.K = kIn;
-    g.A = m->xb.as<uint16_t>(); g.sam = kIn; g.sak = 1;
-    g.B = m->w1.as<uint16_t>(); g.sbk = kHid; g.sbn = 1;
-    g.bias = P + kOffB1; g.relu = 1;
-    g.C16 = m->h1.as<uint16_t>(); g.ldc16 = kHid;
-    gemm(st, g);
-    g.K = kHid;
-    g.A = m->h1.as<uint16_t>(); g.sam = kHid;
-    g.B = m->w2.as<uint16_t>();
-    g.bias = P + kOffB2;
-    g.C16 = m->h2.as<uint16_t>();
-    gemm(st, g);
-}
+// What a step writes besides the parameters: gradients (instead of Adam's
+// update), outputs and loss.
+struct StepOut {
+    float *grads, *y, *loss;
+};
 
-// Loss and gradients of one batch into m->g; y out optional.  Every sum is
-// taken in a fixed order, so a step is bit-reproducible.  With `tab` the
-// batch is minibatch tab[0] mod `steps` of x and t (graph-captured training).
-static int mlp_backward(insp_mlp *m, const float *x, const float *t, int64_t B, hipStream_t st,
-                        int32_t *tab = nullptr, int32_t steps = 0) {
-    float *G = m->g.as<float>();
-    float *part = m->part.as<float>();
-    if (tab) {
-        hipLaunchKernelGGL(k_stage, dim3(blocks(B * kIn, 256)), dim3(256), 0, st, x, t, tab, steps, B,
-                           m->xb.as<uint16_t>(), m->ts.as<float>());
-        x = nullptr;
-        t = m->ts.as<float>();
-    }
-    mlp_forward(m, x, B, st);
-    const int ob = (int)((B + 3) / 4);
-    hipLaunchKernelGGL(k_out, dim3(ob), dim3(256), 0, st, m->h2.as<uint16_t>(), m->w3.as<uint16_t>(),
-                       m->p.as<float>() + kOffB3, B, m->y.as<float>(), t, part, m->dh2.as<uint16_t>(),
-                       (int32_t *)nullptr);
-    // db2 (256 columns), db3 (2) and the loss (1) from the block partials;
-    // with tab the step index advances here
-    hipLaunchKernelGGL(k_reduce_out, dim3(blocks(kHid + 3, 64)), dim3(1024), 0, st, part, ob, G,
-                       m->loss.as<float>(), tab);
-    hipLaunchKernelGGL(k_dw3, dim3(kHid), dim3(256), 0, st, m->h2.as<uint16_t>(), m->y.as<float>(), t, B, G);
-    // dW2 = H1^T dH2 (K split over work-groups) and dH1 = (dH2 W2^T) * (H1 > 0)
-    // with its per-tile column sums, both from dH2: one launch; then the sum
-    // of dW2's partials and db1 (the column sums in order): one more
-    GemmArgs g, gh;
-    memset(&g, 0, sizeof g);
-    g.M = kHid; g.N = kHid; g.K = (int)B;
-    g.A = m->h1.as<uint16_t>(); g.sam = 1; g.sak = kHid;
-    g.B = m->dh2.as<uint16_t>(); g.sbk = kHid; g.sbn = 1;
-    g.C32 = G + kOffW2; g.ldc = kHid;
-    const GemmPlan pw = gemm_plan(g, m->kpart.as<float>());
-    memset(&gh, 0, sizeof gh);
-    gh.M = (int)B; gh.N = kHid; gh.K = kHid;
-    gh.A = m->dh2.as<uint16_t>(); gh.sam = kHid; gh.sak = 1;
-    gh.B = m->w2.as<uint16_t>(); gh.sbk = 1; gh.sbn = kHid;
-    gh.mask = m->h1.as<uint16_t>(); gh.smm = kHid; gh.smn = 1;
-    gh.C16 = m->dh1.as<uint16_t>(); gh.ldc16 = kHid;
-    gh.colpart = part;
-    const GemmPlan ph = gemm_plan(gh, nullptr);
-    const int nw = pw.gx * pw.gy * pw.S, nh = ph.gx * ph.gy;
-    hipLaunchKernelGGL(k_gemm2, dim3(nw + nh), dim3(256), 0, st, g, pw.gx, pw.gy, nw, gh, ph.gx, ph.gy);
-    const int cb = (int)blocks(kHid, 64);
-    if (pw.S > 1)
-        hipLaunchKernelGGL(k_colreduce_ksum, dim3(cb + (int)blocks(g.pstride, 1024)), dim3(1024), 0, st, part,
-                           (int)((B + kTM - 1) / kTM), kHid, G + kOffB1, cb, m->kpart.as<float>(), pw.S, g.pstride,
-                           g.pstride, pw.out);
+// One step over a batch of B rows (a multiple of 32): two launches.  With
+// `tab` the batch is minibatch tab[0] mod `steps` of x and t (graph-captured
+// training).
+static int mlp_step(insp_mlp *m, const float *x, const float *t, int64_t B, const StepOut &out, float lr, float bc1,
+                    float bc2, hipStream_t st, int32_t *tab = nullptr, int32_t steps = 1, int32_t tabn = 0) {
+    StepArgs a;
+    a.x = x;
+    a.t = t;
+    a.rows = B;
+    a.tab = tab;
+    a.steps = steps;
+    a.p = m->p.as<float>();
+    a.w1t = m->w1t.as<uint16_t>();
+    a.w2 = m->w2.as<uint16_t>();
+    a.w2t = m->w2t.as<uint16_t>();
+    a.w3 = m->w3.as<uint16_t>();
+    a.xt = m->xt.as<uint16_t>();
+    a.h1t = m->h1t.as<uint16_t>();
+    a.h2t = m->h2t.as<uint16_t>();
+    a.d2t = m->d2t.as<uint16_t>();
+    a.d1t = m->d1t.as<uint16_t>();
+    a.y = out.y;
+    a.part = m->part.as<float>();
+    a.colpart = m->colpart.as<float>();
+    a.cur = tab ? tab + 1 : nullptr;
+    // rows are 128 bytes, so every minibatch is aligned when x is
+    if (aligned16(x))
+        hipLaunchKernelGGL(k_rows_step<true>, dim3((unsigned)(B / kRows)), dim3(64 * kRowWaves), 0, st, a);
     else
-        hipLaunchKernelGGL(k_colreduce, dim3(cb), dim3(1024), 0, st, part, (int)((B + kTM - 1) / kTM), kHid,
-                           G + kOffB1);
-    // dW1 = X^T dH1
-    memset(&g, 0, sizeof g);
-    g.M = kIn; g.N = kHid; g.K = (int)B;
-    g.A = m->xb.as<uint16_t>(); g.sam = 1; g.sak = kIn;
-    g.B = m->dh1.as<uint16_t>(); g.sbk = kHid; g.sbn = 1;
-    g.C32 = G + kOffW1; g.ldc = kHid;
-    gemm(st, g, m->kpart.as<float>());
+        hipLaunchKernelGGL(k_rows_step<false>, dim3((unsigned)(B / kRows)), dim3(64 * kRowWaves), 0, st, a);
+    ParamArgs q;
+    q.t = t;
+    q.rows = B;
+    q.tab = tab;
+    q.steps = steps;
+    q.tabn = tabn;
+    q.xt = a.xt;
+    q.h1t = a.h1t;
+    q.h2t = a.h2t;
+    q.d2t = a.d2t;
+    q.d1t = a.d1t;
+    q.y = out.y;
+    q.part = a.part;
+    q.colpart = a.colpart;
+    batch_chunks(B, kHid / 64, 128, &q.chunk1, &q.n1);
+    batch_chunks(B, (kHid / 64) * (kHid / 64), 16, &q.chunk2, &q.n2);
+    q.grads = out.grads;
+    q.loss = out.loss;
+    q.p = m->p.as<float>();
+    q.m = m->m.as<float>();
+    q.v = m->v.as<float>();
+    q.lr = lr;
+    q.bc1 = bc1;
+    q.bc2 = bc2;
+    q.w1t = m->w1t.as<uint16_t>();
+    q.w2 = m->w2.as<uint16_t>();
+    q.w2t = m->w2t.as<uint16_t>();
+    q.w3 = m->w3.as<uint16_t>();
+    hipLaunchKernelGGL(k_params_step, dim3(kGrid2), dim3(256), 0, st, q);
     INSP_HIP(hipGetLastError());
     return INSP_OK;
 }
@@ -840,14 +884,15 @@ extern "C" int insp_mlp_create(const float *params, insp_mlp **out) {
     INSP_HIP(hipGetDevice(&m->device));
     int rc;
     if ((rc = m->p.alloc(4 * kParams)) || (rc = m->g.alloc(4 * kParams)) || (rc = m->m.alloc(4 * kParams)) ||
-        (rc = m->v.alloc(4 * kParams)) || (rc = m->w1.alloc(2 * kIn * kHid)) || (rc = m->w2.alloc(2 * kHid * kHid)) ||
-        (rc = m->w3.alloc(2 * kHid * kOut)) || (rc = m->loss.alloc(4)) || (rc = m->kpart.alloc(4 * kKSplitFloats)))
+        (rc = m->v.alloc(4 * kParams)) || (rc = m->w1t.alloc(2 * kIn * kHid)) ||
+        (rc = m->w2.alloc(2 * kHid * kHid)) || (rc = m->w2t.alloc(2 * kHid * kHid)) ||
+        (rc = m->w3.alloc(2 * kHid * kOut)) || (rc = m->loss.alloc(4)))
         return rc;
     INSP_HIP(hipMemcpy(m->p.p, params, 4 * kParams, hipMemcpyHostToDevice));
     INSP_HIP(hipMemset(m->m.p, 0, 4 * kParams));
     INSP_HIP(hipMemset(m->v.p, 0, 4 * kParams));
-    hipLaunchKernelGGL(k_shadow, dim3(blocks(kParams, 256)), dim3(256), 0, 0, m->p.as<float>(), m->w1.as<uint16_t>(),
-                       m->w2.as<uint16_t>(), m->w3.as<uint16_t>());
+    hipLaunchKernelGGL(k_shadow, dim3(blocks(kParams, 256)), dim3(256), 0, 0, m->p.as<float>(), m->w1t.as<uint16_t>(),
+                       m->w2.as<uint16_t>(), m->w2t.as<uint16_t>(), m->w3.as<uint16_t>());
     INSP_HIP(hipGetLastError());
     INSP_HIP(hipDeviceSynchronize());
     *out = m.release();
@@ -865,16 +910,34 @@ static int check_device(const insp_mlp *m) {
     return INSP_OK;
 }
 
+// Whether [p, p + n) and [q, q + k) share a byte.
+static bool overlap(const void *p, size_t n, const void *q, size_t k) {
+    const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
+    return a < b + k && b < a + n;
+}
+
 extern "C" int insp_mlp_grads(insp_mlp *m, const float *x, const float *t, int32_t batch, float *grads, float *y,
                               float *loss, void *stream) {
     if (!m || !x || !t || batch < 1 || batch % 32) return set_error(INSP_E_INVAL, "bad argument");
     hipStream_t st = (hipStream_t)stream;
     int rc;
-    if ((rc = check_device(m))) return rc;
-    if ((rc = mlp_reserve(m, batch)) || (rc = mlp_backward(m, x, t, batch, st))) return rc;
-    if (grads) INSP_HIP(hipMemcpyAsync(grads, m->g.p, 4 * kParams, hipMemcpyDeviceToDevice, st));
-    if (y) INSP_HIP(hipMemcpyAsync(y, m->y.p, 4 * kOut * (size_t)batch, hipMemcpyDeviceToDevice, st));
-    if (loss) INSP_HIP(hipMemcpyAsync(loss, m->loss.p, 4, hipMemcpyDeviceToDevice, st));
+    if ((rc = check_device(m)) || (rc = mlp_reserve(m, batch))) return rc;
+    // results go straight to the caller's arrays; one that shares memory with
+    // the inputs or another result is filled by a copy at the end, as nothing
+    // may change an input that is still read
+    const size_t xb = 4 * kIn * (size_t)batch, tb = 4 * kOut * (size_t)batch;
+    struct { float *user, *own; size_t bytes; float *to; } o[3] = {
+        {grads, m->g.as<float>(), 4 * kParams, nullptr}, {y, m->y.as<float>(), tb, nullptr},
+        {loss, m->loss.as<float>(), 4, nullptr}};
+    for (int i = 0; i < 3; i++) {
+        bool direct = o[i].user && !overlap(o[i].user, o[i].bytes, x, xb) && !overlap(o[i].user, o[i].bytes, t, tb);
+        for (int j = 0; j < 3; j++)
+            if (j != i && o[j].user && direct) direct = !overlap(o[i].user, o[i].bytes, o[j].user, o[j].bytes);
+        o[i].to = direct ? o[i].user : o[i].own;
+    }
+    if ((rc = mlp_step(m, x, t, batch, StepOut{o[0].to, o[1].to, o[2].to}, 0.f, 1.f, 1.f, st))) return rc;
+    for (auto &q : o)
+        if (q.user && q.to != q.user) INSP_HIP(hipMemcpyAsync(q.user, q.to, q.bytes, hipMemcpyDeviceToDevice, st));
     return INSP_OK;
 }
 
@@ -883,31 +946,21 @@ extern "C" int insp_mlp_train_step(insp_mlp *m, const float *x, const float *t, 
     if (!m || !x || !t || batch < 1 || batch % 32 || !(lr > 0.f)) return set_error(INSP_E_INVAL, "bad argument");
     hipStream_t st = (hipStream_t)stream;
     int rc;
-    if ((rc = check_device(m))) return rc;
-    if ((rc = mlp_reserve(m, batch)) || (rc = mlp_backward(m, x, t, batch, st))) return rc;
+    if ((rc = check_device(m)) || (rc = mlp_reserve(m, batch))) return rc;
+    const float bc1 = 1.f - powf(0.9f, (float)(m->step + 1)), bc2 = 1.f - powf(0.999f, (float)(m->step + 1));
+    if ((rc = mlp_step(m, x, t, batch, StepOut{nullptr, m->y.as<float>(), m->loss.as<float>()}, lr, bc1, bc2, st)))
+        return rc;
     m->step++;
-    const float bc1 = 1.f - powf(0.9f, (float)m->step), bc2 = 1.f - powf(0.999f, (float)m->step);
-    hipLaunchKernelGGL(k_adam, dim3(blocks(kParams, 256)), dim3(256), 0, st, m->p.as<float>(), m->g.as<float>(),
-                       m->m.as<float>(), m->v.as<float>(), kParams, lr, bc1, bc2, m->w1.as<uint16_t>(),
-                       m->w2.as<uint16_t>(), m->w3.as<uint16_t>(), (const int32_t *)nullptr, 0);
     if (loss) INSP_HIP(hipMemcpyAsync(loss, m->loss.p, 4, hipMemcpyDeviceToDevice, st));
-    INSP_HIP(hipGetLastError());
     return INSP_OK;
 }
 
-// One step of graph-captured training: minibatch tab[0] mod steps, the step
-// index advances once the minibatch is staged, Adam with the tabled
-// corrections of step tab[0] - 1.
+// One step of graph-captured training: minibatch tab[0] mod steps, Adam with
+// the tabled corrections of that step.
 static int train_enqueue(insp_mlp *m, const float *x, const float *t, int32_t steps, int32_t batch, float lr,
                          int32_t tabn, hipStream_t st) {
-    int32_t *tab = m->tab.as<int32_t>();
-    int rc;
-    if ((rc = mlp_backward(m, x, t, batch, st, tab, steps))) return rc;
-    hipLaunchKernelGGL(k_adam, dim3(blocks(kParams, 256)), dim3(256), 0, st, m->p.as<float>(), m->g.as<float>(),
-                       m->m.as<float>(), m->v.as<float>(), kParams, lr, 1.f, 1.f, m->w1.as<uint16_t>(),
-                       m->w2.as<uint16_t>(), m->w3.as<uint16_t>(), (const int32_t *)tab, tabn);
-    INSP_HIP(hipGetLastError());
-    return INSP_OK;
+    return mlp_step(m, x, t, batch, StepOut{nullptr, m->y.as<float>(), m->loss.as<float>()}, lr, 1.f, 1.f, st,
+                    m->tab.as<int32_t>(), steps, tabn);
 }
 
 // Captures `chunk` consecutive steps into m->exec (on the model's own
@@ -944,7 +997,7 @@ extern "C" int insp_mlp_train(insp_mlp *m, const float *x, const float *t, int64
     if (total == 0) return INSP_OK;
     if (total > kMaxTrainSteps) return set_error(INSP_E_RANGE, "more than 2^28 training steps in one call");
     hipStream_t st = (hipStream_t)stream;
-    const int64_t words = 1 + 2 * total;
+    const int64_t words = 2 + 2 * total;
     int rc;
     if ((rc = check_device(m))) return rc;
     if (m->cap < batch || m->tab.bytes < (size_t)(4 * words)) {
@@ -957,19 +1010,19 @@ extern "C" int insp_mlp_train(insp_mlp *m, const float *x, const float *t, int64
             m->gen++;
         }
     }
-    // step index 0, then the corrections of steps step+1 .. step+total, as
-    // the eager step computes them
+    // step index and step in hand 0, then the corrections of steps step+1 ..
+    // step+total, as the eager step computes them
     std::vector<int32_t> h((size_t)words);
-    h[0] = 0;
+    h[0] = h[1] = 0;
     for (int64_t s = 1; s <= total; s++) {
         const float bc1 = 1.f - powf(0.9f, (float)(m->step + s)), bc2 = 1.f - powf(0.999f, (float)(m->step + s));
-        memcpy(&h[2 * s - 1], &bc1, 4);
-        memcpy(&h[2 * s], &bc2, 4);
+        memcpy(&h[2 * s], &bc1, 4);
+        memcpy(&h[2 * s + 1], &bc2, 4);
     }
     INSP_HIP(hipMemcpyAsync(m->tab.p, h.data(), 4 * words, hipMemcpyHostToDevice, st));
     INSP_HIP(hipStreamSynchronize(st));  // h is released on return
     const int32_t chunk = (int32_t)std::min<int64_t>(total, kTrainChunk);
-    const int32_t tabn = (int32_t)((m->tab.bytes / 4 - 1) / 2);  // entries the table holds
+    const int32_t tabn = (int32_t)((m->tab.bytes / 4 - 2) / 2);  // entries the table holds
     const insp_mlp::Key k{x, t, (int32_t)steps, batch, chunk, lr, m->gen};
     if (!m->exec || !(k == m->key)) {
         m->key = insp_mlp::Key{};
@@ -999,8 +1052,8 @@ extern "C" int insp_mlp_predict(insp_mlp *m, const float *x, int64_t n, float *y
     const int64_t tiles = (n + kRT - 1) / kRT;
     const unsigned grid = (unsigned)std::min<int64_t>(tiles, (int64_t)cus * 2);
     ProfScope ps(st, "mlp_infer");
-    hipLaunchKernelGGL(k_infer<kInferWaves>, dim3(grid), dim3(64 * kInferWaves), 0, st, x, n, m->w1.as<uint16_t>(), m->p.as<float>() + kOffB1,
-                       m->w2.as<uint16_t>(), m->p.as<float>() + kOffB2, m->w3.as<uint16_t>(),
+    hipLaunchKernelGGL(k_infer<kInferWaves>, dim3(grid), dim3(64 * kInferWaves), 0, st, x, n, m->w1t.as<uint16_t>(), m->p.as<float>() + kOffB1,
+                       m->w2t.as<uint16_t>(), m->p.as<float>() + kOffB2, m->w3.as<uint16_t>(),
                        m->p.as<float>() + kOffB3, y, est);
     INSP_HIP(hipGetLastError());
     return INSP_OK;
@@ -1022,7 +1075,7 @@ extern "C" int insp_mlp_state(insp_mlp *m, float *params, float *adam_m, float *
     }
     if (!to_host && params) {
         hipLaunchKernelGGL(k_shadow, dim3(blocks(kParams, 256)), dim3(256), 0, 0, m->p.as<float>(),
-                           m->w1.as<uint16_t>(), m->w2.as<uint16_t>(), m->w3.as<uint16_t>());
+                           m->w1t.as<uint16_t>(), m->w2.as<uint16_t>(), m->w2t.as<uint16_t>(), m->w3.as<uint16_t>());
         INSP_HIP(hipGetLastError());
         INSP_HIP(hipDeviceSynchronize());
     }

@@ -61,6 +61,42 @@ def test_forward_backward_match_reference(insp, B):
     m.free()
 
 
+@pytest.mark.parametrize("B,offset", [(32, 0), (64, 1), (160, 0), (544, 3), (1056, 0), (2080, 2)])
+def test_gradients_at_batch_edges(insp, B, offset):
+    """Batches of one work-group, of an odd number of them, and whose chunks
+    of the weight-gradient sums are ragged, with biases in play; features and
+    targets `offset` floats past a 16-byte boundary; and results written over
+    the inputs they came from."""
+    import ctypes
+    import torch
+    print("[case] mlp grads edges", B, offset, flush=True)
+    rng = np.random.default_rng(B)
+    p = synth.mlp_init()
+    for i in (1, 3, 5):
+        p[i] = rng.normal(0.0, 0.1, p[i].shape).astype(np.float32)
+    X, T = batch(B)
+    xb = torch.zeros(B * 32 + 4, dtype=torch.float32, device="cuda")
+    tb = torch.zeros(B * 2 + 4, dtype=torch.float32, device="cuda")
+    x, t = xb[offset: offset + B * 32].view(B, 32), tb[offset: offset + B * 2].view(B, 2)
+    x.copy_(torch.from_numpy(X))
+    t.copy_(torch.from_numpy(T))
+    m = insp.Mlp(p)
+    g, y, loss = m.grads(x, t)
+    ref_loss, ref_g, c, E = mb.grad_bounds(p, X, T)
+    close(y.cpu().numpy(), c["Y"], E["Y"], "y")
+    close(np.array([loss.item()]), np.array([ref_loss]), np.array([E["loss"]]), "loss")
+    for name, a, b, e in zip(("W1", "b1", "W2", "b2", "W3", "b3"), mlp.unpack(g.cpu().numpy(), synth.MLP_SHAPES),
+                             ref_g, E["grads"]):
+        close(a, b, e, "d" + name)
+    # y over the targets: the same results, bit for bit
+    g2, loss2 = torch.empty_like(g), torch.empty_like(loss)
+    vp = ctypes.c_void_p
+    insp._check(insp.load().insp_mlp_grads(m._h, vp(x.data_ptr()), vp(t.data_ptr()), B, vp(g2.data_ptr()),
+                                           vp(t.data_ptr()), vp(loss2.data_ptr()), insp._stream(None)))
+    assert torch.equal(g, g2) and torch.equal(y, t) and torch.equal(loss, loss2)
+    m.free()
+
+
 def test_adam_step_matches_reference(insp):
     import torch
     print("[case] mlp adam", flush=True)
