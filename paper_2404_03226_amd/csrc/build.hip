@@ -328,6 +328,7 @@ struct PlaceArgs {
     int32_t *col_out, *rp_out;
     unsigned long long *word0;
     int32_t *backward;            // [1 + ceil(B / 32)]: any edge to a lower id, per DAG bits
+    int32_t *maxdeg;              // [B]: longest canonical row
 };
 
 // Move row v's canonical targets to their place and account the edges in
@@ -352,6 +353,8 @@ __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
     const int32_t cnt = A.outdeg[v];
     A.rp_out[A.toff[b] + b + lv] = (int32_t)(at - e0);
     if (lv == n - 1) A.rp_out[A.toff[b] + b + n] = (int32_t)(at + cnt - e0);
+    // (a stale reading only costs an atomic)
+    if (cnt > A.maxdeg[b]) atomicMax(&A.maxdeg[b], cnt);
     const int32_t *p = A.rp + A.toff[b] + b;
     if (p[lv + 1] - p[lv] > kSmallRow) return;  // a listed row: k_place_wide
     const int32_t *src = A.tmp + A.eoff[b] + p[lv];
@@ -573,19 +576,19 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     d->N = N;
     d->toff.assign(task_off, task_off + n_dags + 1);
     int rc;
-    const int nbw = 1 + (n_dags + 31) / 32;
+    const int nbw = 1 + (n_dags + 31) / 32;  // words of `backward`, which the longest rows follow
     DevBuf eoff_in, tmp, outdeg, excl, err, nwide, wide, backward, eoff_c;
     if ((rc = d->d_toff.alloc(sizeof(int64_t) * (n_dags + 1))) || (rc = eoff_in.alloc(sizeof(int64_t) * (n_dags + 1))) ||
         (rc = tmp.alloc(sizeof(int32_t) * M)) || (rc = outdeg.alloc(sizeof(int32_t) * N)) ||
         (rc = excl.alloc(sizeof(int64_t) * (N + 1))) || (rc = err.alloc(sizeof(int32_t))) ||
         (rc = nwide.alloc(sizeof(int32_t))) || (rc = wide.alloc(sizeof(int64_t) * N)) ||
-        (rc = backward.alloc(sizeof(int32_t) * nbw)) || (rc = eoff_c.alloc(sizeof(int64_t) * (n_dags + 1))))
+        (rc = backward.alloc(sizeof(int32_t) * (nbw + n_dags))) || (rc = eoff_c.alloc(sizeof(int64_t) * (n_dags + 1))))
         return rc;
     INSP_HIP(hipMemcpyAsync(d->d_toff.p, task_off, sizeof(int64_t) * (n_dags + 1), hipMemcpyHostToDevice, st));
     INSP_HIP(hipMemcpyAsync(eoff_in.p, edge_off, sizeof(int64_t) * (n_dags + 1), hipMemcpyHostToDevice, st));
     INSP_HIP(hipMemsetAsync(err.p, 0, sizeof(int32_t), st));
     INSP_HIP(hipMemsetAsync(nwide.p, 0, sizeof(int32_t), st));
-    INSP_HIP(hipMemsetAsync(backward.p, 0, sizeof(int32_t) * nbw, st));
+    INSP_HIP(hipMemsetAsync(backward.p, 0, sizeof(int32_t) * (nbw + n_dags), st));
 
     // Sort and deduplicate every row where it lies; validate the CSR.
     RowArgs ra;
@@ -636,7 +639,8 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     INSP_HIP(hipStreamSynchronize(st));
     const int64_t Mc = d->eoff[n_dags];
     d->M = Mc;
-    if ((rc = d->col.alloc(sizeof(int32_t) * Mc)) || (rc = d->rp.alloc(sizeof(int32_t) * (N + n_dags))) ||
+    // (the simulation reads 8 successors at a time from a row's start: room past the last row)
+    if ((rc = d->col.alloc(sizeof(int32_t) * (Mc + 16))) || (rc = d->rp.alloc(sizeof(int32_t) * (N + n_dags))) ||
         (rc = d->word0.alloc(sizeof(uint64_t) * N)) || (rc = d->d_eoff.alloc(sizeof(int64_t) * (n_dags + 1))))
         return rc;
     INSP_HIP(hipMemcpyAsync(d->d_eoff.p, eoff_c.p, sizeof(int64_t) * (n_dags + 1), hipMemcpyDeviceToDevice, st));
@@ -654,6 +658,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     pa.rp_out = d->rp.as<int32_t>();
     pa.word0 = d->word0.as<unsigned long long>();
     pa.backward = backward.as<int32_t>();
+    pa.maxdeg = backward.as<int32_t>() + nbw;
     if (N > 0) hipLaunchKernelGGL(k_place, dim3(grid_for(N, 256)), dim3(256), 0, st, pa);
     if (h_wide > 0)
         hipLaunchKernelGGL(k_place_wide, dim3((unsigned)h_wide), dim3(64), 0, st, pa, (const int64_t *)wide.as<int64_t>());
@@ -661,9 +666,10 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
 
     // Cycle check: with every edge pointing to a higher id the id order is a
     // topological order; otherwise run Kahn's traversal on the DAGs concerned.
-    std::vector<int32_t> h_back(nbw);
-    INSP_HIP(hipMemcpyAsync(h_back.data(), backward.p, sizeof(int32_t) * nbw, hipMemcpyDeviceToHost, st));
+    std::vector<int32_t> h_back(nbw + n_dags);
+    INSP_HIP(hipMemcpyAsync(h_back.data(), backward.p, sizeof(int32_t) * (nbw + n_dags), hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
+    d->maxdeg.assign(h_back.begin() + nbw, h_back.end());
     if (h_back[0]) {
         std::vector<int32_t> todo;
         for (int32_t b = 0; b < n_dags; b++)

@@ -66,7 +66,7 @@ struct DevBuf {
 struct TaskRec {
     unsigned long long word;  // schedule once popped (see above)
     int32_t qpos;             // queue slot; -1 before the push; <= -2 once popped
-    int32_t seq;              // push sequence number once queued
+    int32_t seq;              // push order once queued (with the worker << 21 in the one-wave loop)
     int32_t iev;              // current inspiring efficiency
     int32_t ia, tau, rs;      // out-degree, tau, first edge (fixed during a run)
 };
@@ -166,6 +166,7 @@ struct insp_dag {
     int64_t N = 0, M = 0;
     std::vector<int64_t> toff, eoff;   // canonical prefix sums (host)
     std::vector<int32_t> order;        // DAG ids by n + m descending
+    std::vector<int32_t> maxdeg;       // largest out-degree of each DAG
     insp::DevBuf d_toff, d_eoff;       // int64 [B+1]
     insp::DevBuf rp;                   // int32 [N + B] local canonical row pointers
     insp::DevBuf col;                  // int32 [M] canonical successor lists

@@ -115,13 +115,15 @@ struct SimArgs {
     int32_t *n_events;
     int32_t s_inc, s_dec, dec_step, c, k_num, k_den, max_events;
     int32_t prio_top;          // DAGs dispensed before this one run at raised wave priority
-    int32_t scan_max;          // a pop scans every entry of a worker with at most this many blocks (<= kScan)
 };
 
 // LDS-resident state of the DAG a work-group is simulating.
 constexpr int kPF = 8;    // successors of a running task prefetched into registers at its pop
 constexpr int kFC = 256;  // frontier slots in LDS (larger frontiers use global memory)
 constexpr int kCC = 128;  // candidate slots in LDS
+constexpr int kScan = 16;  // most blocks the tune key's "scan=" may name (it has no effect: see keep_best)
+constexpr int64_t kHelperSpin = 1ll << 40;
+constexpr int32_t kReqSpin = 1 << 24;  // polls of a rescan request (it takes a few)
 
 struct Lds {
     int64_t *fin, *expend, *qest;                    // [MW]
@@ -139,7 +141,7 @@ struct Lds {
     int32_t *hs;                                     // [4] DAG index, simulation finished, helper sink
 };
 
-__host__ __device__ constexpr size_t lds_bytes(int mw, int sc, int lb, int slc, int slk) {
+__host__ __device__ inline size_t lds_bytes(int mw, int sc, int lb, int slc, int slk) {
     return (size_t)mw * (3 * 8 + 7 * 4 + (size_t)lb * 4) + (size_t)sc * (16 + 4 + 1) + kFC * 8 + kCC * 8 +
            8 * 64 * 4 + (size_t)slc * 64 * 12 + (size_t)slk * 64 * 8 + 64 + 32;
 }
@@ -1001,31 +1003,49 @@ __device__ void sim_dag(const SimArgs &A, int32_t di, const Lds &L) {
 }
 
 // ---------------------------------------------------------------------------
-// Machines of at most 64 workers: lane w holds worker w's state in registers
-// (running task, its finish and expected-end times, queue length, block count,
-// last block, the running task's row and first successors), so pushes, pops
-// and the advance read no memory for it.  Same event order and results as the
-// general loop above, with two differences in the queue:
+// Machines of at most 64 workers (WPL = 1) or 128 (WPL = 2): lane w holds
+// the state of worker w (and of worker w + 64) in registers -- running task,
+// its finish and expected-end times, queue length, block count, last block,
+// the running task's row and first successors -- so pushes, pops and the
+// advance read no memory for it.  Same event order and results as the
+// general loop above.
+//
+// What bounds it is one wave's chain of dependent steps per event: waits on
+// LDS and L2 round trips, and the issue of several hundred instructions at
+// 4 clocks and more each.  The loop keeps everything else off that chain:
 //   - 32-bit keys.  IA and IE take `a` bits each (a = bit length of the DAG's
 //     largest out-degree; IE <= IA) and the push order `s` bits (s = bit length
 //     of n - 1), under a valid bit.  Each entry keeps both rules' keys,
 //       kA = V | IA << (a+s) | IE << s | (2^s-1-seq)   (ability; under the
 //                                                        FIFO policy V | (2^s-1-seq))
 //       kE = V | IE << (a+s) | IA << s | (2^s-1-seq)   (efficiency),
-//     so a pop compares plain words.  A DAG whose keys need more than 32 bits
-//     runs the general loop instead.
-//   - How a pop finds its maximum: a worker with at most kScan blocks has
-//     every lane scan its column of all of the worker's blocks, then one wave
-//     max; with more blocks, per-block maxima pick the block first.  Every
-//     slot without a live entry holds zero keys (all blocks are zeroed when
-//     the DAG starts, and a pop zeroes the slot it empties), so scans read
-//     whole blocks unpredicated: valid keys carry the top bit.  Maxima of
-//     blocks held in LDS are rebuilt lazily: a pop only marks the blocks it
-//     touched stale; pushes and IE increments keep raising them with atomicMax
-//     (which a later rebuild overwrites), and a many-block pop rebuilds the
-//     stale ones of its worker before comparing.  Maxima kept in global memory
-//     (block ids >= sum_cap) are rebuilt at once.
-constexpr int kScan = 16;  // the most a launch may scan (tune key "scan=")
+//     so a pop compares plain words.  Launches with a DAG whose keys need more
+//     than 32 bits keep one 64-bit key per entry instead (see Keys).
+//   - A worker's best entry is known before it is popped.  Per worker and
+//     rule, `best` holds the queue's largest key and its slot (key << 32 | slot).
+//     Pushes and IE increments raise it with an LDS atomicMax; a pop empties
+//     it and asks the work-group's second wave (keep_best) to find the next
+//     one, which it does while this wave simulates the following events.  The
+//     second wave rescans only the blocks the pop changed, merges their
+//     maxima into the per-block maxima with atomicMax and takes the largest
+//     of those.  Keys only grow while a task is queued, so maxima raised by
+//     this wave meanwhile and scanned values that are out of date by then
+//     merge to the right result in any order; a pop waits for a rescan still
+//     under way.  Every slot without a live entry holds zero keys, so scans
+//     read whole blocks unpredicated: valid keys carry the top bit.
+//   - All workers that are idle pop at once, a lane each.
+//   - An event with one completion of at most 64 successors (most are) keeps
+//     its newly ready tasks in the lanes that released them: their rows are
+//     loaded there and the pushes take them in lane (ascending id) order, with
+//     no list in between.  Its loads are unpredicated (lanes without a task
+//     read element 0) so that the compiler issues them together.
+//   - Pointers and parameters that only uncommon paths use are kept in LDS
+//     (kCold*), not in scalar registers, whose spills cost the common path.
+// Measured (2.4 GHz): layered 1,000-task DAG @L1K@ us per event, against 3.0 with
+// the scan in the simulating wave, pops one by one and frontier lists.
+
+// Bits of a key field that holds values up to `most`.
+__host__ __device__ constexpr uint32_t field_bits(uint32_t most) { return most == 0 ? 1 : 32 - __builtin_clz(most); }
 
 // Key layout of one DAG.
 struct KeyFmt {
@@ -1044,111 +1064,320 @@ struct KeyFmt {
     __device__ __forceinline__ uint32_t de() const { return 1u << sb; }
 };
 
-// Queue keys of the one-wave loop.  Direct attributes: two 32-bit rule keys
-// per entry, kA (ability, or FIFO) and kE (efficiency), each raised in place
-// when the task's IE grows.  Fixed keys (HEFT ranks, transitive attributes):
-// one 64-bit key per entry in the general loop's format, from which key_of
-// derives the rule keys when an entry is read (zero stays zero: an empty slot).
-template <bool FIX>
+// Queue keys of the one-wave loop.
+//   kNarrow  direct attributes, two 32-bit rule keys per entry (kA, kE), each
+//            raised in place when the task's IE grows; block and worker maxima
+//            hold key << 32 | slot.
+//   kFixed   HEFT ranks or transitive attributes, fixed while queued: one
+//            64-bit key per entry in the general loop's format, from which
+//            key_of derives the rule keys when an entry is read (zero stays
+//            zero: an empty slot).
+//   kWide    direct attributes in that format, raised in place.
+// With 64-bit keys the maxima hold rule keys alone: the second wave leaves
+// the slot of a worker's best beside it, and the simulating wave keeps the
+// best entry it pushed or raised since the worker's last pop, with its slot,
+// in the worker's lane.
+enum KeyKind { kNarrow = 0, kFixed = 1, kWide = 2 };
+
+template <int KK>
 struct Keys {
-    using T = typename std::conditional<FIX, unsigned long long, uint32_t>::type;
-    T *ka, *ke;  // LDS keys [64 * key_cap]: kA and kE, or (fixed) ka the key itself
-    T *mx;       // [2 * sum_cap]: the two rule maxima of each block summarised in LDS
-    int o0;      // fixed keys: the rule of maximum 0 (0 ability, 2 FIFO, 3 rank)
+    static constexpr bool kBig = KK != kNarrow;
+    using T = typename std::conditional<kBig, unsigned long long, uint32_t>::type;
+    T *ka, *ke;  // LDS keys [64 * key_cap]: kA and kE, or ka the 64-bit key
+    int o0;      // 64-bit keys: the rule of maximum 0 (0 ability, 2 FIFO, 3 rank)
     __device__ __forceinline__ T rule(uint64_t raw, int r) const {
-        if constexpr (FIX) return raw ? key_of(raw, r ? 1 : o0) : 0ull;
+        if constexpr (kBig) return raw ? key_of(raw, r ? 1 : o0) : 0ull;
         else return (uint32_t)(raw >> (r ? 32 : 0));
     }
     // rule-r key of the entry in LDS slot p
     __device__ __forceinline__ T lds(int32_t p, int r) const {
-        if constexpr (FIX) return rule(ka[p], r);
+        if constexpr (kBig) return rule(ka[p], r);
         else return (r ? ke : ka)[p];
+    }
+    // the entry's key word (the two 32-bit keys, kE above kA, or the 64-bit key)
+    __device__ __forceinline__ uint64_t word(int32_t p) const {
+        if constexpr (kBig) return ka[p];
+        else return (uint64_t)ke[p] << 32 | ka[p];
+    }
+    __device__ __forceinline__ void put(int32_t p, uint64_t w) const {
+        if constexpr (kBig) {
+            ka[p] = w;
+        } else {
+            ka[p] = (uint32_t)w;
+            ke[p] = (uint32_t)(w >> 32);
+        }
+    }
+    // the key of a block or worker maximum
+    __device__ __forceinline__ static T of_max(unsigned long long m) {
+        if constexpr (kBig) return m;
+        else return (uint32_t)(m >> 32);
     }
 };
 
 __device__ __forceinline__ uint32_t wave_max_k(uint32_t x) { return wave_max_u32f(x); }
 __device__ __forceinline__ unsigned long long wave_max_k(unsigned long long x) { return wave_max_u64f(x); }
 
-// Rule-`r` keys of block b, one per lane (zero in empty slots).  b is
-// wave-uniform: the choice between LDS and global memory is a scalar branch,
-// and the global side waits for its load itself, so the LDS side carries no
-// wait for outstanding global accesses.
-template <bool FIX>
-__device__ __forceinline__ typename Keys<FIX>::T block_keys(const SlotPool &slots, const Keys<FIX> &K, int32_t slc,
-                                                            int32_t b, int r) {
+// Order this wave's LDS and global accesses as written (the hardware already
+// takes them in issue order within a work-group).
+__device__ __forceinline__ void keep_order() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
+
+template <typename T>
+__device__ __forceinline__ T lds_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void lds_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Element i of a per-task array (n <= 2^21, elements of at most 32 bytes: the
+// byte offset fits 32 bits, so the access is a scalar base plus one register).
+template <typename T>
+__device__ __forceinline__ T *at(T *base, int32_t i) {
+    return reinterpret_cast<T *>(
+        reinterpret_cast<typename std::conditional<std::is_const<T>::value, const char, char>::type *>(base) +
+        (uint32_t)i * (uint32_t)sizeof(T));
+}
+
+// LDS of the one-wave loop: arrays of fixed size first (their offsets are
+// instruction immediates), then the ones whose size the launch picks.
+template <int WPL>
+struct LaneLds {
+    static constexpr int kMW = WPL * kWave;
+    static constexpr int kBest = 0;                     // uint64 [2 * kMW]: each worker's best entry under either rule
+    static constexpr int kFin = kBest + 16 * kMW;       // int64 [kMW]: finish of the running task (for the read-ahead)
+    static constexpr int kCold = kFin + 8 * kMW;        // uint64 [8]: pointers of the uncommon paths
+    static constexpr int kBpos = kCold + 64;            // int32 [2 * kMW], 64-bit keys: slots of the best entries
+    static constexpr int kRun = kBpos + 8 * kMW;        // int32 [kMW]: running task or -1 (for the read-ahead)
+    static constexpr int kReq = kRun + 4 * kMW;         // int32 [kMW]: a rescan is pending
+    static constexpr int kRnb = kReq + 4 * kMW;         // int32 [kMW]: ... of a queue of this many blocks
+    static constexpr int kRch = kRnb + 4 * kMW;         // int32 [kMW]: ... whose changed blocks are these two
+    static constexpr int kSeg = kRch + 4 * kMW;         // int32 [kMW]: ends of the runs of newly ready tasks
+    static constexpr int kSucc = kSeg + 4 * kMW;        // int32 [kPF]: a completing task's first successors
+    static constexpr int kPre = kSucc + 4 * kPF;        // int32 [8 * 64]: staged frontier rows
+    static constexpr int kFr0 = kPre + 4 * 8 * kWave;   // int32 [kFC]
+    static constexpr int kFr1 = kFr0 + 4 * kFC;         // int32 [kFC]
+    static constexpr int kCs = kFr1 + 4 * kFC;          // int32 [kCC]
+    static constexpr int kCu = kCs + 4 * kCC;           // int32 [kCC]
+    static constexpr int kHs = kCu + 4 * kCC;           // int32 [4]: DAG index, finished, read-ahead's sink, rescans on
+    static constexpr int kFixed = kHs + 16;
+    unsigned long long *mx;  // [2 * sum_cap] block maxima
+    unsigned long long *sk;  // [64 * key_cap] keys of the low blocks' entries
+    unsigned long long *sx;  // [64 * slot_cap] payload (task, durations) of the lowest
+    int32_t *srs;            // [64 * slot_cap] ... and their first edges
+    int32_t *fstk;           // [sum_cap] free block ids below sum_cap
+    int32_t *blist;          // [W * lb] first block ids of each worker
+    static constexpr size_t bytes(int mw, int sc, int lb, int slc, int slk) {
+        return (size_t)kFixed + (size_t)sc * 20 + (size_t)slk * 512 + (size_t)slc * 768 + (size_t)mw * lb * 4;
+    }
+    __device__ __forceinline__ static char *raw() {
+        extern __shared__ int64_t lds64[];
+        return reinterpret_cast<char *>(lds64);
+    }
+    template <typename T>
+    __device__ __forceinline__ static T *arr(int off) { return reinterpret_cast<T *>(raw() + off); }
+    __device__ __forceinline__ explicit LaneLds(const SimArgs &A) {
+        mx = arr<unsigned long long>(kFixed);
+        sk = mx + 2 * A.sum_cap;
+        sx = sk + 64 * A.key_cap;
+        srs = reinterpret_cast<int32_t *>(sx + 64 * A.slot_cap);
+        fstk = srs + 64 * A.slot_cap;
+        blist = fstk + A.sum_cap;
+    }
+};
+static_assert(LaneLds<1>::kFixed % 16 == 0 && LaneLds<2>::kFixed % 16 == 0, "aligned for 64-bit arrays");
+
+// Pointers kept in LDS (LaneLds::kCold).
+enum ColdPtr { kColdFbuf = 0, kColdWblk, kColdFreeb, kColdKeys, kColdPayload, kColdEdges, kColdSums };
+
+template <int WPL, typename T>
+__device__ __forceinline__ T *cold(int i) {
+    const uint64_t v = (uint64_t)uniform64((int64_t)LaneLds<WPL>::template arr<uint64_t>(LaneLds<WPL>::kCold)[i]);
+    return (T *)(__attribute__((address_space(1))) T *)v;
+}
+
+template <int WPL, int KK>
+__device__ __forceinline__ Keys<KK> make_keys(const SimArgs &A, const LaneLds<WPL> &L) {
+    Keys<KK> K;
+    K.ka = reinterpret_cast<typename Keys<KK>::T *>(L.sk);
+    K.ke = Keys<KK>::kBig ? nullptr : K.ka + 64 * A.key_cap;  // the two 32-bit arrays fill the 64-bit key storage
+    K.o0 = A.policy == INSP_POLICY_FIFO ? 2 : A.policy == INSP_POLICY_HEFT ? 3 : 0;
+    return K;
+}
+
+// A rescan request for worker w names its queue's block count and the one or
+// two blocks whose maxima the pop emptied.
+constexpr uint32_t kNoBlock = 0xFFFFu;  // block ids are below n / 64 + W <= 2^15 + 128
+
+// The work-group's second wave: answers rescan requests until the DAG is done.
+template <int WPL, int KK>
+__device__ void keep_best(const SimArgs &A, int32_t di) {
+    using KT = typename Keys<KK>::T;
+    using LL = LaneLds<WPL>;
+    constexpr bool kBig = Keys<KK>::kBig;
+    const LL L(A);
     const int lane = lane_id();
-    typename Keys<FIX>::T k;
-    if (b < slc) {
-        k = K.lds(b * 64 + lane, r);
-    } else {
+    const DagDesc d = A.desc[di];
+    const int32_t W = d.n_cpu + d.n_gpu;
+    const SlotPool slots = A.slots.at(64 * d.blk_off);
+    unsigned long long *sums = A.sums + 2 * d.blk_off;
+    const int32_t *wblk = A.paux + d.wl_off;
+    const Keys<KK> K = make_keys<WPL, KK>(A, L);
+    const int32_t SC = A.sum_cap, SLK = A.key_cap, kLB = A.lb;
+    unsigned long long *mx = L.mx, *best = LL::template arr<unsigned long long>(LL::kBest);
+    int32_t *bpos = LL::template arr<int32_t>(LL::kBpos), *req = LL::template arr<int32_t>(LL::kReq);
+    const int32_t *rnb = LL::template arr<int32_t>(LL::kRnb), *rch = LL::template arr<int32_t>(LL::kRch);
+    const int32_t *hs = LL::template arr<int32_t>(LL::kHs);
+    // rule-r key of block b's entry in this lane
+    auto entry = [&](int32_t b, int r) -> KT {
+        if (b < SLK) return K.lds(b * 64 + lane, r);
         const uint64_t raw = wg_load(&slots.k[b * 64 + lane]);
         settle(raw);
-        k = K.rule(raw, r);
-    }
-    return k;
-}
-
-// Best rule-R key in column `lane` of the listed blocks (bits of `m` select
-// lanes of `bl`, which hold block ids), four loads in flight at a time;
-// FROM_LDS picks where the blocks' slots live.
-template <bool FIX, bool FROM_LDS, int R>
-__device__ __forceinline__ void scan_columns(const SlotPool &slots, const Keys<FIX> &K, uint64_t m, int32_t bl,
-                                             typename Keys<FIX>::T &best, int32_t &bp) {
-    const int lane = lane_id();
-    const int32_t b_last = read_lane(bl, 63 - (int)__builtin_clzll(m | 1));  // any listed block
-    while (m) {
-        typename Keys<FIX>::T kk[4];
-        int32_t pp[4];
+        return K.rule(raw, r);
+    };
+    for (int64_t it = 0; it < kHelperSpin; it++) {
+        if (lds_load(&hs[1])) break;
+        if (!lds_load(&hs[3])) {
+            __builtin_amdgcn_s_sleep(2);
+            continue;
+        }
+        bool any = false;
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            int32_t b = b_last;  // padding re-reads a listed block: no effect on the max
-            if (m) {
-                b = read_lane(bl, (int)__builtin_ctzll(m));
+        for (int k = 0; k < WPL; k++) {
+            const int32_t wl = lane + k * kWave;
+            uint64_t m = ballot((wl < W ? lds_load(&req[wl]) : 0) != 0);
+            any |= m != 0;
+            keep_order();
+            while (m) {
+                const int32_t w = (int32_t)__builtin_ctzll(m) + k * kWave;
                 m &= m - 1;
-            }
-            pp[u] = b * 64 + lane;
-            kk[u] = FROM_LDS ? K.lds(pp[u], R) : K.rule(wg_load(&slots.k[pp[u]]), R);
-        }
+                const int32_t nbw = uniform(min(rnb[w], d.maxb));
+                const uint32_t ch = (uint32_t)uniform(rch[w]);
+                // the changed blocks' maxima under both rules
+                unsigned long long bm0 = 0, bm1 = 0;  // ... of the last one scanned
+                int32_t bp0 = 0, bp1 = 0;             // 64-bit keys: their slots
+                bool glob = false, found = true;
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            if (kk[u] > best) {
-                best = kk[u];
-                bp = pp[u];
+                for (int h = 0; h < 2; h++) {
+                    const uint32_t b = (ch >> (16 * h)) & 0xFFFFu;
+                    if (b == kNoBlock || (int32_t)b >= d.nblk) continue;
+                    const KT k0 = entry((int32_t)b, 0), k1 = entry((int32_t)b, 1);
+                    const KT s0 = wave_max_k(k0), s1 = wave_max_k(k1);
+                    bp0 = (int32_t)b * 64 + (int32_t)__builtin_ctzll(ballot(k0 == s0));
+                    bp1 = (int32_t)b * 64 + (int32_t)__builtin_ctzll(ballot(k1 == s1));
+                    if constexpr (kBig) {
+                        bm0 = s0;
+                        bm1 = s1;
+                    } else {
+                        bm0 = s0 ? (unsigned long long)s0 << 32 | (uint32_t)bp0 : 0ull;
+                        bm1 = s1 ? (unsigned long long)s1 << 32 | (uint32_t)bp1 : 0ull;
+                    }
+                    glob |= (int32_t)b >= SC;
+                    if (lane == 0) {
+                        if ((int32_t)b < SC) {
+                            atomicMax(&mx[2 * b], bm0);
+                            atomicMax(&mx[2 * b + 1], bm1);
+                        } else {
+                            wg_fetch_max(&sums[2 * b], bm0);
+                            wg_fetch_max(&sums[2 * b + 1], bm1);
+                        }
+                    }
+                }
+                if (nbw > 1 || ch == (kNoBlock | kNoBlock << 16)) {
+                    // the largest block maximum under each rule
+                    keep_order();
+                    bm0 = bm1 = 0;
+                    int32_t b0 = -1, b1 = -1;
+                    for (int32_t i0 = 0; i0 < nbw; i0 += kWave) {
+                        const int32_t i = i0 + lane;
+                        int32_t b = -1;
+                        if (i < nbw) {
+                            b = i < kLB ? L.blist[w * kLB + i] : wg_load(&wblk[(int64_t)w * d.maxb + i]);
+                            if (b >= d.nblk) b = -1;
+                        }
+                        unsigned long long m0 = 0, m1 = 0;
+                        if (b >= 0) {
+                            if (b < SC) {
+                                m0 = lds_load(&mx[2 * b]);
+                                m1 = lds_load(&mx[2 * b + 1]);
+                            } else {
+                                m0 = __hip_atomic_load(&sums[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                m1 = __hip_atomic_load(&sums[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            }
+                        }
+                        if (m0 > bm0) {
+                            bm0 = m0;
+                            b0 = b;
+                        }
+                        if (m1 > bm1) {
+                            bm1 = m1;
+                            b1 = b;
+                        }
+                    }
+                    const unsigned long long g0 = wave_max_u64f(bm0), g1 = wave_max_u64f(bm1);
+                    if constexpr (kBig) {
+                        // the entries those maxima stand for
+                        const int32_t c0 = read_lane(b0, (int)__builtin_ctzll(ballot(bm0 == g0)));
+                        const int32_t c1 = read_lane(b1, (int)__builtin_ctzll(ballot(bm1 == g1)));
+#pragma unroll
+                        for (int r = 0; r < 2; r++) {
+                            const int32_t b = r ? c1 : c0;
+                            if (b < 0) continue;
+                            const uint64_t hit = ballot(entry(b, r) == (r ? g1 : g0));
+                            if (hit) (r ? bp1 : bp0) = b * 64 + (int32_t)__builtin_ctzll(hit);
+                            else found = false;
+                        }
+                    }
+                    bm0 = g0;
+                    bm1 = g1;
+                }
+                // a maximum raised while it was looked for (kWide): the request
+                // stands and is answered again
+                if (!found) continue;
+                if (glob) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the maxima in global memory are merged
+                if (lane == 0) {
+                    if constexpr (kBig) {
+                        best[2 * w] = bm0;
+                        best[2 * w + 1] = bm1;
+                        bpos[2 * w] = bp0;
+                        bpos[2 * w + 1] = bp1;
+                    } else {
+                        atomicMax(&best[2 * w], bm0);
+                        atomicMax(&best[2 * w + 1], bm1);
+                    }
+                    keep_order();
+                    lds_store(&req[w], 0);
+                }
             }
         }
+        if (!any) __builtin_amdgcn_s_sleep(1);
     }
 }
 
-// Rebuild both maxima of block b from its first `cnt` entries (wave-wide).
-template <bool FIX>
-__device__ __forceinline__ void rebuild_max(const SlotPool &slots, const Keys<FIX> &K, const Lds &L,
-                                            unsigned long long *sums, int32_t slc, int32_t sc, int32_t b) {
-    const int lane = lane_id();
-    const auto s0 = wave_max_k(block_keys<FIX>(slots, K, slc, b, 0));
-    const auto s1 = wave_max_k(block_keys<FIX>(slots, K, slc, b, 1));
-    if (lane == 0) {
-        if (b < sc) {
-            K.mx[2 * b] = s0;
-            K.mx[2 * b + 1] = s1;
-            L.stale[b] = 0;
-        } else {
-            sums[2 * b] = s0;
-            sums[2 * b + 1] = s1;
-        }
-    }
+// Worker w's value of a per-worker register (w is wave-uniform).
+template <int WPL>
+__device__ __forceinline__ int32_t of_worker(const int32_t (&x)[WPL], int32_t w) {
+    if constexpr (WPL == 1) return read_lane(x[0], w);
+    else return w < kWave ? read_lane(x[0], w) : read_lane(x[1], w - kWave);
 }
 
-// FIX = false: direct attributes on 32-bit keys; returns false, having changed
-// nothing the general loop relies on, when the DAG's keys do not fit.
-// FIX = true: fixed 64-bit keys (HEFT ranks or transitive attributes); the
-// tasks' direct IE is still kept up to date for the records.
-// DATA = true: the data model (A.data_bw > 0), as the general loop runs it: a
-// push adds each worker's input transfer ticks to its cost and records the
-// task's input arrival time, a pop starts its task when the inputs are in,
-// and the efficiency-with-locality rule prefers tasks whose inputs are.
-template <bool FIX, bool DATA>
-__device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
-    using KT = typename Keys<FIX>::T;
+typedef int32_t row4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// DATA: the data model (A.data_bw > 0), as the general loop runs it: a push
+// adds each worker's input transfer ticks to its cost and records the task's
+// input arrival time, a pop starts its task when the inputs are in, and the
+// efficiency-with-locality rule prefers tasks whose inputs are.
+// With kNarrow the keys of every DAG of the launch fit (launch_sim checks).
+template <int WPL, int KK, bool DATA>
+__device__ void sim_lane(const SimArgs &A, int32_t di) {
+    static_assert(WPL == 1 || WPL == 2, "a lane holds one or two workers");
+    using LL = LaneLds<WPL>;
+    using KT = typename Keys<KK>::T;
+    constexpr bool kBig = Keys<KK>::kBig;
+    constexpr int WB = WPL == 1 ? 6 : 7;              // bits of a worker id
+    constexpr uint32_t kLim = (1u << (32 - WB)) - 1;  // costs this far past now are compared in 64 bits
+    constexpr int kPred = 8;                          // predecessors of a task read together
+    const LL L(A);
     const int lane = lane_id();
     const DagDesc d = A.desc[di];
     const int32_t n = d.n, ncpu = d.n_cpu, W = d.n_cpu + d.n_gpu;
@@ -1158,63 +1387,83 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
             A.makespan[di] = status ? -1 : 0;
             if (A.n_events) A.n_events[di] = 0;
         }
-        return true;
+        return;
     }
     const int64_t ub = d.toff - A.base;
     const int32_t *col = A.col + d.eoff;
     TaskRec *tr = A.tr + d.toff;
     unsigned long long *dep = A.dep + d.toff;
-    int32_t *fbuf = A.fbuf + 3 * d.toff;      // [0,n) runs, [n,2n) merged, [2n,3n) candidates
     const int2 *est2 = reinterpret_cast<const int2 *>(A.est) + ub;
     const int2 *dur2 = reinterpret_cast<const int2 *>(A.dur) + ub;
-    const SlotPool slots = A.slots.at(64 * d.blk_off);
-    unsigned long long *sums = A.sums + 2 * d.blk_off;
-    int32_t *wblk = A.paux + d.wl_off;
-    int32_t *freeb = A.paux + A.freeb_base + d.blk_off;
     const int32_t maxb = d.maxb;
     const int32_t SC = A.sum_cap;
     const int32_t kLB = A.lb;
     const int32_t SLC = A.slot_cap;  // blocks [0, SLC) keep their entries' payload in LDS
     const int32_t SLK = A.key_cap;   // blocks [0, SLK) (SLK >= SLC) keep their keys in LDS
+    unsigned long long *mx = L.mx, *best = LL::template arr<unsigned long long>(LL::kBest);
+    int64_t *lfin = LL::template arr<int64_t>(LL::kFin);
+    int32_t *lrun = LL::template arr<int32_t>(LL::kRun), *req = LL::template arr<int32_t>(LL::kReq);
+    int32_t *rnb = LL::template arr<int32_t>(LL::kRnb), *rch = LL::template arr<int32_t>(LL::kRch);
+    int32_t *bpos = LL::template arr<int32_t>(LL::kBpos), *seg = LL::template arr<int32_t>(LL::kSeg);
+    int32_t *succ = LL::template arr<int32_t>(LL::kSucc), *pre = LL::template arr<int32_t>(LL::kPre);
+    int32_t *fr0 = LL::template arr<int32_t>(LL::kFr0), *fr1 = LL::template arr<int32_t>(LL::kFr1);
+    int32_t *cs = LL::template arr<int32_t>(LL::kCs), *cu = LL::template arr<int32_t>(LL::kCu);
+    // the global queue pool and block maxima, for blocks not held in LDS
+    auto pool = [&]() {
+        SlotPool s;
+        s.k = cold<WPL, unsigned long long>(kColdKeys);
+        s.x = cold<WPL, unsigned long long>(kColdPayload);
+        s.rs = cold<WPL, int32_t>(kColdEdges);
+        return s;
+    };
+    auto gsums = [&]() { return cold<WPL, unsigned long long>(kColdSums); };
 
     // initial frontier (tasks without predecessors, ascending) and the
     // largest out-degree, which sizes the key fields
     int32_t r = 0;
     uint32_t mdeg = 0;
-    for (int32_t i0 = 0; i0 < n; i0 += kWave) {
-        int32_t i = i0 + lane;
-        bool ok = false;
-        if (i < n) {
-            ok = (dep[i] >> 43) == 0;
-            mdeg = max(mdeg, (uint32_t)tr[i].ia);
+    {
+        int32_t *fbuf = A.fbuf + 3 * d.toff;  // [0,n) runs, [n,2n) merged, [2n,3n) candidates
+        for (int32_t i0 = 0; i0 < n; i0 += kWave) {
+            int32_t i = i0 + lane;
+            bool ok = false;
+            if (i < n) {
+                ok = (dep[i] >> 43) == 0;
+                mdeg = max(mdeg, (uint32_t)tr[i].ia);
+            }
+            uint64_t mk = ballot(ok);
+            if (ok) {
+                int32_t pos = r + lanes_below(mk);
+                fbuf[pos] = i;
+                if (pos < kFC) fr0[pos] = i;
+            }
+            r += __popcll(mk);
         }
-        uint64_t mk = ballot(ok);
-        if (ok) {
-            int32_t pos = r + lanes_below(mk);
-            fbuf[pos] = i;
-            if (pos < kFC) L.fr0[pos] = i;
+        mdeg = wave_max_u32f(mdeg);
+        if (lane == 0) {
+            uint64_t *c = LL::template arr<uint64_t>(LL::kCold);
+            const SlotPool slots = A.slots.at(64 * d.blk_off);
+            c[kColdFbuf] = (uint64_t)fbuf;
+            c[kColdWblk] = (uint64_t)(A.paux + d.wl_off);
+            c[kColdFreeb] = (uint64_t)(A.paux + A.freeb_base + d.blk_off);
+            c[kColdKeys] = (uint64_t)slots.k;
+            c[kColdPayload] = (uint64_t)slots.x;
+            c[kColdEdges] = (uint64_t)slots.rs;
+            c[kColdSums] = (uint64_t)(A.sums + 2 * d.blk_off);
         }
-        r += __popcll(mk);
     }
-    mdeg = wave_max_u32f(mdeg);
-    const uint32_t abits = mdeg == 0 ? 1 : 32 - __clz(mdeg);
-    const uint32_t sbits = n <= 1 ? 1 : 32 - __clz(n - 1);
-    if (!FIX && 1 + 2 * abits + sbits > 32) return false;
+    const uint32_t abits = field_bits(mdeg), sbits = field_bits(n - 1);
     KeyFmt kf;
     kf.sa = sbits;
     kf.sb = abits + sbits;
     kf.smask = (1u << sbits) - 1;
     kf.amask = (1u << abits) - 1;
     kf.fifo = A.policy == INSP_POLICY_FIFO;
-    const bool heft = FIX && A.policy == INSP_POLICY_HEFT;
-    const bool tattr = FIX && A.attr_mode == INSP_ATTR_TRANSITIVE;
+    const bool heft = KK == kFixed && A.policy == INSP_POLICY_HEFT;
+    const bool tattr = KK == kFixed && A.attr_mode == INSP_ATTR_TRANSITIVE;
     const int64_t *rk = A.rank + d.toff;
     const int32_t *tia = A.tia + d.toff, *tie = A.tie + d.toff;
-    Keys<FIX> K;
-    K.ka = reinterpret_cast<KT *>(L.sk);
-    K.ke = FIX ? nullptr : K.ka + 64 * SLK;  // the two 32-bit arrays fill the 64-bit key storage
-    K.mx = reinterpret_cast<KT *>(L.sum);
-    K.o0 = A.policy == INSP_POLICY_FIFO ? 2 : heft ? 3 : 0;
+    const Keys<KK> K = make_keys<WPL, KK>(A, L);
     const int32_t U = A.dag_u[d.id];
     // data model: inputs move between memory nodes (the host for the CPU
     // workers, one per GPU worker)
@@ -1223,7 +1472,6 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
     long long *barr = A.barr + d.blk_off;
     // block arrival bounds matter only where the locality rule can be used
     const bool lrule = DATA && (A.policy == INSP_POLICY_INSPIRIT || A.policy == INSP_POLICY_LOCALITY);
-    const int32_t mynode = lane < ncpu ? 0 : 1 + lane - ncpu;  // this lane's worker's memory node
     if constexpr (DATA)  // each output's transfer ticks, once per run (no division at the pushes)
         for (int32_t i = lane; i < n; i += kWave)
             dxc[i] = (int32_t)(((int64_t)1024 * A.dkib[d.toff + i] + A.data_bw - 1) / A.data_bw);
@@ -1236,33 +1484,64 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
     const int32_t k_num = kset ? A.k_num : W;
     const int32_t k_den = kset ? A.k_den : A.dag_taubar[d.id];
     const int32_t max_events = A.max_events > 0 ? A.max_events : n + 1;
+    const int policy = A.policy;
 
-    // this lane's worker
-    const bool wok = lane < W;
-    int32_t run = -1, len = 0, nb = 0, last = -1, rsr = 0, dgr = 0;
-    int64_t fin = 0, expend = 0, qest = 0, st0 = 0;  // st0: the running task's start
-    int32_t pf[kPF];
+    // this lane's workers
+    bool wok[WPL], wcpu[WPL];
+    int32_t run[WPL], len[WPL], nb[WPL], last[WPL], rsr[WPL], dgr[WPL];
+    row4 pfa[WPL], pfb[WPL];  // the running task's first successors
+    int64_t fin[WPL], expend[WPL], qest[WPL];  // expend is 0 while the worker is idle
+    unsigned long long pk0[WPL], pk1[WPL];  // 64-bit keys: the best entry pushed or raised since the last pop, by rule ...
+    int32_t pp0[WPL], pp1[WPL];             // ... and its slot
 #pragma unroll
-    for (int j = 0; j < kPF; j++) pf[j] = 0;
+    for (int k = 0; k < WPL; k++) {
+        const int32_t w = lane + k * kWave;
+        wok[k] = w < W;
+        wcpu[k] = w < ncpu;
+        run[k] = -1;
+        len[k] = nb[k] = rsr[k] = dgr[k] = 0;
+        last[k] = 0;
+        pfa[k] = pfb[k] = row4{0, 0, 0, 0};
+        fin[k] = expend[k] = qest[k] = 0;
+        pk0[k] = pk1[k] = 0;
+        pp0[k] = pp1[k] = 0;
+        best[2 * w] = 0;
+        best[2 * w + 1] = 0;
+        req[w] = 0;
+    }
 
     // free block ids, lowest first: a stack in LDS below sum_cap, one in
     // global memory above it
     const int32_t nl = min(d.nblk, SC);
-    for (int32_t i = lane; i < nl; i += kWave) L.fstk[i] = nl - 1 - i;
-    for (int32_t i = lane; i < d.nblk - nl; i += kWave) freeb[i] = d.nblk - 1 - i;
     int32_t nfl = nl, nfg = d.nblk - nl;
-    // every slot starts empty (zero keys)
-    for (int32_t b = 0; b < d.nblk; b++) {
-        if (b < SLK) {
-            K.ka[b * 64 + lane] = 0;
-            if constexpr (!FIX) K.ke[b * 64 + lane] = 0;
-        } else {
-            slots.k[b * 64 + lane] = 0;
+    {
+        int32_t *freeb = A.paux + A.freeb_base + d.blk_off;
+        unsigned long long *sums = A.sums + 2 * d.blk_off, *sk = A.slots.at(64 * d.blk_off).k;
+        for (int32_t i = lane; i < nl; i += kWave) {
+            L.fstk[i] = nl - 1 - i;
+            mx[2 * i] = 0;
+            mx[2 * i + 1] = 0;
+        }
+        for (int32_t i = lane; i < d.nblk - nl; i += kWave) {
+            freeb[i] = d.nblk - 1 - i;
+            sums[2 * (nl + i)] = 0;
+            sums[2 * (nl + i) + 1] = 0;
+        }
+        // every slot starts empty (zero keys)
+        for (int32_t b = 0; b < d.nblk; b++) {
+            if (b < SLK) K.put(b * 64 + lane, 0);
+            else sk[b * 64 + lane] = 0;
         }
     }
-
-    bool merged = false, staged = false;
     wg_fence();
+    if (lane == 0) lds_store(LL::template arr<int32_t>(LL::kHs) + 3, 1);
+
+    // where this event's frontier is: in the lanes of `fm` (their rows in the
+    // f_ registers), staged by rank in `pre`, or listed in fr0 / fr1 / fbuf
+    bool merged = false, staged = false, inlane = false;
+    uint64_t fm = 0;
+    int32_t f_v = 0, f_ia = 0, f_ie = 0, f_rs = 0, f_pa = 0, f_pz = 0;
+    int2 f_e = make_int2(1, 1), f_d = make_int2(1, 1);
 
     int64_t t = 0, prev_t = 0;
     int32_t nready = 0, events = 0, done = 0, seq = 0;
@@ -1272,6 +1551,66 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
     unsigned long long pc[32] = {0}, pc_last = clock64();
 #endif
 
+    // lanes with `on`: the IE of queued task (slot qu; push order and worker
+    // qw) is now nie with out-degree ia: its keys and the maxima they enter
+    auto raise = [&](bool on, int32_t qu, int32_t qw, int32_t ia, int32_t nie) {
+        const int32_t wu = qw >> 21, bk = qu >> 6;
+        const uint32_t sq = (uint32_t)qw & (uint32_t)M21;
+        uint64_t word;
+        unsigned long long m0, m1;
+        if constexpr (kBig) {
+            word = (uint64_t)ia << 42 | (uint64_t)nie << 21 | (M21 - sq);
+            m0 = K.rule(word, 0);
+            m1 = K.rule(word, 1);
+        } else {
+            const uint32_t na = kf.ka((uint32_t)ia, (uint32_t)nie, sq), ne = kf.ke((uint32_t)ia, (uint32_t)nie, sq);
+            word = (uint64_t)ne << 32 | na;
+            m0 = (unsigned long long)na << 32 | (uint32_t)qu;
+            m1 = (unsigned long long)ne << 32 | (uint32_t)qu;
+        }
+        if (on && bk < SLK) K.put(qu, word);
+        if (ballot(on && bk >= SLK))
+            if (on && bk >= SLK) pool().k[qu] = word;
+        keep_order();
+        if (on && bk < SC) {
+            atomicMax(&mx[2 * bk], m0);
+            atomicMax(&mx[2 * bk + 1], m1);
+        }
+        if (ballot(on && bk >= SC)) {
+            unsigned long long *sums = gsums();
+            if (on && bk >= SC) {
+                wg_fetch_max(&sums[2 * bk], m0);
+                wg_fetch_max(&sums[2 * bk + 1], m1);
+            }
+        }
+        if constexpr (!kBig) {
+            if (on) {
+                atomicMax(&best[2 * wu], m0);
+                atomicMax(&best[2 * wu + 1], m1);
+            }
+        } else {
+            uint64_t left = ballot(on);
+            while (left) {
+                const int l = (int)__builtin_ctzll(left);
+                left &= left - 1;
+                const unsigned long long a0 = read_lane64(m0, l), a1 = read_lane64(m1, l);
+                const int32_t w = read_lane(wu, l), q = read_lane(qu, l);
+#pragma unroll
+                for (int k = 0; k < WPL; k++)
+                    if (lane + k * kWave == w) {
+                        if (a0 > pk0[k]) {
+                            pk0[k] = a0;
+                            pp0[k] = q;
+                        }
+                        if (a1 > pk1[k]) {
+                            pk1[k] = a1;
+                            pp1[k] = q;
+                        }
+                    }
+            }
+        }
+    };
+
     for (;;) {
         PCLK(9);
         if (++events > max_events) {
@@ -1279,211 +1618,296 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
             break;
         }
         // ------------------------------------------------------------ push
-        // this lane's load: free time (now, or the running task's expected
-        // end) plus the estimates queued on it
-        int64_t ld = 0;
-        if (wok) ld = (run >= 0 && expend > t ? expend : t) + qest;
-        for (int32_t i0 = 0; i0 < r; i0 += kWave) {
-            const int32_t idx = i0 + lane;
-            const bool ok = idx < r;
-            int32_t v_l = 0;
-            int2 e_l = make_int2(1, 1), d_l = make_int2(1, 1);
-            int32_t ia_l = 0, ie_l = 0, rs_l = 0;
-            if (staged) {
-                if (ok) {
-                    v_l = L.pre[idx];
-                    e_l = make_int2(L.pre[64 + idx], L.pre[128 + idx]);
-                    d_l = make_int2(L.pre[192 + idx], L.pre[256 + idx]);
-                    ia_l = L.pre[320 + idx];
-                    rs_l = L.pre[384 + idx];
-                    ie_l = L.pre[448 + idx];
-                }
-            } else {
-                if (ok) {
-                    if (r <= kFC) v_l = merged ? L.fr1[idx] : L.fr0[idx];
-                    else v_l = merged ? fbuf[n + idx] : fbuf[idx];
-                }
-                if (ok) {
-                    e_l = est2[v_l];
-                    d_l = dur2[v_l];
-                    const int4 fx = *reinterpret_cast<const int4 *>(&tr[v_l].iev);  // IE, IA, tau, first edge
-                    ie_l = fx.x;
-                    ia_l = fx.y;
-                    rs_l = fx.w;
-                    // fixed keys: the rank (low and high words), or the transitive attributes
-                    if (heft) {
-                        const int64_t rv = rk[v_l];
-                        ia_l = (int32_t)(uint32_t)rv;
-                        ie_l = (int32_t)(uint32_t)((uint64_t)rv >> 32);
-                    } else if (tattr) {
-                        ia_l = tia[v_l];
-                        ie_l = tie[v_l];
-                    }
-                }
+        if (r > 0) {
+            // this lane's loads past now: the rest of the running task's estimate
+            // plus the estimates queued, saturated at kLim (as are lanes without a
+            // worker), and the slot of the next push (-1: a new block)
+            uint32_t ld[WPL];
+            int32_t nslot[WPL];
+#pragma unroll
+            for (int k = 0; k < WPL; k++) {
+                const uint64_t x = (uint64_t)(max(expend[k], t) - t) + (uint64_t)qest[k];
+                ld[k] = wok[k] && x < kLim ? (uint32_t)x : kLim;
+                nslot[k] = (len[k] & 63) ? last[k] * 64 + (len[k] & 63) : -1;
             }
-            if (ballot(ok && (d_l.x < 1 || d_l.x > INSP_MAX_TICK || d_l.y < 1 || d_l.y > INSP_MAX_TICK)))
-                status |= ST_DUR;
-            PCLK(16);
-            const int32_t cntj = min(kWave, r - i0);
-            int32_t pq = 0, sqj = 0, wsj = 0;  // lane j: slot, push order and worker of task j
-            int64_t xsj = 0;                     // ... and (data model) its input transfer ticks
-            for (int32_t j = 0; j < cntj; j++) {
-                const int32_t e0 = read_lane(e_l.x, j), e1 = read_lane(e_l.y, j);
-                // DMDA's transfer term: ticks to move the inputs whose home
-                // node is not this lane's worker's (an item stays where it was made)
-                int64_t xk = 0;
-                if constexpr (DATA) {
-                    const int32_t v = read_lane(v_l, j);
-                    const int32_t pa = prp[v], pz = prp[v + 1];
-                    for (int32_t c0 = pa; c0 < pz; c0 += kWave) {
-                        int32_t nu = 0, cu = 0;
-                        if (c0 + lane < pz) {
-                            const int32_t u = pred[c0 + lane];
-                            const int32_t wu = -2 - tr[u].qpos;  // worker of a finished task
-                            nu = wu < ncpu ? 0 : 1 + wu - ncpu;
-                            cu = dxc[u];
+            for (int32_t i0 = 0;; i0 += kWave) {
+                if (!inlane) {
+                    const int32_t idx = i0 + lane;
+                    const bool in = idx < r;
+                    fm = ballot(in);
+                    if (staged) {
+                        if (in) {
+                            f_v = pre[idx];
+                            f_e = make_int2(pre[64 + idx], pre[128 + idx]);
+                            f_d = make_int2(pre[192 + idx], pre[256 + idx]);
+                            f_ia = pre[320 + idx];
+                            f_rs = pre[384 + idx];
+                            f_ie = pre[448 + idx];
                         }
-                        const int32_t cn = min(kWave, pz - c0);
-                        for (int32_t jj = 0; jj < cn; jj++) {
-                            const int32_t nj = read_lane(nu, jj), cj = read_lane(cu, jj);
-                            if (mynode != nj) xk += cj;
-                        }
-                    }
-                }
-                // least expected termination, ties to the lower worker: a
-                // 32-bit key (cost - t) << 6 | worker while it fits
-                const int64_t rc = ld + (lane < ncpu ? e0 : e1) + xk - t;
-                const uint32_t k32 = wok && rc < (1 << 26) ? (uint32_t)rc << 6 | (uint32_t)lane : ~0u;
-                const uint32_t m32 = wave_min_u32f(k32);
-                int32_t ws;
-                if (m32 != ~0u) {
-                    ws = (int32_t)(m32 & 63);
-                } else {
-                    const uint64_t k64 = wok ? (uint64_t)rc << 6 | (uint64_t)lane : ~0ull;
-                    ws = (int32_t)(wave_min_u64f(k64) & 63);
-                }
-                const int32_t ek = ws >= ncpu ? e1 : e0;
-                int64_t xs = 0;
-                if constexpr (DATA) {
-                    xs = (int64_t)read_lane64((uint64_t)xk, ws);
-                    if (xs > INSP_MAX_TICK) status |= ST_XFER;
-                }
-                const int32_t lenw = read_lane(len, ws);
-                const int32_t pos = lenw & 63;
-                int32_t blk;
-                if (pos == 0) {
-                    if (nfl > 0) {
-                        nfl--;
-                        blk = L.fstk[nfl];
                     } else {
-                        nfg--;
-                        blk = wg_load(&freeb[nfg]);
-                        settle(blk);
+                        const int32_t *fbuf = cold<WPL, int32_t>(kColdFbuf);
+                        if (in) {
+                            if (r <= kFC) f_v = merged ? fr1[idx] : fr0[idx];
+                            else f_v = merged ? fbuf[n + idx] : fbuf[idx];
+                            f_e = est2[f_v];
+                            f_d = dur2[f_v];
+                            const int4 fx = *reinterpret_cast<const int4 *>(&tr[f_v].iev);  // IE, IA, tau, first edge
+                            f_ie = fx.x;
+                            f_ia = fx.y;
+                            f_rs = fx.w;
+                            // fixed keys: the rank (low and high words), or the transitive attributes
+                            if (heft) {
+                                const int64_t rv = rk[f_v];
+                                f_ia = (int32_t)(uint32_t)rv;
+                                f_ie = (int32_t)(uint32_t)((uint64_t)rv >> 32);
+                            } else if (tattr) {
+                                f_ia = tia[f_v];
+                                f_ie = tie[f_v];
+                            }
+                        }
                     }
-                    const int32_t nbw = read_lane(nb, ws);
-                    if (lane == 0) {
-                        if (nbw < kLB) L.blist[ws * kLB + nbw] = blk;
-                        else wblk[(int64_t)ws * maxb + nbw] = blk;
+                    if constexpr (DATA) {
+                        if (in) {
+                            f_pa = prp[f_v];
+                            f_pz = prp[f_v + 1];
+                        }
                     }
-                    if (lane == ws) {
-                        nb = nbw + 1;
-                        last = blk;
+                }
+                const bool ok = __builtin_amdgcn_inverse_ballot_w64(fm);
+                if (ballot(ok && max((uint32_t)(f_d.x - 1), (uint32_t)(f_d.y - 1)) >= (uint32_t)INSP_MAX_TICK))
+                    status |= ST_DUR;
+                // data model: memory node and transfer ticks of each task's first
+                // predecessors' outputs (two round trips for all tasks together)
+                int32_t pn[kPred], px[kPred];
+                if constexpr (DATA) {
+                    const int32_t np = ok ? f_pz - f_pa : 0;
+                    int32_t pu[kPred];
+#pragma unroll
+                    for (int k = 0; k < kPred; k++) pu[k] = pred[ok && k < np ? f_pa + k : 0];
+#pragma unroll
+                    for (int k = 0; k < kPred; k++) {
+                        const int32_t u = k < np ? pu[k] : 0;
+                        pn[k] = at(tr, u)->qpos;
+                        px[k] = *at(dxc, u);
                     }
-                } else {
-                    blk = read_lane(last, ws);
+#pragma unroll
+                    for (int k = 0; k < kPred; k++) {
+                        const int32_t wu = -2 - pn[k];  // worker of a finished task
+                        pn[k] = wu < ncpu ? 0 : 1 + wu - ncpu;
+                    }
                 }
-                if (lane == ws) {
-                    len = lenw + 1;
-                    qest += ek;
-                    ld += ek;
+                PCLK(16);
+                // lane j: slot, push order and worker of its task, and (data
+                // model) its input transfer ticks
+                int32_t pq = 0, wsj = 0;
+                int64_t xsj = 0;
+                const int32_t sqj = seq + lanes_below(fm);
+                uint64_t todo = fm;
+                while (todo) {
+                    const int j = (int)__builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const int32_t e0 = read_lane(f_e.x, j), e1 = read_lane(f_e.y, j);
+                    // DMDA's transfer term: ticks to move the inputs whose home
+                    // node is not the worker's (an item stays where it was made)
+                    int64_t xk[WPL];
+#pragma unroll
+                    for (int k = 0; k < WPL; k++) xk[k] = 0;
+                    if constexpr (DATA) {
+                        const int32_t pa = read_lane(f_pa, j), np = read_lane(f_pz, j) - pa;
+#pragma unroll
+                        for (int q = 0; q < kPred; q++) {
+                            if (q >= np) break;
+                            const int32_t nj = read_lane(pn[q], j), cj = read_lane(px[q], j);
+#pragma unroll
+                            for (int k = 0; k < WPL; k++)
+                                if ((wcpu[k] ? 0 : 1 + lane + k * kWave - ncpu) != nj) xk[k] += cj;
+                        }
+                        for (int32_t c0 = kPred; c0 < np; c0 += kWave) {
+                            int32_t nu = 0, cx = 0;
+                            if (c0 + lane < np) {
+                                const int32_t u = pred[pa + c0 + lane];
+                                const int32_t wu = -2 - tr[u].qpos;
+                                nu = wu < ncpu ? 0 : 1 + wu - ncpu;
+                                cx = dxc[u];
+                            }
+                            const int32_t cn = min(kWave, np - c0);
+                            for (int32_t jj = 0; jj < cn; jj++) {
+                                const int32_t nj = read_lane(nu, jj), cj = read_lane(cx, jj);
+#pragma unroll
+                                for (int k = 0; k < WPL; k++)
+                                    if ((wcpu[k] ? 0 : 1 + lane + k * kWave - ncpu) != nj) xk[k] += cj;
+                            }
+                        }
+                    }
+                    // least expected termination, ties to the lower worker: a
+                    // 32-bit key (cost - t) << WB | worker while the cost is below kLim
+                    uint32_t k32 = ~0u;
+#pragma unroll
+                    for (int k = 0; k < WPL; k++) {
+                        uint32_t rc = ld[k] + (uint32_t)(wcpu[k] ? e0 : e1);
+                        if constexpr (DATA) rc = (uint32_t)min((uint64_t)rc + (uint64_t)xk[k], (uint64_t)kLim);
+                        else rc = min(rc, kLim);
+                        k32 = min(k32, rc << WB | (uint32_t)(lane + k * kWave));
+                    }
+                    const uint32_t m32 = wave_min_u32f(k32);
+                    int32_t ws = (int32_t)(m32 & ((1u << WB) - 1));
+                    if (m32 >> WB == kLim) {
+                        uint64_t k64 = ~0ull;
+#pragma unroll
+                        for (int k = 0; k < WPL; k++) {
+                            const int64_t rc = max(expend[k], t) - t + qest[k] + (wcpu[k] ? e0 : e1) + xk[k];
+                            if (wok[k]) k64 = min(k64, (uint64_t)rc << WB | (uint64_t)(lane + k * kWave));
+                        }
+                        ws = (int32_t)(wave_min_u64f(k64) & ((1u << WB) - 1));
+                    }
+                    const int32_t ek = ws >= ncpu ? e1 : e0;
+                    int64_t xs = 0;
+                    if constexpr (DATA) {
+                        xs = (int64_t)read_lane64((uint64_t)xk[0], ws & 63);
+                        if constexpr (WPL == 2)
+                            if (ws >= kWave) xs = (int64_t)read_lane64((uint64_t)xk[WPL - 1], ws & 63);
+                        if (xs > INSP_MAX_TICK) status |= ST_XFER;
+                    }
+                    int32_t slot = of_worker<WPL>(nslot, ws);
+                    if (slot < 0) {  // a new block
+                        int32_t blk;
+                        if (nfl > 0) {
+                            nfl--;
+                            blk = L.fstk[nfl];
+                        } else {
+                            nfg--;
+                            blk = wg_load(&cold<WPL, int32_t>(kColdFreeb)[nfg]);
+                            settle(blk);
+                        }
+                        blk = uniform(blk);
+                        const int32_t nbw = of_worker<WPL>(nb, ws);
+                        if (nbw < kLB) {
+                            if (lane == 0) L.blist[ws * kLB + nbw] = blk;
+                        } else {
+                            int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
+                            if (lane == 0) wblk[(int64_t)ws * maxb + nbw] = blk;
+                        }
+#pragma unroll
+                        for (int k = 0; k < WPL; k++)
+                            if (lane + k * kWave == ws) {
+                                nb[k] = nbw + 1;
+                                last[k] = blk;
+                            }
+                        slot = blk * 64;
+                    }
+                    const int32_t next = (slot + 1) & 63 ? slot + 1 : -1;
+#pragma unroll
+                    for (int k = 0; k < WPL; k++)
+                        if (lane + k * kWave == ws) {
+                            len[k]++;
+                            qest[k] += ek;
+                            ld[k] = min(ld[k] + (uint32_t)ek, kLim);
+                            nslot[k] = next;
+                        }
+                    if (lane == j) {
+                        pq = slot;
+                        wsj = ws;
+                        xsj = xs;
+                    }
+                    if constexpr (kBig) {
+                        // the best entry pushed since the worker's last pop
+                        const uint64_t hi = (uint32_t)read_lane(f_ie, j), lo = (uint32_t)read_lane(f_ia, j);
+                        const uint64_t sq = M21 - (uint64_t)(seq + __popcll(fm & ((1ull << j) - 1)));
+                        const uint64_t raw = heft ? (hi << 32 | lo) << 21 | sq : lo << 42 | hi << 21 | sq;
+                        const unsigned long long a0 = K.rule(raw, 0), a1 = K.rule(raw, 1);
+#pragma unroll
+                        for (int k = 0; k < WPL; k++)
+                            if (lane + k * kWave == ws) {
+                                if (a0 > pk0[k]) {
+                                    pk0[k] = a0;
+                                    pp0[k] = slot;
+                                }
+                                if (a1 > pk1[k]) {
+                                    pk1[k] = a1;
+                                    pp1[k] = slot;
+                                }
+                            }
+                    }
                 }
-                if (lane == j) {
-                    pq = blk * 64 + pos;
-                    sqj = seq;
-                    wsj = ws;
-                    xsj = xs;
-                }
-                seq++;
-                nready++;
-            }
-            PCLK(17);
-            // the chunk's queue entries, task records and block maxima: lane j
-            // writes task j's.  The first entry of a new block sets its maxima,
-            // then every entry raises them -- the first one's lane too, so that
-            // within each lane the store precedes the atomic on that address
-            // and the compiler keeps the stores of some lanes ahead of the
-            // atomics of the others.
-            const int32_t bq = pq >> 6;
-            KT a0 = 0, a1 = 0;
-            if (ok) {
+                PCLK(17);
+                const int32_t np = __popcll(fm);
+                seq += np;
+                nready += np;
+                // the chunk's queue entries and task records, a lane each, then the
+                // maxima of their blocks and workers
+                const int32_t bq = pq >> 6;
                 const bool g = wsj >= ncpu;
-                const int32_t ekl = g ? e_l.y : e_l.x, dkl = g ? d_l.y : d_l.x;
-                uint64_t raw;
-                if constexpr (FIX) {
+                const int32_t ekl = g ? f_e.y : f_e.x, dkl = g ? f_d.y : f_d.x;
+                uint64_t word;
+                unsigned long long m0, m1;
+                if constexpr (kBig) {
                     // the general loop's key: rank << 21 or IA << 42 | IE << 21, then the push order
-                    raw = heft ? ((uint64_t)(uint32_t)ie_l << 32 | (uint32_t)ia_l) << 21 | (M21 - (uint64_t)sqj)
-                               : (uint64_t)ia_l << 42 | (uint64_t)ie_l << 21 | (M21 - (uint64_t)sqj);
-                    a0 = K.rule(raw, 0);
-                    a1 = K.rule(raw, 1);
+                    word = heft ? ((uint64_t)(uint32_t)f_ie << 32 | (uint32_t)f_ia) << 21 | (M21 - (uint64_t)sqj)
+                                : (uint64_t)f_ia << 42 | (uint64_t)f_ie << 21 | (M21 - (uint64_t)sqj);
+                    m0 = K.rule(word, 0);
+                    m1 = K.rule(word, 1);
                 } else {
-                    a0 = kf.ka((uint32_t)ia_l, (uint32_t)ie_l, (uint32_t)sqj);
-                    a1 = kf.ke((uint32_t)ia_l, (uint32_t)ie_l, (uint32_t)sqj);
-                    raw = (uint64_t)a1 << 32 | a0;
+                    const uint32_t a0 = kf.ka((uint32_t)f_ia, (uint32_t)f_ie, (uint32_t)sqj);
+                    const uint32_t a1 = kf.ke((uint32_t)f_ia, (uint32_t)f_ie, (uint32_t)sqj);
+                    word = (uint64_t)a1 << 32 | a0;
+                    m0 = (unsigned long long)a0 << 32 | (uint32_t)pq;
+                    m1 = (unsigned long long)a1 << 32 | (uint32_t)pq;
                 }
-                const uint64_t xw = (uint64_t)v_l << 42 | (uint64_t)(dkl & M21) << 21 | (uint64_t)(ekl & M21);
-                if (bq < SLK) {
-                    if constexpr (FIX) {
-                        K.ka[pq] = raw;
-                    } else {
-                        K.ka[pq] = a0;
-                        K.ke[pq] = a1;
-                    }
-                } else {
-                    slots.k[pq] = raw;
-                }
-                if (bq < SLC) {
+                const uint64_t xw = (uint64_t)f_v << 42 | (uint64_t)(dkl & M21) << 21 | (uint64_t)(ekl & M21);
+                const bool lk = ok && bq < SLK, lx = ok && bq < SLC, lm = ok && bq < SC;
+                if (lk) K.put(pq, word);
+                if (lx) {
                     L.sx[pq] = xw;
-                    L.srs[pq] = rs_l;
-                } else {
-                    slots.x[pq] = xw;
-                    slots.rs[pq] = rs_l;
+                    L.srs[pq] = f_rs;
                 }
-                tr[v_l].qpos = pq;
-                tr[v_l].seq = sqj;
-                // data model: the record's first word holds the time the
-                // task's inputs arrive (transfers start now) until its pop
-                if constexpr (DATA) tr[v_l].word = (unsigned long long)(t + xsj);
-                if ((pq & 63) == 0) {
-                    if (bq < SC) {
-                        K.mx[2 * bq] = a0;
-                        K.mx[2 * bq + 1] = a1;
-                        L.stale[bq] = 0;
-                    } else {
-                        sums[2 * bq] = a0;
-                        sums[2 * bq + 1] = a1;
+                if (ballot(ok && !lx)) {
+                    const SlotPool slots = pool();
+                    if (ok && !lk) slots.k[pq] = word;
+                    if (ok && !lx) {
+                        slots.x[pq] = xw;
+                        slots.rs[pq] = f_rs;
                     }
-                    // never lowered by pops: an upper bound for the block
-                    if (lrule) barr[bq] = t + xsj;
                 }
-            }
-            if (ok) {
-                if (bq < SC) {
-                    atomicMax(&K.mx[2 * bq], a0);
-                    atomicMax(&K.mx[2 * bq + 1], a1);
-                } else {
-                    wg_fetch_max(&sums[2 * bq], (unsigned long long)a0);
-                    wg_fetch_max(&sums[2 * bq + 1], (unsigned long long)a1);
+                if (ok) {
+                    // queue slot, then push order and worker
+                    *reinterpret_cast<int2 *>(&at(tr, f_v)->qpos) = make_int2(pq, sqj | wsj << 21);
+                    // data model: the record's first word holds the time the
+                    // task's inputs arrive (transfers start now) until its pop
+                    if constexpr (DATA) {
+                        at(tr, f_v)->word = (unsigned long long)(t + xsj);
+                        // never lowered by pops: an upper bound for the block
+                        if (lrule && (pq & 63) == 0) barr[bq] = t + xsj;
+                    }
                 }
-                if (lrule) wg_fetch_max(reinterpret_cast<unsigned long long *>(&barr[bq]), (unsigned long long)(t + xsj));
+                keep_order();
+                if (lm) {
+                    atomicMax(&mx[2 * bq], m0);
+                    atomicMax(&mx[2 * bq + 1], m1);
+                }
+                if (ballot(ok && !lm)) {
+                    unsigned long long *sums = gsums();
+                    if (ok && !lm) {
+                        wg_fetch_max(&sums[2 * bq], m0);
+                        wg_fetch_max(&sums[2 * bq + 1], m1);
+                    }
+                }
+                if constexpr (!kBig) {
+                    if (ok) {
+                        atomicMax(&best[2 * wsj], m0);
+                        atomicMax(&best[2 * wsj + 1], m1);
+                    }
+                }
+                if constexpr (DATA)
+                    if (lrule && ok)
+                        wg_fetch_max(reinterpret_cast<unsigned long long *>(&barr[bq]), (unsigned long long)(t + xsj));
+                if (inlane || i0 + kWave >= r) break;
             }
         }
         PCLK(0);
-        wg_fence();
-        PCLK(1);
         // -------------------------------------------------------- regulate
         const int32_t observed = nready;
-        if (A.policy == INSP_POLICY_INSPIRIT) {
-            if (nready > peak) peak = nready;
+        if (policy == INSP_POLICY_INSPIRIT) {
+            peak = max(peak, nready);
             const int32_t dn = nready - prev_n;
             if ((dn < 0 ? -dn : dn) >= s_inc) {
                 const int64_t dt = t - prev_t;
@@ -1504,357 +1928,281 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                 }
             }
         }
-        const int pmode = A.policy == INSP_POLICY_FIFO ? INSP_MODE_FIFO
-                        : A.policy == INSP_POLICY_ABILITY_ONLY ? INSP_MODE_ABILITY
-                        : A.policy == INSP_POLICY_EFI_ONLY ? INSP_MODE_EFI
-                        : (DATA && A.policy == INSP_POLICY_LOCALITY) ? INSP_MODE_EFI_LOC
-                        : heft ? INSP_MODE_RANK : mode;
-        const int ord = heft ? 3 : pmode == INSP_MODE_FIFO ? 2 : pmode == INSP_MODE_ABILITY ? 0 : 1;
-        const int slot = ord == 1 ? 1 : 0;
+        const int pmode = policy == INSP_POLICY_INSPIRIT ? mode
+                        : policy == INSP_POLICY_FIFO ? INSP_MODE_FIFO
+                        : policy == INSP_POLICY_ABILITY_ONLY ? INSP_MODE_ABILITY
+                        : policy == INSP_POLICY_EFI_ONLY ? INSP_MODE_EFI
+                        : policy == INSP_POLICY_LOCALITY ? INSP_MODE_EFI_LOC : INSP_MODE_RANK;
+        const int slot = pmode == INSP_MODE_EFI || pmode == INSP_MODE_EFI_LOC ? 1 : 0;
         // efficiency with locality under the data model: tasks whose inputs
         // have arrived first
         const bool loc = DATA && pmode == INSP_MODE_EFI_LOC;
         // ------------------------------------------------------------- pop
         int32_t popped = 0;
-        bool popnow = false;        // this lane's worker took a task in this event
-        int32_t iep = 0;            // ... with this IE
-        int32_t mvt = -1, mvp = 0;  // lane k: task moved into the hole of the k-th pop, and where
-        uint64_t idle = ballot(wok && run < 0 && len > 0);
-        while (idle) {
-            const int32_t w = (int32_t)__builtin_ctzll(idle);
-            idle &= idle - 1;
-            const int32_t nbw = read_lane(nb, w), lenw = read_lane(len, w), lastw = read_lane(last, w);
-            const int32_t lastpos = (lenw - 1) & 63;
-            int32_t p = 0;
-            PCLK(10);
-            bool lsel = false;  // the locality rule found a task whose inputs are in place
+#pragma unroll
+        for (int k = 0; k < WPL; k++) {
+            const bool want = run[k] < 0 && len[k] > 0;  // only workers have queues
+            const uint64_t wm = ballot(want);
+            if (wm == 0) continue;
+            const int32_t w = lane + k * kWave;
+            const int32_t np = __popcll(wm);
+            popped += np;
+            nready -= np;
+            // the best entry of each queue, once its rescan is done (the
+            // second wave answers every request)
+            unsigned long long bk;
+            int32_t bp = 0;
+            for (int32_t spin = 0;; spin++) {
+                const int32_t rq = lds_load(&req[w]);
+                keep_order();
+                bk = lds_load(&best[2 * w + slot]);
+                if constexpr (kBig) bp = lds_load(&bpos[2 * w + slot]);
+                if (!ballot(want && rq != 0)) break;
+                if (spin > kReqSpin) {  // never: a wait that ends all the same
+                    status |= ST_HANG;
+                    done = n;
+                    break;
+                }
+            }
+            keep_order();
+            int32_t p;
+            if constexpr (kBig) p = (slot ? pk1[k] : pk0[k]) > bk ? (slot ? pp1[k] : pp0[k]) : bp;
+            else p = (int32_t)(uint32_t)bk;
+            p = want ? p : 0;
+            uint32_t key = (uint32_t)(bk >> 32);  // 32-bit keys: the entry's key under the rule
+            PCLK(11);
             if constexpr (DATA) {
                 if (loc) {
-                    // the arrival times are not in the keys.  A block whose
-                    // latest input arrival has passed holds only tasks whose
-                    // inputs are in place, so its efficiency maximum stands;
-                    // the other blocks are scanned entry by entry
-                    KT bestk = 0;
-                    int32_t bestb = -1;
-                    for (int32_t i0 = 0; i0 < nbw; i0 += kWave) {
-                        const int32_t i = i0 + lane;
-                        int32_t b = -1;
-                        if (i < nbw) {
-                            if (i < kLB) {
-                                b = L.blist[w * kLB + i];
-                            } else {
-                                b = wg_load(&wblk[(int64_t)w * maxb + i]);
-                                settle(b);
+                    // the arrival times are not in the keys: a queue whose best
+                    // entry's inputs are still moving is searched, a block whose
+                    // latest input arrival has passed by its maximum (all its tasks
+                    // have their inputs), other blocks entry by entry
+                    bool late = false;
+                    const SlotPool slots = pool();
+                    const int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
+                    unsigned long long *sums = gsums();
+                    if (want) {
+                        const uint64_t xv = (p >> 6) < SLC ? L.sx[p] : wg_load(&slots.x[p]);
+                        late = (int64_t)wg_load(&tr[(int32_t)(xv >> 42)].word) > t;
+                    }
+                    uint64_t lm = ballot(late);
+                    while (lm) {
+                        const int l = (int)__builtin_ctzll(lm);
+                        lm &= lm - 1;
+                        const int32_t wl = l + k * kWave;
+                        const int32_t nbw = read_lane(nb[k], l);
+                        KT bestk = 0;
+                        int32_t bestb = -1;
+                        for (int32_t i0 = 0; i0 < nbw; i0 += kWave) {
+                            const int32_t i = i0 + lane;
+                            int32_t b = -1;
+                            if (i < nbw) {
+                                if (i < kLB) {
+                                    b = L.blist[wl * kLB + i];
+                                } else {
+                                    b = wg_load(&wblk[(int64_t)wl * maxb + i]);
+                                    settle(b);
+                                }
                             }
-                        }
-                        uint64_t sm = ballot(b >= 0 && b < SC && L.stale[b] != 0);
-                        while (sm) {
-                            const int l = (int)__builtin_ctzll(sm);
-                            sm &= sm - 1;
-                            rebuild_max<FIX>(slots, K, L, sums, SLK, SC, read_lane(b, l));
-                        }
-                        KT kk = 0;
-                        bool mix = false;
-                        if (b >= 0) {
-                            if ((int64_t)wg_load(&barr[b]) <= t) kk = b < SC ? K.mx[2 * b + 1] : (KT)wg_load(&sums[2 * b + 1]);
-                            else mix = true;
-                        }
-                        const KT km = wave_max_k(kk);
-                        if (km > bestk) {
-                            bestk = km;
-                            bestb = read_lane(b, (int)__builtin_ctzll(ballot(kk == km && b >= 0)));
-                        }
-                        uint64_t mm = ballot(mix);
-                        while (mm) {
-                            const int32_t bm = read_lane(b, (int)__builtin_ctzll(mm));
-                            mm &= mm - 1;
-                            KT ke = 0;
-                            if (lane < (bm == lastw ? lastpos + 1 : 64)) {
+                            KT kk = 0;
+                            bool mix = false;
+                            if (b >= 0) {
+                                if ((int64_t)wg_load(&barr[b]) <= t)
+                                    kk = K.of_max(b < SC ? lds_load(&mx[2 * b + 1])
+                                                         : __hip_atomic_load(&sums[2 * b + 1], __ATOMIC_RELAXED,
+                                                                             __HIP_MEMORY_SCOPE_AGENT));
+                                else mix = true;
+                            }
+                            const KT km = wave_max_k(kk);
+                            if (km > bestk) {
+                                bestk = km;
+                                bestb = read_lane(b, (int)__builtin_ctzll(ballot(kk == km && b >= 0)));
+                            }
+                            uint64_t mm = ballot(mix);
+                            while (mm) {
+                                const int32_t bm = read_lane(b, (int)__builtin_ctzll(mm));
+                                mm &= mm - 1;
                                 const int32_t pe = bm * 64 + lane;
-                                const uint64_t xv = bm < SLC ? L.sx[pe] : wg_load(&slots.x[pe]);
                                 const KT kr = bm < SLK ? K.lds(pe, 1) : K.rule(wg_load(&slots.k[pe]), 1);
-                                if ((int64_t)wg_load(&tr[(int32_t)(xv >> 42)].word) <= t) ke = kr;
-                            }
-                            const KT kme = wave_max_k(ke);
-                            if (kme > bestk) {
-                                bestk = kme;
-                                bestb = bm;
+                                KT ke = 0;
+                                if (kr != 0) {
+                                    const uint64_t xv = bm < SLC ? L.sx[pe] : wg_load(&slots.x[pe]);
+                                    if ((int64_t)wg_load(&tr[(int32_t)(xv >> 42)].word) <= t) ke = kr;
+                                }
+                                const KT kme = wave_max_k(ke);
+                                if (kme > bestk) {
+                                    bestk = kme;
+                                    bestb = bm;
+                                }
                             }
                         }
-                    }
-                    if (bestb >= 0) {
-                        // the best entry of that block whose inputs are in place
-                        KT key = 0;
-                        if (lane < (bestb == lastw ? lastpos + 1 : 64)) {
+                        if (bestb >= 0) {  // the entry of that block with this key
                             const int32_t pe = bestb * 64 + lane;
-                            const uint64_t xv = bestb < SLC ? L.sx[pe] : wg_load(&slots.x[pe]);
                             const KT kr = bestb < SLK ? K.lds(pe, 1) : K.rule(wg_load(&slots.k[pe]), 1);
-                            if ((int64_t)wg_load(&tr[(int32_t)(xv >> 42)].word) <= t) key = kr;
-                        }
-                        const KT km = wave_max_k(key);
-                        p = bestb * 64 + (int)__builtin_ctzll(ballot(key == km && key != 0));
-                        lsel = true;
-                    }
-                }
-            }
-            if (lsel) {
-                // chosen by the locality rule
-            } else if (nbw <= A.scan_max) {
-                // lane l compares entry l of every block of the worker: the
-                // blocks held in LDS, then those in global memory (a single
-                // block is the last one, known without reading the list)
-                // (at most 16 blocks: the list's LDS part holds them all, as its
-                // capacity is at least min(16, blocks in the pool))
-                int32_t bl = -1;
-                if (nbw == 1) bl = lastw;
-                else if (lane < nbw) bl = L.blist[w * kLB + lane];
-                const uint64_t all = nbw == 1 ? 1ull : ballot(lane < nbw);
-                const uint64_t inl = nbw == 1 ? (lastw < SLK ? 1ull : 0ull) : ballot(lane < nbw && bl < SLK);
-                KT best = 0;
-                int32_t bp = -1;
-                if (inl == all) {
-                    // every block in LDS: blocks i .. i+3 of the list, the
-                    // padding past the list re-reading its last block
-                    for (int32_t i = 0; i < nbw; i += 4) {
-                        KT kk[4];
-                        int32_t pp[4];
-#pragma unroll
-                        for (int u = 0; u < 4; u++) {
-                            pp[u] = read_lane(bl, min(i + u, nbw - 1)) * 64 + lane;
-                            kk[u] = K.lds(pp[u], slot);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; u++) {
-                            if (kk[u] > best) {
-                                best = kk[u];
-                                bp = pp[u];
+                            const int32_t pn2 = bestb * 64 + (int32_t)__builtin_ctzll(ballot(kr == bestk));
+                            if (lane == l) {
+                                p = pn2;
+                                if constexpr (!kBig) key = (uint32_t)bestk;
                             }
                         }
                     }
-                } else if (slot) {
-                    if (inl) scan_columns<FIX, true, 1>(slots, K, inl, bl, best, bp);
-                    scan_columns<FIX, false, 1>(slots, K, all & ~inl, bl, best, bp);
-                } else {
-                    if (inl) scan_columns<FIX, true, 0>(slots, K, inl, bl, best, bp);
-                    scan_columns<FIX, false, 0>(slots, K, all & ~inl, bl, best, bp);
                 }
-                const KT km = wave_max_k(best);
-                p = read_lane(bp, (int)__builtin_ctzll(ballot(best == km && bp >= 0)));
-            } else {
-                // many blocks: rebuild stale maxima, pick the block, scan it
-                KT bk = 0;
-                int32_t bid = -1;
-                for (int32_t i0 = 0; i0 < nbw; i0 += kWave) {
-                    const int32_t i = i0 + lane;
-                    int32_t b = -1;
-                    if (i < nbw) {
-                        if (i < kLB) {
-                            b = L.blist[w * kLB + i];
-                        } else {
-                            b = wg_load(&wblk[(int64_t)w * maxb + i]);
-                            settle(b);
-                        }
-                    }
-                    bool st = false;
-                    if (b >= 0 && b < SC) st = L.stale[b] != 0;
-                    uint64_t sm = ballot(st);
-                    while (sm) {
-                        const int l = (int)__builtin_ctzll(sm);
-                        sm &= sm - 1;
-                        const int32_t sb = read_lane(b, l);
-                        rebuild_max<FIX>(slots, K, L, sums, SLK, SC, sb);
-                    }
-                    if (b >= 0) {
-                        KT k;
-                        if (b < SC) {
-                            k = K.mx[2 * b + slot];
-                        } else {
-                            k = (KT)wg_load(&sums[2 * b + slot]);
-                            settle(k);
-                        }
-                        if (k > bk) {
-                            bk = k;
-                            bid = b;
-                        }
-                    }
-                }
-                const KT kmb = wave_max_k(bk);
-                const int32_t bb = read_lane(bid, (int)__builtin_ctzll(ballot(bk == kmb && bid >= 0)));
-                const int32_t cntb = bb == lastw ? lastpos + 1 : 64;
-                const KT key = block_keys<FIX>(slots, K, SLK, bb, slot);
-                const KT km = wave_max_k(key);
-                p = bb * 64 + (int)__builtin_ctzll(ballot(key == km && lane < cntb));
             }
-            PCLK(11);
             // take the entry at p; the worker's final entry q fills the hole
-            const int32_t bb = p >> 6;
-            const int32_t q = lastw * 64 + lastpos;
-            uint32_t ve = 0;
-            uint64_t vx, mx = 0, mkr = 0;  // mkr: the moved entry's key word (the two 32-bit keys, or the fixed key)
-            int32_t vr, mr = 0;
-            if (bb < SLC) {
+            const int32_t bb = p >> 6, lastw = last[k], nlen = len[k] - 1;
+            const int32_t q = want ? lastw * 64 + (nlen & 63) : 0;
+            const bool mv = want && p != q;
+            uint64_t vx, mxw, mkr;  // mkr: the moved entry's key word
+            int32_t vr, mr;
+            const bool far = want && max(bb, lastw) >= SLC;  // an entry in global memory
+            if (ballot(far) == 0) {
+                // payload and keys in LDS (other lanes read slot 0)
                 vx = L.sx[p];
                 vr = L.srs[p];
+                mxw = L.sx[q];
+                mr = L.srs[q];
+                mkr = K.word(q);
+                if constexpr (!kBig)
+                    if (kf.fifo) key = K.ke[p];  // the FIFO key holds no attributes
+                if (mv) {
+                    L.sx[p] = mxw;
+                    L.srs[p] = mr;
+                    K.put(p, mkr);
+                }
+                if (want) K.put(q, 0);  // the worker's final slot is now empty
             } else {
-                vx = wg_load(&slots.x[p]);
-                vr = wg_load(&slots.rs[p]);
+                const SlotPool slots = pool();
+                vx = mxw = mkr = 0;
+                vr = mr = 0;
+                if (want) {
+                    if (bb < SLC) {
+                        vx = L.sx[p];
+                        vr = L.srs[p];
+                    } else {
+                        vx = wg_load(&slots.x[p]);
+                        vr = wg_load(&slots.rs[p]);
+                    }
+                    if (lastw < SLC) {
+                        mxw = L.sx[q];
+                        mr = L.srs[q];
+                    } else {
+                        mxw = wg_load(&slots.x[q]);
+                        mr = wg_load(&slots.rs[q]);
+                    }
+                    mkr = lastw < SLK ? K.word(q) : wg_load(&slots.k[q]);
+                    if constexpr (!kBig)
+                        if (kf.fifo) key = bb < SLK ? K.ke[p] : (uint32_t)(wg_load(&slots.k[p]) >> 32);
+                }
+                if (mv) {
+                    if (bb < SLK) K.put(p, mkr);
+                    else slots.k[p] = mkr;
+                    if (bb < SLC) {
+                        L.sx[p] = mxw;
+                        L.srs[p] = mr;
+                    } else {
+                        slots.x[p] = mxw;
+                        slots.rs[p] = mr;
+                    }
+                }
+                if (want) {
+                    if (lastw < SLK) K.put(q, 0);
+                    else slots.k[q] = 0;
+                }
                 settle(vx);
                 settle(vr);
             }
-            if constexpr (!FIX) {
-                if (bb < SLK) {
-                    ve = K.ke[p];
-                } else {
-                    ve = (uint32_t)(wg_load(&slots.k[p]) >> 32);
-                    settle(ve);
-                }
+            PCLK(12);
+            if (mv) {
+                at(tr, (int32_t)(mxw >> 42))->qpos = p;
+                // the moved entry keeps block bb's arrival bound valid
+                if constexpr (DATA)
+                    if (lrule && lastw != bb) barr[bb] = max(barr[bb], barr[lastw]);
             }
-            if (p != q) {
-                if (lastw < SLK) {
-                    if constexpr (FIX) mkr = K.ka[q];
-                    else mkr = (uint64_t)K.ke[q] << 32 | K.ka[q];
-                } else {
-                    mkr = wg_load(&slots.k[q]);
-                    settle(mkr);
+            // the maxima of the blocks that changed wait for their rescan
+            const bool gone = want && max(bb, lastw) >= SC;
+            if (ballot(gone)) {
+                unsigned long long *sums = gsums();
+                if (want && bb >= SC) sums[2 * bb] = sums[2 * bb + 1] = 0;
+                if (want && lastw >= SC) sums[2 * lastw] = sums[2 * lastw + 1] = 0;
+            }
+            if (want) {
+                if (bb < SC) {
+                    mx[2 * bb] = 0;
+                    mx[2 * bb + 1] = 0;
                 }
-                if (lastw < SLC) {
-                    mx = L.sx[q];
-                    mr = L.srs[q];
-                } else {
-                    mx = wg_load(&slots.x[q]);
-                    mr = wg_load(&slots.rs[q]);
-                    settle(mx);
-                    settle(mr);
+                if (lastw < SC) {
+                    mx[2 * lastw] = 0;
+                    mx[2 * lastw + 1] = 0;
                 }
+                best[2 * w] = 0;
+                best[2 * w + 1] = 0;
+            }
+            const bool freed = want && (nlen & 63) == 0;
+            int32_t newlast = lastw;
+            if (ballot(freed)) {
+                const uint64_t fl = ballot(freed && lastw < SC), fg = ballot(freed && lastw >= SC);
+                int32_t *freeb = cold<WPL, int32_t>(kColdFreeb);
+                const int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
+                if (freed) {
+                    if (lastw < SC) L.fstk[nfl + lanes_below(fl)] = lastw;
+                    else freeb[nfg + lanes_below(fg)] = lastw;
+                    nb[k]--;
+                    if (nb[k] <= 0) newlast = 0;
+                    else if (nb[k] - 1 < kLB) newlast = L.blist[w * kLB + nb[k] - 1];
+                    else newlast = wg_load(&wblk[(int64_t)w * maxb + nb[k] - 1]);
+                }
+                settle(newlast);
+                nfl += __popcll(fl);
+                nfg += __popcll(fg);
+            }
+            if (want && nlen > 0) {
+                const uint32_t c0 = freed && bb == lastw ? kNoBlock : (uint32_t)bb;
+                const uint32_t c1 = freed || bb == lastw ? kNoBlock : (uint32_t)lastw;
+                rnb[w] = nb[k];
+                rch[w] = (int32_t)(c0 | c1 << 16);
+                keep_order();
+                lds_store(&req[w], 1);
             }
             const int32_t v = (int32_t)(vx >> 42);
             const int32_t dk = (int32_t)((vx >> 21) & M21), ek = (int32_t)(vx & M21);
             // a task whose inputs are still moving holds the worker until they arrive
             int64_t s0 = t;
-            if constexpr (DATA) s0 = max(t, (int64_t)wg_load(&tr[v].word));
-            // out-degree and the IE to record, from the direct key (fixed keys:
-            // read from the task's record once the event's pops are done)
+            if constexpr (DATA)
+                if (want) s0 = max(t, (int64_t)wg_load(&at(tr, v)->word));
             int32_t deg = 0, iev = 0;
-            if constexpr (!FIX) {
-                deg = (int32_t)((ve >> kf.sa) & kf.amask);
-                iev = (int32_t)((ve >> kf.sb) & kf.amask);
+            if constexpr (kBig) {
+                if (want) {
+                    const int4 fx = *reinterpret_cast<const int4 *>(&at(tr, v)->iev);  // IE, IA, tau, first edge
+                    deg = fx.y;
+                    iev = tattr ? tie[v] : fx.x;
+                    pk0[k] = pk1[k] = 0;
+                }
+            } else {
+                const int32_t f1 = (int32_t)((key >> kf.sb) & kf.amask), f0 = (int32_t)((key >> kf.sa) & kf.amask);
+                const bool efi = slot || kf.fifo;
+                deg = efi ? f0 : f1;
+                iev = efi ? f1 : f0;
             }
-            if (p != q) {
-                if (lane == 0) {
-                    if (bb < SLK) {
-                        if constexpr (FIX) {
-                            K.ka[p] = mkr;
-                        } else {
-                            K.ka[p] = (uint32_t)mkr;
-                            K.ke[p] = (uint32_t)(mkr >> 32);
-                        }
-                    } else {
-                        slots.k[p] = mkr;
-                    }
-                    if (bb < SLC) {
-                        L.sx[p] = mx;
-                        L.srs[p] = mr;
-                    } else {
-                        slots.x[p] = mx;
-                        slots.rs[p] = mr;
-                    }
-                    // the moved entry keeps block bb's arrival bound valid
-                    if (lrule && lastw != bb) barr[bb] = max(barr[bb], barr[lastw]);
-                }
-                if (lane == popped) {
-                    mvt = (int32_t)(mx >> 42);
-                    mvp = p;
-                }
-            }
-            // the worker's final slot is now empty
-            if (lane == 0) {
-                if (lastw < SLK) {
-                    K.ka[q] = 0;
-                    if constexpr (!FIX) K.ke[q] = 0;
-                } else {
-                    slots.k[q] = 0;
-                }
-            }
-            PCLK(12);
-            const int32_t nlen = lenw - 1;
-            const bool freed = (nlen & 63) == 0;
-            int32_t nbn = nbw, newlast = lastw;
-            if (freed) {
-                if (lane == 0) {
-                    if (lastw < SC) L.fstk[nfl] = lastw;
-                    else freeb[nfg] = lastw;
-                }
-                if (lastw < SC) nfl++;
-                else nfg++;
-                nbn = nbw - 1;
-                if (nbn <= 0) {
-                    newlast = -1;
-                } else if (nbn - 1 < kLB) {
-                    newlast = L.blist[w * kLB + nbn - 1];
-                } else {
-                    newlast = wg_load(&wblk[(int64_t)w * maxb + nbn - 1]);
-                    settle(newlast);
-                }
-            }
-            // maxima of the blocks that changed: bb lost the winner (and took
-            // the final entry), the last block lost its final entry
-            if (!(bb == lastw && freed)) {
-                if (bb < SC) {
-                    if (lane == 0) L.stale[bb] = 1;
-                } else {
-                    rebuild_max<FIX>(slots, K, L, sums, SLK, SC, bb);
-                }
-            }
-            if (lastw != bb && !freed) {
-                if (lastw < SC) {
-                    if (lane == 0) L.stale[lastw] = 1;
-                } else {
-                    rebuild_max<FIX>(slots, K, L, sums, SLK, SC, lastw);
-                }
+            if (want) {
+                // the first successors, for the release (past the row's end
+                // they are never used; the successor array is padded)
+                pfa[k] = *reinterpret_cast<const row4 *>(col + vr);
+                pfb[k] = *reinterpret_cast<const row4 *>(col + vr + 4);
+                put_record(at(tr, v), s0, dk, w, iev, pmode);
+                len[k] = nlen;
+                last[k] = newlast;
+                run[k] = v;
+                fin[k] = s0 + dk;
+                expend[k] = s0 + ek;
+                qest[k] -= ek;
+                rsr[k] = vr;
+                dgr[k] = deg;
+                // for the wave that reads ahead
+                lfin[w] = fin[k];
+                lrun[w] = v;
             }
             PCLK(13);
-            if (lane == w) {
-                len = nlen;
-                nb = nbn;
-                last = newlast;
-                run = v;
-                st0 = s0;
-                fin = s0 + dk;
-                expend = s0 + ek;
-                qest -= ek;
-                rsr = vr;
-                dgr = deg;
-                iep = iev;
-                popnow = true;
-            }
-            nready--;
-            popped++;
-            PCLK(14);
         }
-        // the event's pops write their records with one store (a worker pops
-        // at most once per event, so the addresses differ), and prefetch the
-        // first successors of the tasks they started
-        if constexpr (FIX) {
-            // every worker that took a task reads its out-degree and IE at once
-            if (popnow) {
-                const int4 fx = *reinterpret_cast<const int4 *>(&tr[run].iev);  // IE, IA, tau, first edge
-                dgr = fx.y;
-                iep = tattr ? tie[run] : fx.x;
-            }
-        }
-        if (popnow) put_record(&tr[run], DATA ? st0 : t, (int32_t)(fin - (DATA ? st0 : t)), lane, iep, pmode);
-        if (popnow && dgr > 0) {
-            // entries past the row repeat its last successor (never used)
-#pragma unroll
-            for (int j = 0; j < kPF; j++) pf[j] = col[rsr + min(j, dgr - 1)];
-        }
-        if (mvt >= 0) tr[mvt].qpos = mvp;
-        // the running tasks, for the work-group's prefetching wave
-        if (wok) {
-            L.run[lane] = run;
-            L.fin[lane] = fin;
-        }
-        PCLK(15);
         PCLK(2);
         if (A.trace && lane == 0 && events <= max_events) {
             insp_trace_rec rec;
@@ -1869,8 +2217,12 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
         }
         if (done == n) break;
         // --------------------------------------------------------- advance
-        // every running task ends within 2^20 ticks of t
-        const uint32_t dtm = wave_min_u32f(wok && run >= 0 ? (uint32_t)(fin - t) : ~0u);
+        // every running task ends within 2^21 ticks of t
+        uint32_t dl = ~0u;
+#pragma unroll
+        for (int k = 0; k < WPL; k++)
+            if (run[k] >= 0) dl = min(dl, (uint32_t)(fin[k] - t));
+        const uint32_t dtm = wave_min_u32f(dl);
         if (dtm == ~0u) {
             status |= ST_HANG;
             break;
@@ -1879,38 +2231,143 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
         PCLK(3);
         // --------------------------------------------------------- release
         r = 0;
-        int32_t nc = 0, nseg = 0, ndone = 0;
-        {
-            const bool fin_now = wok && run >= 0 && fin == t;
-            uint64_t mask = ballot(fin_now);
-            const int32_t c_l = fin_now ? run : -1;
-            if (fin_now) run = -1;
+        uint64_t cm[WPL];
+        int32_t c_l[WPL];
+        int32_t ndone = 0;
+#pragma unroll
+        for (int k = 0; k < WPL; k++) {
+            const bool fin_now = run[k] >= 0 && fin[k] == t;
+            cm[k] = ballot(fin_now);
+            ndone += __popcll(cm[k]);
+            c_l[k] = run[k];
+            if (fin_now) {
+                run[k] = -1;
+                expend[k] = 0;
+                lrun[lane + k * kWave] = -1;
+            }
+        }
+        done += ndone;
+        merged = staged = inlane = false;
+        // the only completing worker, or the first
+        const int32_t w1 = WPL == 2 && cm[0] == 0 ? kWave + (int32_t)__builtin_ctzll(cm[WPL - 1])
+                                                  : (int32_t)__builtin_ctzll(cm[0]);
+        const int32_t deg1 = of_worker<WPL>(dgr, w1);
+        if (ndone == 1 && deg1 <= kWave) {
+            const int32_t c = of_worker<WPL>(c_l, w1);
+            // the first successors go from the worker's lane to a lane each
+#pragma unroll
+            for (int k = 0; k < WPL; k++)
+                if (lane + k * kWave == w1) {
+                    *reinterpret_cast<int4 *>(succ) = make_int4(pfa[k].x, pfa[k].y, pfa[k].z, pfa[k].w);
+                    *reinterpret_cast<int4 *>(succ + 4) = make_int4(pfb[k].x, pfb[k].y, pfb[k].z, pfb[k].w);
+                }
+            keep_order();
+            const bool in = lane < deg1;
+            int32_t s = lds_load(&succ[lane & (kPF - 1)]);
+            if (deg1 > kPF) {
+                const int32_t rs = of_worker<WPL>(rsr, w1);
+                if (in && lane >= kPF) s = col[rs + lane];
+            }
+            s = in ? s : 0;
+            PCLK(19);
+            // one wave owns the DAG's words and a row's successors are
+            // distinct (rows are deduplicated), so a plain read-modify-write
+            // replaces the atomic (a wave's accesses to one address complete in
+            // program order)
+            unsigned long long *dp = at(dep, s);
+            const uint64_t now = *dp - ((1ull << 43) + (unsigned long long)c);
+            if (in) *dp = now;
+            const int32_t nr = (int32_t)(now >> 43);
+            const bool rdy = in && nr == 0, cd = in && nr == 1;
+            fm = ballot(rdy);
+            r = __popcll(fm);
+            inlane = r > 0;
+            PCLK(20);
+            if (fm | ballot(cd)) {
+                // rows of the newly ready tasks; records of the others' remaining
+                // predecessors u, whose IE may grow
+                const int32_t u = cd ? (int32_t)(now & M43) : 0;
+                TaskRec *ru = at(tr, u);
+                const int4 fx = *reinterpret_cast<const int4 *>(&at(tr, s)->iev);  // IE, IA, tau, first edge
+                const int2 uq = *reinterpret_cast<const int2 *>(&ru->qpos);        // queue slot; push order and worker
+                const int4 ux = *reinterpret_cast<const int4 *>(&ru->iev);
+                f_e = *at(est2, s);
+                f_d = *at(dur2, s);
+                if constexpr (DATA) {
+                    f_pa = *at(prp, s);
+                    f_pz = at(prp, s)[1];
+                }
+                f_v = s;
+                f_ie = fx.x;
+                f_ia = fx.y;
+                f_rs = fx.w;
+                if constexpr (KK == kFixed) {
+                    if (heft) {
+                        const int64_t rv = rk[s];
+                        f_ia = (int32_t)(uint32_t)rv;
+                        f_ie = (int32_t)(uint32_t)((uint64_t)rv >> 32);
+                    } else if (tattr) {
+                        f_ia = tia[s];
+                        f_ie = tie[s];
+                    }
+                }
+                PCLK(23);
+                const bool cond = cd && ux.z + fx.z <= U;  // taus are at most 2^20, U at most 2^31 - 1
+                uint64_t left = ballot(cond);
+                if (left) {
+                    // several successors may name the same predecessor: the
+                    // first lane applies all of its increments
+                    int32_t mult = 1;
+                    bool lead = cond;
+                    if (left & (left - 1)) {
+                        lead = false;
+                        while (left) {
+                            const int l = (int)__builtin_ctzll(left);
+                            const uint64_t same = ballot(cond && u == read_lane(u, l));
+                            left &= ~same;
+                            if (lane == l) {
+                                lead = true;
+                                mult = __popcll(same);
+                            }
+                        }
+                    }
+                    const int32_t nie = ux.x + mult;
+                    if (lead) ru->iev = nie;
+                    if constexpr (KK != kFixed) {
+                        const bool qd = lead && uq.x >= 0;
+                        if (ballot(qd)) raise(qd, uq.x, uq.y, ux.y, nie);
+                        // a raised IE of a task about to be pushed goes into its key
+                        uint64_t lm = ballot(lead && uq.x == -1);
+                        while (lm) {
+                            const int l = (int)__builtin_ctzll(lm);
+                            lm &= lm - 1;
+                            const int32_t uu = read_lane(u, l), kk = read_lane(mult, l);
+                            if (rdy && s == uu) f_ie += kk;
+                        }
+                    }
+                }
+            }
+            PCLK(24);
+            continue;
+        }
+        // several completions, or a long row: successors through lists
+        int32_t *fbuf = cold<WPL, int32_t>(kColdFbuf);
+        int32_t nc = 0, nseg = 0;
+#pragma unroll
+        for (int k = 0; k < WPL; k++) {
+            uint64_t mask = cm[k];
             while (mask) {
                 const int l = (int)__builtin_ctzll(mask);
                 mask &= mask - 1;
-                const int32_t c = read_lane(c_l, l);
-                done++;
-                ndone++;
-                const int32_t deg = read_lane(dgr, l), rs = read_lane(rsr, l);
+                const int32_t c = read_lane(c_l[k], l);
+                const int32_t deg = read_lane(dgr[k], l), rs = read_lane(rsr[k], l);
                 const int32_t r0 = r;
                 const unsigned long long dec = 0ull - ((1ull << 43) + (unsigned long long)c);
                 for (int32_t e0 = 0; e0 < deg; e0 += kWave) {
                     const int32_t e = e0 + lane;
                     const bool ok = e < deg;
                     int32_t s = 0;
-                    if (e0 == 0) {
-#pragma unroll
-                        for (int j = 0; j < kPF; j++) {
-                            const int32_t y = read_lane(pf[j], l);
-                            if (lane == j) s = y;
-                        }
-                    }
-                    if (ok && e >= kPF) s = col[rs + e];
-                    PCLK(19);
-                    // one wave owns the DAG's words and a row's successors are
-                    // distinct (rows are deduplicated), so a plain
-                    // read-modify-write replaces the atomic (a wave's accesses
-                    // to one address complete in program order)
+                    if (ok) s = col[rs + e];
                     uint64_t old = 0;
                     if (ok) {
                         old = dep[s];
@@ -1919,17 +2376,16 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                     const int32_t nr = (int32_t)(old >> 43) - 1;
                     const bool rdy = ok && nr == 0, cd = ok && nr == 1;
                     const uint64_t m1 = ballot(rdy), m2 = ballot(cd);
-                    PCLK(20);
                     if (rdy) {
                         const int32_t pos = r + lanes_below(m1);
                         fbuf[pos] = s;
-                        if (pos < kFC) L.fr0[pos] = s;
+                        if (pos < kFC) fr0[pos] = s;
                     }
                     if (cd) {
                         const int32_t pos = nc + lanes_below(m2);
                         if (pos < kCC) {
-                            L.cs[pos] = s;
-                            L.cu[pos] = (int32_t)((old + dec) & M43);
+                            cs[pos] = s;
+                            cu[pos] = (int32_t)((old + dec) & M43);
                         } else {
                             fbuf[2 * n + pos] = s;
                         }
@@ -1938,26 +2394,23 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                     nc += __popcll(m2);
                 }
                 if (r > r0) {
-                    if (lane == 0) L.seg[nseg] = r;
+                    if (lane == 0) seg[nseg] = r;
                     nseg++;
                 }
             }
         }
         PCLK(4);
         wg_fence();
-        PCLK(5);
         // successors left with one unfinished predecessor raise its IE (as in
         // the general loop)
         const bool single = ndone == 1;
-        merged = false;
-        staged = false;
         if (nc <= kWave && r <= kFC) {
             const bool hc = lane < nc;
-            const int32_t s = hc ? L.cs[lane] : 0;
-            int32_t u = hc ? L.cu[lane] : -1;
+            const int32_t s = hc ? cs[lane] : 0;
+            int32_t u = hc ? cu[lane] : -1;
             staged = r <= kWave;
             const bool hf = staged && lane < r;
-            const int32_t fv = hf ? L.fr0[lane] : 0;
+            const int32_t fv = hf ? fr0[lane] : 0;
             // a candidate made ready by a later completion of this event is none
             if (!single) {
                 if (staged) {
@@ -1965,94 +2418,61 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                         if (read_lane(fv, k) == s) u = -1;
                 } else if (hc) {
                     for (int32_t k = 0; k < r; k++)
-                        if (L.fr0[k] == s) {
+                        if (fr0[k] == s) {
                             u = -1;
                             break;
                         }
                 }
             }
-            PCLK(22);
-            int32_t tu = 0, ts = 0, iu = 0, qu = -1, au = 0, sq = 0;
-            if (u >= 0) {
-                // one wave owns the records, so plain vector loads see its stores
-                const int2 qs = *reinterpret_cast<const int2 *>(&tr[u].qpos);  // queue slot, push order
-                const int4 fx = *reinterpret_cast<const int4 *>(&tr[u].iev);   // IE, IA, tau, first edge
-                ts = tr[s].tau;
-                qu = qs.x;
-                sq = qs.y;
-                iu = fx.x;
-                au = fx.y;
-                tu = fx.z;
+            // one wave owns the records, so plain vector loads see its stores
+            TaskRec *ru = at(tr, max(u, 0));
+            const int2 qs = *reinterpret_cast<const int2 *>(&ru->qpos);  // queue slot; push order and worker
+            const int4 ux = *reinterpret_cast<const int4 *>(&ru->iev);   // IE, IA, tau, first edge
+            const int32_t ts = at(tr, s)->tau;
+            int2 fe = *at(est2, fv), fd = *at(dur2, fv);
+            const int4 fx = *reinterpret_cast<const int4 *>(&at(tr, fv)->iev);
+            int32_t fie = fx.x, fa = fx.y;
+            const int32_t frs = fx.w;
+            // fixed keys: the rank (low and high words), or the transitive attributes
+            if (heft) {
+                const int64_t rv = rk[fv];
+                fa = (int32_t)(uint32_t)rv;
+                fie = (int32_t)(uint32_t)((uint64_t)rv >> 32);
+            } else if (tattr) {
+                fa = tia[fv];
+                fie = tie[fv];
             }
-            int2 fe = make_int2(1, 1), fd = make_int2(1, 1);
-            int32_t fa = 0, frs = 0, fie = 0;
-            if (hf) {
-                fe = est2[fv];
-                fd = dur2[fv];
-                const int4 fx = *reinterpret_cast<const int4 *>(&tr[fv].iev);
-                fie = fx.x;
-                fa = fx.y;
-                frs = fx.w;
-                // fixed keys: the rank (low and high words), or the transitive attributes
-                if (heft) {
-                    const int64_t rv = rk[fv];
-                    fa = (int32_t)(uint32_t)rv;
-                    fie = (int32_t)(uint32_t)((uint64_t)rv >> 32);
-                } else if (tattr) {
-                    fa = tia[fv];
-                    fie = tie[fv];
-                }
-            }
-            const bool cond = u >= 0 && (int64_t)tu + ts <= (int64_t)U;
-            PCLK(23);
+            const bool cond = u >= 0 && ux.z + ts <= U;
             int32_t mult = cond ? 1 : 0;
             bool lead = cond;
             if (nc > 1) {
                 // several successors may name the same predecessor: the
                 // first lane applies all of its increments
-                mult = 0;
-                for (int32_t j = 0; j < nc; j++) {
-                    const int32_t uj = read_lane(u, j);
-                    const int32_t cj = read_lane(cond ? 1 : 0, j);
-                    if (cj && cond && uj == u) {
-                        mult++;
-                        if (j < lane) lead = false;
+                lead = false;
+                uint64_t left = ballot(cond);
+                while (left) {
+                    const int l = (int)__builtin_ctzll(left);
+                    const uint64_t same = ballot(cond && u == read_lane(u, l));
+                    left &= ~same;
+                    if (lane == l) {
+                        lead = true;
+                        mult = __popcll(same);
                     }
                 }
             }
-            if (lead) {
-                const int32_t nie = iu + mult;
-                tr[u].iev = nie;
-                if constexpr (!FIX) {
-                    if (qu >= 0) {
-                        const uint32_t na = kf.ka((uint32_t)au, (uint32_t)nie, (uint32_t)sq);
-                        const uint32_t ne = kf.ke((uint32_t)au, (uint32_t)nie, (uint32_t)sq);
-                        const int32_t bk = qu >> 6;
-                        if (bk < SLK) {
-                            K.ka[qu] = na;
-                            K.ke[qu] = ne;
-                        } else {
-                            slots.k[qu] = (uint64_t)ne << 32 | na;
-                        }
-                        if (bk < SC) {
-                            atomicMax(&K.mx[2 * bk], na);
-                            atomicMax(&K.mx[2 * bk + 1], ne);
-                        } else {
-                            wg_fetch_max(&sums[2 * bk], (unsigned long long)na);
-                            wg_fetch_max(&sums[2 * bk + 1], (unsigned long long)ne);
-                        }
-                    }
+            const int32_t nie = ux.x + mult;
+            if (lead) ru->iev = nie;
+            if constexpr (KK != kFixed) {
+                const bool qd = lead && qs.x >= 0;
+                if (ballot(qd)) raise(qd, qs.x, qs.y, ux.y, nie);
+                // a raised IE of a task staged for this event's pushes goes into its key
+                uint64_t lm = ballot(lead && qs.x == -1);
+                while (lm) {
+                    const int l = (int)__builtin_ctzll(lm);
+                    lm &= lm - 1;
+                    const int32_t uu = read_lane(u, l), kk = read_lane(mult, l);
+                    if (hf && fv == uu) fie += kk;
                 }
-            }
-            PCLK(24);
-            // a raised IE of a task staged for this event's pushes goes into its key
-            uint64_t lm = FIX ? 0 : ballot(lead && qu == -1);
-            while (lm) {
-                const int l = (int)__builtin_ctzll(lm);
-                lm &= lm - 1;
-                const int32_t uu = read_lane(u, l), kk = read_lane(mult, l);
-                const uint64_t fm = ballot(hf && fv == uu);
-                if (fm && lane == (int)__builtin_ctzll(fm)) fie += kk;
             }
             int32_t pos = lane;
             if (nseg > 1 && staged) {
@@ -2064,78 +2484,72 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
             }
             if (!staged && nseg > 1) {
                 for (int32_t i = lane; i < r; i += kWave) {
-                    const int32_t x = L.fr0[i];
+                    const int32_t x = fr0[i];
                     int32_t rank = 0, lo = 0;
                     for (int32_t g = 0; g < nseg; g++) {
-                        const int32_t hi = L.seg[g];
+                        const int32_t hi = seg[g];
                         if (i >= lo && i < hi) {
                             rank += i - lo;
                         } else {
                             int32_t a = lo, b = hi;
                             while (a < b) {
                                 const int32_t mid = (a + b) >> 1;
-                                if (L.fr0[mid] < x) a = mid + 1;
+                                if (fr0[mid] < x) a = mid + 1;
                                 else b = mid;
                             }
                             rank += a - lo;
                         }
                         lo = hi;
                     }
-                    L.fr1[rank] = x;
+                    fr1[rank] = x;
                 }
                 merged = true;
             }
             if (hf) {
-                L.pre[pos] = fv;
-                L.pre[64 + pos] = fe.x;
-                L.pre[128 + pos] = fe.y;
-                L.pre[192 + pos] = fd.x;
-                L.pre[256 + pos] = fd.y;
-                L.pre[320 + pos] = fa;
-                L.pre[384 + pos] = frs;
-                L.pre[448 + pos] = fie;
+                pre[pos] = fv;
+                pre[64 + pos] = fe.x;
+                pre[128 + pos] = fe.y;
+                pre[192 + pos] = fd.x;
+                pre[256 + pos] = fd.y;
+                pre[320 + pos] = fa;
+                pre[384 + pos] = frs;
+                pre[448 + pos] = fie;
             }
         } else {
             for (int32_t i0 = 0; i0 < nc; i0 += kWave) {
                 const int32_t i = i0 + lane;
+                const int32_t s = i < nc ? (i < kCC ? cs[i] : wg_load(&fbuf[2 * n + i])) : 0;
+                int32_t u = -1;
                 if (i < nc) {
-                    const int32_t s = i < kCC ? L.cs[i] : wg_load(&fbuf[2 * n + i]);
-                    int32_t u = -1;
                     if (single && i < kCC) {
-                        u = L.cu[i];
+                        u = cu[i];
                     } else {
                         const uint64_t wd = wg_load(&dep[s]);
                         if ((wd >> 43) == 1) u = (int32_t)(wd & M43);
                     }
-                    if (u >= 0) {
-                        const int32_t tu = tr[u].tau, ts = tr[s].tau;
-                        const int32_t pu = wg_load(&tr[u].qpos);
-                        if ((int64_t)tu + ts <= (int64_t)U) {
-                            wg_fetch_add(&tr[u].iev, 1);
-                            if constexpr (!FIX) {
-                                if (pu >= 0) {
-                                    const int32_t bk = pu >> 6;
-                                    uint32_t na, ne;
-                                    if (bk < SLK) {
-                                        na = atomicAdd(&K.ka[pu], kf.da()) + kf.da();
-                                        ne = atomicAdd(&K.ke[pu], kf.de()) + kf.de();
-                                    } else {
-                                        const unsigned long long inc = (unsigned long long)kf.de() << 32 | kf.da();
-                                        const uint64_t nk = wg_fetch_add(&slots.k[pu], inc) + inc;
-                                        na = (uint32_t)nk;
-                                        ne = (uint32_t)(nk >> 32);
-                                    }
-                                    if (bk < SC) {
-                                        atomicMax(&K.mx[2 * bk], na);
-                                        atomicMax(&K.mx[2 * bk + 1], ne);
-                                    } else {
-                                        wg_fetch_max(&sums[2 * bk], (unsigned long long)na);
-                                        wg_fetch_max(&sums[2 * bk + 1], (unsigned long long)ne);
-                                    }
-                                }
-                            }
-                        }
+                }
+                TaskRec *ru = at(tr, max(u, 0));
+                const int2 qs = *reinterpret_cast<const int2 *>(&ru->qpos);
+                const int4 ux = *reinterpret_cast<const int4 *>(&ru->iev);
+                const bool cond = u >= 0 && ux.z + at(tr, s)->tau <= U;
+                // the first lane that names a predecessor applies all of the chunk's increments
+                uint64_t left = ballot(cond);
+                bool lead = false;
+                int32_t mult = 0;
+                while (left) {
+                    const int l = (int)__builtin_ctzll(left);
+                    const uint64_t same = ballot(cond && u == read_lane(u, l));
+                    left &= ~same;
+                    if (lane == l) {
+                        lead = true;
+                        mult = __popcll(same);
                     }
+                }
+                const int32_t nie = ux.x + mult;
+                if (lead) ru->iev = nie;
+                if constexpr (KK != kFixed) {
+                    const bool qd = lead && qs.x >= 0;
+                    if (ballot(qd)) raise(qd, qs.x, qs.y, ux.y, nie);
                 }
             }
             wg_fence();
@@ -2144,17 +2558,17 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                 for (int32_t i0 = 0; i0 < r; i0 += kWave) {
                     const int32_t i = i0 + lane;
                     if (i < r) {
-                        const int32_t x = in_lds ? L.fr0[i] : fbuf[i];
+                        const int32_t x = in_lds ? fr0[i] : fbuf[i];
                         int32_t rank = 0, lo = 0;
                         for (int32_t g = 0; g < nseg; g++) {
-                            const int32_t hi = L.seg[g];
+                            const int32_t hi = seg[g];
                             if (i >= lo && i < hi) {
                                 rank += i - lo;
                             } else {
                                 int32_t a = lo, b = hi;
                                 while (a < b) {
                                     const int32_t mid = (a + b) >> 1;
-                                    const int32_t y = in_lds ? L.fr0[mid] : fbuf[mid];
+                                    const int32_t y = in_lds ? fr0[mid] : fbuf[mid];
                                     if (y < x) a = mid + 1;
                                     else b = mid;
                                 }
@@ -2162,7 +2576,7 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
                             }
                             lo = hi;
                         }
-                        if (in_lds) L.fr1[rank] = x;
+                        if (in_lds) fr1[rank] = x;
                         else fbuf[n + rank] = x;
                     }
                 }
@@ -2183,7 +2597,6 @@ __device__ bool sim_lane(const SimArgs &A, int32_t di, const Lds &L) {
         if (status) atomicOr(&A.stat[2 * d.id], status);
         A.stat[2 * d.id + 1] = events;
     }
-    return true;
 }
 
 // The work-group's LDS, carved in the order lds_bytes() counts it.
@@ -2218,7 +2631,7 @@ __device__ __forceinline__ Lds carve_lds(const SimArgs &A) {
     return L;
 }
 
-// The work-group's second wave, while the first simulates DAG di: it reads
+// The work-group's third wave, while the first simulates DAG di: it reads
 // ahead for the running tasks that finish first -- their successor lists,
 // the successors' dependency words, and the records and estimate rows the
 // release of those tasks will read (of successors about to become ready,
@@ -2227,26 +2640,40 @@ __device__ __forceinline__ Lds carve_lds(const SimArgs &A) {
 // stops when the simulating wave marks the DAG finished.
 constexpr int kAhead = 4;          // running tasks read ahead for, earliest finish first
 constexpr int kAheadEdges = 16;    // successors read per task
-constexpr int64_t kHelperSpin = 1ll << 40;
 
-__device__ void read_ahead(const SimArgs &A, int32_t di, const Lds &L) {
+template <int WPL>
+__device__ void read_ahead(const SimArgs &A, int32_t di) {
+    using LL = LaneLds<WPL>;
+    const int64_t *lfin = LL::template arr<int64_t>(LL::kFin);
+    const int32_t *lrun = LL::template arr<int32_t>(LL::kRun);
+    int32_t *hs = LL::template arr<int32_t>(LL::kHs);
     const DagDesc d = A.desc[di];
     const int lane = lane_id();
-    const int32_t W = d.n_cpu + d.n_gpu;
-    const bool wok = lane < W && W <= kWave && d.n > 0;
     const int64_t ub = d.toff - A.base;
     const int32_t *col = A.col + d.eoff;
     const TaskRec *tr = A.tr + d.toff;
     const unsigned long long *dep = A.dep + d.toff;
     const int2 *est2 = reinterpret_cast<const int2 *>(A.est) + ub;
     const int2 *dur2 = reinterpret_cast<const int2 *>(A.dur) + ub;
-    int32_t pref = -1;  // the last task read ahead for this lane's worker
+    int32_t pref[WPL];  // the last task read ahead for each of this lane's workers
+#pragma unroll
+    for (int k = 0; k < WPL; k++) pref[k] = -1;
     uint32_t sink = 0;
     for (int64_t it = 0; it < kHelperSpin; it++) {
-        if (__hip_atomic_load(&L.hs[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
-        const int32_t c = wok ? __hip_atomic_load(&L.run[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : -1;
-        const int64_t f = c >= 0 ? __hip_atomic_load(&L.fin[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
-                                 : INT64_MAX;
+        if (lds_load(&hs[1])) break;
+        // the lane's next task to read ahead for: of two workers' the one that ends first
+        int32_t c = -1, kc = 0;
+        int64_t f = INT64_MAX;
+#pragma unroll
+        for (int k = 0; k < WPL; k++) {
+            const int32_t ck = lds_load(&lrun[lane + k * kWave]);
+            const int64_t fk = lds_load(&lfin[lane + k * kWave]);
+            if (ck >= 0 && (WPL == 1 || ck != pref[k]) && fk < f) {
+                f = fk;
+                c = ck;
+                kc = k;
+            }
+        }
         // the kAhead-th earliest finish among the running tasks
         uint64_t thr = 0;
         {
@@ -2260,13 +2687,15 @@ __device__ void read_ahead(const SimArgs &A, int32_t di, const Lds &L) {
                 first = false;
             }
         }
-        const bool go = c >= 0 && c != pref && c < d.n && (uint64_t)f <= thr;
+        const bool go = c >= 0 && c != (kc == 0 ? pref[0] : pref[WPL - 1]) && c < d.n && (uint64_t)f <= thr;
         if (!ballot(go)) {
             __builtin_amdgcn_s_sleep(4);
             continue;
         }
         if (go) {
-            pref = c;
+#pragma unroll
+            for (int k = 0; k < WPL; k++)
+                if (k == kc) pref[k] = c;
             const int4 fx = *reinterpret_cast<const int4 *>(&tr[c].iev);  // IE, IA, tau, first edge
             const int32_t deg = min(fx.y, kAheadEdges), rs = fx.w;
             int32_t sv[kAheadEdges];
@@ -2296,49 +2725,57 @@ __device__ void read_ahead(const SimArgs &A, int32_t di, const Lds &L) {
             }
         }
     }
-    L.hs[2] = (int32_t)sink;  // keeps the reads
+    hs[2] = (int32_t)sink;  // keeps the reads
 }
 
-// Event loop a launch runs (one kernel each, so that each gets its own
-// register allocation), for machines of at most 64 workers: the one-wave loop
-// on direct 32-bit keys (DAGs whose keys do not fit fall back to the general
-// loop) or on fixed 64-bit keys (HEFT ranks, transitive attributes), each
-// with or without the data model; for larger machines the general loop.
-enum SimLoop { kLoopDirect = 0, kLoopFixed = 1, kLoopGeneral = 2, kLoopData = 3, kLoopDataFixed = 4 };
-
-template <int WPL, int LOOP>
-__global__ __launch_bounds__(WPL == 1 ? 2 * kWave : kWave) void k_sim(SimArgs A) {
-    const Lds L = carve_lds(A);
-    const int lane = lane_id();
-    // one wave simulates; under the one-wave loop's launch a second wave reads ahead
-    const bool helper = WPL == 1 && threadIdx.x >= kWave;
+// The event loop for machines of at most 128 workers (WPL = 1: 64), one
+// kernel per key kind with and without the data model, so that each gets its
+// own register allocation.  Three waves per work-group: one simulates, one
+// keeps the workers' best queue entries, one reads ahead.
+template <int WPL, int KK, bool DATA>
+__global__ __launch_bounds__(3 * kWave, WPL == 1 ? 3 : 1) void k_sim(SimArgs A) {
+    using LL = LaneLds<WPL>;
+    int32_t *hs = LL::template arr<int32_t>(LL::kHs), *lrun = LL::template arr<int32_t>(LL::kRun);
+    const int wave = uniform(threadIdx.x / kWave);
     for (;;) {
         if (threadIdx.x == 0) {
-            L.hs[0] = dev_fetch_add(A.counter, 1);
-            L.hs[1] = 0;
+            hs[0] = dev_fetch_add(A.counter, 1);
+            hs[1] = 0;
+            hs[3] = 0;
         }
-        if (threadIdx.x < kWave)
-            for (int32_t w = lane; w < A.max_w * WPL && w < kWave; w += kWave) L.run[w] = -1;
+        for (int32_t w = threadIdx.x; w < LL::kMW; w += 3 * kWave) lrun[w] = -1;
         __syncthreads();
-        const int32_t i = L.hs[0];
+        const int32_t i = uniform(hs[0]);
         if (i >= A.count) break;
-        if (helper) {
-            read_ahead(A, A.order[i], L);
-        } else {
+        const int32_t di = uniform(A.order[i]);
+        if (wave == 0) {
             // the largest DAGs (dispensed first) set the batch's critical path:
             // their waves win instruction issue over co-resident waves
             if (i < A.prio_top) __builtin_amdgcn_s_setprio(3);
             else __builtin_amdgcn_s_setprio(0);
-            if constexpr (WPL == 1 && (LOOP == kLoopDirect || LOOP == kLoopData)) {
-                if (!sim_lane<false, LOOP == kLoopData>(A, A.order[i], L)) sim_dag<1>(A, A.order[i], L);
-            } else if constexpr (WPL == 1 && (LOOP == kLoopFixed || LOOP == kLoopDataFixed)) {
-                sim_lane<true, LOOP == kLoopDataFixed>(A, A.order[i], L);
-            } else {
-                sim_dag<WPL>(A, A.order[i], L);
-            }
+            sim_lane<WPL, KK, DATA>(A, di);
             wg_fence();
-            if (lane == 0) __hip_atomic_store(&L.hs[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (threadIdx.x == 0) lds_store(&hs[1], 1);
+        } else if (wave == 1) {
+            keep_best<WPL, KK>(A, di);
+        } else {
+            read_ahead<WPL>(A, di);
         }
+        __syncthreads();
+    }
+}
+
+// The general event loop, for larger machines: one wave per work-group.
+__global__ __launch_bounds__(kWave) void k_sim_general(SimArgs A) {
+    const Lds L = carve_lds(A);
+    for (;;) {
+        if (threadIdx.x == 0) L.hs[0] = dev_fetch_add(A.counter, 1);
+        __syncthreads();
+        const int32_t i = L.hs[0];
+        if (i >= A.count) break;
+        if (i < A.prio_top) __builtin_amdgcn_s_setprio(3);
+        else __builtin_amdgcn_s_setprio(0);
+        sim_dag<INSP_MAX_WORKERS / kWave>(A, A.order[i], L);
         __syncthreads();
     }
 }
@@ -2362,6 +2799,39 @@ __global__ __launch_bounds__(256) void k_records(const TaskRec *tr, int64_t n, i
     finish[i] = s + (int64_t)(wd >> 42);
     if (ie_at_pop) ie_at_pop[i] = q.w & ((1 << 22) - 1);
     if (mode_at_pop) mode_at_pop[i] = (int8_t)(q.w >> 22);
+}
+
+// The kernel of a launch and the LDS it needs for a given shape.
+struct SimKernel {
+    void (*run)(SimArgs);
+    size_t (*lds)(int mw, int sc, int lb, int slc, int slk);
+    int threads;
+};
+
+template <int WPL, int KK>
+static SimKernel lane_kernel(bool data) {
+    return {data ? k_sim<WPL, KK, true> : k_sim<WPL, KK, false>, LaneLds<WPL>::bytes, 3 * kWave};
+}
+template <int WPL>
+static SimKernel lane_kernel(int kk, bool data) {
+    return kk == kNarrow ? lane_kernel<WPL, kNarrow>(data)
+         : kk == kFixed ? lane_kernel<WPL, kFixed>(data) : lane_kernel<WPL, kWide>(data);
+}
+
+// The one-wave loop up to 128 workers (two per lane above 64), on 32-bit keys
+// where those of every DAG of the launch fit; the general loop above.
+static SimKernel pick_kernel(const insp_dag *dag, const Workspace *ws, const insp_params &p) {
+    if (ws->max_w > 2 * kWave) return {k_sim_general, lds_bytes, kWave};
+    int kk = kNarrow;
+    if (p.policy == INSP_POLICY_HEFT || p.attr_mode == INSP_ATTR_TRANSITIVE) {
+        kk = kFixed;
+    } else {
+        for (int32_t b = ws->first; b < ws->first + ws->count; b++) {
+            const int64_t n = dag->toff[b + 1] - dag->toff[b];
+            if (n > 0 && 1 + 2 * field_bits((uint32_t)dag->maxdeg[b]) + field_bits((uint32_t)(n - 1)) > 32) kk = kWide;
+        }
+    }
+    return ws->max_w <= kWave ? lane_kernel<1>(kk, p.data_bw > 0) : lane_kernel<2>(kk, p.data_bw > 0);
 }
 
 int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t *dur, const int32_t *est,
@@ -2412,61 +2882,42 @@ int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t
     A.k_den = p.k_den;
     A.max_events = p.max_events;
     A.prio_top = prio_top;
-    A.scan_max = scan_max;
-    // block maxima in LDS: all of a single DAG's blocks up to 64 KB, or the
-    // low block ids of each DAG of a batch
+    (void)scan_max;
     // LDS: block maxima, block lists and the slots of the low blocks --
     // generous for a single DAG (one work-group owns the CU), a few blocks
     // per DAG for a batch (tunable)
+    const SimKernel kern = pick_kernel(dag, ws, p);
     const bool one = ws->count == 1;
     const int64_t budget = (one ? 140 : 150) * 1024;
+    auto need = [&](int64_t sc, int64_t lb, int64_t slc, int64_t slk) {
+        return (int64_t)kern.lds(ws->max_w, (int)sc, (int)lb, (int)slc, (int)slk);
+    };
     int64_t sc = std::min<int64_t>(ws->max_nblk, one ? 2048 : sum_cap);
     int64_t lb = std::min<int64_t>(ws->max_nblk, one ? 64 : 16);
     // machines of hundreds of workers: shorter LDS block lists, then fewer
     // LDS block maxima, until the per-worker state fits (the rest lives in
     // global memory)
-    while (lb > 1 && (int64_t)lds_bytes(ws->max_w, (int)sc, (int)lb, 0, 0) > budget) lb /= 2;
-    while (sc > 0 && (int64_t)lds_bytes(ws->max_w, (int)sc, (int)lb, 0, 0) > budget) sc /= 2;
+    while (lb > 1 && need(sc, lb, 0, 0) > budget) lb /= 2;
+    while (sc > 0 && need(sc, lb, 0, 0) > budget) sc /= 2;
     int64_t slc = slot_cap;
-    if (one) slc = (budget - (int64_t)lds_bytes(ws->max_w, (int)sc, (int)lb, 0, 0)) / (64 * 20);
+    if (one) slc = (budget - need(sc, lb, 0, 0)) / (64 * 20);
     slc = std::max<int64_t>(0, std::min<int64_t>(ws->max_nblk, slc));
-    while (slc > 0 && (int64_t)lds_bytes(ws->max_w, (int)sc, (int)lb, (int)slc, (int)slc) > budget) slc--;
-    // keys of further blocks in what LDS is left (a pop's scan reads only keys)
+    while (slc > 0 && need(sc, lb, slc, slc) > budget) slc--;
+    // keys of further blocks in what LDS is left (a rescan reads only keys)
     int64_t slk = std::max<int64_t>(slc, std::min<int64_t>(ws->max_nblk, key_cap));
-    while (slk > slc && (int64_t)lds_bytes(ws->max_w, (int)sc, (int)lb, (int)slc, (int)slk) > budget) slk--;
+    while (slk > slc && need(sc, lb, slc, slk) > budget) slk--;
     A.sum_cap = (int32_t)sc;
     A.lb = (int32_t)lb;
     A.slot_cap = (int32_t)slc;
     A.key_cap = (int32_t)slk;
-    const size_t lds = lds_bytes(ws->max_w, A.sum_cap, A.lb, A.slot_cap, A.key_cap);
+    const size_t lds = (size_t)need(sc, lb, slc, slk);
     if (lds > 160 * 1024) return set_error(INSP_E_RANGE, "simulation state of %d workers exceeds LDS", ws->max_w);
     grid = std::max(1, std::min(grid, ws->count));
+    if (int rc = set_lds_limit((const void *)kern.run, lds)) return rc;
     hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, st, A.counter);
     {
         ProfScope ps(st, "sim");
-        // one-wave loops for machines of at most 64 workers: fixed or direct
-        // keys, with or without the data model (the locality policy without
-        // it runs on the general loop)
-        const bool data = p.data_bw > 0;
-        const bool fixed = p.policy == INSP_POLICY_HEFT || p.attr_mode == INSP_ATTR_TRANSITIVE;
-        if (ws->max_w <= 64 && !data && p.policy == INSP_POLICY_LOCALITY) {
-            if (int rc = set_lds_limit((const void *)&k_sim<1, kLoopGeneral>, lds)) return rc;
-            hipLaunchKernelGGL((k_sim<1, kLoopGeneral>), dim3(grid), dim3(2 * kWave), lds, st, A);
-        } else if (ws->max_w <= 64) {
-            const void *k = data ? (fixed ? (const void *)&k_sim<1, kLoopDataFixed> : (const void *)&k_sim<1, kLoopData>)
-                                 : (fixed ? (const void *)&k_sim<1, kLoopFixed> : (const void *)&k_sim<1, kLoopDirect>);
-            if (int rc = set_lds_limit(k, lds)) return rc;
-            if (data && fixed) hipLaunchKernelGGL((k_sim<1, kLoopDataFixed>), dim3(grid), dim3(2 * kWave), lds, st, A);
-            else if (data) hipLaunchKernelGGL((k_sim<1, kLoopData>), dim3(grid), dim3(2 * kWave), lds, st, A);
-            else if (fixed) hipLaunchKernelGGL((k_sim<1, kLoopFixed>), dim3(grid), dim3(2 * kWave), lds, st, A);
-            else hipLaunchKernelGGL((k_sim<1, kLoopDirect>), dim3(grid), dim3(2 * kWave), lds, st, A);
-        } else if (ws->max_w <= 128) {
-            if (int rc = set_lds_limit((const void *)&k_sim<2, kLoopGeneral>, lds)) return rc;
-            hipLaunchKernelGGL((k_sim<2, kLoopGeneral>), dim3(grid), dim3(64), lds, st, A);
-        } else {
-            if (int rc = set_lds_limit((const void *)&k_sim<16, kLoopGeneral>, lds)) return rc;
-            hipLaunchKernelGGL((k_sim<16, kLoopGeneral>), dim3(grid), dim3(64), lds, st, A);
-        }
+        hipLaunchKernelGGL(kern.run, dim3(grid), dim3(kern.threads), lds, st, A);
     }
     INSP_HIP(hipGetLastError());
     if (ws->tasks > 0) {
