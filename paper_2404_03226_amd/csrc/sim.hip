@@ -1026,13 +1026,17 @@ __device__ void sim_dag(const SimArgs &A, int32_t di, const Lds &L) {
 //     Pushes and IE increments raise it with an LDS atomicMax; a pop empties
 //     it and asks the work-group's second wave (keep_best) to find the next
 //     one, which it does while this wave simulates the following events.  The
-//     second wave rescans only the blocks the pop changed, merges their
-//     maxima into the per-block maxima with atomicMax and takes the largest
-//     of those.  Keys only grow while a task is queued, so maxima raised by
+//     second wave rescans only the block the pop changed, merges its maximum
+//     into the per-block maxima with atomicMax and takes the largest of
+//     those.  Keys only grow while a task is queued, so maxima raised by
 //     this wave meanwhile and scanned values that are out of date by then
 //     merge to the right result in any order; a pop waits for a rescan still
 //     under way.  Every slot without a live entry holds zero keys, so scans
 //     read whole blocks unpredicated: valid keys carry the top bit.
+//   - A popped entry's slot stays empty for one of the worker's next pushes
+//     (empty slots are chained through their first-edge field), so a pop
+//     moves no other entry; a queue keeps its blocks, of which each push adds
+//     at most one entry's share: n / 64 + W blocks hold any run.
 //   - All workers that are idle pop at once, a lane each.
 //   - An event with one completion of at most 64 successors (most are) keeps
 //     its newly ready tasks in the lanes that released them: their rows are
@@ -1145,14 +1149,12 @@ template <int WPL>
 struct LaneLds {
     static constexpr int kMW = WPL * kWave;
     static constexpr int kBest = 0;                     // uint64 [2 * kMW]: each worker's best entry under either rule
-    static constexpr int kFin = kBest + 16 * kMW;       // int64 [kMW]: finish of the running task (for the read-ahead)
-    static constexpr int kCold = kFin + 8 * kMW;        // uint64 [8]: pointers of the uncommon paths
+    static constexpr int kRun = kBest + 16 * kMW;       // int2 [kMW]: running task or -1 and its finish (read-ahead)
+    static constexpr int kCold = kRun + 8 * kMW;        // uint64 [8]: pointers of the uncommon paths
     static constexpr int kBpos = kCold + 64;            // int32 [2 * kMW], 64-bit keys: slots of the best entries
-    static constexpr int kRun = kBpos + 8 * kMW;        // int32 [kMW]: running task or -1 (for the read-ahead)
-    static constexpr int kReq = kRun + 4 * kMW;         // int32 [kMW]: a rescan is pending
-    static constexpr int kRnb = kReq + 4 * kMW;         // int32 [kMW]: ... of a queue of this many blocks
-    static constexpr int kRch = kRnb + 4 * kMW;         // int32 [kMW]: ... whose changed blocks are these two
-    static constexpr int kSeg = kRch + 4 * kMW;         // int32 [kMW]: ends of the runs of newly ready tasks
+    static constexpr int kReq = kBpos + 8 * kMW;        // int32 [kMW]: block to rescan + 1, or 0
+    static constexpr int kRnb = kReq + 4 * kMW;         // int32 [kMW]: blocks of the queue
+    static constexpr int kSeg = kRnb + 4 * kMW;         // int32 [kMW]: ends of the runs of newly ready tasks
     static constexpr int kSucc = kSeg + 4 * kMW;        // int32 [kPF]: a completing task's first successors
     static constexpr int kPre = kSucc + 4 * kPF;        // int32 [8 * 64]: staged frontier rows
     static constexpr int kFr0 = kPre + 4 * 8 * kWave;   // int32 [kFC]
@@ -1165,10 +1167,9 @@ struct LaneLds {
     unsigned long long *sk;  // [64 * key_cap] keys of the low blocks' entries
     unsigned long long *sx;  // [64 * slot_cap] payload (task, durations) of the lowest
     int32_t *srs;            // [64 * slot_cap] ... and their first edges
-    int32_t *fstk;           // [sum_cap] free block ids below sum_cap
     int32_t *blist;          // [W * lb] first block ids of each worker
     static constexpr size_t bytes(int mw, int sc, int lb, int slc, int slk) {
-        return (size_t)kFixed + (size_t)sc * 20 + (size_t)slk * 512 + (size_t)slc * 768 + (size_t)mw * lb * 4;
+        return (size_t)kFixed + (size_t)sc * 16 + (size_t)slk * 512 + (size_t)slc * 768 + (size_t)mw * lb * 4;
     }
     __device__ __forceinline__ static char *raw() {
         extern __shared__ int64_t lds64[];
@@ -1181,14 +1182,13 @@ struct LaneLds {
         sk = mx + 2 * A.sum_cap;
         sx = sk + 64 * A.key_cap;
         srs = reinterpret_cast<int32_t *>(sx + 64 * A.slot_cap);
-        fstk = srs + 64 * A.slot_cap;
-        blist = fstk + A.sum_cap;
+        blist = srs + 64 * A.slot_cap;
     }
 };
 static_assert(LaneLds<1>::kFixed % 16 == 0 && LaneLds<2>::kFixed % 16 == 0, "aligned for 64-bit arrays");
 
 // Pointers kept in LDS (LaneLds::kCold).
-enum ColdPtr { kColdFbuf = 0, kColdWblk, kColdFreeb, kColdKeys, kColdPayload, kColdEdges, kColdSums };
+enum ColdPtr { kColdFbuf = 0, kColdWblk, kColdKeys, kColdPayload, kColdEdges, kColdSums };
 
 template <int WPL, typename T>
 __device__ __forceinline__ T *cold(int i) {
@@ -1205,10 +1205,6 @@ __device__ __forceinline__ Keys<KK> make_keys(const SimArgs &A, const LaneLds<WP
     return K;
 }
 
-// A rescan request for worker w names its queue's block count and the one or
-// two blocks whose maxima the pop emptied.
-constexpr uint32_t kNoBlock = 0xFFFFu;  // block ids are below n / 64 + W <= 2^15 + 128
-
 // The work-group's second wave: answers rescan requests until the DAG is done.
 template <int WPL, int KK>
 __device__ void keep_best(const SimArgs &A, int32_t di) {
@@ -1218,7 +1214,6 @@ __device__ void keep_best(const SimArgs &A, int32_t di) {
     const LL L(A);
     const int lane = lane_id();
     const DagDesc d = A.desc[di];
-    const int32_t W = d.n_cpu + d.n_gpu;
     const SlotPool slots = A.slots.at(64 * d.blk_off);
     unsigned long long *sums = A.sums + 2 * d.blk_off;
     const int32_t *wblk = A.paux + d.wl_off;
@@ -1226,8 +1221,7 @@ __device__ void keep_best(const SimArgs &A, int32_t di) {
     const int32_t SC = A.sum_cap, SLK = A.key_cap, kLB = A.lb;
     unsigned long long *mx = L.mx, *best = LL::template arr<unsigned long long>(LL::kBest);
     int32_t *bpos = LL::template arr<int32_t>(LL::kBpos), *req = LL::template arr<int32_t>(LL::kReq);
-    const int32_t *rnb = LL::template arr<int32_t>(LL::kRnb), *rch = LL::template arr<int32_t>(LL::kRch);
-    const int32_t *hs = LL::template arr<int32_t>(LL::kHs);
+    const int32_t *rnb = LL::template arr<int32_t>(LL::kRnb), *hs = LL::template arr<int32_t>(LL::kHs);
     // rule-r key of block b's entry in this lane
     auto entry = [&](int32_t b, int r) -> KT {
         if (b < SLK) return K.lds(b * 64 + lane, r);
@@ -1244,74 +1238,69 @@ __device__ void keep_best(const SimArgs &A, int32_t di) {
         bool any = false;
 #pragma unroll
         for (int k = 0; k < WPL; k++) {
-            const int32_t wl = lane + k * kWave;
-            uint64_t m = ballot((wl < W ? lds_load(&req[wl]) : 0) != 0);
+            const int32_t wl = lane + k * kWave, rq = lds_load(&req[wl]);
+            uint64_t m = ballot(rq != 0);
             any |= m != 0;
             keep_order();
             while (m) {
-                const int32_t w = (int32_t)__builtin_ctzll(m) + k * kWave;
+                const int l = (int)__builtin_ctzll(m);
+                const int32_t w = l + k * kWave;
                 m &= m - 1;
-                const int32_t nbw = uniform(min(rnb[w], d.maxb));
-                const uint32_t ch = (uint32_t)uniform(rch[w]);
-                // the changed blocks' maxima under both rules
-                unsigned long long bm0 = 0, bm1 = 0;  // ... of the last one scanned
-                int32_t bp0 = 0, bp1 = 0;             // 64-bit keys: their slots
-                bool glob = false, found = true;
-#pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    const uint32_t b = (ch >> (16 * h)) & 0xFFFFu;
-                    if (b == kNoBlock || (int32_t)b >= d.nblk) continue;
-                    const KT k0 = entry((int32_t)b, 0), k1 = entry((int32_t)b, 1);
-                    const KT s0 = wave_max_k(k0), s1 = wave_max_k(k1);
-                    bp0 = (int32_t)b * 64 + (int32_t)__builtin_ctzll(ballot(k0 == s0));
-                    bp1 = (int32_t)b * 64 + (int32_t)__builtin_ctzll(ballot(k1 == s1));
-                    if constexpr (kBig) {
-                        bm0 = s0;
-                        bm1 = s1;
+                const int32_t b = read_lane(rq, l) - 1, nbw = uniform(min(rnb[w], d.maxb));
+                if (b < 0 || b >= d.nblk) continue;  // never
+                // the changed block's maxima under both rules, and their slots
+                const KT k0 = entry(b, 0), k1 = entry(b, 1);
+                const KT s0 = wave_max_k(k0), s1 = wave_max_k(k1);
+                int32_t bp0 = b * 64 + (int32_t)__builtin_ctzll(ballot(k0 == s0));
+                int32_t bp1 = b * 64 + (int32_t)__builtin_ctzll(ballot(k1 == s1));
+                unsigned long long bm0, bm1;
+                if constexpr (kBig) {
+                    bm0 = s0;
+                    bm1 = s1;
+                } else {
+                    bm0 = s0 ? (unsigned long long)s0 << 32 | (uint32_t)bp0 : 0ull;
+                    bm1 = s1 ? (unsigned long long)s1 << 32 | (uint32_t)bp1 : 0ull;
+                }
+                const bool glob = b >= SC;
+                bool found = true;
+                if (lane == 0) {
+                    if (!glob) {
+                        atomicMax(&mx[2 * b], bm0);
+                        atomicMax(&mx[2 * b + 1], bm1);
                     } else {
-                        bm0 = s0 ? (unsigned long long)s0 << 32 | (uint32_t)bp0 : 0ull;
-                        bm1 = s1 ? (unsigned long long)s1 << 32 | (uint32_t)bp1 : 0ull;
-                    }
-                    glob |= (int32_t)b >= SC;
-                    if (lane == 0) {
-                        if ((int32_t)b < SC) {
-                            atomicMax(&mx[2 * b], bm0);
-                            atomicMax(&mx[2 * b + 1], bm1);
-                        } else {
-                            wg_fetch_max(&sums[2 * b], bm0);
-                            wg_fetch_max(&sums[2 * b + 1], bm1);
-                        }
+                        wg_fetch_max(&sums[2 * b], bm0);
+                        wg_fetch_max(&sums[2 * b + 1], bm1);
                     }
                 }
-                if (nbw > 1 || ch == (kNoBlock | kNoBlock << 16)) {
+                if (nbw > 1) {
                     // the largest block maximum under each rule
                     keep_order();
                     bm0 = bm1 = 0;
                     int32_t b0 = -1, b1 = -1;
                     for (int32_t i0 = 0; i0 < nbw; i0 += kWave) {
                         const int32_t i = i0 + lane;
-                        int32_t b = -1;
+                        int32_t bi = -1;
                         if (i < nbw) {
-                            b = i < kLB ? L.blist[w * kLB + i] : wg_load(&wblk[(int64_t)w * d.maxb + i]);
-                            if (b >= d.nblk) b = -1;
+                            bi = i < kLB ? L.blist[w * kLB + i] : wg_load(&wblk[(int64_t)w * d.maxb + i]);
+                            if (bi >= d.nblk) bi = -1;
                         }
                         unsigned long long m0 = 0, m1 = 0;
-                        if (b >= 0) {
-                            if (b < SC) {
-                                m0 = lds_load(&mx[2 * b]);
-                                m1 = lds_load(&mx[2 * b + 1]);
+                        if (bi >= 0) {
+                            if (bi < SC) {
+                                m0 = lds_load(&mx[2 * bi]);
+                                m1 = lds_load(&mx[2 * bi + 1]);
                             } else {
-                                m0 = __hip_atomic_load(&sums[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                m1 = __hip_atomic_load(&sums[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                m0 = __hip_atomic_load(&sums[2 * bi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                m1 = __hip_atomic_load(&sums[2 * bi + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             }
                         }
                         if (m0 > bm0) {
                             bm0 = m0;
-                            b0 = b;
+                            b0 = bi;
                         }
                         if (m1 > bm1) {
                             bm1 = m1;
-                            b1 = b;
+                            b1 = bi;
                         }
                     }
                     const unsigned long long g0 = wave_max_u64f(bm0), g1 = wave_max_u64f(bm1);
@@ -1321,10 +1310,10 @@ __device__ void keep_best(const SimArgs &A, int32_t di) {
                         const int32_t c1 = read_lane(b1, (int)__builtin_ctzll(ballot(bm1 == g1)));
 #pragma unroll
                         for (int r = 0; r < 2; r++) {
-                            const int32_t b = r ? c1 : c0;
-                            if (b < 0) continue;
-                            const uint64_t hit = ballot(entry(b, r) == (r ? g1 : g0));
-                            if (hit) (r ? bp1 : bp0) = b * 64 + (int32_t)__builtin_ctzll(hit);
+                            const int32_t br = r ? c1 : c0;
+                            if (br < 0) continue;
+                            const uint64_t hit = ballot(entry(br, r) == (r ? g1 : g0));
+                            if (hit) (r ? bp1 : bp0) = br * 64 + (int32_t)__builtin_ctzll(hit);
                             else found = false;
                         }
                     }
@@ -1400,10 +1389,10 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
     const int32_t kLB = A.lb;
     const int32_t SLC = A.slot_cap;  // blocks [0, SLC) keep their entries' payload in LDS
     const int32_t SLK = A.key_cap;   // blocks [0, SLK) (SLK >= SLC) keep their keys in LDS
+    const int32_t NB = min(SLC, SC); // blocks [0, NB) are in LDS with all they have
     unsigned long long *mx = L.mx, *best = LL::template arr<unsigned long long>(LL::kBest);
-    int64_t *lfin = LL::template arr<int64_t>(LL::kFin);
-    int32_t *lrun = LL::template arr<int32_t>(LL::kRun), *req = LL::template arr<int32_t>(LL::kReq);
-    int32_t *rnb = LL::template arr<int32_t>(LL::kRnb), *rch = LL::template arr<int32_t>(LL::kRch);
+    int2 *lrun = LL::template arr<int2>(LL::kRun);
+    int32_t *req = LL::template arr<int32_t>(LL::kReq), *rnb = LL::template arr<int32_t>(LL::kRnb);
     int32_t *bpos = LL::template arr<int32_t>(LL::kBpos), *seg = LL::template arr<int32_t>(LL::kSeg);
     int32_t *succ = LL::template arr<int32_t>(LL::kSucc), *pre = LL::template arr<int32_t>(LL::kPre);
     int32_t *fr0 = LL::template arr<int32_t>(LL::kFr0), *fr1 = LL::template arr<int32_t>(LL::kFr1);
@@ -1445,7 +1434,6 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             const SlotPool slots = A.slots.at(64 * d.blk_off);
             c[kColdFbuf] = (uint64_t)fbuf;
             c[kColdWblk] = (uint64_t)(A.paux + d.wl_off);
-            c[kColdFreeb] = (uint64_t)(A.paux + A.freeb_base + d.blk_off);
             c[kColdKeys] = (uint64_t)slots.k;
             c[kColdPayload] = (uint64_t)slots.x;
             c[kColdEdges] = (uint64_t)slots.rs;
@@ -1488,7 +1476,8 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
 
     // this lane's workers
     bool wok[WPL], wcpu[WPL];
-    int32_t run[WPL], len[WPL], nb[WPL], last[WPL], rsr[WPL], dgr[WPL];
+    int32_t run[WPL], len[WPL], nb[WPL], rsr[WPL], dgr[WPL];
+    int32_t hole[WPL], tail[WPL];  // slots for the next pushes: an empty one (or -1), and the one past the last entry
     row4 pfa[WPL], pfb[WPL];  // the running task's first successors
     int64_t fin[WPL], expend[WPL], qest[WPL];  // expend is 0 while the worker is idle
     unsigned long long pk0[WPL], pk1[WPL];  // 64-bit keys: the best entry pushed or raised since the last pop, by rule ...
@@ -1500,7 +1489,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         wcpu[k] = w < ncpu;
         run[k] = -1;
         len[k] = nb[k] = rsr[k] = dgr[k] = 0;
-        last[k] = 0;
+        hole[k] = tail[k] = -1;
         pfa[k] = pfb[k] = row4{0, 0, 0, 0};
         fin[k] = expend[k] = qest[k] = 0;
         pk0[k] = pk1[k] = 0;
@@ -1510,24 +1499,20 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         req[w] = 0;
     }
 
-    // free block ids, lowest first: a stack in LDS below sum_cap, one in
-    // global memory above it
-    const int32_t nl = min(d.nblk, SC);
-    int32_t nfl = nl, nfg = d.nblk - nl;
+    // blocks are taken in order, lowest first; every slot starts empty (zero keys)
+    int32_t nused = 0;
     {
-        int32_t *freeb = A.paux + A.freeb_base + d.blk_off;
         unsigned long long *sums = A.sums + 2 * d.blk_off, *sk = A.slots.at(64 * d.blk_off).k;
-        for (int32_t i = lane; i < nl; i += kWave) {
-            L.fstk[i] = nl - 1 - i;
-            mx[2 * i] = 0;
-            mx[2 * i + 1] = 0;
+        for (int32_t b = lane; b < d.nblk; b += kWave) {
+            if (b < SC) {
+                mx[2 * b] = 0;
+                mx[2 * b + 1] = 0;
+            } else {
+                sums[2 * b] = 0;
+                sums[2 * b + 1] = 0;
+            }
+            if constexpr (DATA) barr[b] = 0;
         }
-        for (int32_t i = lane; i < d.nblk - nl; i += kWave) {
-            freeb[i] = d.nblk - 1 - i;
-            sums[2 * (nl + i)] = 0;
-            sums[2 * (nl + i) + 1] = 0;
-        }
-        // every slot starts empty (zero keys)
         for (int32_t b = 0; b < d.nblk; b++) {
             if (b < SLK) K.put(b * 64 + lane, 0);
             else sk[b * 64 + lane] = 0;
@@ -1568,19 +1553,27 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             m0 = (unsigned long long)na << 32 | (uint32_t)qu;
             m1 = (unsigned long long)ne << 32 | (uint32_t)qu;
         }
-        if (on && bk < SLK) K.put(qu, word);
-        if (ballot(on && bk >= SLK))
-            if (on && bk >= SLK) pool().k[qu] = word;
-        keep_order();
-        if (on && bk < SC) {
-            atomicMax(&mx[2 * bk], m0);
-            atomicMax(&mx[2 * bk + 1], m1);
-        }
-        if (ballot(on && bk >= SC)) {
-            unsigned long long *sums = gsums();
-            if (on && bk >= SC) {
-                wg_fetch_max(&sums[2 * bk], m0);
-                wg_fetch_max(&sums[2 * bk + 1], m1);
+        const uint64_t onm = ballot(on);
+        if ((onm & ballot(bk >= NB)) == 0) {
+            if (on) {
+                K.put(qu, word);
+                keep_order();
+                atomicMax(&mx[2 * bk], m0);
+                atomicMax(&mx[2 * bk + 1], m1);
+            }
+        } else {
+            unsigned long long *gk = pool().k, *sums = gsums();
+            if (on) {
+                if (bk < SLK) K.put(qu, word);
+                else gk[qu] = word;
+                keep_order();
+                if (bk < SC) {
+                    atomicMax(&mx[2 * bk], m0);
+                    atomicMax(&mx[2 * bk + 1], m1);
+                } else {
+                    wg_fetch_max(&sums[2 * bk], m0);
+                    wg_fetch_max(&sums[2 * bk + 1], m1);
+                }
             }
         }
         if constexpr (!kBig) {
@@ -1589,7 +1582,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 atomicMax(&best[2 * wu + 1], m1);
             }
         } else {
-            uint64_t left = ballot(on);
+            uint64_t left = onm;
             while (left) {
                 const int l = (int)__builtin_ctzll(left);
                 left &= left - 1;
@@ -1623,12 +1616,13 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             // plus the estimates queued, saturated at kLim (as are lanes without a
             // worker), and the slot of the next push (-1: a new block)
             uint32_t ld[WPL];
-            int32_t nslot[WPL];
+            int32_t nslot[WPL], used[WPL];  // used: the empty slot a push took
 #pragma unroll
             for (int k = 0; k < WPL; k++) {
                 const uint64_t x = (uint64_t)(max(expend[k], t) - t) + (uint64_t)qest[k];
                 ld[k] = wok[k] && x < kLim ? (uint32_t)x : kLim;
-                nslot[k] = (len[k] & 63) ? last[k] * 64 + (len[k] & 63) : -1;
+                nslot[k] = hole[k] >= 0 ? hole[k] : tail[k];
+                used[k] = -1;
             }
             for (int32_t i0 = 0;; i0 += kWave) {
                 if (!inlane) {
@@ -1770,16 +1764,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     }
                     int32_t slot = of_worker<WPL>(nslot, ws);
                     if (slot < 0) {  // a new block
-                        int32_t blk;
-                        if (nfl > 0) {
-                            nfl--;
-                            blk = L.fstk[nfl];
-                        } else {
-                            nfg--;
-                            blk = wg_load(&cold<WPL, int32_t>(kColdFreeb)[nfg]);
-                            settle(blk);
-                        }
-                        blk = uniform(blk);
+                        const int32_t blk = nused++;
                         const int32_t nbw = of_worker<WPL>(nb, ws);
                         if (nbw < kLB) {
                             if (lane == 0) L.blist[ws * kLB + nbw] = blk;
@@ -1787,22 +1772,27 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                             int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
                             if (lane == 0) wblk[(int64_t)ws * maxb + nbw] = blk;
                         }
+                        if (lane == 0) rnb[ws] = nbw + 1;
+                        slot = blk * 64;
 #pragma unroll
                         for (int k = 0; k < WPL; k++)
                             if (lane + k * kWave == ws) {
                                 nb[k] = nbw + 1;
-                                last[k] = blk;
+                                tail[k] = slot;
                             }
-                        slot = blk * 64;
                     }
-                    const int32_t next = (slot + 1) & 63 ? slot + 1 : -1;
+                    // the slot was the worker's empty one or its tail
 #pragma unroll
                     for (int k = 0; k < WPL; k++)
                         if (lane + k * kWave == ws) {
                             len[k]++;
                             qest[k] += ek;
                             ld[k] = min(ld[k] + (uint32_t)ek, kLim);
-                            nslot[k] = next;
+                            const bool h = slot == hole[k];
+                            used[k] = h ? slot : used[k];
+                            hole[k] = h ? -1 : hole[k];
+                            tail[k] = h ? tail[k] : (slot + 1) & 63 ? slot + 1 : -1;
+                            nslot[k] = tail[k];
                         }
                     if (lane == j) {
                         pq = slot;
@@ -1854,49 +1844,69 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     m1 = (unsigned long long)a1 << 32 | (uint32_t)pq;
                 }
                 const uint64_t xw = (uint64_t)f_v << 42 | (uint64_t)(dkl & M21) << 21 | (uint64_t)(ekl & M21);
-                const bool lk = ok && bq < SLK, lx = ok && bq < SLC, lm = ok && bq < SC;
-                if (lk) K.put(pq, word);
-                if (lx) {
-                    L.sx[pq] = xw;
-                    L.srs[pq] = f_rs;
+                // the next empty slot of each worker whose first one was taken
+                // (read before the entries overwrite the chain)
+#pragma unroll
+                for (int k = 0; k < WPL; k++) {
+                    const uint64_t um = ballot(used[k] >= 0);
+                    if (um) {
+                        if ((um & ballot((used[k] >> 6) >= SLC)) == 0) {
+                            if (used[k] >= 0) hole[k] = L.srs[used[k]];
+                        } else {
+                            const int32_t *grs = pool().rs;
+                            if (used[k] >= 0) {
+                                if ((used[k] >> 6) < SLC) hole[k] = L.srs[used[k]];
+                                else hole[k] = wg_load(&grs[used[k]]);
+                            }
+                        }
+                        used[k] = -1;
+                    }
                 }
-                if (ballot(ok && !lx)) {
+                keep_order();
+                if ((fm & ballot(bq >= NB)) == 0) {
+                    if (ok) {
+                        K.put(pq, word);
+                        L.sx[pq] = xw;
+                        L.srs[pq] = f_rs;
+                        keep_order();
+                        atomicMax(&mx[2 * bq], m0);
+                        atomicMax(&mx[2 * bq + 1], m1);
+                    }
+                } else {
                     const SlotPool slots = pool();
-                    if (ok && !lk) slots.k[pq] = word;
-                    if (ok && !lx) {
-                        slots.x[pq] = xw;
-                        slots.rs[pq] = f_rs;
+                    unsigned long long *sums = gsums();
+                    if (ok) {
+                        if (bq < SLK) K.put(pq, word);
+                        else slots.k[pq] = word;
+                        if (bq < SLC) {
+                            L.sx[pq] = xw;
+                            L.srs[pq] = f_rs;
+                        } else {
+                            slots.x[pq] = xw;
+                            slots.rs[pq] = f_rs;
+                        }
+                        keep_order();
+                        if (bq < SC) {
+                            atomicMax(&mx[2 * bq], m0);
+                            atomicMax(&mx[2 * bq + 1], m1);
+                        } else {
+                            wg_fetch_max(&sums[2 * bq], m0);
+                            wg_fetch_max(&sums[2 * bq + 1], m1);
+                        }
                     }
                 }
                 if (ok) {
                     // queue slot, then push order and worker
                     *reinterpret_cast<int2 *>(&at(tr, f_v)->qpos) = make_int2(pq, sqj | wsj << 21);
-                    // data model: the record's first word holds the time the
-                    // task's inputs arrive (transfers start now) until its pop
-                    if constexpr (DATA) {
-                        at(tr, f_v)->word = (unsigned long long)(t + xsj);
-                        // never lowered by pops: an upper bound for the block
-                        if (lrule && (pq & 63) == 0) barr[bq] = t + xsj;
-                    }
-                }
-                keep_order();
-                if (lm) {
-                    atomicMax(&mx[2 * bq], m0);
-                    atomicMax(&mx[2 * bq + 1], m1);
-                }
-                if (ballot(ok && !lm)) {
-                    unsigned long long *sums = gsums();
-                    if (ok && !lm) {
-                        wg_fetch_max(&sums[2 * bq], m0);
-                        wg_fetch_max(&sums[2 * bq + 1], m1);
-                    }
-                }
-                if constexpr (!kBig) {
-                    if (ok) {
+                    if constexpr (!kBig) {
                         atomicMax(&best[2 * wsj], m0);
                         atomicMax(&best[2 * wsj + 1], m1);
                     }
+                    // data model: the record's first word holds the time the
+                    // task's inputs arrive (transfers start now) until its pop
+                    if constexpr (DATA) at(tr, f_v)->word = (unsigned long long)(t + xsj);
                 }
+                // never lowered by pops: an upper bound for the block
                 if constexpr (DATA)
                     if (lrule && ok)
                         wg_fetch_max(reinterpret_cast<unsigned long long *>(&barr[bq]), (unsigned long long)(t + xsj));
@@ -1941,9 +1951,10 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         int32_t popped = 0;
 #pragma unroll
         for (int k = 0; k < WPL; k++) {
-            const bool want = run[k] < 0 && len[k] > 0;  // only workers have queues
-            const uint64_t wm = ballot(want);
+            // (only workers have queues)
+            const uint64_t wm = ballot(run[k] < 0) & ballot(len[k] > 0);
             if (wm == 0) continue;
+            const bool want = __builtin_amdgcn_inverse_ballot_w64(wm);
             const int32_t w = lane + k * kWave;
             const int32_t np = __popcll(wm);
             popped += np;
@@ -1957,7 +1968,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 keep_order();
                 bk = lds_load(&best[2 * w + slot]);
                 if constexpr (kBig) bp = lds_load(&bpos[2 * w + slot]);
-                if (!ballot(want && rq != 0)) break;
+                if ((wm & ballot(rq != 0)) == 0) break;
                 if (spin > kReqSpin) {  // never: a wait that ends all the same
                     status |= ST_HANG;
                     done = n;
@@ -2048,120 +2059,56 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     }
                 }
             }
-            // take the entry at p; the worker's final entry q fills the hole
-            const int32_t bb = p >> 6, lastw = last[k], nlen = len[k] - 1;
-            const int32_t q = want ? lastw * 64 + (nlen & 63) : 0;
-            const bool mv = want && p != q;
-            uint64_t vx, mxw, mkr;  // mkr: the moved entry's key word
-            int32_t vr, mr;
-            const bool far = want && max(bb, lastw) >= SLC;  // an entry in global memory
-            if (ballot(far) == 0) {
-                // payload and keys in LDS (other lanes read slot 0)
-                vx = L.sx[p];
-                vr = L.srs[p];
-                mxw = L.sx[q];
-                mr = L.srs[q];
-                mkr = K.word(q);
-                if constexpr (!kBig)
-                    if (kf.fifo) key = K.ke[p];  // the FIFO key holds no attributes
-                if (mv) {
-                    L.sx[p] = mxw;
-                    L.srs[p] = mr;
-                    K.put(p, mkr);
+            // take the entry at p: its slot joins the worker's empty ones, and its
+            // block's maxima and the worker's best wait for the rescan
+            const int32_t bb = p >> 6;
+            uint64_t vx = 0;
+            int32_t vr = 0;
+            if ((wm & ballot(bb >= NB)) == 0) {
+                if (want) {
+                    vx = L.sx[p];
+                    vr = L.srs[p];
+                    if constexpr (!kBig)
+                        if (kf.fifo) key = K.ke[p];  // the FIFO key holds no attributes
+                    K.put(p, 0);
+                    L.srs[p] = hole[k];
+                    mx[2 * bb] = 0;
+                    mx[2 * bb + 1] = 0;
                 }
-                if (want) K.put(q, 0);  // the worker's final slot is now empty
             } else {
                 const SlotPool slots = pool();
-                vx = mxw = mkr = 0;
-                vr = mr = 0;
+                unsigned long long *sums = gsums();
                 if (want) {
+                    if constexpr (!kBig)
+                        if (kf.fifo) key = bb < SLK ? K.ke[p] : (uint32_t)(wg_load(&slots.k[p]) >> 32);
                     if (bb < SLC) {
                         vx = L.sx[p];
                         vr = L.srs[p];
+                        L.srs[p] = hole[k];
                     } else {
                         vx = wg_load(&slots.x[p]);
                         vr = wg_load(&slots.rs[p]);
+                        slots.rs[p] = hole[k];
                     }
-                    if (lastw < SLC) {
-                        mxw = L.sx[q];
-                        mr = L.srs[q];
+                    if (bb < SLK) K.put(p, 0);
+                    else slots.k[p] = 0;
+                    if (bb < SC) {
+                        mx[2 * bb] = 0;
+                        mx[2 * bb + 1] = 0;
                     } else {
-                        mxw = wg_load(&slots.x[q]);
-                        mr = wg_load(&slots.rs[q]);
+                        sums[2 * bb] = 0;
+                        sums[2 * bb + 1] = 0;
                     }
-                    mkr = lastw < SLK ? K.word(q) : wg_load(&slots.k[q]);
-                    if constexpr (!kBig)
-                        if (kf.fifo) key = bb < SLK ? K.ke[p] : (uint32_t)(wg_load(&slots.k[p]) >> 32);
-                }
-                if (mv) {
-                    if (bb < SLK) K.put(p, mkr);
-                    else slots.k[p] = mkr;
-                    if (bb < SLC) {
-                        L.sx[p] = mxw;
-                        L.srs[p] = mr;
-                    } else {
-                        slots.x[p] = mxw;
-                        slots.rs[p] = mr;
-                    }
-                }
-                if (want) {
-                    if (lastw < SLK) K.put(q, 0);
-                    else slots.k[q] = 0;
                 }
                 settle(vx);
                 settle(vr);
             }
             PCLK(12);
-            if (mv) {
-                at(tr, (int32_t)(mxw >> 42))->qpos = p;
-                // the moved entry keeps block bb's arrival bound valid
-                if constexpr (DATA)
-                    if (lrule && lastw != bb) barr[bb] = max(barr[bb], barr[lastw]);
-            }
-            // the maxima of the blocks that changed wait for their rescan
-            const bool gone = want && max(bb, lastw) >= SC;
-            if (ballot(gone)) {
-                unsigned long long *sums = gsums();
-                if (want && bb >= SC) sums[2 * bb] = sums[2 * bb + 1] = 0;
-                if (want && lastw >= SC) sums[2 * lastw] = sums[2 * lastw + 1] = 0;
-            }
             if (want) {
-                if (bb < SC) {
-                    mx[2 * bb] = 0;
-                    mx[2 * bb + 1] = 0;
-                }
-                if (lastw < SC) {
-                    mx[2 * lastw] = 0;
-                    mx[2 * lastw + 1] = 0;
-                }
                 best[2 * w] = 0;
                 best[2 * w + 1] = 0;
-            }
-            const bool freed = want && (nlen & 63) == 0;
-            int32_t newlast = lastw;
-            if (ballot(freed)) {
-                const uint64_t fl = ballot(freed && lastw < SC), fg = ballot(freed && lastw >= SC);
-                int32_t *freeb = cold<WPL, int32_t>(kColdFreeb);
-                const int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
-                if (freed) {
-                    if (lastw < SC) L.fstk[nfl + lanes_below(fl)] = lastw;
-                    else freeb[nfg + lanes_below(fg)] = lastw;
-                    nb[k]--;
-                    if (nb[k] <= 0) newlast = 0;
-                    else if (nb[k] - 1 < kLB) newlast = L.blist[w * kLB + nb[k] - 1];
-                    else newlast = wg_load(&wblk[(int64_t)w * maxb + nb[k] - 1]);
-                }
-                settle(newlast);
-                nfl += __popcll(fl);
-                nfg += __popcll(fg);
-            }
-            if (want && nlen > 0) {
-                const uint32_t c0 = freed && bb == lastw ? kNoBlock : (uint32_t)bb;
-                const uint32_t c1 = freed || bb == lastw ? kNoBlock : (uint32_t)lastw;
-                rnb[w] = nb[k];
-                rch[w] = (int32_t)(c0 | c1 << 16);
                 keep_order();
-                lds_store(&req[w], 1);
+                lds_store(&req[w], bb + 1);
             }
             const int32_t v = (int32_t)(vx >> 42);
             const int32_t dk = (int32_t)((vx >> 21) & M21), ek = (int32_t)(vx & M21);
@@ -2189,8 +2136,8 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 pfa[k] = *reinterpret_cast<const row4 *>(col + vr);
                 pfb[k] = *reinterpret_cast<const row4 *>(col + vr + 4);
                 put_record(at(tr, v), s0, dk, w, iev, pmode);
-                len[k] = nlen;
-                last[k] = newlast;
+                len[k]--;
+                hole[k] = p;
                 run[k] = v;
                 fin[k] = s0 + dk;
                 expend[k] = s0 + ek;
@@ -2198,8 +2145,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 rsr[k] = vr;
                 dgr[k] = deg;
                 // for the wave that reads ahead
-                lfin[w] = fin[k];
-                lrun[w] = v;
+                lrun[w] = make_int2(v, (int32_t)fin[k]);
             }
             PCLK(13);
         }
@@ -2236,14 +2182,14 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         int32_t ndone = 0;
 #pragma unroll
         for (int k = 0; k < WPL; k++) {
-            const bool fin_now = run[k] >= 0 && fin[k] == t;
-            cm[k] = ballot(fin_now);
+            cm[k] = ballot(run[k] >= 0) & ballot(fin[k] == t);
+            const bool fin_now = __builtin_amdgcn_inverse_ballot_w64(cm[k]);
             ndone += __popcll(cm[k]);
             c_l[k] = run[k];
             if (fin_now) {
                 run[k] = -1;
                 expend[k] = 0;
-                lrun[lane + k * kWave] = -1;
+                lrun[lane + k * kWave].x = -1;
             }
         }
         done += ndone;
@@ -2277,13 +2223,15 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             unsigned long long *dp = at(dep, s);
             const uint64_t now = *dp - ((1ull << 43) + (unsigned long long)c);
             if (in) *dp = now;
-            const int32_t nr = (int32_t)(now >> 43);
-            const bool rdy = in && nr == 0, cd = in && nr == 1;
-            fm = ballot(rdy);
+            const uint32_t nr = (uint32_t)(now >> 43);
+            const uint64_t inm = deg1 < 64 ? (1ull << deg1) - 1 : ~0ull;
+            const uint64_t cdm = inm & ballot(nr == 1);
+            fm = inm & ballot(nr == 0);
             r = __popcll(fm);
             inlane = r > 0;
+            const bool rdy = __builtin_amdgcn_inverse_ballot_w64(fm), cd = __builtin_amdgcn_inverse_ballot_w64(cdm);
             PCLK(20);
-            if (fm | ballot(cd)) {
+            if (fm | cdm) {
                 // rows of the newly ready tasks; records of the others' remaining
                 // predecessors u, whose IE may grow
                 const int32_t u = cd ? (int32_t)(now & M43) : 0;
@@ -2312,8 +2260,9 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     }
                 }
                 PCLK(23);
-                const bool cond = cd && ux.z + fx.z <= U;  // taus are at most 2^20, U at most 2^31 - 1
-                uint64_t left = ballot(cond);
+                // (taus are at most 2^20, U at most 2^31 - 1)
+                uint64_t left = cdm & ballot(ux.z + fx.z <= U);
+                const bool cond = __builtin_amdgcn_inverse_ballot_w64(left);
                 if (left) {
                     // several successors may name the same predecessor: the
                     // first lane applies all of its increments
@@ -2323,7 +2272,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                         lead = false;
                         while (left) {
                             const int l = (int)__builtin_ctzll(left);
-                            const uint64_t same = ballot(cond && u == read_lane(u, l));
+                            const uint64_t same = left & ballot(u == read_lane(u, l));
                             left &= ~same;
                             if (lane == l) {
                                 lead = true;
@@ -2644,8 +2593,7 @@ constexpr int kAheadEdges = 16;    // successors read per task
 template <int WPL>
 __device__ void read_ahead(const SimArgs &A, int32_t di) {
     using LL = LaneLds<WPL>;
-    const int64_t *lfin = LL::template arr<int64_t>(LL::kFin);
-    const int32_t *lrun = LL::template arr<int32_t>(LL::kRun);
+    const uint64_t *lrun = LL::template arr<uint64_t>(LL::kRun);
     int32_t *hs = LL::template arr<int32_t>(LL::kHs);
     const DagDesc d = A.desc[di];
     const int lane = lane_id();
@@ -2666,8 +2614,9 @@ __device__ void read_ahead(const SimArgs &A, int32_t di) {
         int64_t f = INT64_MAX;
 #pragma unroll
         for (int k = 0; k < WPL; k++) {
-            const int32_t ck = lds_load(&lrun[lane + k * kWave]);
-            const int64_t fk = lds_load(&lfin[lane + k * kWave]);
+            const uint64_t rf = lds_load(&lrun[lane + k * kWave]);
+            const int32_t ck = (int32_t)(uint32_t)rf;
+            const int64_t fk = (int64_t)(rf >> 32);  // low 32 bits: good for an order of finishes, which is all it is for
             if (ck >= 0 && (WPL == 1 || ck != pref[k]) && fk < f) {
                 f = fk;
                 c = ck;
@@ -2735,7 +2684,8 @@ __device__ void read_ahead(const SimArgs &A, int32_t di) {
 template <int WPL, int KK, bool DATA>
 __global__ __launch_bounds__(3 * kWave, WPL == 1 ? 3 : 1) void k_sim(SimArgs A) {
     using LL = LaneLds<WPL>;
-    int32_t *hs = LL::template arr<int32_t>(LL::kHs), *lrun = LL::template arr<int32_t>(LL::kRun);
+    int32_t *hs = LL::template arr<int32_t>(LL::kHs);
+    int2 *lrun = LL::template arr<int2>(LL::kRun);
     const int wave = uniform(threadIdx.x / kWave);
     for (;;) {
         if (threadIdx.x == 0) {
@@ -2743,7 +2693,7 @@ __global__ __launch_bounds__(3 * kWave, WPL == 1 ? 3 : 1) void k_sim(SimArgs A) 
             hs[1] = 0;
             hs[3] = 0;
         }
-        for (int32_t w = threadIdx.x; w < LL::kMW; w += 3 * kWave) lrun[w] = -1;
+        for (int32_t w = threadIdx.x; w < LL::kMW; w += 3 * kWave) lrun[w] = make_int2(-1, 0);
         __syncthreads();
         const int32_t i = uniform(hs[0]);
         if (i >= A.count) break;
