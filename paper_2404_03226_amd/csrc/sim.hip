@@ -123,6 +123,10 @@ constexpr int kFC = 256;  // frontier slots in LDS (larger frontiers use global 
 constexpr int kCC = 128;  // candidate slots in LDS
 constexpr int kScan = 16;  // most blocks the tune key's "scan=" may name (it has no effect: see keep_best)
 constexpr int64_t kHelperSpin = 1ll << 40;
+// Which way a branch of the one-wave loop nearly always goes.
+#define USUALLY(x) __builtin_expect(!!(x), 1)
+#define RARELY(x) __builtin_expect(!!(x), 0)
+
 constexpr int32_t kReqSpin = 1 << 24;  // polls of a rescan request (it takes a few)
 
 struct Lds {
@@ -1045,6 +1049,12 @@ __device__ void sim_dag(const SimArgs &A, int32_t di, const Lds &L) {
 //     read element 0) so that the compiler issues them together.
 //   - Pointers and parameters that only uncommon paths use are kept in LDS
 //     (kCold*), not in scalar registers, whose spills cost the common path.
+//   - A wave that runs alone issues an instruction every 4 clocks; a scalar
+//     instruction that reads what a vector compare has just written waits 16
+//     more, a taken branch costs 21, an untaken one 7 and an LDS round trip 48
+//     (measured).  So uniform tests are made on scalar state where it allows
+//     (no queue block past the ones in LDS, no bad duration), lane updates are
+//     selects instead of masked blocks, and uncommon code is out of line.
 // Measured (2.4 GHz): layered 1,000-task DAG @L1K@ us per event, against 3.0 with
 // the scan in the simulating wave, pops one by one and frontier lists.
 
@@ -1410,7 +1420,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
     // initial frontier (tasks without predecessors, ascending) and the
     // largest out-degree, which sizes the key fields
     int32_t r = 0;
-    uint32_t mdeg = 0;
+    uint32_t mdeg = 0, longest = 0;
     {
         int32_t *fbuf = A.fbuf + 3 * d.toff;  // [0,n) runs, [n,2n) merged, [2n,3n) candidates
         for (int32_t i0 = 0; i0 < n; i0 += kWave) {
@@ -1419,6 +1429,8 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             if (i < n) {
                 ok = (dep[i] >> 43) == 0;
                 mdeg = max(mdeg, (uint32_t)tr[i].ia);
+                const int2 du = dur2[i];
+                longest = max(longest, max((uint32_t)(du.x - 1), (uint32_t)(du.y - 1)));
             }
             uint64_t mk = ballot(ok);
             if (ok) {
@@ -1429,6 +1441,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             r += __popcll(mk);
         }
         mdeg = wave_max_u32f(mdeg);
+        longest = wave_max_u32f(longest);
         if (lane == 0) {
             uint64_t *c = LL::template arr<uint64_t>(LL::kCold);
             const SlotPool slots = A.slots.at(64 * d.blk_off);
@@ -1440,6 +1453,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             c[kColdSums] = (uint64_t)(A.sums + 2 * d.blk_off);
         }
     }
+    const bool bad_dur = longest >= (uint32_t)INSP_MAX_TICK;  // some duration is out of range: the pushes look for it
     const uint32_t abits = field_bits(mdeg), sbits = field_bits(n - 1);
     KeyFmt kf;
     kf.sa = sbits;
@@ -1553,8 +1567,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             m0 = (unsigned long long)na << 32 | (uint32_t)qu;
             m1 = (unsigned long long)ne << 32 | (uint32_t)qu;
         }
-        const uint64_t onm = ballot(on);
-        if ((onm & ballot(bk >= NB)) == 0) {
+        if (USUALLY(nused <= NB) || (ballot(on) & ballot(bk >= NB)) == 0) {
             if (on) {
                 K.put(qu, word);
                 keep_order();
@@ -1582,7 +1595,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 atomicMax(&best[2 * wu + 1], m1);
             }
         } else {
-            uint64_t left = onm;
+            uint64_t left = ballot(on);
             while (left) {
                 const int l = (int)__builtin_ctzll(left);
                 left &= left - 1;
@@ -1606,7 +1619,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
 
     for (;;) {
         PCLK(9);
-        if (++events > max_events) {
+        if (RARELY(++events > max_events)) {
             status |= ST_HANG;
             break;
         }
@@ -1625,7 +1638,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 used[k] = -1;
             }
             for (int32_t i0 = 0;; i0 += kWave) {
-                if (!inlane) {
+                if (RARELY(!inlane)) {
                     const int32_t idx = i0 + lane;
                     const bool in = idx < r;
                     fm = ballot(in);
@@ -1668,8 +1681,9 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     }
                 }
                 const bool ok = __builtin_amdgcn_inverse_ballot_w64(fm);
-                if (ballot(ok && max((uint32_t)(f_d.x - 1), (uint32_t)(f_d.y - 1)) >= (uint32_t)INSP_MAX_TICK))
-                    status |= ST_DUR;
+                if (RARELY(bad_dur))
+                    if (fm & ballot(max((uint32_t)(f_d.x - 1), (uint32_t)(f_d.y - 1)) >= (uint32_t)INSP_MAX_TICK))
+                        status |= ST_DUR;
                 // data model: memory node and transfer ticks of each task's first
                 // predecessors' outputs (two round trips for all tasks together)
                 int32_t pn[kPred], px[kPred];
@@ -1745,7 +1759,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     }
                     const uint32_t m32 = wave_min_u32f(k32);
                     int32_t ws = (int32_t)(m32 & ((1u << WB) - 1));
-                    if (m32 >> WB == kLim) {
+                    if (RARELY(m32 >> WB == kLim)) {
                         uint64_t k64 = ~0ull;
 #pragma unroll
                         for (int k = 0; k < WPL; k++) {
@@ -1763,7 +1777,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                         if (xs > INSP_MAX_TICK) status |= ST_XFER;
                     }
                     int32_t slot = of_worker<WPL>(nslot, ws);
-                    if (slot < 0) {  // a new block
+                    if (RARELY(slot < 0)) {  // a new block
                         const int32_t blk = nused++;
                         const int32_t nbw = of_worker<WPL>(nb, ws);
                         if (nbw < kLB) {
@@ -1782,23 +1796,21 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                             }
                     }
                     // the slot was the worker's empty one or its tail
+                    const int32_t next = (slot + 1) & 63 ? slot + 1 : -1;
 #pragma unroll
-                    for (int k = 0; k < WPL; k++)
-                        if (lane + k * kWave == ws) {
-                            len[k]++;
-                            qest[k] += ek;
-                            ld[k] = min(ld[k] + (uint32_t)ek, kLim);
-                            const bool h = slot == hole[k];
-                            used[k] = h ? slot : used[k];
-                            hole[k] = h ? -1 : hole[k];
-                            tail[k] = h ? tail[k] : (slot + 1) & 63 ? slot + 1 : -1;
-                            nslot[k] = tail[k];
-                        }
-                    if (lane == j) {
-                        pq = slot;
-                        wsj = ws;
-                        xsj = xs;
+                    for (int k = 0; k < WPL; k++) {
+                        const bool is = lane + k * kWave == ws, h = is && slot == hole[k], tl = is && slot != hole[k];
+                        len[k] += is ? 1 : 0;
+                        qest[k] += is ? ek : 0;
+                        ld[k] = min(ld[k] + (is ? (uint32_t)ek : 0u), kLim);
+                        used[k] = h ? slot : used[k];
+                        hole[k] = h ? -1 : hole[k];
+                        tail[k] = tl ? next : tail[k];
+                        nslot[k] = is ? tail[k] : nslot[k];
                     }
+                    pq = lane == j ? slot : pq;
+                    wsj = lane == j ? ws : wsj;
+                    xsj = lane == j ? xs : xsj;
                     if constexpr (kBig) {
                         // the best entry pushed since the worker's last pop
                         const uint64_t hi = (uint32_t)read_lane(f_ie, j), lo = (uint32_t)read_lane(f_ia, j);
@@ -1848,22 +1860,23 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 // (read before the entries overwrite the chain)
 #pragma unroll
                 for (int k = 0; k < WPL; k++) {
-                    const uint64_t um = ballot(used[k] >= 0);
-                    if (um) {
-                        if ((um & ballot((used[k] >> 6) >= SLC)) == 0) {
-                            if (used[k] >= 0) hole[k] = L.srs[used[k]];
-                        } else {
-                            const int32_t *grs = pool().rs;
-                            if (used[k] >= 0) {
-                                if ((used[k] >> 6) < SLC) hole[k] = L.srs[used[k]];
-                                else hole[k] = wg_load(&grs[used[k]]);
-                            }
+                    int32_t nh;
+                    if (USUALLY(nused <= SLC) || ballot(used[k] >= SLC * 64) == 0) {
+                        nh = L.srs[max(used[k], 0)];
+                    } else {
+                        const int32_t *grs = pool().rs;
+                        nh = -1;
+                        if (used[k] >= 0) {
+                            if ((used[k] >> 6) < SLC) nh = L.srs[used[k]];
+                            else nh = wg_load(&grs[used[k]]);
                         }
-                        used[k] = -1;
+                        settle(nh);
                     }
+                    hole[k] = used[k] >= 0 ? nh : hole[k];
+                    used[k] = -1;
                 }
                 keep_order();
-                if ((fm & ballot(bq >= NB)) == 0) {
+                if (USUALLY(nused <= NB) || (fm & ballot(bq >= NB)) == 0) {
                     if (ok) {
                         K.put(pq, word);
                         L.sx[pq] = xw;
@@ -1968,8 +1981,8 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 keep_order();
                 bk = lds_load(&best[2 * w + slot]);
                 if constexpr (kBig) bp = lds_load(&bpos[2 * w + slot]);
-                if ((wm & ballot(rq != 0)) == 0) break;
-                if (spin > kReqSpin) {  // never: a wait that ends all the same
+                if (USUALLY((wm & ballot(rq != 0)) == 0)) break;
+                if (RARELY(spin > kReqSpin)) {  // never: a wait that ends all the same
                     status |= ST_HANG;
                     done = n;
                     break;
@@ -2064,7 +2077,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             const int32_t bb = p >> 6;
             uint64_t vx = 0;
             int32_t vr = 0;
-            if ((wm & ballot(bb >= NB)) == 0) {
+            if (USUALLY(nused <= NB) || (wm & ballot(bb >= NB)) == 0) {
                 if (want) {
                     vx = L.sx[p];
                     vr = L.srs[p];
@@ -2150,7 +2163,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             PCLK(13);
         }
         PCLK(2);
-        if (A.trace && lane == 0 && events <= max_events) {
+        if (RARELY(A.trace != nullptr) && lane == 0 && events <= max_events) {
             insp_trace_rec rec;
             rec.t = t;
             rec.nready = observed;
@@ -2161,7 +2174,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             rec.popped = popped;
             A.trace[(d.toff - A.base) + di + events - 1] = rec;
         }
-        if (done == n) break;
+        if (RARELY(done == n)) break;
         // --------------------------------------------------------- advance
         // every running task ends within 2^21 ticks of t
         uint32_t dl = ~0u;
@@ -2169,7 +2182,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         for (int k = 0; k < WPL; k++)
             if (run[k] >= 0) dl = min(dl, (uint32_t)(fin[k] - t));
         const uint32_t dtm = wave_min_u32f(dl);
-        if (dtm == ~0u) {
+        if (RARELY(dtm == ~0u)) {
             status |= ST_HANG;
             break;
         }
@@ -2198,7 +2211,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         const int32_t w1 = WPL == 2 && cm[0] == 0 ? kWave + (int32_t)__builtin_ctzll(cm[WPL - 1])
                                                   : (int32_t)__builtin_ctzll(cm[0]);
         const int32_t deg1 = of_worker<WPL>(dgr, w1);
-        if (ndone == 1 && deg1 <= kWave) {
+        if (USUALLY(ndone == 1) && USUALLY(deg1 <= kWave)) {
             const int32_t c = of_worker<WPL>(c_l, w1);
             // the first successors go from the worker's lane to a lane each
 #pragma unroll
@@ -2210,7 +2223,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             keep_order();
             const bool in = lane < deg1;
             int32_t s = lds_load(&succ[lane & (kPF - 1)]);
-            if (deg1 > kPF) {
+            if (RARELY(deg1 > kPF)) {
                 const int32_t rs = of_worker<WPL>(rsr, w1);
                 if (in && lane >= kPF) s = col[rs + lane];
             }
@@ -2231,7 +2244,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
             inlane = r > 0;
             const bool rdy = __builtin_amdgcn_inverse_ballot_w64(fm), cd = __builtin_amdgcn_inverse_ballot_w64(cdm);
             PCLK(20);
-            if (fm | cdm) {
+            if (USUALLY(fm | cdm)) {
                 // rows of the newly ready tasks; records of the others' remaining
                 // predecessors u, whose IE may grow
                 const int32_t u = cd ? (int32_t)(now & M43) : 0;
@@ -2268,7 +2281,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     // first lane applies all of its increments
                     int32_t mult = 1;
                     bool lead = cond;
-                    if (left & (left - 1)) {
+                    if (RARELY(left & (left - 1))) {
                         lead = false;
                         while (left) {
                             const int l = (int)__builtin_ctzll(left);
@@ -2283,16 +2296,16 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     const int32_t nie = ux.x + mult;
                     if (lead) ru->iev = nie;
                     if constexpr (KK != kFixed) {
-                        const bool qd = lead && uq.x >= 0;
-                        if (ballot(qd)) raise(qd, uq.x, uq.y, ux.y, nie);
+                        raise(lead && uq.x >= 0, uq.x, uq.y, ux.y, nie);
                         // a raised IE of a task about to be pushed goes into its key
                         uint64_t lm = ballot(lead && uq.x == -1);
-                        while (lm) {
-                            const int l = (int)__builtin_ctzll(lm);
-                            lm &= lm - 1;
-                            const int32_t uu = read_lane(u, l), kk = read_lane(mult, l);
-                            if (rdy && s == uu) f_ie += kk;
-                        }
+                        if (fm)
+                            while (lm) {
+                                const int l = (int)__builtin_ctzll(lm);
+                                lm &= lm - 1;
+                                const int32_t uu = read_lane(u, l), kk = read_lane(mult, l);
+                                if (rdy && s == uu) f_ie += kk;
+                            }
                     }
                 }
             }
