@@ -138,7 +138,7 @@ struct Workspace {
     DevBuf paux;                  // int32: per-worker block lists, then free-block stacks
     DevBuf barr;                  // int64 per block: latest input arrival (data model)
     DevBuf counter;               // int32 [4]: DAG dispenser
-    DevBuf tlong, tu;             // transitive attributes: longest path per DAG (+ a counter), chosen U
+    DevBuf tlong, tu;             // transitive attributes: longest path per DAG (+ largest tau, lists), chosen U
     std::vector<int32_t> h_order, h_sorder;
     std::vector<int32_t> h_large;      // desc indices of the DAGs of the grid-wide attribute pass
     std::vector<DagDesc> h_desc;
@@ -203,11 +203,8 @@ struct insp_dag {
     insp::DevBuf rank;                 // int64 [N]: upward rank of the last HEFT call
     // transitive attributes: positions in level order (built on first use),
     // per-call tau by position and ladder counts, attributes for the simulation
-    insp::DevBuf prow;                 // int2 [N]: row of the task at each position
-    insp::DevBuf plev;                 // int32 [N]: level of each position
-    insp::DevBuf pcol;                 // int32 [M]: position of each edge's target
+    insp::DevBuf rrec, rmore;          // uint4 [N]: successors' positions of the task at each position; further ones
     insp::DevBuf ptau;                 // int32 [N]: tau by position
-    insp::DevBuf pedge;                // int2 [M]: each edge's target position and its tau
     insp::DevBuf tcum;                 // int32 [N * kTRungs]: members within 2^j
     insp::DevBuf tia, tie;             // int32 [N]: transitive IA, IE of the last schedule call
     // data model: output KiB per task (insp_set_task_data), predecessor lists

@@ -1026,6 +1026,54 @@ def test_transitive_batch_match_oracle(insp):
         assert U[k] == rU and lp[k] == rcp, k
 
 
+def _window_dag(n, tick, chain, hubs):
+    """Tasks of 0 to 13 successors within the next 400, with `chain` one after
+    another, with `hubs` some of 100 and one of up to 4,000."""
+    rng = np.random.default_rng([n, tick, chain, hubs])
+    rows = []
+    for v in range(n):
+        k = (v * 5) % 14 if v % 11 == 0 else v % 7
+        span = 400
+        if hubs and v % 500 == 17:
+            k = 100
+        if hubs and v == 40:
+            k, span = 4000, n
+        t = np.unique(rng.integers(v + 1, min(n, v + 1 + span), k)) if v + 1 < n and k else np.zeros(0, np.int64)
+        if chain and v + 1 < n:
+            t = np.union1d(t, [v + 1])
+        rows.append(t)
+    rp = np.concatenate([[0], np.cumsum([len(t) for t in rows])]).astype(np.int32)
+    col = np.concatenate(rows).astype(np.int32) if rp[-1] else np.zeros(1, np.int32)
+    est = np.full((n, 2), tick, np.int32) if chain else rng.integers(1, tick + 1, (n, 2)).astype(np.int32)
+    return rp, col[: rp[-1]], est
+
+
+# the windows' lines (2,500, 8,600 and 19,900 positions), records of more than
+# eight successors and rows the whole wave takes, 16-bit paths up to 65,000 and
+# the first DAG past them, paths of millions
+@pytest.mark.parametrize("sizes, tick, chain, hubs", [
+    ([1, 2, 3, 4, 5, 63, 64, 65, 600, 2500, 2501, 2504], 12, 0, 0), ([2600], 25, 1, 0), ([2600], 26, 1, 0),
+    ([8600, 8603, 40], 20, 0, 1), ([19903], 20, 0, 1), ([300, 8700, 7], 1 << 18, 0, 1)])
+def test_transitive_windows_match_oracle(insp, sizes, tick, chain, hubs):
+    import torch
+    parts = [_window_dag(n, tick, chain, hubs) for n in sizes]
+    toff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    eoff = np.concatenate([[0], np.cumsum([len(c) for _, c, _ in parts])]).astype(np.int64)
+    rp, col = np.concatenate([r for r, _, _ in parts]), np.concatenate([c for _, c, _ in parts] + [np.zeros(1, np.int32)])
+    say("transitive windows", sizes, tick)
+    dag = insp.build_dag(toff, eoff, torch.from_numpy(rp).cuda(), torch.from_numpy(col.astype(np.int32)).cuda())
+    est = torch.from_numpy(np.concatenate([e for _, _, e in parts])).cuda()
+    for U in (0, 5 * tick) if max(sizes) < 10000 else (0,):
+        ia, ie, used, lp = insp.transitive_attributes(dag, insp.ALL_DAGS, est, [(3, 1)] * len(sizes), unit_time=U)
+        ia, ie = ia.cpu().numpy(), ie.cpu().numpy()
+        for k, (r, c, e) in enumerate(parts):
+            a, z = int(toff[k]), int(toff[k + 1])
+            ria, rie, rU, rcp = oracle.transitive(sizes[k], r, c, e, 1, unit_time=U)
+            assert np.array_equal(ia[a:z], ria) and np.array_equal(ie[a:z], rie), (sizes[k], U)
+            assert used[k] == rU and lp[k] == rcp, (sizes[k], U)
+    dag.free()
+
+
 @pytest.mark.parametrize("policy", ["inspirit", "ability", "efi", "fifo", "heft"])
 def test_transitive_schedule_match_oracle(insp, policy):
     for i in range(16):
