@@ -1087,6 +1087,38 @@ def test_transitive_schedule_match_oracle(insp, policy):
         check_schedule(w, g["worker"], g["start"], g["finish"], g["makespan"])
 
 
+# placement of the canonical rows: work-groups by the DAG's tasks (lines at
+# 1,024 and 20,000), repeated edges, long rows, edges to lower ids, no tasks
+@pytest.mark.parametrize("sizes", [[0, 1, 2, 1023, 0, 1024, 1025, 3], [19999, 20000, 700], [20001, 0, 1500]])
+def test_build_sizes_match_oracle(insp, sizes):
+    say("build sizes", sizes)
+    ws, canon = [], []
+    for k, n in enumerate(sizes):
+        rp, col, est = _window_dag(n, 30, 0, 1 if n > 500 else 0)
+        w = NS(n=n, row_ptr=rp, col=col, dur=est, est=est, n_cpu=3, n_gpu=1, m=int(col.size),
+               type=np.zeros(n, np.int32), name="build")
+        if k % 2 and n > 2:
+            w = _permuted(w, k)
+        crp, ccol = np.asarray(w.row_ptr, np.int64), np.asarray(w.col, np.int32)
+        # the first two entries of each row a second time, at its end
+        rows = [np.concatenate([ccol[a:z], ccol[a:min(z, a + 2)]]) for a, z in zip(crp[:-1], crp[1:])]
+        dup = NS(**vars(w))
+        dup.row_ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+        dup.col = np.concatenate(rows + [np.zeros(0, np.int32)]).astype(np.int32)
+        dup.m = int(dup.col.size)
+        ws.append(dup)
+        canon.append(w)
+    dag, dur, est = insp.batch_to_device(synth.concat(ws))
+    assert list(dag.m) == [w.m for w in canon]
+    for policy in ("inspirit", "heft"):
+        o = insp.schedule_batch(dag, [(3, 1)] * len(ws), dur, est, insp.params(policy=policy))
+        insp.sync_status(dag)
+        r = oracle.schedule_batch(synth.concat(canon), policy=policy, variant=oracle.HEAP)
+        for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+            assert np.array_equal(o[k].cpu().numpy(), r[k]), (policy, k)
+    dag.free()
+
+
 def test_transitive_schedule_batch(insp):
     ws = synth.cfg3(select=list(range(5, 4096, 400))) + [_hubs(6)]
     b = synth.concat(ws)
