@@ -173,6 +173,10 @@ void insp_free_dag(insp_dag *dag);
 /* Task and edge counts of DAG `dag` after canonicalisation (host outputs). */
 int insp_dag_info(const insp_dag *dag, int32_t index, int64_t *n_tasks, int64_t *n_edges, int32_t *n_dags);
 
+/* The same of all DAGs at once: prefix sums of their tasks and of their
+ * canonical edges, n_dags + 1 entries each (NULL to skip one). */
+int insp_dag_offsets(const insp_dag *dag, int64_t *task_off, int64_t *edge_off);
+
 /*
  * insp_attributes -- inspiring ability and efficiency of every task
  * (Section 4.2 definitions, Section 4.3 computation).

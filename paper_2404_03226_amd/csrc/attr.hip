@@ -975,7 +975,7 @@ static AttrArgs make_args(insp_dag *dag, Workspace *ws, const int32_t *est, int3
     a.part = ws->apart;
     a.pkg = ws->apkg;
     a.summ = ws->asumm;
-    a.srow = reinterpret_cast<uint32_t *>(ws->fbuf);
+    a.srow = ws->srow;
     a.first = ws->first;
     a.rp = dag->rp.as<int32_t>();
     a.col = dag->col.as<int32_t>();
@@ -1085,17 +1085,6 @@ int run_attributes(insp_dag *dag, Workspace *ws, const int32_t *est, int32_t uni
     return INSP_OK;
 }
 
-int alloc_status(insp_dag *dag) {
-    int rc;
-    if ((rc = dag->dag_stat.alloc(8 * dag->B)) || (rc = dag->dag_astat.alloc(8 * dag->B)) ||
-        (rc = dag->dag_sticky.alloc(4 * dag->B)))
-        return rc;
-    INSP_HIP(hipMemset(dag->dag_stat.p, 0, 8 * dag->B));
-    INSP_HIP(hipMemset(dag->dag_astat.p, 0, 8 * dag->B));
-    INSP_HIP(hipMemset(dag->dag_sticky.p, 0, 4 * dag->B));
-    return INSP_OK;
-}
-
 int32_t large_rows(const insp_dag *dag) {
     int32_t m = 0;
     for (int32_t b = 0; b < dag->B; b++) {
@@ -1107,18 +1096,52 @@ int32_t large_rows(const insp_dag *dag) {
 
 int ensure_state(insp_dag *dag, hipStream_t st) {
     (void)st;
-    if (dag->tr.p) return INSP_OK;
-    const int64_t N = std::max<int64_t>(dag->N, 1);
+    if (dag->state_arena.p) return INSP_OK;
+    const int64_t N = std::max<int64_t>(dag->N, 1), B = dag->B, rows = large_rows(dag);
+    Carve c;
+    c.add(&dag->srow, 4 * N);
+    c.add(&dag->dag_taubar, 4 * B);
+    c.add(&dag->dag_maxtau, 4 * B);
+    c.add(&dag->dag_tausum, 8 * B);
+    c.add(&dag->dag_score, 4 * kRungs * B);
+    c.add(&dag->dag_done, 4 * B);
+    c.add(&dag->apart, 4 * 32 * kBigGrid);
+    c.add(&dag->apkg, 4 * rows);
+    c.add(&dag->asumm, 8 * rows);
+    return c.alloc(&dag->state_arena);
+}
+
+// Allocations that a capturing stream would otherwise refuse: none of them is
+// part of the graph.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+int ensure_sim(insp_dag *dag, Workspace *ws) {
     int rc;
-    if ((rc = dag->tr.alloc(sizeof(TaskRec) * N)) || (rc = dag->dep.alloc(8 * N)) || (rc = dag->fbuf.alloc(12 * N)) ||
-        (rc = dag->dag_u.alloc(4 * dag->B)) ||
-        (rc = dag->dag_taubar.alloc(4 * dag->B)) || (rc = dag->dag_maxtau.alloc(4 * dag->B)) ||
-        (rc = dag->dag_tausum.alloc(8 * dag->B)) || (rc = dag->dag_score.alloc(4 * kRungs * dag->B)) ||
-        (rc = dag->dag_done.alloc(4 * dag->B)) || (rc = dag->apart.alloc(4 * 32 * kBigGrid)) ||
-        (rc = dag->apkg.alloc(4 * (size_t)large_rows(dag))) || (rc = dag->asumm.alloc(8 * (size_t)large_rows(dag)))) {
-        dag->tr.release();
-        return rc;
+    if (!dag->sim_arena.p) {
+        const int64_t N = std::max<int64_t>(dag->N, 1);
+        RelaxedCapture relaxed;
+        Carve c;
+        c.add(&dag->tr, sizeof(TaskRec) * N);
+        c.add(&dag->dep, 8 * N);
+        c.add(&dag->fbuf, 12 * N);
+        if ((rc = c.alloc(&dag->sim_arena))) return rc;
     }
+    if (!ws->sim_arena.p) {
+        RelaxedCapture relaxed;
+        Carve c;
+        c.add(&ws->slots, sizeof(Slot) * 64 * (size_t)ws->boff);
+        c.add(&ws->sums, 16 * (size_t)ws->boff);
+        c.add(&ws->paux, 4 * (size_t)(ws->total_wl + ws->boff));
+        c.add(&ws->barr, 8 * (size_t)ws->boff);
+        if ((rc = c.alloc(&ws->sim_arena))) return rc;
+    }
+    ws->tr = dag->tr.as<TaskRec>();
+    ws->dep = dag->dep.as<unsigned long long>();
+    ws->fbuf = dag->fbuf.as<int32_t>();
     return INSP_OK;
 }
 
@@ -1182,9 +1205,9 @@ int64_t workspace_shape(const insp_dag *dag, int32_t first, int32_t count, const
 
 int get_workspace(insp_dag *dag, int32_t first, int32_t count, const insp_workers *workers, bool per_dag,
                   Workspace **out) {
-    std::string key = std::to_string(first) + ":" + std::to_string(count);
-    for (int32_t i = 0; i < (per_dag ? count : 1); i++)
-        key += ":" + std::to_string(workers[i].n_cpu) + "," + std::to_string(workers[i].n_gpu);
+    const int32_t shape[2] = {first, count};
+    std::string key(reinterpret_cast<const char *>(shape), sizeof shape);
+    key.append(reinterpret_cast<const char *>(workers), sizeof(insp_workers) * (size_t)(per_dag ? count : 1));
     auto it = dag->ws.find(key);
     Workspace *w = nullptr;
     if (it != dag->ws.end()) {
@@ -1192,28 +1215,24 @@ int get_workspace(insp_dag *dag, int32_t first, int32_t count, const insp_worker
     } else {
         std::unique_ptr<Workspace> nw(new Workspace());
         std::vector<DagDesc> desc;
-        const int64_t boff = workspace_shape(dag, first, count, workers, per_dag, nw.get(), &desc);
-        int rc;
-        if ((rc = nw->desc.alloc(sizeof(DagDesc) * count)) ||
-            (rc = nw->order.alloc(sizeof(int32_t) * count)) || (rc = nw->sorder.alloc(sizeof(int32_t) * count)) ||
-            (rc = nw->slots.alloc(sizeof(Slot) * 64 * (size_t)boff)) ||
-            (rc = nw->sums.alloc(16 * (size_t)boff)) || (rc = nw->paux.alloc(4 * (size_t)(nw->total_wl + boff))) ||
-            (rc = nw->barr.alloc(8 * (size_t)boff)) ||
-            (rc = nw->counter.alloc(16)))
-            return rc;
-        INSP_HIP(hipMemcpy(nw->desc.p, desc.data(), sizeof(DagDesc) * count, hipMemcpyHostToDevice));
-        INSP_HIP(hipMemcpy(nw->order.p, nw->h_order.data(), sizeof(int32_t) * count, hipMemcpyHostToDevice));
-        if (nw->n_small > 0)
-            INSP_HIP(hipMemcpy(nw->sorder.p, nw->h_sorder.data(), sizeof(int32_t) * nw->n_small,
-                               hipMemcpyHostToDevice));
+        nw->boff = workspace_shape(dag, first, count, workers, per_dag, nw.get(), &desc);
+        Carve c;
+        const size_t o_desc = c.add(&nw->desc, sizeof(DagDesc) * count), o_order = c.add(&nw->order, sizeof(int32_t) * count);
+        const size_t o_sorder = c.add(&nw->sorder, sizeof(int32_t) * count);
+        c.add(&nw->u, sizeof(int32_t) * (count + 4));
+        if (int rc = c.alloc(&nw->arena)) return rc;
+        std::vector<char> host(o_sorder + sizeof(int32_t) * count);
+        memcpy(host.data() + o_desc, desc.data(), sizeof(DagDesc) * count);
+        memcpy(host.data() + o_order, nw->h_order.data(), sizeof(int32_t) * count);
+        memcpy(host.data() + o_sorder, nw->h_sorder.data(), sizeof(int32_t) * nw->n_small);
+        nw->counter.borrow(nw->u.as<int32_t>() + count, 16);
+        INSP_HIP(hipMemcpy(nw->arena.p, host.data(), host.size(), hipMemcpyHostToDevice));
         w = nw.get();
         dag->ws[key] = std::move(nw);
     }
     // the handle's per-call state (ensure_state has run)
-    w->tr = dag->tr.as<TaskRec>();
-    w->dep = dag->dep.as<unsigned long long>();
-    w->fbuf = dag->fbuf.as<int32_t>();
-    w->dag_u = dag->dag_u.as<int32_t>();
+    w->srow = dag->srow.as<uint32_t>();
+    w->dag_u = w->u.as<int32_t>() - first;
     w->dag_taubar = dag->dag_taubar.as<int32_t>();
     w->dag_maxtau = dag->dag_maxtau.as<int32_t>();
     w->dag_score = dag->dag_score.as<int32_t>();
@@ -1260,13 +1279,17 @@ extern "C" int insp_attributes(const insp_dag *cdag, int32_t index, const int32_
     Workspace *ws;
     if ((rc = get_workspace(dag, first, count, workers, true, &ws))) return rc;
     if ((rc = run_attributes(dag, ws, est, unit_time, rem, ia, ie, false, st))) return rc;
-    std::vector<int32_t> stat(2 * dag->B), uu(count);
-    INSP_HIP(hipMemcpyAsync(uu.data(), ws->dag_u + first, sizeof(int32_t) * count,
-                            hipMemcpyDeviceToHost, st));
-    INSP_HIP(hipMemcpyAsync(stat.data(), dag->dag_astat.p, sizeof(int32_t) * 2 * dag->B, hipMemcpyDeviceToHost, st));
+    // every U, and behind them the counter words, the failure flag last
+    std::vector<int32_t> uu(count + 4);
+    INSP_HIP(hipMemcpyAsync(uu.data(), ws->u.p, sizeof(int32_t) * uu.size(), hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
-    for (int32_t i = first; i < first + count; i++)
-        if (stat[2 * i] & ST_EST) return set_error(INSP_E_RANGE, "estimate outside [1, 2^20] in DAG %d", i);
+    if (uu.back()) {
+        std::vector<int32_t> stat(2 * dag->B);
+        INSP_HIP(hipMemcpyAsync(stat.data(), dag->dag_astat.p, sizeof(int32_t) * 2 * dag->B, hipMemcpyDeviceToHost, st));
+        INSP_HIP(hipStreamSynchronize(st));
+        for (int32_t i = first; i < first + count; i++)
+            if (stat[2 * i] & ST_EST) return set_error(INSP_E_RANGE, "estimate outside [1, 2^20] in DAG %d", i);
+    }
     for (int32_t i = 0; i < count; i++) unit_time_used[i] = uu[i];
     return INSP_OK;
 }

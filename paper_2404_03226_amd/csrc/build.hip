@@ -625,6 +625,13 @@ extern "C" int insp_dag_info(const insp_dag *dag, int32_t index, int64_t *n_task
     return INSP_OK;
 }
 
+extern "C" int insp_dag_offsets(const insp_dag *dag, int64_t *task_off, int64_t *edge_off) {
+    if (!dag) return set_error(INSP_E_INVAL, "null handle");
+    if (task_off) std::copy(dag->toff.begin(), dag->toff.end(), task_off);
+    if (edge_off) std::copy(dag->eoff.begin(), dag->eoff.end(), edge_off);
+    return INSP_OK;
+}
+
 extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int64_t *edge_off,
                               const int32_t *row_ptr, const int32_t *col, const int32_t *type, void *stream_,
                               insp_dag **out) {
@@ -653,19 +660,43 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     d->N = N;
     d->toff.assign(task_off, task_off + n_dags + 1);
     int rc;
-    const int nbw = 1 + (n_dags + 31) / 32;  // words of `backward`; the longest rows and the DAGs by size follow
-    DevBuf eoff_in, tmp, outdeg, excl, err, nwide, wide, backward, eoff_c;
-    if ((rc = d->d_toff.alloc(sizeof(int64_t) * (n_dags + 1))) || (rc = eoff_in.alloc(sizeof(int64_t) * (n_dags + 1))) ||
-        (rc = tmp.alloc(sizeof(int32_t) * M)) || (rc = outdeg.alloc(sizeof(int32_t) * N)) ||
-        (rc = excl.alloc(sizeof(int64_t) * (N + 1))) || (rc = err.alloc(sizeof(int32_t))) ||
-        (rc = nwide.alloc(sizeof(int32_t))) || (rc = wide.alloc(sizeof(int64_t) * N)) ||
-        (rc = backward.alloc(sizeof(int32_t) * (nbw + 2 * n_dags))) || (rc = eoff_c.alloc(sizeof(int64_t) * (n_dags + 1))))
-        return rc;
-    INSP_HIP(hipMemcpyAsync(d->d_toff.p, task_off, sizeof(int64_t) * (n_dags + 1), hipMemcpyHostToDevice, st));
-    INSP_HIP(hipMemcpyAsync(eoff_in.p, edge_off, sizeof(int64_t) * (n_dags + 1), hipMemcpyHostToDevice, st));
-    INSP_HIP(hipMemsetAsync(err.p, 0, sizeof(int32_t), st));
-    INSP_HIP(hipMemsetAsync(nwide.p, 0, sizeof(int32_t), st));
-    INSP_HIP(hipMemsetAsync(backward.p, 0, sizeof(int32_t) * (nbw + n_dags), st));
+    const int nbw = 1 + (n_dags + 31) / 32;  // words of `backward`
+    const size_t offs = sizeof(int64_t) * (n_dags + 1);
+    DevBuf scratch, eoff_in, bysize, tmp, outdeg, excl, flags, wide, tiles;
+    Carve c;
+    // the offsets and the DAGs by size, which one copy fills, and the status words
+    c.add(&d->d_toff, offs);
+    const size_t o_eoff = c.add(&eoff_in, offs), o_bysize = c.add(&bysize, sizeof(int32_t) * n_dags);
+    c.add(&d->d_eoff, offs);
+    const size_t o_stat = c.add(&d->dag_stat, 8 * n_dags);
+    c.add(&d->dag_astat, 8 * n_dags);
+    c.add(&d->dag_sticky, 4 * n_dags);
+    if ((rc = c.alloc(&d->base_arena))) return rc;
+    Carve r;
+    r.add(&d->rp, sizeof(int32_t) * (N + n_dags));
+    r.add(&d->word0, sizeof(uint64_t) * N);
+    if ((rc = r.alloc(&d->row_arena))) return rc;
+    Carve t;
+    t.add(&tmp, sizeof(int32_t) * M);
+    t.add(&outdeg, sizeof(int32_t) * N);
+    t.add(&excl, sizeof(int64_t) * (N + 1));
+    t.add(&wide, sizeof(int64_t) * N);
+    t.add(&tiles, sizeof(int64_t) * scan_scratch(N));
+    // cleared: error, long rows, `backward`; longest rows
+    t.add(&flags, sizeof(int32_t) * (2 + nbw + n_dags));
+    if ((rc = t.alloc(&scratch))) return rc;
+    int32_t *err = flags.as<int32_t>(), *nwide = err + 1, *backward = err + 2;
+    // DAGs by size, largest first
+    auto tasks = [&](int32_t b) { return task_off[b + 1] - task_off[b]; };
+    std::vector<char> host(o_bysize + sizeof(int32_t) * n_dags);
+    int32_t *order = reinterpret_cast<int32_t *>(host.data() + o_bysize);
+    std::iota(order, order + n_dags, 0);
+    std::sort(order, order + n_dags, [&](int32_t x, int32_t y) { return tasks(x) > tasks(y); });
+    memcpy(host.data(), task_off, offs);
+    memcpy(host.data() + o_eoff, edge_off, offs);
+    INSP_HIP(hipMemcpyAsync(d->base_arena.p, host.data(), host.size(), hipMemcpyHostToDevice, st));
+    INSP_HIP(hipMemsetAsync(d->dag_stat.p, 0, c.total - o_stat, st));
+    INSP_HIP(hipMemsetAsync(flags.p, 0, flags.bytes, st));
 
     // Sort and deduplicate every row where it lies; validate the CSR.
     RowArgs ra;
@@ -676,17 +707,18 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     ra.col = col;
     ra.tmp = tmp.as<int32_t>();
     ra.outdeg = outdeg.as<int32_t>();
-    ra.err = err.as<int32_t>();
-    ra.nwide = nwide.as<int32_t>();
+    ra.err = err;
+    ra.nwide = nwide;
     ra.wide = wide.as<int64_t>();
     ra.bits = nullptr;
     ra.bit_words = 0;
     if (N > 0) hipLaunchKernelGGL(k_rows, dim3(grid_for(N, 256)), dim3(256), 0, st, ra);
     INSP_HIP(hipGetLastError());
-    int32_t h_err = 0, h_wide = 0;
-    INSP_HIP(hipMemcpyAsync(&h_err, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    INSP_HIP(hipMemcpyAsync(&h_wide, nwide.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    int32_t h_flags[2] = {0, 0};
+    INSP_HIP(hipMemcpyAsync(h_flags, err, sizeof h_flags, hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
+    int32_t h_err = h_flags[0];
+    const int32_t h_wide = h_flags[1];
     if (!(h_err & ERR_ROWPTR) && h_wide > 0) {
         // the listed rows: a wave each up to kWaveRow entries, a work-group
         // each up to kBlockRow, bitmaps above (each kernel skips the others' rows)
@@ -698,7 +730,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
         ra.bits = bits.as<uint32_t>();
         hipLaunchKernelGGL(k_rows_huge, dim3((unsigned)std::min(h_wide, kHugeSlots)), dim3(256), 0, st, ra, h_wide);
         INSP_HIP(hipGetLastError());
-        INSP_HIP(hipMemcpyAsync(&h_err, err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        INSP_HIP(hipMemcpyAsync(&h_err, err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
         INSP_HIP(hipStreamSynchronize(st));  // before the bitmaps are released
     }
     if (h_err & ERR_ROWPTR) return set_error(INSP_E_INVAL, "row_ptr is not a valid CSR row pointer");
@@ -707,20 +739,17 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
 
     // Place the canonical rows: an exclusive scan of their lengths gives the
     // global row starts; DAG b's local row pointers subtract its first edge.
-    if ((rc = exclusive_scan(outdeg.as<int32_t>(), N, excl.as<int64_t>(), st))) return rc;
+    if ((rc = exclusive_scan(outdeg.as<int32_t>(), N, excl.as<int64_t>(), tiles.as<int64_t>(), st))) return rc;
     hipLaunchKernelGGL(k_dag_edges, dim3(grid_for(n_dags + 1, 256)), dim3(256), 0, st, n_dags,
-                       d->d_toff.as<int64_t>(), excl.as<int64_t>(), eoff_c.as<int64_t>());
+                       d->d_toff.as<int64_t>(), excl.as<int64_t>(), d->d_eoff.as<int64_t>());
     INSP_HIP(hipGetLastError());
     d->eoff.resize(n_dags + 1);
-    INSP_HIP(hipMemcpyAsync(d->eoff.data(), eoff_c.p, sizeof(int64_t) * (n_dags + 1), hipMemcpyDeviceToHost, st));
+    INSP_HIP(hipMemcpyAsync(d->eoff.data(), d->d_eoff.p, offs, hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
     const int64_t Mc = d->eoff[n_dags];
     d->M = Mc;
     // (the simulation reads 8 successors at a time from a row's start: room past the last row)
-    if ((rc = d->col.alloc(sizeof(int32_t) * (Mc + 16))) || (rc = d->rp.alloc(sizeof(int32_t) * (N + n_dags))) ||
-        (rc = d->word0.alloc(sizeof(uint64_t) * N)) || (rc = d->d_eoff.alloc(sizeof(int64_t) * (n_dags + 1))))
-        return rc;
-    INSP_HIP(hipMemcpyAsync(d->d_eoff.p, eoff_c.p, sizeof(int64_t) * (n_dags + 1), hipMemcpyDeviceToDevice, st));
+    if ((rc = d->col.alloc(sizeof(int32_t) * (Mc + 16)))) return rc;
     if (max_n > kPlaceMax) INSP_HIP(hipMemsetAsync(d->word0.p, 0, sizeof(uint64_t) * N, st));
     PlaceArgs pa;
     pa.B = n_dags;
@@ -733,28 +762,22 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     pa.col_out = d->col.as<int32_t>();
     pa.rp_out = d->rp.as<int32_t>();
     pa.word0 = d->word0.as<unsigned long long>();
-    pa.backward = backward.as<int32_t>();
-    pa.maxdeg = backward.as<int32_t>() + nbw;
-    // DAGs by size, largest first: those above kPlaceMax, the large, the small
-    std::vector<int32_t> bysize(n_dags);
-    std::iota(bysize.begin(), bysize.end(), 0);
-    auto tasks = [&](int32_t b) { return task_off[b + 1] - task_off[b]; };
-    std::sort(bysize.begin(), bysize.end(), [&](int32_t x, int32_t y) { return tasks(x) > tasks(y); });
+    pa.backward = backward;
+    pa.maxdeg = backward + nbw;
+    // those above kPlaceMax, the large, the small
     auto above = [&](int32_t n) {
-        return (int32_t)(std::partition_point(bysize.begin(), bysize.end(), [&](int32_t b) { return tasks(b) > n; }) -
-                         bysize.begin());
+        return (int32_t)(std::partition_point(order, order + n_dags, [&](int32_t b) { return tasks(b) > n; }) - order);
     };
     const int32_t n_huge = above(kPlaceMax), n_large = above(kPlaceSmall) - n_huge, n_small = n_dags - n_huge - n_large;
-    int32_t *dags = backward.as<int32_t>() + nbw + n_dags;
-    INSP_HIP(hipMemcpyAsync(dags, bysize.data(), sizeof(int32_t) * n_dags, hipMemcpyHostToDevice, st));
+    const int32_t *dags = bysize.as<int32_t>();
     if (n_large > 0) {
-        const size_t lds = sizeof(uint64_t) * (size_t)tasks(bysize[n_huge]);
+        const size_t lds = sizeof(uint64_t) * (size_t)tasks(order[n_huge]);
         if ((rc = set_lds_limit((const void *)&k_place_dag<1024>, lds))) return rc;
         hipLaunchKernelGGL(k_place_dag<1024>, dim3((unsigned)n_large), dim3(1024), lds, st, pa, dags + n_huge);
     }
     if (n_small > 0)
         hipLaunchKernelGGL(k_place_dag<128>, dim3((unsigned)n_small), dim3(128),
-                           sizeof(uint64_t) * (size_t)tasks(bysize[n_huge + n_large]), st, pa, dags + n_huge + n_large);
+                           sizeof(uint64_t) * (size_t)tasks(order[n_huge + n_large]), st, pa, dags + n_huge + n_large);
     if (max_n > kPlaceMax) hipLaunchKernelGGL(k_place, dim3(grid_for(N, 256)), dim3(256), 0, st, pa);
     if (max_n > kPlaceMax && h_wide > 0)
         hipLaunchKernelGGL(k_place_wide, dim3((unsigned)h_wide), dim3(64), 0, st, pa, (const int64_t *)wide.as<int64_t>());
@@ -763,7 +786,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     // Cycle check: with every edge pointing to a higher id the id order is a
     // topological order; otherwise run Kahn's traversal on the DAGs concerned.
     std::vector<int32_t> h_back(nbw + n_dags);
-    INSP_HIP(hipMemcpyAsync(h_back.data(), backward.p, sizeof(int32_t) * (nbw + n_dags), hipMemcpyDeviceToHost, st));
+    INSP_HIP(hipMemcpyAsync(h_back.data(), backward, sizeof(int32_t) * (nbw + n_dags), hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
     d->maxdeg.assign(h_back.begin() + nbw, h_back.end());
     if (h_back[0]) {
@@ -789,7 +812,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
                 return set_error(INSP_E_CYCLE, "DAG %d has a dependency cycle", b);
         }
     }
-    if ((rc = alloc_status(d.get())) || (rc = build_hubs(d.get(), st))) return rc;
+    if ((rc = build_hubs(d.get(), st))) return rc;
     if (type && N > 0) {
         if ((rc = d->type.alloc(sizeof(int32_t) * N))) return rc;
         INSP_HIP(hipMemcpyAsync(d->type.p, type, sizeof(int32_t) * N, hipMemcpyDeviceToDevice, st));

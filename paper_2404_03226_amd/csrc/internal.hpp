@@ -54,6 +54,29 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+// One allocation cut into the arrays that live and die together (a hipMalloc
+// and hipFree of tens of megabytes take 50 and 250 us each, whatever is in
+// them): add() every array, then alloc(), which points each DevBuf at its part.
+struct Carve {
+    std::vector<std::pair<DevBuf *, size_t>> parts;
+    size_t total = 0;
+    size_t add(DevBuf *b, size_t nbytes) {
+        const size_t at = total;
+        parts.emplace_back(b, nbytes ? nbytes : 16);
+        total += (parts.back().second + 255) & ~(size_t)255;
+        return at;
+    }
+    int alloc(DevBuf *arena) {
+        if (int rc = arena->alloc(total)) return rc;
+        size_t at = 0;
+        for (auto &q : parts) {
+            q.first->borrow(arena->as<char>() + at, q.second);
+            at += (q.second + 255) & ~(size_t)255;
+        }
+        return INSP_OK;
+    }
+};
+
 // Per-task simulation record (32 bytes, 32-byte aligned).  Bytes 16..31 are
 // one aligned vector (IE, IA, tau, first edge) read together; bytes 8..15
 // (queue slot, push order) likewise.  The dependency word lives apart, in a
@@ -130,14 +153,16 @@ struct Workspace {
     int64_t tasks = 0;
     int32_t n_small = 0;          // non-empty DAGs of the per-DAG attribute pass
     int32_t max_small = 0;        // tasks of the largest of them
+    DevBuf arena, sim_arena;      // memory of the arrays below: up to counter; the queue pools
     DevBuf desc;                  // DagDesc [count]
     DevBuf order;                 // int32 [count]: desc indices, largest first
     DevBuf sorder;                // int32 [n_small]: desc indices of the per-DAG pass, largest first
+    DevBuf u;                     // int32 [count]: chosen U, followed by
+    DevBuf counter;               // int32 [4]: DAG dispenser; [3] some estimate of an attribute call is out of range
     DevBuf slots;                 // Slot [64 per block]: queue entries
     DevBuf sums;                  // uint64 x2 per block: max key under each rule
     DevBuf paux;                  // int32: per-worker block lists, then free-block stacks
     DevBuf barr;                  // int64 per block: latest input arrival (data model)
-    DevBuf counter;               // int32 [4]: DAG dispenser
     DevBuf tlong, tu;             // transitive attributes: longest path per DAG (+ largest tau, lists), chosen U
     std::vector<int32_t> h_order, h_sorder;
     std::vector<int32_t> h_large;      // desc indices of the DAGs of the grid-wide attribute pass
@@ -148,7 +173,9 @@ struct Workspace {
     TaskRec *tr = nullptr;             // [N]
     unsigned long long *dep = nullptr; // [N]: dependency words (remaining in-degree << 43 | sum of unfinished predecessors)
     int32_t *fbuf = nullptr;           // [3 N]
-    int32_t *dag_u = nullptr, *dag_taubar = nullptr, *dag_maxtau = nullptr;  // [B]
+    uint32_t *srow = nullptr;          // [N]: decision words of the attribute pass
+    int64_t boff = 0;                  // blocks of the queue pools
+    int32_t *dag_u = nullptr, *dag_taubar = nullptr, *dag_maxtau = nullptr;  // [B] (dag_u: the range's DAGs only)
     int32_t *dag_score = nullptr;      // [B * kRungs]
     unsigned long long *dag_tausum = nullptr;  // [B]
     int32_t *dag_done = nullptr;       // [B]: finished blocks of the grid-wide attribute pass
@@ -167,17 +194,19 @@ struct insp_dag {
     std::vector<int64_t> toff, eoff;   // canonical prefix sums (host)
     std::vector<int32_t> order;        // DAG ids by n + m descending
     std::vector<int32_t> maxdeg;       // largest out-degree of each DAG
+    insp::DevBuf base_arena, row_arena, state_arena, sim_arena;  // memory of the arrays below
     insp::DevBuf d_toff, d_eoff;       // int64 [B+1]
     insp::DevBuf rp;                   // int32 [N + B] local canonical row pointers
     insp::DevBuf col;                  // int32 [M] canonical successor lists
     insp::DevBuf type;                 // int32 [N] (may be empty)
     insp::DevBuf word0;                // uint64 [N] in-degree << 43 | sum of predecessor ids
-    // per-task simulation state, shared by every shape (allocated on first use)
+    // per-task simulation state, shared by every shape (allocated by the first schedule)
     insp::DevBuf tr;                   // TaskRec [N]
     insp::DevBuf dep;                  // uint64 [N]: dependency words of the simulation
     insp::DevBuf fbuf;                 // int32 [3 N]: frontier runs, merged frontier, candidates
-    // per-DAG attribute and status records
-    insp::DevBuf dag_u, dag_taubar;    // int32 [B]
+    // attribute pass (allocated on first use)
+    insp::DevBuf srow;                 // uint32 [N]: decision words
+    insp::DevBuf dag_taubar;           // int32 [B]
     insp::DevBuf dag_maxtau;           // int32 [B]
     insp::DevBuf dag_tausum;           // int64 [B]
     insp::DevBuf dag_score;            // int32 [B * 24] ladder score, difference form
@@ -236,11 +265,12 @@ int build_hubs(insp_dag *dag, hipStream_t st);
 
 int ensure_state(insp_dag *dag, hipStream_t st);
 
+// What a schedule needs besides: the handle's simulation state and the
+// workspace's queue pools (also allocated when the caller is capturing).
+int ensure_sim(insp_dag *dag, Workspace *ws);
+
 // Tasks of the handle's largest DAG of the grid-wide attribute pass (0: none).
 int32_t large_rows(const insp_dag *dag);
-
-// The handle's status words, zeroed (called once, by insp_build_dag).
-int alloc_status(insp_dag *dag);
 
 // Raise a kernel's dynamic LDS limit to at least `bytes` on the current
 // device, once: later launches of the same size make no attribute call (so a
@@ -283,6 +313,9 @@ int run_rank(insp_dag *dag, Workspace *ws, const int32_t *est, hipStream_t st);
 // enqueued on `st` (the call may synchronise `st` before it returns).
 int exclusive_scan(const int32_t *in, int64_t n, int64_t *out, hipStream_t st);
 int exclusive_scan(const int64_t *in, int64_t n, int64_t *out, hipStream_t st);
+// ... with scan_scratch(n) words of scratch from the caller (never synchronises).
+int64_t scan_scratch(int64_t n);
+int exclusive_scan(const int32_t *in, int64_t n, int64_t *out, int64_t *scratch, hipStream_t st);
 
 // Predecessor lists of every DAG of the handle (built once).
 int ensure_preds(insp_dag *dag, hipStream_t st);

@@ -1046,8 +1046,8 @@ extern "C" int insp_mlp_predict(insp_mlp *m, const float *x, int64_t n, float *y
     hipStream_t st = (hipStream_t)stream;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) cus = n;
     }
     const int64_t tiles = (n + kRT - 1) / kRT;
     const unsigned grid = (unsigned)std::min<int64_t>(tiles, (int64_t)cus * 2);

@@ -92,6 +92,7 @@ int prepare(insp_dag *dag, const insp_workers *workers, DeviceScratch *ds, hipSt
     w.tr = reinterpret_cast<TaskRec *>(p + o_tr);
     w.dep = reinterpret_cast<unsigned long long *>(p + o_dep);
     w.fbuf = reinterpret_cast<int32_t *>(p + o_fbuf);
+    w.srow = reinterpret_cast<uint32_t *>(p + o_fbuf);  // (free until the simulation starts)
     w.dag_u = reinterpret_cast<int32_t *>(p + o_u);
     w.dag_taubar = reinterpret_cast<int32_t *>(p + o_taubar);
     w.dag_maxtau = reinterpret_cast<int32_t *>(p + o_maxtau);

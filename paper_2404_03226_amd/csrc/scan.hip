@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(const T *in, int64_t
 }
 
 template <typename T>
-static int scan_rec(const T *in, int64_t n, int64_t *out, int last, hipStream_t st) {
+static int scan_rec(const T *in, int64_t n, int64_t *out, int last, int64_t *scratch, hipStream_t st) {
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
     if (tiles <= 1) {
         hipLaunchKernelGGL(k_tile_scan<T>, dim3(1), dim3(kScanThreads), 0, st, in, n, (const int64_t *)nullptr, out,
@@ -105,16 +105,31 @@ static int scan_rec(const T *in, int64_t n, int64_t *out, int last, hipStream_t 
         INSP_HIP(hipGetLastError());
         return INSP_OK;
     }
-    DevBuf sums, offs;
-    int rc;
-    if ((rc = sums.alloc(sizeof(int64_t) * tiles)) || (rc = offs.alloc(sizeof(int64_t) * (tiles + 1)))) return rc;
-    hipLaunchKernelGGL(k_tile_sums<T>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st, in, n, sums.as<int64_t>());
+    int64_t *sums = scratch, *offs = sums + tiles;
+    hipLaunchKernelGGL(k_tile_sums<T>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st, in, n, sums);
     INSP_HIP(hipGetLastError());
-    if ((rc = scan_rec<int64_t>(sums.as<int64_t>(), tiles, offs.as<int64_t>(), 0, st))) return rc;
+    if (int rc = scan_rec<int64_t>(sums, tiles, offs, 0, offs + tiles + 1, st)) return rc;
     hipLaunchKernelGGL(k_tile_scan<T>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st, in, n,
-                       (const int64_t *)offs.as<int64_t>(), out, last);
+                       (const int64_t *)offs, out, last);
     INSP_HIP(hipGetLastError());
-    // the temporaries are released on return: wait for the kernels using them
+    return INSP_OK;
+}
+
+// Tile sums and their offsets, of every level of the recursion.
+int64_t scan_scratch(int64_t n) {
+    int64_t words = 0;
+    for (int64_t t = (n + kScanTile - 1) / kScanTile; t > 1; t = (t + kScanTile - 1) / kScanTile) words += 2 * t + 1;
+    return words;
+}
+
+template <typename T>
+static int scan_owning(const T *in, int64_t n, int64_t *out, hipStream_t st) {
+    DevBuf scratch;
+    const int64_t words = scan_scratch(n);
+    if (words == 0) return scan_rec<T>(in, n, out, 1, nullptr, st);
+    if (int rc = scratch.alloc(sizeof(int64_t) * words)) return rc;
+    if (int rc = scan_rec<T>(in, n, out, 1, scratch.as<int64_t>(), st)) return rc;
+    // the scratch is released on return: wait for the kernels using it
     INSP_HIP(hipStreamSynchronize(st));
     return INSP_OK;
 }
@@ -124,7 +139,15 @@ int exclusive_scan(const int32_t *in, int64_t n, int64_t *out, hipStream_t st) {
         INSP_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), st));
         return INSP_OK;
     }
-    return scan_rec<int32_t>(in, n, out, 1, st);
+    return scan_owning<int32_t>(in, n, out, st);
+}
+
+int exclusive_scan(const int32_t *in, int64_t n, int64_t *out, int64_t *scratch, hipStream_t st) {
+    if (n <= 0) {
+        INSP_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), st));
+        return INSP_OK;
+    }
+    return scan_rec<int32_t>(in, n, out, 1, scratch, st);
 }
 
 int exclusive_scan(const int64_t *in, int64_t n, int64_t *out, hipStream_t st) {
@@ -132,7 +155,7 @@ int exclusive_scan(const int64_t *in, int64_t n, int64_t *out, hipStream_t st) {
         INSP_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), st));
         return INSP_OK;
     }
-    return scan_rec<int64_t>(in, n, out, 1, st);
+    return scan_owning<int64_t>(in, n, out, st);
 }
 
 }  // namespace insp

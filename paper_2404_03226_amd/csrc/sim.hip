@@ -2934,8 +2934,8 @@ static int check_workers(const insp_workers *w, int32_t count) {
 static int default_grid(int count) {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) cus = n;
     }
     return std::max(1, std::min(count, cus * 3));
 }
@@ -2957,7 +2957,7 @@ extern "C" int insp_schedule(const insp_dag *cdag, int32_t index, const insp_wor
     INSP_HIP(hipSetDevice(dag->device));
     if ((rc = ensure_state(dag, st))) return rc;
     Workspace *ws;
-    if ((rc = get_workspace(dag, index, 1, workers, true, &ws))) return rc;
+    if ((rc = get_workspace(dag, index, 1, workers, true, &ws)) || (rc = ensure_sim(dag, ws))) return rc;
     if ((rc = run_attributes(dag, ws, est, params->unit_time, nullptr, nullptr, nullptr, true, st))) return rc;
     if (params->policy == INSP_POLICY_HEFT && (rc = run_rank(dag, ws, est, st))) return rc;
     if (params->attr_mode == INSP_ATTR_TRANSITIVE && (rc = run_sim_transitive(dag, ws, est, params->unit_time, st)))
@@ -3026,7 +3026,7 @@ static int schedule_batch(const insp_dag *cdag, const insp_workers *workers, con
     hipStream_t st = (hipStream_t)stream;
     if ((rc = ensure_state(dag, st))) return rc;
     Workspace *ws;
-    if ((rc = get_workspace(dag, 0, dag->B, workers, true, &ws))) return rc;
+    if ((rc = get_workspace(dag, 0, dag->B, workers, true, &ws)) || (rc = ensure_sim(dag, ws))) return rc;
     if ((rc = run_attributes(dag, ws, est, params->unit_time, nullptr, nullptr, nullptr, true, st))) return rc;
     if (params->policy == INSP_POLICY_HEFT && (rc = run_rank(dag, ws, est, st))) return rc;
     if (params->attr_mode == INSP_ATTR_TRANSITIVE && (rc = run_sim_transitive(dag, ws, est, params->unit_time, st)))

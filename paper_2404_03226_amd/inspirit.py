@@ -8,7 +8,9 @@ supplies device memory and the stream.  The functions mirror the C ABI in
 """
 from __future__ import annotations
 
+import array
 import ctypes as C
+import itertools
 import os
 
 import numpy as np
@@ -25,7 +27,7 @@ ATTR_MODE = {"direct": 0, "transitive": 1}
 MAX_TRANSITIVE_TASKS = 1 << 15
 ALL_DAGS = -1
 
-EXPORTS = ("insp_build_dag", "insp_set_task_data", "insp_free_dag", "insp_dag_info", "insp_attributes",
+EXPORTS = ("insp_build_dag", "insp_set_task_data", "insp_free_dag", "insp_dag_info", "insp_dag_offsets", "insp_attributes",
            "insp_transitive_attributes",
            "insp_schedule",
            "insp_schedule_batch", "insp_schedule_batch_trace", "insp_schedule_batch_noalloc", "insp_batch_graph_create",
@@ -78,6 +80,7 @@ def load(path: str = LIB_PATH):
     lib.insp_free_dag.argtypes = [P]
     lib.insp_free_dag.restype = None
     lib.insp_dag_info.argtypes = [P, i32, C.POINTER(i64), C.POINTER(i64), C.POINTER(i32)]
+    lib.insp_dag_offsets.argtypes = [P, P, P]
     lib.insp_attributes.argtypes = [P, i32, P, P, i32, P, P, P, P, P]
     lib.insp_transitive_attributes.argtypes = [P, i32, P, P, i32, P, P, P, P, P]
     lib.insp_schedule.argtypes = [P, i32, P, P, P, C.POINTER(Params), P, P, P, P, P, P, P, P, P]
@@ -168,15 +171,10 @@ class Dag:
     def __init__(self, handle, n_dags):
         self._h = handle
         self.n_dags = n_dags
-        tn, te = C.c_int64(), C.c_int64()
-        nd = C.c_int32()
-        self.n = []
-        self.m = []
-        for b in range(n_dags):
-            _check(load().insp_dag_info(self._h, b, C.byref(tn), C.byref(te), C.byref(nd)))
-            self.n.append(tn.value)
-            self.m.append(te.value)
-        self.task_off = np.concatenate([[0], np.cumsum(self.n)]).astype(np.int64)
+        self.task_off, edge_off = np.zeros(n_dags + 1, np.int64), np.zeros(n_dags + 1, np.int64)
+        _check(load().insp_dag_offsets(self._h, _ptr(self.task_off), _ptr(edge_off)))
+        self.n = np.diff(self.task_off).tolist()
+        self.m = np.diff(edge_off).tolist()
 
     @property
     def handle(self):
@@ -205,9 +203,19 @@ def build_dag(task_off, edge_off, row_ptr, col, type=None, stream=None) -> Dag:
 
 
 def _workers(w, count):
-    arr = (Workers * count)()
     if isinstance(w, (tuple, list)) and len(w) == 2 and not isinstance(w[0], (tuple, list)) and count == 1:
         w = [w]
+    if count > 1 and type(w) is list and type(w[0]) in (tuple, list) and len(w) == count:
+        # one machine for all DAGs, or pairs of integers
+        try:
+            if w.count(w[0]) == count:
+                one = Workers(int(w[0][0]), int(w[0][1]))
+                return (Workers * count).from_buffer_copy(bytes(one) * count)
+            if set(map(len, w)) == {2}:
+                return (Workers * count).from_buffer_copy(array.array("i", itertools.chain.from_iterable(w)))
+        except (TypeError, ValueError, OverflowError):
+            pass
+    arr = (Workers * count)()
     for i in range(count):
         arr[i].n_cpu, arr[i].n_gpu = int(w[i][0]), int(w[i][1])
     return arr

@@ -5,6 +5,7 @@ import re
 import subprocess
 import tempfile
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -102,3 +103,15 @@ def test_missing_library_fails_loudly(tmp_path):
             inspirit.load(str(tmp_path / "absent.so"))
     finally:
         inspirit._lib = saved
+
+
+@pytest.mark.parametrize("w", [[(3, 1)] * 5, [(k, 2 * k) for k in range(5)], [[3, 1], (4, 0), [5, 2], (6, 1), (7, 7)],
+                               [(3, 1)] * 4 + [(4, 2, 9)], [(3.7, 1)] * 4 + [(4, 2.2)], ((3, 1),) * 5,
+                               np.arange(10).reshape(5, 2), [np.array([k, 1]) for k in range(5)],
+                               [(3, 1)] * 4 + [np.array([4, 2])], [(np.int64(5), True)] * 5, [(3, 1)] * 7,
+                               [(2 ** 31 + 5, 1)] + [(1, 1)] * 4])
+def test_workers_of_a_batch_as_one_by_one(w):
+    from paper_2404_03226_amd import inspirit
+    want = [(inspirit.Workers(int(w[i][0]), int(w[i][1]))) for i in range(5)]
+    got = inspirit._workers(w, 5)
+    assert [(g.n_cpu, g.n_gpu) for g in got] == [(x.n_cpu, x.n_gpu) for x in want]

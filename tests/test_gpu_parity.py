@@ -1119,6 +1119,34 @@ def test_build_sizes_match_oracle(insp, sizes):
     dag.free()
 
 
+@pytest.mark.parametrize("rem", [False, True])
+def test_schedule_captured_after_attributes_alone(insp, rem):
+    """A handle that has only computed attributes: its first schedule of the
+    same machines allocates what it simulates with, also under capture."""
+    import torch
+    say("capture after attributes", rem)
+    ws = synth.cfg3(select=list(range(7, 4096, 500)))
+    b = synth.concat(ws)
+    machines = [(w.n_cpu, w.n_gpu) for w in ws]
+    dag, dur, est = insp.batch_to_device(b)
+    insp.schedule_batch(insp.batch_to_device(b)[0], machines, dur, est)  # code loaded, limits raised
+    left = torch.ones(int(b.task_off[-1]), dtype=torch.int32, device="cuda") if rem else None
+    insp.attributes(dag, insp.ALL_DAGS, est, machines, rem=left)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        o = insp.schedule_batch(dag, machines, dur, est)
+    r = oracle.schedule_batch(b)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(o["start"].cpu().numpy(), r["start"])
+        assert np.array_equal(o["makespan"].cpu().numpy(), r["makespan"])
+        o["start"].zero_()
+    insp.sync_status(dag)
+    del g
+    dag.free()
+
+
 def test_transitive_schedule_batch(insp):
     ws = synth.cfg3(select=list(range(5, 4096, 400))) + [_hubs(6)]
     b = synth.concat(ws)
