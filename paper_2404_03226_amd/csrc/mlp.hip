@@ -582,14 +582,20 @@ __global__ void k_shadow(const float *p, uint16_t *w1t, uint16_t *w2, uint16_t *
 // integer estimates, for many rows.  A block of NW waves is persistent over
 // 64-row tiles; wave w owns hidden columns [w C, w C + C), C = 256 / NW, of
 // both layers and keeps their W1 and W2 MFMA B-fragments in registers for the
-// whole run.  Per tile: layer 1 (K = 32) from x straight into MFMA
-// fragments, bf16 hidden activations through LDS, layer 2 (K = 256) from LDS
+// whole run.  Per tile: layer 1 (K = 32) from the features' bf16 fragments in
+// LDS, bf16 hidden activations through LDS, layer 2 (K = 256) from LDS
 // fragments, then the two outputs as per-wave partial dot products summed in
 // a fixed order.  Both layers are computed transposed (weights as the A
 // operand), so that a lane's accumulator holds consecutive hidden units of
-// one row.  With NW = 8 the fragments take half the registers of
-// NW = 4, so two waves share each SIMD and one's MFMA overlaps the other's
-// conversions and LDS traffic.
+// one row.
+//
+// What bounds it is how well the three busy units overlap (per tile and CU:
+// MFMA 2,300 clocks on each SIMD, the VALU's conversions about as many, LDS
+// 3,200), which takes two work-groups out of step on a CU, so the kernel stays
+// within 128 registers: a thread reads and converts four features of a tile,
+// once, two tiles ahead (all waves reading all features took 32 registers and
+// eight times the loads), and biases and output weights wait in LDS.  On 2 M
+// rows: 280 us a call, and 373 with one work-group a CU (190 registers).
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 // ReLU of two packed bf16 values at once: a bf16 is negative exactly when its
@@ -599,22 +605,23 @@ __device__ __forceinline__ uint32_t relu_bf2(uint32_t q) {
     const s16x2 z = {0, 0};
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, q), z));
 }
-constexpr int kRT = 64, kH1Row = kHid + 8;
+constexpr int kRT = 64, kH1Row = kHid + 8, kXRow = kIn + 8;
 
 constexpr int kInferWaves = 8;
 
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows, const uint16_t *W1t, const float *b1,
-                                                    const uint16_t *W2t, const float *b2, const uint16_t *W3,
-                                                    const float *b3, float *Y, int32_t *est) {
+__global__ __launch_bounds__(64 * NW, 4) void k_infer(const float *x, int64_t rows, const uint16_t *W1t, const float *b1,
+                                                       const uint16_t *W2t, const float *b2, const uint16_t *W3,
+                                                       const float *b3, float *Y, int32_t *est) {
     constexpr int CT = kHid / NW / 16;  // 16-column MFMA tiles per wave
     __shared__ __attribute__((aligned(16))) uint16_t H1s[kRT * kH1Row];
+    __shared__ __attribute__((aligned(16))) uint16_t Xs[2][kRT * kXRow];
     __shared__ float yp[NW][kRT][2];
+    __shared__ __attribute__((aligned(16))) float sb1[kHid], sb2[kHid];
+    __shared__ uint32_t sw[2][kHid / 2];  // output weights of hidden units (i, i + 1), as packed bf16 pairs
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wn = wv * (kHid / NW), lc = lane & 15, lk = (lane >> 4) * 8;
     bf16x8 w1f[CT], w2f[8][CT];
-    float bias1[CT][4], bias2[CT][4];
-    bf16x2_t w30[CT][2], w31[CT][2];  // output weights of hidden units (i, i + 1), as packed bf16 pairs
 #pragma unroll
     for (int ct = 0; ct < CT; ct++) {
         const int nt = wv * CT + ct;  // the tile's place among the fragments
@@ -622,68 +629,66 @@ __global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows,
 #pragma unroll
         for (int ks = 0; ks < 8; ks++)
             w2f[ks][ct] = *reinterpret_cast<const bf16x8 *>(W2t + ((nt * 8 + ks) * 64 + lane) * 8);
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            // the hidden unit this lane's accumulator value i holds in either layer
-            const int h = wn + ct * 16 + (lane >> 4) * 4 + i;
-            bias1[ct][i] = b1[h];
-            bias2[ct][i] = b2[h];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {
-            const int h = wn + ct * 16 + (lane >> 4) * 4 + i;
-            w30[ct][i / 2] = __builtin_bit_cast(bf16x2_t, (uint32_t)W3[h * 2] | (uint32_t)W3[h * 2 + 2] << 16);
-            w31[ct][i / 2] = __builtin_bit_cast(bf16x2_t, (uint32_t)W3[h * 2 + 1] | (uint32_t)W3[h * 2 + 3] << 16);
-        }
+    }
+    for (int h = tid; h < kHid; h += 64 * NW) {
+        sb1[h] = b1[h];
+        sb2[h] = b2[h];
+        sw[h & 1][h >> 1] = (uint32_t)W3[(h & ~1) * 2 + (h & 1)] | (uint32_t)W3[(h & ~1) * 2 + 2 + (h & 1)] << 16;
     }
     const float b30 = b3[0], b31 = b3[1];
     const int64_t tiles = (rows + kRT - 1) / kRT;
-    // features of the next tile are read while the current one is in layer 2
-    float4 xa[4], xb[4];
-    auto load_x = [&](int64_t t0) {
-#pragma unroll
-        for (int rt = 0; rt < 4; rt++) {
-            const int64_t r = t0 * kRT + rt * 16 + lc;
-            if (r < rows) {
-                xa[rt] = *reinterpret_cast<const float4 *>(x + r * kIn + lk);
-                xb[rt] = *reinterpret_cast<const float4 *>(x + r * kIn + lk + 4);
-            } else {
-                xa[rt] = float4{0.f, 0.f, 0.f, 0.f};
-                xb[rt] = float4{0.f, 0.f, 0.f, 0.f};
-            }
-        }
+    const int hl = wn + (lane >> 4) * 4;  // first hidden unit of this lane's accumulators
+    // features: four of one row per thread, two tiles ahead
+    static_assert(kRT * kIn == 64 * NW * 4, "a tile's features take one load per thread");
+    const int xrow = tid >> 3, xcol = (tid & 7) * 4;
+    float4 xr;
+    auto load_x = [&](int64_t t) {
+        const int64_t r = t * kRT + xrow;
+        xr = r < rows ? *reinterpret_cast<const float4 *>(x + r * kIn + xcol) : float4{0.f, 0.f, 0.f, 0.f};
     };
-    if ((int64_t)blockIdx.x < tiles) load_x(blockIdx.x);
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    auto put_x = [&](int b) {
+        *reinterpret_cast<uint2 *>(&Xs[b][xrow * kXRow + xcol]) = make_uint2(f2bf2(xr.x, xr.y), f2bf2(xr.z, xr.w));
+    };
+    load_x(blockIdx.x);
+    put_x(0);
+    load_x(blockIdx.x + (int64_t)gridDim.x);
+    __syncthreads();
+    for (int64_t tile = blockIdx.x, b = 0; tile < tiles; tile += gridDim.x, b ^= 1) {
         const int64_t r0 = tile * kRT;
-        // layer 1: A-fragment row lc of each 16-row tile, K = lk .. lk+7
-        bf16x8 af1[4];
+        put_x((int)b ^ 1);
+        load_x(tile + 2 * (int64_t)gridDim.x);
+        f32x4 bias[CT];
 #pragma unroll
-        for (int rt = 0; rt < 4; rt++) {
-            const uint4 t = {f2bf2(xa[rt].x, xa[rt].y), f2bf2(xa[rt].z, xa[rt].w), f2bf2(xb[rt].x, xb[rt].y),
-                             f2bf2(xb[rt].z, xb[rt].w)};
-            af1[rt] = __builtin_bit_cast(bf16x8, t);
-        }
-        if (tile + gridDim.x < tiles) load_x(tile + gridDim.x);
+        for (int ct = 0; ct < CT; ct++) bias[ct] = *reinterpret_cast<const f32x4 *>(&sb1[hl + ct * 16]);
         // computed transposed (W1^T as the A operand), so that a lane holds 4
         // consecutive hidden units of one row and stores them as one 8-byte write
 #pragma unroll
         for (int rt = 0; rt < 4; rt++) {
+            // A-fragment row lc of the 16-row tile, K = lk .. lk+7
+            const bf16x8 af1 = *reinterpret_cast<const bf16x8 *>(&Xs[b][(rt * 16 + lc) * kXRow + lk]);
 #pragma unroll
             for (int ct = 0; ct < CT; ct++) {
-                f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f[ct], af1[rt], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0,
-                                                                    0);
+                f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f[ct], af1, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 uint2 h;
-                h.x = relu_bf2(f2bf2(acc[0] + bias1[ct][0], acc[1] + bias1[ct][1]));
-                h.y = relu_bf2(f2bf2(acc[2] + bias1[ct][2], acc[3] + bias1[ct][3]));
-                *reinterpret_cast<uint2 *>(&H1s[(rt * 16 + lc) * kH1Row + wn + ct * 16 + (lane >> 4) * 4]) = h;
+                h.x = relu_bf2(f2bf2(acc[0] + bias[ct][0], acc[1] + bias[ct][1]));
+                h.y = relu_bf2(f2bf2(acc[2] + bias[ct][2], acc[3] + bias[ct][3]));
+                *reinterpret_cast<uint2 *>(&H1s[(rt * 16 + lc) * kH1Row + hl + ct * 16]) = h;
             }
         }
         __syncthreads();
         // layer 2, transposed as well: per 16-column tile a lane holds 4
         // consecutive hidden units of row rt * 16 + lc, so its output partials
         // cover 4 CT units and only the 4 lane groups of a row remain to be added
-        float p0[4], p1[4];
+        bf16x2_t w30[CT][2], w31[CT][2];
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) {
+            bias[ct] = *reinterpret_cast<const f32x4 *>(&sb2[hl + ct * 16]);
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                w30[ct][i] = __builtin_bit_cast(bf16x2_t, sw[0][(hl + ct * 16) / 2 + i]);
+                w31[ct][i] = __builtin_bit_cast(bf16x2_t, sw[1][(hl + ct * 16) / 2 + i]);
+            }
+        }
 #pragma unroll
         for (int rt = 0; rt < 4; rt++) {
             f32x4 acc[CT];
@@ -705,25 +710,16 @@ __global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows,
                     // their products with the output weights as one bf16 dot
                     // product per output
                     const bf16x2_t q = __builtin_bit_cast(
-                        bf16x2_t, relu_bf2(f2bf2(acc[ct][i] + bias2[ct][i], acc[ct][i + 1] + bias2[ct][i + 1])));
+                        bf16x2_t, relu_bf2(f2bf2(acc[ct][i] + bias[ct][i], acc[ct][i + 1] + bias[ct][i + 1])));
                     s0 = __builtin_amdgcn_fdot2_f32_bf16(q, w30[ct][i / 2], s0, false);
                     s1 = __builtin_amdgcn_fdot2_f32_bf16(q, w31[ct][i / 2], s1, false);
                 }
-            p0[rt] = s0;
-            p1[rt] = s1;
-        }
-        // lanes lc, lc + 16, lc + 32, lc + 48 hold the same row
-#pragma unroll
-        for (int rt = 0; rt < 4; rt++) {
-            float s0 = p0[rt], s1 = p1[rt];
+            // lanes lc, lc + 16, lc + 32, lc + 48 hold the same row
             s0 += __shfl_xor(s0, 16, 64);
             s1 += __shfl_xor(s1, 16, 64);
             s0 += __shfl_xor(s0, 32, 64);
             s1 += __shfl_xor(s1, 32, 64);
-            if (lane < 16) {
-                yp[wv][rt * 16 + lc][0] = s0;
-                yp[wv][rt * 16 + lc][1] = s1;
-            }
+            if (lane < 16) *reinterpret_cast<float2 *>(yp[wv][rt * 16 + lc]) = make_float2(s0, s1);
         }
         __syncthreads();
         if (tid < kRT * 2) {
@@ -738,7 +734,6 @@ __global__ __launch_bounds__(64 * NW) void k_infer(const float *x, int64_t rows,
                 if (est) est[2 * r + c] = (int32_t)fminf(fmaxf(rintf(expf(y)), 1.f), (float)(1 << 20));
             }
         }
-        __syncthreads();
     }
 }
 

@@ -167,6 +167,29 @@ def test_predict_small_and_empty(insp, n):
     m.free()
 
 
+@pytest.mark.parametrize("n", [32704, 32768, 32769, 65536, 65601, 98369])
+def test_predict_at_tiles_of_a_group(insp, n):
+    """One, two and three 64-row tiles per work-group (512 of them), with and
+    without a ragged last one: the features are read two tiles ahead into
+    alternating buffers.  Each row depends on itself alone, so its output is
+    the same bits wherever it lies."""
+    import torch
+    print(f"[case] mlp predict tiles n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    p = synth.mlp_init()
+    for i in (1, 3, 5):
+        p[i] = rng.normal(0.0, 0.1, p[i].shape).astype(np.float32)
+    X, _ = batch(4096)
+    X = X + np.float32(0.01) * rng.normal(size=X.shape).astype(np.float32)
+    m = insp.Mlp(p)
+    ref, ref_est = m.predict(torch.from_numpy(X).cuda())
+    check_y(ref.cpu().numpy(), p, X)
+    rows = torch.from_numpy(rng.integers(0, 4096, n)).cuda()
+    y, est = m.predict(torch.from_numpy(X).cuda()[rows].contiguous())
+    assert torch.equal(y, ref[rows]) and torch.equal(est, ref_est[rows])
+    m.free()
+
+
 def test_predict_full_batch_sampled(insp):
     """Prediction at the size the benchmark times (one row per task of the
     4096-DAG batch: 17,723,451 rows, so a ragged last tile) in the same
