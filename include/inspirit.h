@@ -270,11 +270,11 @@ int insp_schedule(const insp_dag *dag, int32_t index, const insp_workers *worker
  * keys live in LDS, at least lds_slots: a pop's scan reads only keys; the
  * default is 128 maxima, 24 full blocks and keys of 40, with three
  * work-groups per CU), "prio=<k>" (the k largest DAGs run at raised
- * wave priority), "scan=<k>" (<= 16: a pop reads every queue entry of a
- * worker with at most k queue blocks, and picks a block by its maximum
- * first above that) and "waves=1" (the only accepted value; any other is
- * INSP_E_INVAL).  Each work-group of the launch is one wave that simulates
- * and, for machines of at most 64 workers, one that reads ahead for it.
+ * wave priority), "scan=<k>" (<= 16, without effect: a worker's
+ * best entry is known before it is popped) and "waves=1" (the only accepted
+ * value; any other is INSP_E_INVAL).  Each work-group of the launch is one
+ * wave that simulates and, for machines of at most 128 workers, one that keeps
+ * the workers' best queue entries and one that reads ahead for it.
  * Results never depend on the key.  The first call with a new machine shape
  * allocates workspace; later calls reuse it.
  */

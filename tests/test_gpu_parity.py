@@ -1119,6 +1119,38 @@ def test_build_sizes_match_oracle(insp, sizes):
     dag.free()
 
 
+# the one-wave loop at its lines: 64 and 128 workers (one and two a lane; the
+# general loop above), keys of 32 and of 64 bits, keys fixed while queued; the
+# empty slots of popped entries taken again in blocks in LDS and far from it
+@pytest.mark.parametrize("kind", ["narrow", "wide"])
+@pytest.mark.parametrize("machine", [(4, 1), (60, 4), (60, 5), (120, 8), (121, 8)])
+def test_one_wave_loop_at_its_lines(insp, machine, kind):
+    ws = []
+    for k, (n, hubs) in enumerate([(700, 0), (1300, 0)] + [(5000, 1)] * (kind == "wide")):
+        rp, col, est = _window_dag(n, 60, 0, hubs)
+        dur = np.random.default_rng(k).integers(1, 70, (n, 2)).astype(np.int32)
+        w = NS(n=n, row_ptr=rp, col=col, dur=dur, est=est, n_cpu=machine[0], n_gpu=machine[1], m=int(col.size),
+               type=np.zeros(n, np.int32), name=kind)
+        ws.append(_permuted(w, 3) if k == 1 else w)
+    b = synth.concat(ws)
+    b.data_kib = np.random.default_rng(9).integers(0, 600, int(b.task_off[-1])).astype(np.int32)
+    import torch
+    dag, dur, est = insp.batch_to_device(b)
+    insp.set_task_data(dag, torch.from_numpy(b.data_kib).cuda())
+    for policy, kw in (("inspirit", {}), ("fifo", {}), ("efi", {}), ("locality", {}), ("heft", {}),
+                       ("inspirit", dict(attr_mode="transitive")), ("inspirit", dict(data_bw=40)),
+                       ("locality", dict(data_bw=40))):
+        r = oracle.schedule_batch(b, policy=policy, **kw)
+        for key in (None, "grid=2,lds_blocks=0,lds_slots=0,lds_keys=0", "grid=3,lds_blocks=3,lds_slots=1,lds_keys=2"):
+            say("lines", machine, kind, policy, kw, key)
+            o = insp.schedule_batch(dag, [machine] * len(ws), dur, est, insp.params(policy=policy, **kw), tune_key=key)
+            insp.sync_status(dag)
+            for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+                assert np.array_equal(o[k].cpu().numpy(), r[k]), (policy, kw, key, k)
+            assert np.array_equal(o["makespan"].cpu().numpy(), r["makespan"]), (policy, kw, key)
+    dag.free()
+
+
 @pytest.mark.parametrize("rem", [False, True])
 def test_schedule_captured_after_attributes_alone(insp, rem):
     """A handle that has only computed attributes: its first schedule of the
