@@ -2771,7 +2771,7 @@ static SimKernel pick_kernel(const insp_dag *dag, const Workspace *ws, const ins
 int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t *dur, const int32_t *est,
                int32_t *worker, int64_t *start, int64_t *finish, int64_t *makespan, int32_t *ie_at_pop,
                int8_t *mode_at_pop, insp_trace_rec *trace, int32_t *n_events, int waves, int grid,
-               int sum_cap, int slot_cap, int key_cap, hipStream_t st, int prio_top, int scan_max) {
+               int sum_cap, int slot_cap, int key_cap, hipStream_t st, int prio_top, int scan_max, int per_cu) {
     (void)waves;
     SimArgs A;
     memset(&A, 0, sizeof A);
@@ -2817,24 +2817,24 @@ int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t
     A.max_events = p.max_events;
     A.prio_top = prio_top;
     (void)scan_max;
-    // LDS: block maxima, block lists and the slots of the low blocks --
-    // generous for a single DAG (one work-group owns the CU), a few blocks
-    // per DAG for a batch (tunable)
+    // LDS: block maxima, block lists and the slots of the low blocks -- as
+    // many as fit where one or two work-groups have the CU to themselves, a
+    // few blocks per DAG for a larger batch (tunable)
     const SimKernel kern = pick_kernel(dag, ws, p);
-    const bool one = ws->count == 1;
-    const int64_t budget = (one ? 140 : 150) * 1024;
+    const bool one = ws->count == 1, fill = one || per_cu < 3;
+    const int64_t budget = (one || per_cu == 1 ? 140 : per_cu == 2 ? 78 : 150) * 1024;
     auto need = [&](int64_t sc, int64_t lb, int64_t slc, int64_t slk) {
         return (int64_t)kern.lds(ws->max_w, (int)sc, (int)lb, (int)slc, (int)slk);
     };
-    int64_t sc = std::min<int64_t>(ws->max_nblk, one ? 2048 : sum_cap);
-    int64_t lb = std::min<int64_t>(ws->max_nblk, one ? 64 : 16);
+    int64_t sc = std::min<int64_t>(ws->max_nblk, one ? 2048 : fill ? 512 : sum_cap);
+    int64_t lb = std::min<int64_t>(ws->max_nblk, one ? 64 : fill ? 32 : 16);
     // machines of hundreds of workers: shorter LDS block lists, then fewer
     // LDS block maxima, until the per-worker state fits (the rest lives in
     // global memory)
     while (lb > 1 && need(sc, lb, 0, 0) > budget) lb /= 2;
     while (sc > 0 && need(sc, lb, 0, 0) > budget) sc /= 2;
     int64_t slc = slot_cap;
-    if (one) slc = (budget - need(sc, lb, 0, 0)) / (64 * 20);
+    if (fill) slc = (budget - need(sc, lb, 0, 0)) / (64 * 20);
     slc = std::max<int64_t>(0, std::min<int64_t>(ws->max_nblk, slc));
     while (slc > 0 && need(sc, lb, slc, slc) > budget) slc--;
     // keys of further blocks in what LDS is left (a rescan reads only keys)
@@ -2899,16 +2899,31 @@ static int check_workers(const insp_workers *w, int32_t count) {
     return INSP_OK;
 }
 
-// Three work-groups per CU: what the default LDS shape (128 block maxima, 24
-// blocks of full entries, keys of 40) leaves room for on machines of up to 20
-// workers; larger grids only add work-groups that start when the DAGs are gone.
-static int default_grid(int count) {
+static int cu_count() {
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
         int n = 0;
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) cus = n;
     }
-    return std::max(1, std::min(count, cus * 3));
+    return cus;
+}
+
+// Work-groups per CU of a batch: three, which is what the default LDS shape
+// (128 block maxima, 24 blocks of full entries, keys of 40) leaves room for on
+// machines of up to 20 workers, and fewer, with more of each queue in LDS,
+// where each DAG has a work-group of its own or the batch still ends with its
+// largest DAG: a work-group's share of all tasks stays below three quarters of
+// that DAG's.
+// Measured, layered DAGs on 20 workers: 600 of 200-5,000 tasks with the data
+// model 16.3 ms with three, 15.2 with one; 256 of 20,000 tasks 42.5 with three,
+// 34.6 with one, 512 of them 51.1 and 47.1 (two); 4,096 of 200-20,000 tasks 66
+// with two, 52.7 with three.
+static int groups_per_cu(const insp_dag *dag, int cus) {
+    int64_t most = 0;
+    for (int32_t b = 0; b < dag->B; b++) most = std::max(most, dag->toff[b + 1] - dag->toff[b]);
+    int k = 1;
+    while (k < 3 && dag->B > cus * k && 4 * dag->N > 3 * most * cus * k) k++;
+    return k;
 }
 
 extern "C" int insp_schedule(const insp_dag *cdag, int32_t index, const insp_workers *workers, const int32_t *dur,
@@ -2937,7 +2952,7 @@ extern "C" int insp_schedule(const insp_dag *cdag, int32_t index, const insp_wor
     if (params->data_bw > 0 && !dag->dxc.p && (rc = dag->dxc.alloc(sizeof(int32_t) * std::max<int64_t>(dag->N, 1))))
         return rc;
     return launch_sim(dag, ws, *params, dur, est, worker, start, finish, makespan, ie_at_pop, mode_at_pop, trace,
-                      n_events, 1, 1, 4096, 0, 0, st, 0, kScan);
+                      n_events, 1, 1, 4096, 0, 0, st, 0, kScan, 1);
 }
 
 static void parse_tune(const char *key, int *waves, int *grid, int *sum_cap, int *slot_cap, int *key_cap, int *prio,
@@ -2967,7 +2982,12 @@ int batch_prologue(insp_dag *dag, const insp_workers *workers, const int32_t *du
     if (dag->N > 0 && (!dur || !est || !worker || !start || !finish)) return set_error(INSP_E_INVAL, "null array");
     if ((((uintptr_t)dur | (uintptr_t)est) & 7) != 0) return set_error(INSP_E_INVAL, "dur/est rows must be 8-byte aligned");
     INSP_HIP(hipSetDevice(dag->device));
-    int waves = 1, grid = default_grid(dag->B), sum_cap = 128, slot_cap = 24, key_cap = 40, prio = 0, scan = kScan;
+    const int cus = cu_count();
+    int waves = 1, grid = std::max(1, std::min(dag->B, 3 * cus)), sum_cap = 128, slot_cap = 24, key_cap = 40, prio = 0,
+        scan = kScan;
+    // a key that shapes the launch has its own way
+    launch->per_cu = tune_key && (strstr(tune_key, "grid=") || strstr(tune_key, "lds_")) ? 3 : groups_per_cu(dag, cus);
+    if (launch->per_cu < 3) grid = std::max(1, std::min(dag->B, launch->per_cu * cus));
     parse_tune(tune_key, &waves, &grid, &sum_cap, &slot_cap, &key_cap, &prio, &scan);
     if (grid < 1 || sum_cap < 0 || sum_cap > 8192 || slot_cap < 0 || key_cap < 0 || prio < 0 || scan < 0 ||
         scan > kScan || lds_bytes(1, sum_cap, 16, slot_cap, std::max(slot_cap, key_cap)) > 150 * 1024)
@@ -3006,7 +3026,7 @@ static int schedule_batch(const insp_dag *cdag, const insp_workers *workers, con
     if (params->data_bw > 0 && !dag->dxc.p && (rc = dag->dxc.alloc(sizeof(int32_t) * std::max<int64_t>(dag->N, 1))))
         return rc;
     return launch_sim(dag, ws, *params, dur, est, worker, start, finish, makespan, ie_at_pop, mode_at_pop, trace,
-                      n_events, 1, bl.grid, bl.sum_cap, bl.slot_cap, bl.key_cap, st, bl.prio, bl.scan);
+                      n_events, 1, bl.grid, bl.sum_cap, bl.slot_cap, bl.key_cap, st, bl.prio, bl.scan, bl.per_cu);
 }
 
 extern "C" int insp_schedule_batch(const insp_dag *cdag, const insp_workers *workers, const int32_t *dur,

@@ -1151,6 +1151,26 @@ def test_one_wave_loop_at_its_lines(insp, machine, kind):
     dag.free()
 
 
+@pytest.mark.parametrize("count", [255, 257, 512, 513, 800])
+def test_batch_shapes_by_count(insp, count):
+    """One, two and three work-groups per CU (256 of them), by the number of
+    DAGs when they are much alike, and by the largest when one stands out."""
+    parts = [_window_dag(20 + (k * 37) % 150, 40, 0, 0) for k in range(count)]
+    for big in (0, 6000):
+        sub = parts[: count - 1] + [_window_dag(big, 40, 0, 1)] if big else parts
+        ws = [NS(n=len(r) - 1, row_ptr=r, col=c, dur=e, est=e, n_cpu=5, n_gpu=2, m=int(c.size),
+                 type=np.zeros(len(r) - 1, np.int32), name="shape") for r, c, e in sub]
+        b = synth.concat(ws)
+        say("batch shapes", count, big)
+        dag, dur, est = insp.batch_to_device(b)
+        o = insp.schedule_batch(dag, [(5, 2)] * count, dur, est)
+        insp.sync_status(dag)
+        r = oracle.schedule_batch(b)
+        for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+            assert np.array_equal(o[k].cpu().numpy(), r[k]), (count, big, k)
+        dag.free()
+
+
 @pytest.mark.parametrize("rem", [False, True])
 def test_schedule_captured_after_attributes_alone(insp, rem):
     """A handle that has only computed attributes: its first schedule of the
