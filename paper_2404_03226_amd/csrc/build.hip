@@ -104,11 +104,12 @@ struct RowArgs {
     int32_t B;
     const int64_t *toff, *eoff;  // task offsets, input edge offsets
     const int32_t *rp, *col;     // the caller's CSR
-    int32_t *tmp;                // [M] sorted, deduplicated rows at their input offsets
+    int32_t *tmp;                // [M] sorted, deduplicated long rows at their input offsets
     int32_t *outdeg;             // [N] canonical row lengths
     int32_t *err;
     int32_t *nwide;              // rows longer than kSmallRow ...
-    int64_t *wide;               // ... listed here
+    int64_t *wide;               // ... listed here, up to max_wide (no valid CSR has more)
+    int64_t max_wide;
     uint32_t *bits;              // [kHugeSlots][bit_words] bitmaps for the longest rows
     int64_t bit_words;
 };
@@ -154,8 +155,29 @@ __device__ __forceinline__ void sort_registers(int32_t (&x)[P]) {
             }
 }
 
+// A row of up to kSmallRow targets: sorted in registers.
+__device__ __forceinline__ void load_sorted(const int32_t *src, int32_t deg, int32_t (&x)[kSmallRow]) {
+#pragma unroll
+    for (int i = 0; i < kSmallRow; i++) x[i] = i < deg ? src[i] : kPad;
+    sort_registers<kSmallRow>(x);
+}
+
+// ... and its distinct targets, in order, to put(place in the row, target).
+template <typename Put>
+__device__ __forceinline__ void each_distinct(const int32_t (&x)[kSmallRow], int32_t deg, Put put) {
+    int32_t cnt = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallRow; i++)
+        if (i < deg && (i == 0 || x[i] != x[i ? i - 1 : 0])) put(cnt++, x[i]);
+}
+
 // One thread per task: validate the row pointer and, for short rows, the
-// targets; sort and deduplicate short rows in registers; list the others.
+// targets, and count the distinct ones; list the other rows.  The placement
+// sorts short rows again, from the caller's array: sorting 16 registers costs
+// less than an array of all edges written here and read there (1,024 DAGs with
+// 21 M edges: both passes 289 us with it, 205 without), and such an array is
+// the larger half of what a build allocates, at the driver's 300 us a time and,
+// once its cleared memory is used up, 28 us for each megabyte.
 __global__ __launch_bounds__(256) void k_rows(RowArgs A) {
     const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (v >= A.toff[A.B]) return;
@@ -172,26 +194,17 @@ __global__ __launch_bounds__(256) void k_rows(RowArgs A) {
     }
     const int32_t deg = r.z - r.a;
     if (deg > kSmallRow) {
-        A.wide[atomicAdd(A.nwide, 1)] = v;
+        const int32_t at = atomicAdd(A.nwide, 1);
+        if (at < A.max_wide) A.wide[at] = v;
         return;
     }
     const int32_t *src = A.col + A.eoff[r.b] + r.a;
-    int32_t *dst = A.tmp + A.eoff[r.b] + r.a;
-    int32_t x[kSmallRow];
-#pragma unroll
-    for (int i = 0; i < kSmallRow; i++) {
-        x[i] = i < deg ? src[i] : kPad;
-        if (i < deg) bad |= check_target(x[i], r.n, r.lv);
-    }
-    sort_registers<kSmallRow>(x);
-    int32_t cnt = 0, prev = -1;
-#pragma unroll
-    for (int i = 0; i < kSmallRow; i++) {
-        if (i < deg && x[i] != prev) {
-            dst[cnt++] = x[i];
-            prev = x[i];
-        }
-    }
+    int32_t x[kSmallRow], cnt = 0;
+    load_sorted(src, deg, x);
+    each_distinct(x, deg, [&](int32_t, int32_t s) {
+        cnt++;
+        bad |= check_target(s, r.n, r.lv);
+    });
     A.outdeg[v] = cnt;
     if (bad) atomicOr(A.err, bad);
 }
@@ -322,8 +335,9 @@ __global__ __launch_bounds__(256) void k_rows_huge(RowArgs A, int32_t nlisted) {
 struct PlaceArgs {
     int32_t B;
     const int64_t *toff, *eoff;   // task offsets, input edge offsets
-    const int32_t *rp;            // the caller's row pointers
-    const int32_t *tmp, *outdeg;
+    const int32_t *rp, *col;      // the caller's CSR
+    const int32_t *tmp;           // long rows, sorted
+    const int32_t *outdeg;
     const int64_t *excl;          // [N + 1] exclusive scan of outdeg: global canonical row starts
     int32_t *col_out, *rp_out;
     unsigned long long *word0;
@@ -348,7 +362,7 @@ __device__ __forceinline__ void place_edge(const PlaceArgs &A, int32_t b, int32_
 // writes them once, in order; neither they nor the row pointers are cleared
 // first.  160 KB hold 20,000 tasks; DAGs of up to kPlaceSmall get a small
 // work-group, of which a CU holds many.  Measured on 1,024 layered DAGs of
-// 200-20,000 tasks (21 M edges): 174 us, against 893 with global atomics.
+// 200-20,000 tasks (21 M edges): 123 us, against 893 with global atomics.
 constexpr int32_t kPlaceSmall = 1024, kPlaceMax = 20000;
 
 template <int THREADS>
@@ -361,7 +375,7 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int64_t e0 = A.excl[t0];  // the DAG's first canonical edge
     const int32_t *p = A.rp + t0 + b;
-    const int32_t *tmp = A.tmp + A.eoff[b];
+    const int32_t *in = A.col + A.eoff[b];
     int32_t *rp = A.rp_out + t0 + b, *col = A.col_out + e0;
     for (int32_t v = tid; v < n; v += THREADS) word[v] = 0;
     if (tid == 0) {
@@ -375,23 +389,26 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
         const int32_t at = (int32_t)(A.excl[t0 + v] - e0), cnt = A.outdeg[t0 + v], a = p[v];
         rp[v] = at;
         longest = max(longest, cnt);
-        if (p[v + 1] - a > kSmallRow) {
+        const int32_t deg = p[v + 1] - a;
+        if (deg > kSmallRow) {
             wide = true;
             continue;
         }
-        for (int32_t i = 0; i < cnt; i++) {
-            const int32_t s = tmp[a + i];
+        int32_t x[kSmallRow];
+        load_sorted(in + a, deg, x);
+        each_distinct(x, deg, [&](int32_t i, int32_t s) {
             col[at + i] = s;
             atomicAdd(&word[s], (1ull << 43) + (unsigned long long)v);
             back |= s < v;
-        }
+        });
     }
     longest = (int32_t)wave_max_u32f((uint32_t)longest);
     if (lane == 0) atomicMax(&s_max, longest);
     if (wide) s_wide = 1;
     __syncthreads();
     // long rows: a wave each
-    if (s_wide)
+    if (s_wide) {
+        const int32_t *tmp = A.tmp + A.eoff[b];
         for (int32_t v0 = tid - lane; v0 < n; v0 += THREADS) {
             const int32_t u = v0 + lane;
             for (uint64_t rows = ballot(u < n && p[min(u + 1, n)] - p[min(u, n)] > kSmallRow); rows; rows &= rows - 1) {
@@ -405,6 +422,7 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
                 }
             }
         }
+    }
     if (back) s_back = 1;
     __syncthreads();
     for (int32_t v = tid; v < n; v += THREADS) A.word0[t0 + v] = word[v];
@@ -432,10 +450,12 @@ __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
     A.rp_out[A.toff[b] + b + lv] = (int32_t)(at - e0);
     if (lv == n - 1) A.rp_out[A.toff[b] + b + n] = (int32_t)(at + cnt - e0);
     const int32_t *p = A.rp + A.toff[b] + b;
-    if (p[lv + 1] - p[lv] > kSmallRow) return;  // a listed row: k_place_wide
-    const int32_t *src = A.tmp + A.eoff[b] + p[lv];
+    const int32_t deg = p[lv + 1] - p[lv];
+    if (deg > kSmallRow) return;  // a listed row: k_place_wide
+    int32_t x[kSmallRow];
+    load_sorted(A.col + A.eoff[b] + p[lv], deg, x);
     bool back = false;
-    for (int32_t i = 0; i < cnt; i++) place_edge(A, b, lv, src[i], at + i, back);
+    each_distinct(x, deg, [&](int32_t i, int32_t s) { place_edge(A, b, lv, s, at + i, back); });
     if (back) atomicOr(A.backward, 1), atomicOr(&A.backward[1 + (b >> 5)], 1 << (b & 31));
 }
 
@@ -677,10 +697,10 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     r.add(&d->word0, sizeof(uint64_t) * N);
     if ((rc = r.alloc(&d->row_arena))) return rc;
     Carve t;
-    t.add(&tmp, sizeof(int32_t) * M);
     t.add(&outdeg, sizeof(int32_t) * N);
     t.add(&excl, sizeof(int64_t) * (N + 1));
-    t.add(&wide, sizeof(int64_t) * N);
+    const int64_t max_wide = std::min(N, M / (kSmallRow + 1));
+    t.add(&wide, sizeof(int64_t) * max_wide);
     t.add(&tiles, sizeof(int64_t) * scan_scratch(N));
     // cleared: error, long rows, `backward`; longest rows
     t.add(&flags, sizeof(int32_t) * (2 + nbw + n_dags));
@@ -698,18 +718,19 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     INSP_HIP(hipMemsetAsync(d->dag_stat.p, 0, c.total - o_stat, st));
     INSP_HIP(hipMemsetAsync(flags.p, 0, flags.bytes, st));
 
-    // Sort and deduplicate every row where it lies; validate the CSR.
+    // Validate the CSR, count the distinct targets of every row, and sort the long rows.
     RowArgs ra;
     ra.B = n_dags;
     ra.toff = d->d_toff.as<int64_t>();
     ra.eoff = eoff_in.as<int64_t>();
     ra.rp = row_ptr;
     ra.col = col;
-    ra.tmp = tmp.as<int32_t>();
+    ra.tmp = nullptr;
     ra.outdeg = outdeg.as<int32_t>();
     ra.err = err;
     ra.nwide = nwide;
     ra.wide = wide.as<int64_t>();
+    ra.max_wide = max_wide;
     ra.bits = nullptr;
     ra.bit_words = 0;
     if (N > 0) hipLaunchKernelGGL(k_rows, dim3(grid_for(N, 256)), dim3(256), 0, st, ra);
@@ -720,6 +741,8 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     int32_t h_err = h_flags[0];
     const int32_t h_wide = h_flags[1];
     if (!(h_err & ERR_ROWPTR) && h_wide > 0) {
+        if ((rc = tmp.alloc(sizeof(int32_t) * M))) return rc;
+        ra.tmp = tmp.as<int32_t>();
         // the listed rows: a wave each up to kWaveRow entries, a work-group
         // each up to kBlockRow, bitmaps above (each kernel skips the others' rows)
         hipLaunchKernelGGL((k_rows_lds<64, kWaveRow, kSmallRow>), dim3((unsigned)h_wide), dim3(64), 0, st, ra);
@@ -756,6 +779,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     pa.toff = d->d_toff.as<int64_t>();
     pa.eoff = eoff_in.as<int64_t>();
     pa.rp = row_ptr;
+    pa.col = col;
     pa.tmp = tmp.as<int32_t>();
     pa.outdeg = outdeg.as<int32_t>();
     pa.excl = excl.as<int64_t>();

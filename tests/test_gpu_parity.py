@@ -1119,6 +1119,33 @@ def test_build_sizes_match_oracle(insp, sizes):
     dag.free()
 
 
+# short rows, which their placement sorts: targets given in falling order, no
+# edge twice and one (in the last DAG), either side of the placement's line
+@pytest.mark.parametrize("repeats", [0, 1])
+def test_build_falling_rows_match_oracle(insp, repeats):
+    say("build falling rows", repeats)
+    ws = []
+    for n in (700, 0, 20001, 1025):
+        rp, col, est = _window_dag(n, 30, 0, 1 if n > 500 else 0)
+        rows = [np.asarray(col[a:z], np.int32)[::-1] for a, z in zip(rp[:-1], rp[1:])]
+        if n == 1025 and repeats:
+            v = next(v for v, r in enumerate(rows) if r.size)
+            rows[v] = np.concatenate([rows[v], rows[v][:1]])
+        rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+        col = np.concatenate(rows + [np.zeros(0, np.int32)]).astype(np.int32)
+        ws.append(NS(n=n, row_ptr=rp, col=col, dur=est, est=est, n_cpu=3, n_gpu=1, m=int(col.size),
+                     type=np.zeros(n, np.int32), name="falling"))
+    dag, dur, est = insp.batch_to_device(synth.concat(ws))
+    canon = [oracle.canon(w.n, w.row_ptr, w.col) for w in ws]
+    assert list(dag.m) == [len(c) for _, c in canon] and sum(w.m for w in ws) - sum(dag.m) == repeats
+    o = insp.schedule_batch(dag, [(3, 1)] * len(ws), dur, est, insp.params(policy="inspirit"))
+    insp.sync_status(dag)
+    r = oracle.schedule_batch(synth.concat(ws), policy="inspirit", variant=oracle.HEAP)
+    for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+        assert np.array_equal(o[k].cpu().numpy(), r[k]), k
+    dag.free()
+
+
 # the one-wave loop at its lines: 64 and 128 workers (one and two a lane; the
 # general loop above), keys of 32 and of 64 bits, keys fixed while queued; the
 # empty slots of popped entries taken again in blocks in LDS and far from it
