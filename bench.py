@@ -474,8 +474,8 @@ def transitive_measure(dag, workers, ws, b, dur, est, steps, warmup, tune_key):
         exact &= bool(all(np.array_equal(res[f][a:z], r[f]) for f in ("worker", "start", "finish", "ie_at_pop",
                                                                         "mode_at_pop")))
         exact &= int(res["makespan"][k]) == r["makespan"]
-    # k_trans: per descendant pair one LDS read and one clear, and one LDS
-    # atomicMax per edge out of it; edges approximated by the mean out-degree
+    # the forward pass: per descendant pair one LDS read and one clear, and one
+    # maximum per edge out of it; edges approximated by the mean out-degree
     lds_ops = pairs * (2.0 + b.edge_off[-1] / max(N, 1))
     lds_peak = 256 * 32 * 2.4e9  # CUs x LDS banks x clock
     t = {"attr_ms_per_call": round(wall * 1e3, 3), "k_trans_avg_ms": round(k_ms, 3),

@@ -76,10 +76,10 @@ void DevBuf::release() {
 
 enum { ERR_ROWPTR = 1, ERR_COL = 2, ERR_SELF = 4 };
 
-// Canonical rows are built where the input rows lie: each row is sorted and
-// its repeats dropped into a scratch copy at the row's own input offset, its
-// canonical length counted; an exclusive scan of those lengths places the
-// canonical rows, and a last pass moves them there.  Rows are sorted by
+// Canonical rows are built in two passes: the first counts each row's distinct
+// targets, and an exclusive scan of those lengths gives the rows' places; the
+// second puts them there.  Short rows are sorted in both; a long one, by the
+// first, into a scratch array at its own input offset.  Rows are sorted by
 // whoever fits them: a thread in registers (up to kSmallRow entries), one
 // wave in LDS (kWaveRow), a 256-thread work-group in LDS (kBlockRow), and
 // above that a work-group marks the row's targets in a bitmap of the DAG's
