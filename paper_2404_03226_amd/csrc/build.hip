@@ -175,9 +175,10 @@ __device__ __forceinline__ void each_distinct(const int32_t (&x)[kSmallRow], int
 // targets, and count the distinct ones; list the other rows.  The placement
 // sorts short rows again, from the caller's array: sorting 16 registers costs
 // less than an array of all edges written here and read there (1,024 DAGs with
-// 21 M edges: both passes 289 us with it, 205 without), and such an array is
-// the larger half of what a build allocates, at the driver's 300 us a time and,
-// once its cleared memory is used up, 28 us for each megabyte.
+// 21 M edges: both passes 289 us with it, 205 without).  Such an array is also
+// the larger half of what a build allocates: hipMalloc and hipFree take 300 us
+// for a large one, and 28 us more for each megabyte once the process has been
+// through the card's cleared memory.
 __global__ __launch_bounds__(256) void k_rows(RowArgs A) {
     const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (v >= A.toff[A.B]) return;
