@@ -41,12 +41,11 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "keys.hpp"
 
 namespace insp {
 
-constexpr uint64_t M21 = (1ull << 21) - 1;
 constexpr uint64_t M43 = (1ull << 43) - 1;
-constexpr uint64_t BIT63 = 1ull << 63;
 
 #ifdef INSP_PHASE_CLOCKS
 // Diagnostic build only: per-DAG core-clock totals of each event phase.
@@ -55,14 +54,6 @@ __device__ unsigned long long g_phase_clk[8192 * 32];
 #else
 #define PCLK(i) do {} while (0)
 #endif
-
-// Sort key of a queue entry under rule `ord`: 0 ability, 1 efficiency,
-// 2 FIFO, 3 HEFT (whose entries hold rank << 21 | (2^21-1-seq) instead).
-__device__ __forceinline__ uint64_t key_of(uint64_t k, int ord) {
-    if (ord == 0 || ord == 3) return k | BIT63;
-    if (ord == 1) return ((k >> 21) & M21) << 42 | (k >> 42) << 21 | (k & M21) | BIT63;
-    return (k & M21) | BIT63;
-}
 
 // Makes the compiler wait for a global load inside the branch that issued it.
 // A value read from LDS on one side of a uniform branch and from global memory
@@ -1029,76 +1020,6 @@ __device__ void sim_dag(const SimArgs &A, int32_t di, const Lds &L) {
 // with the scan in the simulating wave (above 64 workers in the general loop),
 // pops one by one and frontier lists.
 
-// Bits of a key field that holds values up to `most`.
-__host__ __device__ constexpr uint32_t field_bits(uint32_t most) { return most == 0 ? 1 : 32 - __builtin_clz(most); }
-
-// Key layout of one DAG.
-struct KeyFmt {
-    uint32_t sa, sb;    // shifts of the second and first key fields (s, a + s)
-    uint32_t smask;     // 2^s - 1
-    uint32_t amask;     // 2^a - 1
-    bool fifo;          // kA holds the FIFO key
-    __device__ __forceinline__ uint32_t ka(uint32_t ia, uint32_t ie, uint32_t seq) const {
-        return 0x80000000u | (fifo ? 0u : ia << sb | ie << sa) | (smask - seq);
-    }
-    __device__ __forceinline__ uint32_t ke(uint32_t ia, uint32_t ie, uint32_t seq) const {
-        return 0x80000000u | ie << sb | ia << sa | (smask - seq);
-    }
-    // increments of kA and kE when IE grows by one
-    __device__ __forceinline__ uint32_t da() const { return fifo ? 0u : 1u << sa; }
-    __device__ __forceinline__ uint32_t de() const { return 1u << sb; }
-};
-
-// Queue keys of the one-wave loop.
-//   kNarrow  direct attributes, two 32-bit rule keys per entry (kA, kE), each
-//            raised in place when the task's IE grows; block and worker maxima
-//            hold key << 32 | slot.
-//   kFixed   HEFT ranks or transitive attributes, fixed while queued: one
-//            64-bit key per entry in the general loop's format, from which
-//            key_of derives the rule keys when an entry is read (zero stays
-//            zero: an empty slot).
-//   kWide    direct attributes in that format, raised in place.
-// With 64-bit keys the maxima hold rule keys alone: the second wave leaves
-// the slot of a worker's best beside it, and the simulating wave keeps the
-// best entry it pushed or raised since the worker's last pop, with its slot,
-// in the worker's lane.
-enum KeyKind { kNarrow = 0, kFixed = 1, kWide = 2 };
-
-template <int KK>
-struct Keys {
-    static constexpr bool kBig = KK != kNarrow;
-    using T = typename std::conditional<kBig, unsigned long long, uint32_t>::type;
-    T *ka, *ke;  // LDS keys [64 * key_cap]: kA and kE, or ka the 64-bit key
-    int o0;      // 64-bit keys: the rule of maximum 0 (0 ability, 2 FIFO, 3 rank)
-    __device__ __forceinline__ T rule(uint64_t raw, int r) const {
-        if constexpr (kBig) return raw ? key_of(raw, r ? 1 : o0) : 0ull;
-        else return (uint32_t)(raw >> (r ? 32 : 0));
-    }
-    // rule-r key of the entry in LDS slot p
-    __device__ __forceinline__ T lds(int32_t p, int r) const {
-        if constexpr (kBig) return rule(ka[p], r);
-        else return (r ? ke : ka)[p];
-    }
-    // the entry's key word (the two 32-bit keys, kE above kA, or the 64-bit key)
-    __device__ __forceinline__ uint64_t word(int32_t p) const {
-        if constexpr (kBig) return ka[p];
-        else return (uint64_t)ke[p] << 32 | ka[p];
-    }
-    __device__ __forceinline__ void put(int32_t p, uint64_t w) const {
-        if constexpr (kBig) {
-            ka[p] = w;
-        } else {
-            ka[p] = (uint32_t)w;
-            ke[p] = (uint32_t)(w >> 32);
-        }
-    }
-    // the key of a block or worker maximum
-    __device__ __forceinline__ static T of_max(unsigned long long m) {
-        if constexpr (kBig) return m;
-        else return (uint32_t)(m >> 32);
-    }
-};
-
 __device__ __forceinline__ uint32_t wave_max_k(uint32_t x) { return wave_max_u32f(x); }
 __device__ __forceinline__ unsigned long long wave_max_k(unsigned long long x) { return wave_max_u64f(x); }
 
@@ -1481,6 +1402,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         pp0[k] = pp1[k] = 0;
         best[2 * w] = 0;
         best[2 * w + 1] = 0;
+        if constexpr (kBig) bpos[2 * w] = bpos[2 * w + 1] = 0;
         req[w] = 0;
     }
 
@@ -1529,7 +1451,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
         uint64_t word;
         unsigned long long m0, m1;
         if constexpr (kBig) {
-            word = (uint64_t)ia << 42 | (uint64_t)nie << 21 | (M21 - sq);
+            word = K.big((uint64_t)ia << 21 | (uint64_t)nie, sq);
             m0 = K.rule(word, 0);
             m1 = K.rule(word, 1);
         } else {
@@ -1785,8 +1707,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                     if constexpr (kBig) {
                         // the best entry pushed since the worker's last pop
                         const uint64_t hi = (uint32_t)read_lane(f_ie, j), lo = (uint32_t)read_lane(f_ia, j);
-                        const uint64_t sq = M21 - (uint64_t)(seq + __popcll(fm & ((1ull << j) - 1)));
-                        const uint64_t raw = heft ? (hi << 32 | lo) << 21 | sq : lo << 42 | hi << 21 | sq;
+                        const uint64_t raw = K.big(heft ? hi << 32 | lo : lo << 21 | hi, seq + __popcll(fm & ((1ull << j) - 1)));
                         const unsigned long long a0 = K.rule(raw, 0), a1 = K.rule(raw, 1);
 #pragma unroll
                         for (int k = 0; k < WPL; k++)
@@ -1815,8 +1736,7 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 unsigned long long m0, m1;
                 if constexpr (kBig) {
                     // the general loop's key: rank << 21 or IA << 42 | IE << 21, then the push order
-                    word = heft ? ((uint64_t)(uint32_t)f_ie << 32 | (uint32_t)f_ia) << 21 | (M21 - (uint64_t)sqj)
-                                : (uint64_t)f_ia << 42 | (uint64_t)f_ie << 21 | (M21 - (uint64_t)sqj);
+                    word = K.big(heft ? (uint64_t)(uint32_t)f_ie << 32 | (uint32_t)f_ia : (uint64_t)f_ia << 21 | (uint64_t)f_ie, sqj);
                     m0 = K.rule(word, 0);
                     m1 = K.rule(word, 1);
                 } else {

@@ -810,6 +810,24 @@ def test_keys_wider_than_32_bits(insp):
     dag.free()
 
 
+# The largest task count with a row too long for 32-bit keys: the last task
+# pushed has push order 2^21 - 1 and no successors.
+@pytest.mark.parametrize("machine", [(60, 4), (100, 28)])
+def test_largest_task_count_with_wide_keys(insp, machine):
+    n, layer = 1 << 21, 1024
+    deg = np.ones(n, np.int64)
+    deg[-layer:] = 0
+    deg[0] = 40
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.arange(layer, layer + 40), np.arange(layer + 1, n)]).astype(np.int32)
+    ticks = np.full((n, 2), 7, np.int32)
+    w = NS(n=n, row_ptr=rp, col=col, dur=ticks, est=ticks, n_cpu=machine[0], n_gpu=machine[1], m=int(col.size),
+           type=np.zeros(n, np.int32), name="2^21")
+    for policy in ("inspirit", "fifo"):
+        say("2^21 tasks", machine, policy)
+        assert_same(run_gpu(insp, w, policy), oracle.schedule(w, policy, variant=oracle.HEAP), f"2^21 {machine} {policy}")
+
+
 def test_queue_spill_paths_batch_small_lds(insp):
     ws = [_wide(6000 + 1000 * i, 10 + i) for i in range(3)] + [_hubs(3)] + synth.cfg3(select=[4, 44])
     b = synth.concat(ws)
