@@ -65,8 +65,10 @@ int ensure_preds(insp_dag *dag, hipStream_t st) {
     int rc;
     if ((rc = indeg.alloc(sizeof(int64_t) * N)) || (rc = excl.alloc(sizeof(int64_t) * (N + 1))) ||
         (rc = fill.alloc(sizeof(int32_t) * N)) || (rc = dag->pprp.alloc(sizeof(int32_t) * (N + dag->B))) ||
-        (rc = ppred.alloc(sizeof(int32_t) * M)))
+        (rc = ppred.alloc(sizeof(int32_t) * (M + 16))))
         return rc;
+    // (the simulation's lanes without a predecessor read their DAG's first
+    // entry, which for a last DAG without edges is the one past the end)
     INSP_HIP(hipMemsetAsync(fill.p, 0, sizeof(int32_t) * N, st));
     INSP_HIP(hipMemsetAsync(dag->pprp.p, 0, sizeof(int32_t) * (N + dag->B), st));  // empty DAGs: {0}
     if (dag->N > 0) {

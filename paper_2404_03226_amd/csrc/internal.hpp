@@ -239,7 +239,7 @@ struct insp_dag {
     // data model: output KiB per task (insp_set_task_data), predecessor lists
     insp::DevBuf dkib;                 // int32 [N]
     insp::DevBuf pprp;                 // int32 [N + B]: local predecessor row pointers (as rp)
-    insp::DevBuf ppred;                // int32 [M]: predecessor ids (local)
+    insp::DevBuf ppred;                // int32 [M + 16]: predecessor ids (local)
     insp::DevBuf dxc;                  // int32 [N]: transfer ticks of each output (per run)
     std::map<std::string, std::unique_ptr<insp::Workspace>> ws;
 };

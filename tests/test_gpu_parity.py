@@ -1380,6 +1380,38 @@ def test_data_model_batch(insp):
     dag.free()
 
 
+@pytest.mark.parametrize("edges", [0, 1024, 4096, 5000])
+@pytest.mark.parametrize("machine", [(5, 2), (70, 3)])
+def test_data_model_batch_ending_without_edges(insp, edges, machine):
+    """The last DAGs have tasks and no edges, so their predecessor lists start
+    at the end of the handle's (a whole number of pages at 1,024 and 4,096)."""
+    import torch
+    rng = np.random.default_rng(edges + 1)
+    ws = []
+    for n, m in ((1300, edges), (1, 0), (200, 0)):
+        if n == 1300 and m == 0:
+            continue
+        key = np.sort(rng.choice(600 * 700, m, replace=False)) if m else np.zeros(0, np.int64)
+        rp = np.concatenate([[0], np.cumsum(np.bincount(key // 700, minlength=n))]).astype(np.int32)
+        t = rng.integers(1, 60, (n, 2)).astype(np.int32)
+        ws.append(NS(n=n, row_ptr=rp, col=(600 + key % 700).astype(np.int32), dur=t, est=t, n_cpu=machine[0],
+                     n_gpu=machine[1], m=m, type=np.zeros(n, np.int32), name="edgeless"))
+    b = synth.concat(ws)
+    b.data_kib = rng.integers(0, 64, int(b.task_off[-1])).astype(np.int32)
+    dag, dur, est = insp.batch_to_device(b)
+    assert sum(dag.m) == edges
+    insp.set_task_data(dag, torch.from_numpy(b.data_kib).cuda())
+    for policy in ("inspirit", "locality", "heft"):
+        say("data, no edges at the end", edges, machine, policy)
+        o = insp.schedule_batch(dag, [machine] * len(ws), dur, est, insp.params(policy=policy, data_bw=40))
+        insp.sync_status(dag)
+        r = oracle.schedule_batch(b, policy=policy, data_bw=40)
+        for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+            assert np.array_equal(o[k].cpu().numpy(), r[k]), (policy, k)
+        assert np.array_equal(o["makespan"].cpu().numpy(), r["makespan"]), policy
+    dag.free()
+
+
 def test_data_model_errors(insp):
     import torch
     say("data errors")
