@@ -1148,7 +1148,8 @@ __device__ void keep_best(const SimArgs &A, int32_t di) {
                 const int l = (int)__builtin_ctzll(m);
                 const int32_t w = l + k * kWave;
                 m &= m - 1;
-                const int32_t b = read_lane(rq, l) - 1, nbw = uniform(min(rnb[w], d.maxb));
+                const int32_t b = read_lane(rq, l) - 1, nbw = uniform(min(lds_load(&rnb[w]), d.maxb));
+                keep_order();
                 if (b < 0 || b >= d.nblk) continue;  // never
                 // the changed block's maxima under both rules, and their slots
                 const KT k0 = entry(b, 0), k1 = entry(b, 1);
@@ -1679,13 +1680,15 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                             int32_t *wblk = cold<WPL, int32_t>(kColdWblk);
                             if (lane == 0) wblk[(int64_t)ws * maxb + nbw] = blk;
                         }
-                        if (lane == 0) rnb[ws] = nbw + 1;
                         slot = blk * 64;
 #pragma unroll
                         for (int k = 0; k < WPL; k++)
                             if (lane + k * kWave == ws) {
                                 nb[k] = nbw + 1;
                                 tail[k] = slot;
+                                // (the second wave reads the count first, then that many ids)
+                                keep_order();
+                                lds_store(&rnb[lane + k * kWave], nbw + 1);
                             }
                     }
                     // the slot was the worker's empty one or its tail

@@ -844,6 +844,39 @@ def test_queue_spill_paths_batch_small_lds(insp):
     dag.free()
 
 
+# Queues that take blocks all along the run, past the 16 a worker's list holds
+# in LDS, with a pop and its rescan before nearly every new block.
+@pytest.mark.parametrize("policy", ["inspirit", "fifo", "heft"])
+@pytest.mark.parametrize("machine", [(2, 1), (66, 1)])
+def test_queues_growing_between_pops(insp, machine, policy):
+    ws = []
+    for k, hub in enumerate((0, 3000)):  # the second DAG's keys take 64 bits
+        spread, leaves = 200, 9000 if machine[0] == 2 else 90000
+        n = spread + leaves
+        per = leaves // spread
+        edges = [np.arange(spread + i * per, spread + (i + 1) * per) for i in range(spread)]
+        if hub:
+            edges[0] = np.unique(np.concatenate([edges[0], np.arange(n - hub, n)]))
+        rp = np.concatenate([[0], np.cumsum([len(e) for e in edges]), np.full(leaves, sum(len(e) for e in edges))])
+        col = np.concatenate(edges).astype(np.int32)
+        t = np.random.default_rng(k).integers(1, 30, (n, 2)).astype(np.int32)
+        t[:spread] = 2
+        ws.append(NS(n=n, row_ptr=rp.astype(np.int32), col=col, dur=t, est=t, n_cpu=machine[0], n_gpu=machine[1],
+                     m=int(col.size), type=np.zeros(n, np.int32), name="growing"))
+    for part in (ws[:1], ws):
+        b = synth.concat(part)
+        say("growing queues", machine, policy, len(part))
+        dag, dur, est = insp.batch_to_device(b)
+        o = insp.schedule_batch(dag, [machine] * len(part), dur, est, insp.params(policy=policy),
+                                tune_key="grid=2,lds_blocks=8,lds_slots=4,lds_keys=6")
+        insp.sync_status(dag)
+        r = oracle.schedule_batch(b, policy=policy)
+        for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+            assert np.array_equal(o[k].cpu().numpy(), r[k]), k
+        assert np.array_equal(o["makespan"].cpu().numpy(), r["makespan"])
+        dag.free()
+
+
 def test_many_candidates_per_event(insp):
     for seed in range(3):
         w = _hubs(seed)
