@@ -1050,11 +1050,9 @@ int run_attributes(insp_dag *dag, Workspace *ws, const int32_t *est, int32_t uni
         ProfScope ps(st, "attr_dag");
         // the DAGs above kMidTasks (first in sorder) get 1024 threads each,
         // the others 256, so that several of them share a CU
-        int32_t n_big = 0;
-        while (n_big < ws->n_small && ws->h_desc[ws->h_sorder[n_big]].n > kMidTasks) n_big++;
-        const int32_t n_mid = ws->n_small - n_big;
+        const int32_t n_big = ws->n_big, n_mid = ws->n_small - n_big;
         const size_t lds_big = 4 * (((size_t)std::max(ws->max_small, 1) + 1) / 2);
-        const size_t lds_mid = 4 * (((size_t)std::max(n_mid > 0 ? ws->h_desc[ws->h_sorder[n_big]].n : 1, 1) + 1) / 2);
+        const size_t lds_mid = 4 * (((size_t)std::max(ws->max_mid, 1) + 1) / 2);
         int rc = rem        ? launch_attr_dag<true, false>(a, o, n_big, n_mid, lds_big, lds_mid, st)
                  : sim_init ? launch_attr_dag<false, true>(a, o, n_big, n_mid, lds_big, lds_mid, st)
                             : launch_attr_dag<false, false>(a, o, n_big, n_mid, lds_big, lds_mid, st);
@@ -1162,7 +1160,7 @@ int64_t workspace_shape(const insp_dag *dag, int32_t first, int32_t count, const
     w->h_order.clear();
     w->h_sorder.clear();
     w->h_large.clear();
-    w->max_small = 0;
+    w->max_small = w->max_mid = 0;
     int64_t boff = 0, wloff = 0;
     for (int32_t i = 0; i < count; i++) {
         const insp_workers &wk = workers[per_dag ? i : 0];
@@ -1190,6 +1188,7 @@ int64_t workspace_shape(const insp_dag *dag, int32_t first, int32_t count, const
         w->max_nblk = std::max<int64_t>(w->max_nblk, d.nblk);
         if (d.path) w->h_large.push_back(i);
         else w->max_small = std::max(w->max_small, d.n);
+        if (d.n <= kMidTasks) w->max_mid = std::max(w->max_mid, d.n);
     }
     w->h_desc = *desc;
     // simulation and per-DAG attribute order: largest DAGs first
@@ -1199,6 +1198,9 @@ int64_t workspace_shape(const insp_dag *dag, int32_t first, int32_t count, const
             if (dag->toff[b + 1] - dag->toff[b] > 0 && !(*desc)[b - first].path) w->h_sorder.push_back(b - first);
         }
     w->n_small = (int32_t)w->h_sorder.size();
+    // (the order counts edges too: a DAG of few tasks may come before larger ones)
+    w->n_big = (int32_t)(std::stable_partition(w->h_sorder.begin(), w->h_sorder.end(),
+                                               [&](int32_t i) { return (*desc)[i].n > kMidTasks; }) - w->h_sorder.begin());
     w->total_wl = wloff;
     return boff;
 }

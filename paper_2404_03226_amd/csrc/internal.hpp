@@ -153,10 +153,12 @@ struct Workspace {
     int64_t tasks = 0;
     int32_t n_small = 0;          // non-empty DAGs of the per-DAG attribute pass
     int32_t max_small = 0;        // tasks of the largest of them
+    int32_t n_big = 0;            // of them, above the 256-thread work-groups' limit ...
+    int32_t max_mid = 0;          // ... and the tasks of the largest at or below it
     DevBuf arena, sim_arena;      // memory of the arrays below: up to counter; the queue pools
     DevBuf desc;                  // DagDesc [count]
     DevBuf order;                 // int32 [count]: desc indices, largest first
-    DevBuf sorder;                // int32 [n_small]: desc indices of the per-DAG pass, largest first
+    DevBuf sorder;                // int32 [n_small]: desc indices of the per-DAG pass, the n_big first, each by tasks + edges
     DevBuf u;                     // int32 [count]: chosen U, followed by
     DevBuf counter;               // int32 [4]: DAG dispenser; [3] some estimate of an attribute call is out of range
     DevBuf slots;                 // Slot [64 per block]: queue entries

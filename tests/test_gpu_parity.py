@@ -290,6 +290,43 @@ def test_attribute_paths_in_one_batch(insp):
     dag.free()
 
 
+# DAGs of few tasks and many edges before larger ones in the order by tasks and
+# edges together, either side of the 256-thread work-groups' 4,096 tasks
+@pytest.mark.parametrize("shapes", [[(700, 90000), (4097, 9000), (20000, 4000)], [(4096, 200000), (4097, 100), (9, 12)],
+                                    [(600, 30000), (3000, 5000), (4096, 4000)], [(300, 20000), (33000, 500), (10000, 30)]])
+def test_attributes_of_dense_beside_sparse_dags(insp, shapes):
+    import torch
+    ws = []
+    for k, (n, m) in enumerate(shapes):
+        rng = np.random.default_rng(k)
+        a, b = rng.integers(0, n - 1, m), rng.integers(1, n, m)
+        key = np.unique(np.minimum(a, b - 1) * n + np.maximum(a + 1, b))
+        t = rng.integers(1, 60, (n, 2)).astype(np.int32)
+        rp = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int32)
+        ws.append(NS(n=n, row_ptr=rp, col=(key % n).astype(np.int32), dur=t, est=t, n_cpu=3, n_gpu=1, m=int(key.size),
+                     type=np.zeros(n, np.int32), name="dense"))
+    b = synth.concat(ws)
+    dag, dur, est = insp.batch_to_device(b)
+    for U in (0, 40):
+        say("dense beside sparse", shapes, U)
+        ia, ie, Ug = insp.attributes(dag, insp.ALL_DAGS, est, [(3, 1)] * len(ws), unit_time=U)
+        for k, w in enumerate(ws):
+            a, z = int(b.task_off[k]), int(b.task_off[k + 1])
+            ria, rie, rU = oracle.attributes(w.n, w.row_ptr, w.col, w.est, 1, unit_time=U)
+            assert Ug[k] == rU
+            assert np.array_equal(ia[a:z].cpu().numpy(), ria) and np.array_equal(ie[a:z].cpu().numpy(), rie)
+    rem = torch.from_numpy(np.concatenate([np.bincount(w.col, minlength=w.n) for w in ws]).astype(np.int32)).cuda()
+    ia2, ie2, _ = insp.attributes(dag, insp.ALL_DAGS, est, [(3, 1)] * len(ws), unit_time=40, rem=rem)
+    assert torch.equal(ia2, ia) and torch.equal(ie2, ie)
+    r = oracle.schedule_batch(b)
+    for call in (insp.schedule_batch, insp.schedule_batch_noalloc):
+        o = call(dag, [(3, 1)] * len(ws), dur, est)
+        insp.sync_status(dag)
+        for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+            assert np.array_equal(o[k].cpu().numpy(), r[k]), k
+    dag.free()
+
+
 @pytest.mark.parametrize("policy", ["inspirit", "fifo", "ability", "efi", "heft"])
 def test_random_small_dags(insp, policy):
     for i in range(40):
