@@ -8,6 +8,7 @@
 #include <climits>
 #include <atomic>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -346,6 +347,36 @@ struct PlaceArgs {
     int32_t *maxdeg;              // [B]: longest canonical row
 };
 
+// Rows of a DAG are placed by one work-group, or by the whole grid.
+//
+// What bounds the grid's placement is its 64-bit atomics on the dependency
+// words, one per edge, at the far end of the memory system (21 M edges: 0.9 ms,
+// or 23 a nanosecond).  A work-group adds up its DAG's words in LDS instead and
+// writes them once, in order; neither they nor the row pointers are cleared
+// first.  160 KB hold 20,000 tasks; DAGs of up to kPlaceSmall tasks and
+// kPlaceSmallEdges edges get a small work-group, of which a CU holds many.
+// Measured on 1,024 layered DAGs of 200-20,000 tasks (21 M edges): 123 us,
+// against 893 with global atomics.
+//
+// But one work-group places no more than 1.5 to 2 edges a nanosecond, so that
+// a DAG which holds much of all edges is left to the grid.  Builds by
+// work-groups and by the grid: one DAG of 5,000 tasks and 24 K edges 122 and
+// 114 us, of 20,000 and 290 K 396 and 134, a complete DAG of 1,000 1,484 (small
+// work-group; large: 578) and 294; 8 and 16 DAGs of 20,000 and 290 K 384 and
+// 318, 422 and 455; where most rows are long, which a wave each places, 16, 32
+// and 64 complete DAGs of 700 1,135 and 958, 1,863 and 1,731, 3,704 and 3,648.
+// Below kPlaceEdges both take the same.
+constexpr int32_t kPlaceSmall = 1024, kPlaceMax = 20000;
+constexpr int64_t kPlaceEdges = 4096, kPlaceSmallEdges = 16384;
+
+// Whether the grid places a DAG of n tasks and m of the call's `all` edges.
+__host__ __device__ __forceinline__ bool by_grid(int64_t n, int64_t m, int64_t all) {
+    return n > kPlaceMax || (m > kPlaceEdges && m > all / (m > kSmallRow * n ? 64 : 16));
+}
+__device__ __forceinline__ bool by_grid(const PlaceArgs &A, int32_t b) {
+    return by_grid(A.toff[b + 1] - A.toff[b], A.eoff[b + 1] - A.eoff[b], A.eoff[A.B]);
+}
+
 // Move row v's canonical targets to their place and account the edges in
 // the targets' dependency words (in-degree << 43 | sum of predecessor ids).
 __device__ __forceinline__ void place_edge(const PlaceArgs &A, int32_t b, int32_t lv, int32_t s, int64_t to,
@@ -355,17 +386,7 @@ __device__ __forceinline__ void place_edge(const PlaceArgs &A, int32_t b, int32_
     back |= s < lv;
 }
 
-// Rows of a DAG of up to kPlaceMax tasks: one work-group per DAG.
-//
-// What bounded the placement was its 64-bit atomics on the dependency words,
-// one per edge, at the far end of the memory system (21 M edges: 0.9 ms, or 23
-// a nanosecond).  A work-group adds up its DAG's words in LDS instead and
-// writes them once, in order; neither they nor the row pointers are cleared
-// first.  160 KB hold 20,000 tasks; DAGs of up to kPlaceSmall get a small
-// work-group, of which a CU holds many.  Measured on 1,024 layered DAGs of
-// 200-20,000 tasks (21 M edges): 123 us, against 893 with global atomics.
-constexpr int32_t kPlaceSmall = 1024, kPlaceMax = 20000;
-
+// One work-group per DAG.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_t *dags) {
     extern __shared__ unsigned long long word[];  // [n]
@@ -433,14 +454,14 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
     }
 }
 
-// Larger DAGs, one thread per task: the canonical row pointer, and the row
+// The grid's DAGs, one thread per task: the canonical row pointer, and the row
 // itself when it is short.  (Their dependency words start out cleared.)
 __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
     const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, last = A.toff[A.B] - 1;
     const int32_t b = dag_of(A.toff, A.B, min(v, last));
     const int32_t lv = (int32_t)(v - A.toff[b]);
     const int32_t n = (int32_t)(A.toff[b + 1] - A.toff[b]);
-    const bool on = v <= last && n > kPlaceMax;
+    const bool on = v <= last && by_grid(A, b);
     const int32_t cnt = on ? A.outdeg[v] : 0;
     // the longest row: one atomic a wave for the DAG of its first lane
     const int32_t b0 = uniform(b), most = (int32_t)wave_max_u32f(b == b0 ? (uint32_t)cnt : 0u);
@@ -464,7 +485,7 @@ __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
 __global__ __launch_bounds__(64) void k_place_wide(PlaceArgs A, const int64_t *wide) {
     const int64_t v = wide[blockIdx.x];
     const int32_t b = dag_of(A.toff, A.B, v);
-    if (A.toff[b + 1] - A.toff[b] <= kPlaceMax) return;
+    if (!by_grid(A, b)) return;
     const int32_t lv = (int32_t)(v - A.toff[b]);
     const int32_t *p = A.rp + A.toff[b] + b;
     const int32_t *src = A.tmp + A.eoff[b] + p[lv];
@@ -707,12 +728,21 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     t.add(&flags, sizeof(int32_t) * (2 + nbw + n_dags));
     if ((rc = t.alloc(&scratch))) return rc;
     int32_t *err = flags.as<int32_t>(), *nwide = err + 1, *backward = err + 2;
-    // DAGs by size, largest first
+    // DAGs by who places them -- the grid (2), a large (1) or a small work-group
+    // -- and by size, largest first
     auto tasks = [&](int32_t b) { return task_off[b + 1] - task_off[b]; };
+    std::vector<uint64_t> keys(n_dags);
+    int32_t by[3] = {0, 0, 0};
+    for (int32_t b = 0; b < n_dags; b++) {
+        const int64_t n = tasks(b), m = edge_off[b + 1] - edge_off[b];
+        const uint64_t q = by_grid(n, m, M) ? 2 : n > kPlaceSmall || m > kPlaceSmallEdges ? 1 : 0;
+        by[q]++;
+        keys[b] = q << 62 | (uint64_t)n << 32 | (uint32_t)b;
+    }
+    std::sort(keys.begin(), keys.end(), std::greater<uint64_t>());
     std::vector<char> host(o_bysize + sizeof(int32_t) * n_dags);
     int32_t *order = reinterpret_cast<int32_t *>(host.data() + o_bysize);
-    std::iota(order, order + n_dags, 0);
-    std::sort(order, order + n_dags, [&](int32_t x, int32_t y) { return tasks(x) > tasks(y); });
+    for (int32_t i = 0; i < n_dags; i++) order[i] = (int32_t)(uint32_t)keys[i];
     memcpy(host.data(), task_off, offs);
     memcpy(host.data() + o_eoff, edge_off, offs);
     INSP_HIP(hipMemcpyAsync(d->base_arena.p, host.data(), host.size(), hipMemcpyHostToDevice, st));
@@ -774,7 +804,8 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     d->M = Mc;
     // (the simulation reads 8 successors at a time from a row's start: room past the last row)
     if ((rc = d->col.alloc(sizeof(int32_t) * (Mc + 16)))) return rc;
-    if (max_n > kPlaceMax) INSP_HIP(hipMemsetAsync(d->word0.p, 0, sizeof(uint64_t) * N, st));
+    const int32_t n_grid = by[2], n_large = by[1], n_small = by[0];
+    if (n_grid > 0) INSP_HIP(hipMemsetAsync(d->word0.p, 0, sizeof(uint64_t) * N, st));
     PlaceArgs pa;
     pa.B = n_dags;
     pa.toff = d->d_toff.as<int64_t>();
@@ -789,22 +820,17 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     pa.word0 = d->word0.as<unsigned long long>();
     pa.backward = backward;
     pa.maxdeg = backward + nbw;
-    // those above kPlaceMax, the large, the small
-    auto above = [&](int32_t n) {
-        return (int32_t)(std::partition_point(order, order + n_dags, [&](int32_t b) { return tasks(b) > n; }) - order);
-    };
-    const int32_t n_huge = above(kPlaceMax), n_large = above(kPlaceSmall) - n_huge, n_small = n_dags - n_huge - n_large;
     const int32_t *dags = bysize.as<int32_t>();
     if (n_large > 0) {
-        const size_t lds = sizeof(uint64_t) * (size_t)tasks(order[n_huge]);
+        const size_t lds = sizeof(uint64_t) * (size_t)tasks(order[n_grid]);
         if ((rc = set_lds_limit((const void *)&k_place_dag<1024>, lds))) return rc;
-        hipLaunchKernelGGL(k_place_dag<1024>, dim3((unsigned)n_large), dim3(1024), lds, st, pa, dags + n_huge);
+        hipLaunchKernelGGL(k_place_dag<1024>, dim3((unsigned)n_large), dim3(1024), lds, st, pa, dags + n_grid);
     }
     if (n_small > 0)
         hipLaunchKernelGGL(k_place_dag<128>, dim3((unsigned)n_small), dim3(128),
-                           sizeof(uint64_t) * (size_t)tasks(order[n_huge + n_large]), st, pa, dags + n_huge + n_large);
-    if (max_n > kPlaceMax) hipLaunchKernelGGL(k_place, dim3(grid_for(N, 256)), dim3(256), 0, st, pa);
-    if (max_n > kPlaceMax && h_wide > 0)
+                           sizeof(uint64_t) * (size_t)tasks(order[n_grid + n_large]), st, pa, dags + n_grid + n_large);
+    if (n_grid > 0) hipLaunchKernelGGL(k_place, dim3(grid_for(N, 256)), dim3(256), 0, st, pa);
+    if (n_grid > 0 && h_wide > 0)
         hipLaunchKernelGGL(k_place_wide, dim3((unsigned)h_wide), dim3(64), 0, st, pa, (const int64_t *)wide.as<int64_t>());
     INSP_HIP(hipGetLastError());
 

@@ -1207,6 +1207,76 @@ def test_build_sizes_match_oracle(insp, sizes):
     dag.free()
 
 
+def _random_edges(n, m, seed):
+    """m edges drawn with repeats between n tasks, from lower to higher ids, or
+    (odd seeds) with the ids relabelled so that they point both ways."""
+    rng = np.random.default_rng(seed)
+    a, b = rng.integers(0, n - 1, m), rng.integers(1, n, m)
+    src, dst = np.minimum(a, b - 1), np.maximum(a + 1, b)
+    if seed % 2:
+        perm = rng.permutation(n)
+        src, dst = perm[src], perm[dst]
+    at = np.argsort(src, kind="stable")
+    rp = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+    t = rng.integers(1, 60, (n, 2)).astype(np.int32)
+    return NS(n=n, row_ptr=rp, col=dst[at].astype(np.int32), dur=t, est=t, n_cpu=3, n_gpu=1, m=m,
+              type=np.zeros(n, np.int32), name="edges")
+
+
+def _none():
+    return NS(n=0, row_ptr=np.zeros(1, np.int32), col=np.zeros(0, np.int32), dur=np.zeros((0, 2), np.int32),
+              est=np.zeros((0, 2), np.int32), n_cpu=3, n_gpu=1, m=0, type=np.zeros(0, np.int32), name="none")
+
+
+# who places a DAG's rows, by its edges and its share of all: alone either side
+# of 4,096; one of 15, 16 and 17 alike (short rows) and of 63, 64 and 65 (rows
+# of 25 on average); few tasks with many edges; and all of them in one call
+@pytest.mark.parametrize("shapes", [[(900, 4096)], [(900, 4097)], [(3000, 5000)] * 15, [(3000, 5000)] * 16,
+                                    [(3000, 5000)] * 17, [(400, 10000)] * 63, [(400, 10000)] * 64, [(400, 10000)] * 65,
+                                    [(600, 16384), (600, 16385)] * 20, [(1024, 60000)] + [(300, 900)] * 30,
+                                    [(20000, 4097), (20001, 300), None, (700, 90000), (5, 8), None] + [(2000, 9000)] * 30])
+def test_build_by_share_of_edges_match_oracle(insp, shapes):
+    say("build by edges", shapes[0], len(shapes))
+    ws = [_random_edges(*x, seed=k) if x else _none() for k, x in enumerate(shapes)]
+    b = synth.concat(ws)
+    canon = [oracle.canon(w.n, w.row_ptr, w.col) for w in ws]
+    dag, dur, est = insp.batch_to_device(b)
+    assert list(dag.m) == [len(c) for _, c in canon]
+    ia, _, _ = insp.attributes(dag, insp.ALL_DAGS, est, [(3, 1)] * len(ws))
+    assert np.array_equal(ia.cpu().numpy(), np.concatenate([np.diff(rp) for rp, _ in canon]))
+    o = insp.schedule_batch(dag, [(3, 1)] * len(ws), dur, est)
+    insp.sync_status(dag)
+    r = oracle.schedule_batch(b)
+    for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+        assert np.array_equal(o[k].cpu().numpy(), r[k]), k
+    assert np.array_equal(o["makespan"].cpu().numpy(), r["makespan"])
+    dag.free()
+
+
+def test_build_of_one_dense_dag_uses_the_chip(insp):
+    """A complete DAG of 1,000 tasks builds in about the time of eight with as
+    many edges together (placed by one work-group it took four times that)."""
+    import time
+    import torch
+
+    def best(sizes):
+        rp = np.concatenate([np.concatenate([[0], np.cumsum(np.arange(n - 1, -1, -1))]) for n in sizes])
+        col = np.concatenate([np.concatenate([np.arange(v + 1, n) for v in range(n)]) for n in sizes])
+        edges = [n * (n - 1) // 2 for n in sizes]
+        a = (np.concatenate([[0], np.cumsum(sizes)]), np.concatenate([[0], np.cumsum(edges)]),
+             torch.from_numpy(rp.astype(np.int32)).cuda(), torch.from_numpy(col.astype(np.int32)).cuda())
+        times = []
+        for _ in range(15):
+            t = time.perf_counter()
+            insp.build_dag(*a).free()
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    one, parts = best([1000]), best([354] * 8)
+    say("build of one and of eight: %.0f us, %.0f us" % (one * 1e6, parts * 1e6))
+    assert one < 2.2 * parts
+
+
 # short rows, which their placement sorts: targets given in falling order, no
 # edge twice and one (in the last DAG), either side of the placement's line
 @pytest.mark.parametrize("repeats", [0, 1])
