@@ -150,7 +150,10 @@ typedef struct {
  * Rows are sorted and repeated edges merged on the device.  Errors:
  * INSP_E_INVAL for a non-monotone row pointer, an id out of range or a self
  * loop; INSP_E_CYCLE for a cycle; INSP_E_RANGE for n_b > 2^21.  The call
- * synchronises `stream` to report these.  The caller keeps its buffers.
+ * synchronises `stream` to report these.  The caller keeps its buffers; the
+ * device arrays are read more than once and must not change until the call
+ * returns (a successor that changes meanwhile is INSP_E_INVAL or taken as it
+ * was read last; a row pointer that does is not looked for).
  * The handle lives on the device current at this call; the calls that take
  * it make that device current before they launch.
  */

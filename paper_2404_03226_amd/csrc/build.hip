@@ -75,7 +75,7 @@ void DevBuf::release() {
     own = true;
 }
 
-enum { ERR_ROWPTR = 1, ERR_COL = 2, ERR_SELF = 4 };
+enum { ERR_ROWPTR = 1, ERR_COL = 2, ERR_SELF = 4, ERR_CHANGED = 8 };
 
 // Canonical rows are built in two passes: the first counts each row's distinct
 // targets, and an exclusive scan of those lengths gives the rows' places; the
@@ -163,13 +163,15 @@ __device__ __forceinline__ void load_sorted(const int32_t *src, int32_t deg, int
     sort_registers<kSmallRow>(x);
 }
 
-// ... and its distinct targets, in order, to put(place in the row, target).
+// ... and its distinct targets, in order, to put(place in the row, target);
+// returns how many they are.
 template <typename Put>
-__device__ __forceinline__ void each_distinct(const int32_t (&x)[kSmallRow], int32_t deg, Put put) {
+__device__ __forceinline__ int32_t each_distinct(const int32_t (&x)[kSmallRow], int32_t deg, Put put) {
     int32_t cnt = 0;
 #pragma unroll
     for (int i = 0; i < kSmallRow; i++)
         if (i < deg && (i == 0 || x[i] != x[i ? i - 1 : 0])) put(cnt++, x[i]);
+    return cnt;
 }
 
 // One thread per task: validate the row pointer and, for short rows, the
@@ -201,13 +203,9 @@ __global__ __launch_bounds__(256) void k_rows(RowArgs A) {
         return;
     }
     const int32_t *src = A.col + A.eoff[r.b] + r.a;
-    int32_t x[kSmallRow], cnt = 0;
+    int32_t x[kSmallRow];
     load_sorted(src, deg, x);
-    each_distinct(x, deg, [&](int32_t, int32_t s) {
-        cnt++;
-        bad |= check_target(s, r.n, r.lv);
-    });
-    A.outdeg[v] = cnt;
+    A.outdeg[v] = each_distinct(x, deg, [&](int32_t, int32_t s) { bad |= check_target(s, r.n, r.lv); });
     if (bad) atomicOr(A.err, bad);
 }
 
@@ -345,6 +343,7 @@ struct PlaceArgs {
     unsigned long long *word0;
     int32_t *backward;            // [1 + ceil(B / 32)]: any edge to a lower id, per DAG bits
     int32_t *maxdeg;              // [B]: longest canonical row
+    int32_t *err;                 // a short row is no longer what was counted
 };
 
 // Rows of a DAG are placed by one work-group, or by the whole grid.
@@ -406,7 +405,7 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
     }
     __syncthreads();
     int32_t longest = 0;
-    bool back = false, wide = false;
+    bool back = false, wide = false, bad = false;
     for (int32_t v = tid; v < n; v += THREADS) {
         const int32_t at = (int32_t)(A.excl[t0 + v] - e0), cnt = A.outdeg[t0 + v], a = p[v];
         rp[v] = at;
@@ -418,15 +417,23 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
         }
         int32_t x[kSmallRow];
         load_sorted(in + a, deg, x);
-        each_distinct(x, deg, [&](int32_t i, int32_t s) {
+        // (read again from the caller's array: a target is checked before it
+        // is used as an index)
+        const int32_t got = each_distinct(x, deg, [&](int32_t i, int32_t s) {
+            if (check_target(s, n, v)) {
+                bad = true;
+                return;
+            }
             col[at + i] = s;
             atomicAdd(&word[s], (1ull << 43) + (unsigned long long)v);
             back |= s < v;
         });
+        bad |= got != cnt;
     }
     longest = (int32_t)wave_max_u32f((uint32_t)longest);
     if (lane == 0) atomicMax(&s_max, longest);
     if (wide) s_wide = 1;
+    if (bad) atomicOr(A.err, ERR_CHANGED);
     __syncthreads();
     // long rows: a wave each
     if (s_wide) {
@@ -476,8 +483,12 @@ __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
     if (deg > kSmallRow) return;  // a listed row: k_place_wide
     int32_t x[kSmallRow];
     load_sorted(A.col + A.eoff[b] + p[lv], deg, x);
-    bool back = false;
-    each_distinct(x, deg, [&](int32_t i, int32_t s) { place_edge(A, b, lv, s, at + i, back); });
+    bool back = false, bad = false;
+    const int32_t got = each_distinct(x, deg, [&](int32_t i, int32_t s) {
+        if (check_target(s, n, lv)) bad = true;
+        else place_edge(A, b, lv, s, at + i, back);
+    });
+    if (bad || got != cnt) atomicOr(A.err, ERR_CHANGED);
     if (back) atomicOr(A.backward, 1), atomicOr(&A.backward[1 + (b >> 5)], 1 << (b & 31));
 }
 
@@ -820,6 +831,7 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
     pa.word0 = d->word0.as<unsigned long long>();
     pa.backward = backward;
     pa.maxdeg = backward + nbw;
+    pa.err = err;
     const int32_t *dags = bysize.as<int32_t>();
     if (n_large > 0) {
         const size_t lds = sizeof(uint64_t) * (size_t)tasks(order[n_grid]);
@@ -836,10 +848,12 @@ extern "C" int insp_build_dag(int32_t n_dags, const int64_t *task_off, const int
 
     // Cycle check: with every edge pointing to a higher id the id order is a
     // topological order; otherwise run Kahn's traversal on the DAGs concerned.
-    std::vector<int32_t> h_back(nbw + n_dags);
-    INSP_HIP(hipMemcpyAsync(h_back.data(), backward, sizeof(int32_t) * (nbw + n_dags), hipMemcpyDeviceToHost, st));
+    std::vector<int32_t> h_all(2 + nbw + n_dags);  // error, long rows, `backward`, longest rows
+    INSP_HIP(hipMemcpyAsync(h_all.data(), err, sizeof(int32_t) * h_all.size(), hipMemcpyDeviceToHost, st));
     INSP_HIP(hipStreamSynchronize(st));
-    d->maxdeg.assign(h_back.begin() + nbw, h_back.end());
+    if (h_all[0] & ERR_CHANGED) return set_error(INSP_E_INVAL, "col changed while the handle was built");
+    const int32_t *h_back = h_all.data() + 2;
+    d->maxdeg.assign(h_back + nbw, h_back + nbw + n_dags);
     if (h_back[0]) {
         std::vector<int32_t> todo;
         for (int32_t b = 0; b < n_dags; b++)

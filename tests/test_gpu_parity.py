@@ -566,6 +566,61 @@ def test_build_rows_of_every_length(insp, backward):
     assert_same(g, oracle.schedule(w, variant=oracle.HEAP), "wide rows")
 
 
+@pytest.mark.parametrize("count", [1, 40])
+def test_build_of_successors_that_change_meanwhile(insp, count):
+    """A host thread switches successors between a right and a wrong id while
+    handles are built from host memory that the GPU reads: a build either fails
+    or holds the right ones (one DAG placed by the grid, forty by a work-group
+    each)."""
+    import threading
+    import torch
+    n, m = 3000, 12000
+    rng = np.random.default_rng(count)
+    a, b = rng.integers(0, n - 1, m * count), rng.integers(1, n, m * count)
+    rps, cols = [], []
+    for k in range(count):
+        src = np.minimum(a[k * m:(k + 1) * m], b[k * m:(k + 1) * m] - 1)
+        dst = np.maximum(a[k * m:(k + 1) * m] + 1, b[k * m:(k + 1) * m])
+        at = np.argsort(src, kind="stable")
+        rps.append(np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]))
+        cols.append(dst[at])
+    rp = torch.from_numpy(np.concatenate(rps).astype(np.int32)).cuda()
+    col = torch.empty(m * count, dtype=torch.int32, pin_memory=True)
+    right = np.concatenate(cols).astype(np.int32)
+    col.numpy()[:] = right
+    off = np.arange(count + 1, dtype=np.int64)
+    want = [len(oracle.canon(n, r, c)[1]) for r, c in zip(rps, cols)]
+    where = rng.choice(m * count, 40, replace=False)
+    wrong = rng.choice(np.array([-1, n, n + 7, 1 << 28, 0x7fffffff], np.int32), 40)
+    stop = threading.Event()
+
+    def switch():
+        c = col.numpy()
+        while not stop.is_set():
+            c[where] = wrong
+            c[where] = right[where]
+            stop.wait(0.0002)
+
+    say("successors that change", count)
+    th = threading.Thread(target=switch)
+    th.start()
+    try:
+        for _ in range(60):
+            try:
+                dag = insp.build_dag(off * n, off * m, rp, col)
+            except insp.InspError as e:
+                assert e.code == insp.E_INVAL, e
+                continue
+            assert dag.m == want
+            dag.free()
+    finally:
+        stop.set()
+        th.join()
+    dag = insp.build_dag(off * n, off * m, rp, col)
+    assert dag.m == want
+    dag.free()
+
+
 @pytest.mark.parametrize("where", [1, 5, 7, 8])
 def test_build_rejects_bad_targets_in_long_rows(insp, where):
     """A self loop or an id out of range in a row of each sorting path is
