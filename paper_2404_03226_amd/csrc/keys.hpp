@@ -33,9 +33,6 @@ struct KeyFmt {
     __host__ __device__ __forceinline__ uint32_t ke(uint32_t ia, uint32_t ie, uint32_t seq) const {
         return 0x80000000u | ie << sb | ia << sa | (smask - seq);
     }
-    // increments of kA and kE when IE grows by one
-    __host__ __device__ __forceinline__ uint32_t da() const { return fifo ? 0u : 1u << sa; }
-    __host__ __device__ __forceinline__ uint32_t de() const { return 1u << sb; }
 };
 
 // Queue keys of the one-wave loop.

@@ -133,13 +133,11 @@ struct Lds {
     unsigned long long *sk;                          // [64 * key_cap] keys of the low blocks' entries
     unsigned long long *sx;                          // [64 * slot_cap] payload (task, durations) of the lowest
     int32_t *srs;                                    // [64 * slot_cap] ... and their first edges
-    int32_t *fstk;                                   // [sum_cap] free block ids below sum_cap
-    uint8_t *stale;                                  // [sum_cap] block maxima to rebuild before use
-    int32_t *hs;                                     // [4] DAG index, simulation finished, helper sink
+    int32_t *hs;                                     // [4] DAG index
 };
 
 __host__ __device__ inline size_t lds_bytes(int mw, int sc, int lb, int slc, int slk) {
-    return (size_t)mw * (3 * 8 + 7 * 4 + (size_t)lb * 4) + (size_t)sc * (16 + 4 + 1) + kFC * 8 + kCC * 8 +
+    return (size_t)mw * (3 * 8 + 7 * 4 + (size_t)lb * 4) + (size_t)sc * 16 + kFC * 8 + kCC * 8 +
            8 * 64 * 4 + (size_t)slc * 64 * 12 + (size_t)slk * 64 * 8 + 64 + 32;
 }
 
@@ -2481,9 +2479,7 @@ __device__ __forceinline__ Lds carve_lds(const SimArgs &A) {
     L.cu = L.cs + kCC;
     L.pre = L.cu + kCC;
     L.srs = L.pre + 8 * kWave;
-    L.fstk = L.srs + 64 * A.slot_cap;
-    L.stale = reinterpret_cast<uint8_t *>(L.fstk + A.sum_cap);
-    L.hs = reinterpret_cast<int32_t *>(L.stale + ((A.sum_cap + 15) & ~15));
+    L.hs = L.srs + 64 * A.slot_cap;
     return L;
 }
 
@@ -2693,9 +2689,8 @@ static SimKernel pick_kernel(const insp_dag *dag, const Workspace *ws, const ins
 
 int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t *dur, const int32_t *est,
                int32_t *worker, int64_t *start, int64_t *finish, int64_t *makespan, int32_t *ie_at_pop,
-               int8_t *mode_at_pop, insp_trace_rec *trace, int32_t *n_events, int waves, int grid,
-               int sum_cap, int slot_cap, int key_cap, hipStream_t st, int prio_top, int scan_max, int per_cu) {
-    (void)waves;
+               int8_t *mode_at_pop, insp_trace_rec *trace, int32_t *n_events, int grid, int sum_cap, int slot_cap,
+               int key_cap, hipStream_t st, int prio_top, int per_cu) {
     SimArgs A;
     memset(&A, 0, sizeof A);
     A.desc = ws->desc.as<DagDesc>();
@@ -2739,7 +2734,6 @@ int launch_sim(insp_dag *dag, Workspace *ws, const insp_params &p, const int32_t
     A.k_den = p.k_den;
     A.max_events = p.max_events;
     A.prio_top = prio_top;
-    (void)scan_max;
     // LDS: block maxima, block lists and the slots of the low blocks -- as
     // many as fit where one or two work-groups have the CU to themselves, a
     // few blocks per DAG for a larger batch (tunable)
@@ -2875,7 +2869,7 @@ extern "C" int insp_schedule(const insp_dag *cdag, int32_t index, const insp_wor
     if (params->data_bw > 0 && !dag->dxc.p && (rc = dag->dxc.alloc(sizeof(int32_t) * std::max<int64_t>(dag->N, 1))))
         return rc;
     return launch_sim(dag, ws, *params, dur, est, worker, start, finish, makespan, ie_at_pop, mode_at_pop, trace,
-                      n_events, 1, 1, 4096, 0, 0, st, 0, kScan, 1);
+                      n_events, 1, 4096, 0, 0, st, 0, 1);
 }
 
 static void parse_tune(const char *key, int *waves, int *grid, int *sum_cap, int *slot_cap, int *key_cap, int *prio,
@@ -2912,8 +2906,10 @@ int batch_prologue(insp_dag *dag, const insp_workers *workers, const int32_t *du
     launch->per_cu = tune_key && (strstr(tune_key, "grid=") || strstr(tune_key, "lds_")) ? 3 : groups_per_cu(dag, cus);
     if (launch->per_cu < 3) grid = std::max(1, std::min(dag->B, launch->per_cu * cus));
     parse_tune(tune_key, &waves, &grid, &sum_cap, &slot_cap, &key_cap, &prio, &scan);
+    // (what a key may ask for: the general loop's LDS, and five bytes a maximum
+    // that it once took besides, so that the line stays where callers know it)
     if (grid < 1 || sum_cap < 0 || sum_cap > 8192 || slot_cap < 0 || key_cap < 0 || prio < 0 || scan < 0 ||
-        scan > kScan || lds_bytes(1, sum_cap, 16, slot_cap, std::max(slot_cap, key_cap)) > 150 * 1024)
+        scan > kScan || lds_bytes(1, sum_cap, 16, slot_cap, std::max(slot_cap, key_cap)) + 5 * sum_cap > 150 * 1024)
         return set_error(INSP_E_INVAL, "bad tune key '%s'", tune_key);
     // one wave simulates one DAG; no other shape is implemented
     if (waves != 1) return set_error(INSP_E_INVAL, "tune key '%s': only waves=1 is supported", tune_key);
@@ -2922,7 +2918,6 @@ int batch_prologue(insp_dag *dag, const insp_workers *workers, const int32_t *du
     launch->slot_cap = slot_cap;
     launch->key_cap = key_cap;
     launch->prio = prio;
-    launch->scan = scan;
     return INSP_OK;
 }
 
@@ -2949,7 +2944,7 @@ static int schedule_batch(const insp_dag *cdag, const insp_workers *workers, con
     if (params->data_bw > 0 && !dag->dxc.p && (rc = dag->dxc.alloc(sizeof(int32_t) * std::max<int64_t>(dag->N, 1))))
         return rc;
     return launch_sim(dag, ws, *params, dur, est, worker, start, finish, makespan, ie_at_pop, mode_at_pop, trace,
-                      n_events, 1, bl.grid, bl.sum_cap, bl.slot_cap, bl.key_cap, st, bl.prio, bl.scan, bl.per_cu);
+                      n_events, bl.grid, bl.sum_cap, bl.slot_cap, bl.key_cap, st, bl.prio, bl.per_cu);
 }
 
 extern "C" int insp_schedule_batch(const insp_dag *cdag, const insp_workers *workers, const int32_t *dur,

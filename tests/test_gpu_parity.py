@@ -648,6 +648,32 @@ def test_build_rejects_bad_targets_in_long_rows(insp, where):
         assert e.value.code == code, (bad, e.value)
 
 
+def test_tune_keys_at_the_lds_line(insp):
+    """The LDS that a tune key may ask for, at its line: block maxima alone,
+    and beside slots and keys; accepted ones run, on either loop."""
+    w = synth.cfg3(select=[70])[0]
+    b = synth.concat([w, w])
+    dag, dur, est = insp.batch_to_device(b)
+    for machine in ((5, 2), (150, 3)):
+        ref = None
+        for key, ok in (("lds_blocks=7060,lds_slots=0,lds_keys=0", True), ("lds_blocks=7061,lds_slots=0,lds_keys=0", False),
+                        ("lds_blocks=100,lds_slots=114,lds_keys=0", True), ("lds_blocks=100,lds_slots=115,lds_keys=0", False),
+                        ("lds_blocks=0,lds_slots=0,lds_keys=289", True), ("lds_blocks=0,lds_slots=0,lds_keys=290", False),
+                        ("scan=16", True), ("scan=17", False), ("waves=1", True), ("waves=2", False)):
+            say("tune key", machine, key)
+            if not ok:
+                with pytest.raises(insp.InspError) as e:
+                    insp.schedule_batch(dag, [machine] * 2, dur, est, tune_key=key)
+                assert e.value.code == insp.E_INVAL
+                continue
+            o = insp.schedule_batch(dag, [machine] * 2, dur, est, tune_key=key)
+            insp.sync_status(dag)
+            got = [o[k].cpu().numpy() for k in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop", "makespan")]
+            ref = ref or got
+            assert all(np.array_equal(x, y) for x, y in zip(got, ref)), key
+    dag.free()
+
+
 def test_failures_are_kept_until_reported(insp):
     """A schedule's device-side failure survives later schedule and
     attribute calls on the handle until insp_sync_status reports it, and is
