@@ -597,7 +597,7 @@ static int simulate(int32_t n, const int32_t *rp, const int32_t *col, int32_t n_
         /* predecessor lists: a successor's last unfinished predecessor; inputs */
         prp = (int32_t *)calloc((size_t)n + 1, sizeof(int32_t));
         pcol = (int32_t *)malloc(sizeof(int32_t) * (size_t)(rp[n] > 0 ? rp[n] : 1));
-        touched = (int32_t *)malloc(sizeof(int32_t) * (size_t)n);
+        touched = (int32_t *)malloc(sizeof(int32_t) * (size_t)(rp[n] > 0 ? rp[n] : 1)); /* an entry per edge */
         if (!prp || !pcol || !touched) { rc = ORC_E_NOMEM; goto out; }
         for (int32_t e = 0; e < rp[n]; e++) prp[col[e] + 1]++;
         for (int32_t v = 0; v < n; v++) prp[v + 1] += prp[v];

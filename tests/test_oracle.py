@@ -343,6 +343,19 @@ def test_c_plain_heap_and_python_twin_agree(chunk):
             assert [tuple(x) for x in a["trace"].tolist()] == c["trace"]
 
 
+def test_variants_agree_on_many_releases_in_one_event():
+    """Forty tasks that end together and share their eight successors: more
+    releases in one event than the DAG has tasks."""
+    k, m = 40, 8
+    rp, col = csr(k + m, [(a, k + b) for a in range(k) for b in range(m)])
+    for ticks in ([3, 3], [3, 5]):
+        w = wl(k + m, rp, col, 30, 10, np.tile(ticks, (k + m, 1)))
+        for pol in ("inspirit", "fifo", "efi"):
+            a, b = oracle.schedule(w, policy=pol), oracle.schedule(w, policy=pol, variant=oracle.HEAP)
+            for f in ("worker", "start", "finish", "ie_at_pop", "mode_at_pop"):
+                assert np.array_equal(a[f], b[f]), (pol, f)
+
+
 def test_plain_and_heap_agree_on_cholesky_and_layered():
     for w in (synth.cfg1(), synth.cfg2(nb=20), *synth.cfg3(select=[5, 6])):
         a = oracle.schedule(w, variant=oracle.PLAIN)
