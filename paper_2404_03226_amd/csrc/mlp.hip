@@ -288,6 +288,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_rows_step(StepArgs A) {
             }
         }
         if (lane == 0) {
+            // (sums of rounded values: not fused with the products they add up)
+#pragma clang fp contract(off)
             float *pp = A.part + (r0 / 4 + wv) * kPart + kHid;
             pp[0] = ((d0[0] + d0[1]) + d0[2]) + d0[3];
             pp[1] = ((d1[0] + d1[1]) + d1[2]) + d1[3];

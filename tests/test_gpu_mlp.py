@@ -347,3 +347,24 @@ def test_learned_estimates_schedules_and_gain(insp):
     assert gaps["paired_gain"] > 0.01 and gaps["frac_improved"] > 0.75
     m.free()
     dag.free()
+
+
+@pytest.mark.parametrize("B, seed, bits", [(96, 7, 0x4116b011), (96, 11, 0x410b03bd), (160, 0, 0x410e1bc7),
+                                           (224, 14, 0x4114bf7d), (480, 6, 0x410ef813), (1056, 3, 0x410ca237),
+                                           (2016, 7, 0x41123589)])
+def test_loss_adds_rounded_rows(insp, B, seed, bits):
+    """The loss adds up per-row values rounded to fp32 (1 / batch is inexact at
+    these batches, so that a product fused with the sum shows in the last bit);
+    the bits are those of a kernel that stored the rows before adding them."""
+    import torch
+    r = np.random.default_rng(seed * 10000 + B)
+    x = r.random((B, 32), dtype=np.float32)
+    t = r.random((B, 2), dtype=np.float32) * np.float32(5)
+    print("[case] loss bits", B, seed, flush=True)
+    m = insp.Mlp(synth.mlp_init(5))
+    x, t = torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda()
+    _, _, loss = m.grads(x, t)
+    assert int(loss.cpu().numpy().view(np.uint32)[0]) == bits
+    loss.zero_()
+    m.train_step(x, t, loss=loss)
+    assert int(loss.cpu().numpy().view(np.uint32)[0]) == bits
