@@ -30,7 +30,8 @@ TILE_BW = 61440
 HBM_PEAK_GBS = 8000.0
 BF16_PEAK_TFLOPS = 2500.0  # dense bf16 MFMA
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_batch4096.txt")
-SIM_SOURCES = [os.path.join(ROOT, "paper_2404_03226_amd", "csrc", f) for f in ("sim.hip", "common.hpp", "internal.hpp")]
+SIM_SOURCES = [os.path.join(ROOT, "paper_2404_03226_amd", "csrc", f)
+               for f in ("sim.hip", "keys.hpp", "common.hpp", "internal.hpp")]
 # Algorithmic bytes of the simulation kernel (the dependency release,
 # frontier, push, pop and outputs): 76 B per task and 24 B per edge -- per
 # edge the successor id (4), the dependency word read and write (8 + 8) and
@@ -90,15 +91,16 @@ def sources_sha256():
     return h.hexdigest()
 
 
-def measured_traffic():
+def measured_traffic(launch):
     """HBM bytes per launch of the simulation kernel from the committed
     rocprofv3 counter summary, or None when the kernel's sources changed
-    since the counters were taken."""
+    since the counters were taken or none were taken at this launch (a tuning
+    key, or "default")."""
     try:
         for line in open(TRAFFIC_FILE):
             if line.startswith("# bench: "):
                 kv = dict(x.split("=", 1) for x in line[len("# bench: "):].split())
-                if kv.get("sources_sha256") == sources_sha256():
+                if kv.get("sources_sha256") == sources_sha256() and kv.get("launch") == launch:
                     return int(kv["traffic_bytes"])
     except (OSError, ValueError, KeyError):
         pass
@@ -271,7 +273,7 @@ def main():
     dom = "sim"
     roof = {"bound": "hbm", "kernel": dom, "achieved": kern[dom]["achieved_GBs"],
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": kern[dom]["frac_hbm_peak"],
-            "traffic": measured_traffic(),
+            "traffic": measured_traffic(tune_key or "default"),
             "bytes_per_launch": kern[dom]["algorithmic_bytes"],
             "note": "76 B per task + 24 B per edge; the simulation is latency-bound along each DAG's chain of "
                     "dependent events, not HBM-bound (see events)"}
