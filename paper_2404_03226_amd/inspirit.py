@@ -211,7 +211,7 @@ def _workers(w, count):
             if w.count(w[0]) == count:
                 one = Workers(int(w[0][0]), int(w[0][1]))
                 return (Workers * count).from_buffer_copy(bytes(one) * count)
-            if set(map(len, w)) == {2}:
+            if set(map(type, w)) <= {tuple, list} and set(map(len, w)) == {2}:
                 return (Workers * count).from_buffer_copy(array.array("i", itertools.chain.from_iterable(w)))
         except (TypeError, ValueError, OverflowError):
             pass

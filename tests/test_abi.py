@@ -115,3 +115,15 @@ def test_workers_of_a_batch_as_one_by_one(w):
     want = [(inspirit.Workers(int(w[i][0]), int(w[i][1]))) for i in range(5)]
     got = inspirit._workers(w, 5)
     assert [(g.n_cpu, g.n_gpu) for g in got] == [(x.n_cpu, x.n_gpu) for x in want]
+
+
+@pytest.mark.parametrize("w", [[(3, 1)] * 4 + [{0: 4, 1: 2}], [(3, 1), {1: 2, 0: 4}, (5, 5), [6, 6], (7, 7)]])
+def test_workers_given_as_mappings(w):
+    from paper_2404_03226_amd import inspirit
+    assert [(g.n_cpu, g.n_gpu) for g in inspirit._workers(w, 5)] == [(int(x[0]), int(x[1])) for x in w]
+
+
+def test_workers_that_have_no_order_are_refused():
+    from paper_2404_03226_amd import inspirit
+    with pytest.raises(TypeError):
+        inspirit._workers([(3, 1)] * 4 + [{4, 2}], 5)
