@@ -178,7 +178,7 @@ __device__ __forceinline__ int32_t each_distinct(const int32_t (&x)[kSmallRow], 
 // targets, and count the distinct ones; list the other rows.  The placement
 // sorts short rows again, from the caller's array: sorting 16 registers costs
 // less than an array of all edges written here and read there (1,024 DAGs with
-// 21 M edges: both passes 289 us with it, 205 without).  Such an array is also
+// 21 M edges: both passes 289 us with it, 208 without).  Such an array is also
 // the larger half of what a build allocates: hipMalloc and hipFree take 300 us
 // for a large one, and 28 us more for each megabyte once the process has been
 // through the card's cleared memory.
@@ -354,17 +354,17 @@ struct PlaceArgs {
 // writes them once, in order; neither they nor the row pointers are cleared
 // first.  160 KB hold 20,000 tasks; DAGs of up to kPlaceSmall tasks and
 // kPlaceSmallEdges edges get a small work-group, of which a CU holds many.
-// Measured on 1,024 layered DAGs of 200-20,000 tasks (21 M edges): 123 us,
-// against 893 with global atomics.
+// Measured on 1,024 layered DAGs of 200-20,000 tasks (21 M edges): 126 us
+// (101 + 25), against 893 with global atomics.
 //
 // But one work-group places no more than 1.5 to 2 edges a nanosecond, so that
-// a DAG which holds much of all edges is left to the grid.  Builds by
-// work-groups and by the grid: one DAG of 5,000 tasks and 24 K edges 122 and
-// 114 us, of 20,000 and 290 K 396 and 134, a complete DAG of 1,000 1,484 (small
-// work-group; large: 578) and 294; 8 and 16 DAGs of 20,000 and 290 K 384 and
-// 318, 422 and 455; where most rows are long, which a wave each places, 16, 32
-// and 64 complete DAGs of 700 1,135 and 958, 1,863 and 1,731, 3,704 and 3,648.
-// Below kPlaceEdges both take the same.
+// a DAG which holds much of all edges is left to the grid.  Whole builds by
+// work-groups and by the grid: one DAG of 5,000 tasks and 24 K edges 125 and
+// 115 us, of 20,000 and 290 K 400 and 135, a complete DAG of 1,000 572 (1,484 in
+// a small work-group) and 294; 8 and 16 DAGs of 20,000 and 290 K 383 and 321, 433
+// and 455; where most rows are long, which a wave each places, 16, 32 and 64
+// complete DAGs of 700 1,129 and 961, 1,854 and 1,731, 3,685 and 3,645.  Below
+// kPlaceEdges both take the same (200 tasks: 104 and 107).
 constexpr int32_t kPlaceSmall = 1024, kPlaceMax = 20000;
 constexpr int64_t kPlaceEdges = 4096, kPlaceSmallEdges = 16384;
 
@@ -382,7 +382,7 @@ __device__ __forceinline__ void place_edge(const PlaceArgs &A, int32_t b, int32_
                                            bool &back) {
     A.col_out[to] = s;
     atomicAdd(&A.word0[A.toff[b] + s], (1ull << 43) + (unsigned long long)lv);
-    back |= s < lv;
+    back |= s <= lv;
 }
 
 // One work-group per DAG.
@@ -417,18 +417,16 @@ __global__ __launch_bounds__(THREADS) void k_place_dag(PlaceArgs A, const int32_
         }
         int32_t x[kSmallRow];
         load_sorted(in + a, deg, x);
-        // (read again from the caller's array: a target is checked before it
-        // is used as an index)
+        // (read again from the caller's array: kept within the DAG as an index,
+        // and the row checked by its ends)
+        int32_t top = -1;
         const int32_t got = each_distinct(x, deg, [&](int32_t i, int32_t s) {
-            if (check_target(s, n, v)) {
-                bad = true;
-                return;
-            }
             col[at + i] = s;
-            atomicAdd(&word[s], (1ull << 43) + (unsigned long long)v);
-            back |= s < v;
+            atomicAdd(&word[min((uint32_t)s, (uint32_t)n - 1)], (1ull << 43) + (unsigned long long)v);
+            back |= s <= v;
+            top = s;
         });
-        bad |= got != cnt;
+        bad |= got != cnt || x[0] < 0 || top >= n;
     }
     longest = (int32_t)wave_max_u32f((uint32_t)longest);
     if (lane == 0) atomicMax(&s_max, longest);
@@ -483,12 +481,13 @@ __global__ __launch_bounds__(256) void k_place(PlaceArgs A) {
     if (deg > kSmallRow) return;  // a listed row: k_place_wide
     int32_t x[kSmallRow];
     load_sorted(A.col + A.eoff[b] + p[lv], deg, x);
-    bool back = false, bad = false;
+    bool back = false;
+    int32_t top = -1;
     const int32_t got = each_distinct(x, deg, [&](int32_t i, int32_t s) {
-        if (check_target(s, n, lv)) bad = true;
-        else place_edge(A, b, lv, s, at + i, back);
+        place_edge(A, b, lv, (int32_t)min((uint32_t)s, (uint32_t)n - 1), at + i, back);
+        top = s;
     });
-    if (bad || got != cnt) atomicOr(A.err, ERR_CHANGED);
+    if (got != cnt || x[0] < 0 || top >= n) atomicOr(A.err, ERR_CHANGED);
     if (back) atomicOr(A.backward, 1), atomicOr(&A.backward[1 + (b >> 5)], 1 << (b & 31));
 }
 
