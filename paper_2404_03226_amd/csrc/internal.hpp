@@ -54,9 +54,10 @@ struct DevBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
-// One allocation cut into the arrays that live and die together (a hipMalloc
-// and hipFree of tens of megabytes take 50 and 250 us each, whatever is in
-// them): add() every array, then alloc(), which points each DevBuf at its part.
+// One allocation cut into the arrays that live and die together (a large
+// hipMalloc and its hipFree take about 300 us, and 28 us more for each megabyte
+// once the process has been through the card's cleared memory): add() every
+// array, then alloc(), which points each DevBuf at its part.
 struct Carve {
     std::vector<std::pair<DevBuf *, size_t>> parts;
     size_t total = 0;

@@ -61,15 +61,16 @@ __device__ __forceinline__ int64_t frag(int n, int64_t k, int64_t K) {
 //
 // What bounds a step: not the matrix cores (0.46 GFLOP at batch 1024 is 0.2 us
 // of them) but the launches (about 3.4 us each, however little they do) and
-// the chain of dependent loads, LDS trips and barriers inside.  A step of
-// batch 1024 takes 16.6 us (10.3 + 6.3; gradients alone 17.2 us with the
-// caller's launch gaps, 61.7 before), against 58.7 as eleven kernels, one per
-// product, reduction and update.
+// the chain of dependent loads, LDS trips and barriers inside.  A training step
+// of batch 1024 takes 17.0 us (10.7 + 6.4), against 58.7 as eleven kernels, one
+// per product, reduction and update; a gradients call among others 15.2 to 16.8
+// (11.0 + 5.0 in the kernels), against 61.7.
 //
-// Between the two kernels the activations travel transposed, [unit][row]:
-// a lane's MFMA accumulator holds four consecutive rows of one unit (one
-// 8-byte store), and the weight-gradient products then read both operands
-// as 16-byte fragments along the batch with no LDS staging.
+// Between the two kernels the activations travel by unit, along the batch: a
+// lane's MFMA accumulator holds four consecutive rows of one unit (one 8-byte
+// store), and the weight-gradient products then read both operands as 16-byte
+// fragments with no LDS staging.  All but H2, which no product reads that way,
+// are in fragment order (frag).
 constexpr int kRows = 32;               // rows per work-group of k_rows_step
 constexpr int kRowWaves = 8;            // its waves; wave w owns hidden units [32 w, 32 w + 32)
 constexpr int kRowLds = kHid + 8;       // LDS row of activations (16-byte aligned, rows 4 banks apart)
@@ -82,8 +83,8 @@ struct StepArgs {
     const int32_t *tab;                 // graph-captured training: see k_params_step
     int32_t steps;                      // ... minibatches per epoch
     const float *p;                     // fp32 parameters (biases)
-    const uint16_t *w1t, *w2, *w2t, *w3;  // bf16 weights: [256][32], [256][256], its transpose, [256][2]
-    uint16_t *xt, *h1t, *h2t, *d2t, *d1t; // bf16 [unit][rows]: features, hidden layers, their gradients
+    const uint16_t *w1t, *w2, *w2t, *w3;  // bf16 weights: W1^T, W2 and W2^T in fragment order, W3 [256][2]
+    uint16_t *xt, *h1t, *h2t, *d2t, *d1t; // bf16 by unit: features, hidden layers, their gradients (fragment order; h2t [unit][rows])
     float *y;                           // [rows][2]
     float *part;                        // [rows / 4][kPart] column sums of dH2, dY and the loss per 4 rows
     float *colpart;                     // [rows / 32][256] column sums of dH1 per 32 rows
@@ -117,11 +118,11 @@ __device__ __forceinline__ void lds_barrier() {
 // row 4 (lane / 16) + i, unit lane % 16, in all three products, so masks and
 // hidden values stay in the lane that made them.  A work-group is bound by
 // its 272 KB of weights, read cold (1.8 us at the L1's 64 bytes a clock), and
-// by its five short phases (0.7 to 1 us each) between barriers: 7.4 us in all
-// at batch 1024.  Weights in row-major order (half-used cache lines) took 8 us
-// instead of 1.8, and barriers that also wait for the global stores 1 us
-// each; 16 waves of 16 columns measured 13.7 against 10.3 us a launch.  32
-// rows per work-group because the reduction order of db1 is by 32 rows.
+// by its five short phases (0.7 to 1 us each) between barriers; with the launch
+// 10.7 us at batch 1024.  Weights in row-major order (half-used cache lines)
+// made that 15.8, barriers that also wait for the global stores cost 1 us
+// each, and 16 waves of 16 columns took 13.7.  32 rows per work-group because
+// the reduction order of db1 is by 32 rows.
 // X16: x is 16-byte aligned (rows are then read as float4).
 template <bool X16>
 __global__ __launch_bounds__(64 * kRowWaves) void k_rows_step(StepArgs A) {
@@ -395,7 +396,7 @@ __device__ __forceinline__ void put_param(const ParamArgs &A, int64_t i, float g
 }
 
 // A 16 x 16 tile of a weight gradient, sum over the batch of P[m0 + r][k]
-// Q[n0 + c][k] (operands [unit][rows]): the batch in `nch` chunks, each
+// Q[n0 + c][k] (operands in fragment order along the batch): the batch in `nch` chunks, each
 // chunk's product accumulated on the matrix cores, the chunks summed in
 // order.  A wave takes four chunks of every kChunks; returns element
 // (tid / 16, tid % 16).
@@ -759,10 +760,10 @@ struct insp_mlp {
     int device = 0;
     int64_t step = 0;
     DevBuf p, g, m, v;            // fp32 [kParams]
-    DevBuf w1t, w2, w2t, w3;      // bf16 shadows: [256][32], [256][256], its transpose, [256][2]
+    DevBuf w1t, w2, w2t, w3;      // bf16 shadows: W1^T, W2 and W2^T in fragment order, W3 [256][2]
     DevBuf loss;                  // fp32 [1]
     int64_t cap = 0;              // rows the activation buffers hold
-    DevBuf xt, h1t, h2t, d2t, d1t;  // bf16 [unit][rows] activations and gradients
+    DevBuf xt, h1t, h2t, d2t, d1t;  // bf16 activations and gradients by unit (fragment order; h2t [unit][rows])
     DevBuf y;                     // fp32 [cap, 2]
     DevBuf part, colpart;         // fp32 partial sums for the fixed-order reductions
     int64_t gen = 0;              // bumped whenever a buffer above moves

@@ -1874,7 +1874,9 @@ __device__ void sim_lane(const SimArgs &A, int32_t di) {
                 bk = lds_load(&best[2 * w + slot]);
                 if constexpr (kBig) bp = lds_load(&bpos[2 * w + slot]);
                 if (USUALLY((wm & ballot(rq != 0)) == 0)) break;
-                if (RARELY(spin > kReqSpin)) {  // never: a wait that ends all the same
+                if (RARELY(spin > kReqSpin)) {
+                    // never: a wait that ends all the same.  What is popped then is
+                    // some task whose slot the queue has used; the DAG fails
                     status |= ST_HANG;
                     done = n;
                     break;
